@@ -148,28 +148,34 @@ struct Workspace {
 
 // FP64 scratch of the refinement per problem with n stages.  The stage
 // blocks come first, each stored compactly (only the entries that can be
-// nonzero; the register tiles are rebuilt from them entry by entry):
-//   T    stage input: per contact its 6 x 6 diagonal block (row-major), then
-//        its 6 offsets (face projector and point, or the interior-point input
-//        Hessian and linear term)
-//   K    gains, 12 x 13 row-major
-//   L    inverse input Hessian, 12 x 12 row-major (interior-point steps)
-//   Hwx  12 x 13 row-major (interior-point steps)
+// nonzero; the register tiles are rebuilt from them entry by entry).  A
+// contact's 6 x 6 input blocks are a 3 x 3 force block and three moment
+// diagonals, so with a 6-vector they take 18 doubles: rows f_x, f_y, f_z (three
+// entries and the vector's), then (diagonal, vector) of each moment.
+//   T    stage input: per contact the face projector and point (equality
+//        passes) or the interior-point input Hessian and linear term
+//   T2   equality passes: P R P + I - P and P R (c - u_ref) in the same layout
+//   K    gains and feedforward [K | kap], 12 x 14 row-major
+//   F    factors of the input Hessian, 12 x 12 (interior-point steps)
 //   S    value function: lower triangle of S (13 x 13, row by row), then s
-// Then per stage: feedforward (12), inputs (12), costates (13), gradient (12),
-// row multipliers, slacks, interior-point multipliers and their steps
-// (5 x 22) and step du (12); and states x and dx ((n+1) x 13 each).
+// Then per stage: inputs (12), state cost gradients (13), slacks, multipliers,
+// their steps and the complementarity target of the interior point (5 x 22),
+// input step or copy (12); and states x and their copy ((n+1) x 13 each).
 // Horizons beyond PINMPC_NMAX (the long-horizon path) keep two more 16-wide
 // per-stage vectors there (the costate chain's and the rollout's stage
 // buffers, which live in LDS for shorter horizons).
-constexpr int TS_T = 2 * (36 + 6);
-constexpr int TS_K = NU * NX;
-constexpr int TS_L = NU * NU;
-constexpr int TS_H = NU * NX;
+// TS_PAD keeps the block at the size that callers' HBM budgets and the static
+// scratch of the allocation-free entry point were sized for.
+constexpr int TS_T = 2 * 18;
+constexpr int TS_K = NU * (NX + 1);
+constexpr int TS_F = NU * NU;
 constexpr int TS_S = NX * (NX + 1) / 2 + NX;
+constexpr int TS_STAGE = 815;
+constexpr int TS_PAD = TS_STAGE - (2 * TS_T + TS_K + TS_F + TS_S + NU + NX + 5 * 2 * NROW + NU);
+static_assert(TS_PAD >= 0, "the stage's arrays fit its share of the block");
 __host__ __device__ constexpr size_t refine_block_doubles(int n) {
-  return (((size_t)n * (TS_T + TS_K + TS_L + TS_H + TS_S + NU + NU + NX + NU + 5 * 2 * NROW + NU) +
-           2 * (size_t)(n + 1) * NX + (n > PINMPC_NMAX ? (size_t)n * 32 : 0)) + 3) & ~(size_t)3;
+  return (((size_t)n * TS_STAGE + 2 * (size_t)(n + 1) * NX +
+           (n > PINMPC_NMAX ? (size_t)n * 32 : 0)) + 3) & ~(size_t)3;
 }
 
 // FP64 scratch of the four-contact refinement (refine_wide.hip) per problem
@@ -250,26 +256,13 @@ __device__ inline void fmac_row_bcast12(double (&c)[12], double s) {
 #undef PINMPC_FMAC
 }
 
-// The same elimination as gj_columns (the same roundings in the same order),
-// for a 12-row system whose leading 12 x 12 block sits in lanes 0..11 of
-// every 16-lane row of the wave (column c in lane c of each row, the rows
-// identical) and whose other columns occupy the remaining lanes of the rows:
-// the pivot column reaches its row's lanes through the DPP row broadcast of
-// the update instructions themselves.
-template <int p = 0>
-__device__ inline void gj_rows(double (&col)[12], uint32_t unit = 0) {
-  if constexpr (p < 12) {
-    if (!((unit >> p) & 1u)) {
-      const double t = col[p] * recip(row_bcast<p>(col[p]));
-      fmac_row_bcast12<p>(col, -t);   // col[r] - pc[r] t; col[p] is replaced next
-      col[p] = t;
-    }
-    gj_rows<p + 1>(col, unit);
-  }
-}
-
-// gj_rows on two systems with the same leading block (so the same pivots):
-// one reciprocal per pivot, two independent update blocks.
+// The elimination of gj_columns (the same roundings in the same order) on two
+// 12-row systems with the same leading block (so the same pivots: one
+// reciprocal, two independent update blocks), which sits in lanes 0..11 of every
+// 16-lane row of the wave (column c in lane c of each row, the rows identical)
+// while their other columns occupy the remaining lanes of the rows: the pivot
+// column reaches its row's lanes through the DPP row broadcast of the update
+// instructions themselves.
 template <int p = 0>
 __device__ inline void gj_rows2(double (&a)[12], double (&b)[12], uint32_t unit = 0) {
   if constexpr (p < 12) {

@@ -46,8 +46,8 @@ struct Ctx {
   const LMEM double* R;
   gcf A, B, e, x_ref, u_ref, x0;
   const GMEM uint8_t* contact;
-  gd rT, rK, rL, rHwx, rS;   // per-stage compact blocks (TS_T, TS_K, ... doubles)
-  gd rkap, ru, rx, rlam, rg, rmu, rs, rz, rds, rdz, rdu, rdx;
+  gd rT, rT2, rK, rF, rS;    // per-stage compact blocks (TS_T, TS_K, ... doubles)
+  gd ru, rx, rq, rs, rz, rds, rdz, rrc, rdu, rdx;
   gd rPV, rGV;   // long horizons: the stage buffers of the rollout and costates
   GMEM int32_t* faces;
 };
@@ -240,25 +240,28 @@ __device__ inline void face_affine(int code, const Ctx& C, double P[6][6], doubl
 
 // Hand-off buffers of the stage recursion; everything else of a stage lives
 // in registers as 16 x 16 tiles.
-constexpr int GS = NU + NX + 2;   // row stride of the Gauss-Jordan hand-off
+constexpr int GC = 14;            // column stride of the elimination's hand-off
 struct ShR {
-  double G[NU * GS];     // [H | Hwx | hw] of the stage, row-major
-  double KK[NU * 16];    // [K | 0 | kap]: gains, feedforward in column 13
-  double HI[NU * 16];    // H^{-1} (Newton steps, chunk summaries)
-  double ST[16 * 17];    // S of the stage, for its transpose
+  // [H | Hwx | hw | 0] of the stage by column, 12 + 16 columns: a lane moves its
+  // column as 16-byte pairs, and the stride spreads both that and the tile
+  // accesses over all banks
+  alignas(16) double G[(NU + 16) * GC];
+  double ST[16 * 17];             // a tile for its transpose
+  alignas(16) double HI[NU * GC];             // H^{-1} by column (chunk summaries)
 };
 struct Sh {
-  // the Riccati recursion's hand-off buffers and the costate recursion's
-  // stage vectors share storage: the two never run at the same time
+  // the Riccati recursion's hand-off buffers and the stage vectors of the
+  // rollout and the costates share storage: they are never in use together
   union {
     ShR r;
     struct {
-      double PV[PINMPC_NMAX * 16];   // Q (x_{k+1} - r_k), then p_{k+1}
-      double GV[PINMPC_NMAX * 16];   // R (u_k - u_ref_k), then g_k
+      double PV[PINMPC_NMAX * 16];   // x_{k+1}, Q (x_{k+1} - r_k), p_{k+1}
+      double GV[PINMPC_NMAX * 16];   // w_k, R (u_k - u_ref_k), g_k
     } c;
   };
-  double xv[NX], xn[NX];
   double Qd[NX], Rd[NU]; // diagonal weights of the problem
+  // inputs of each contact-stage whose pivot is a unit vector (see build_eq)
+  uint8_t unit[2 * PINMPC_NMAX_LONG];
 };
 
 // The per-stage 16-wide vectors of the rollout and the costate chain: in LDS
@@ -314,18 +317,10 @@ __device__ inline d4 mmT(d4 u, d4 v, d4 acc) {
   return acc;
 }
 
-// Column-VC vector of a tile to / from memory (len entries).
-__device__ inline void vec_store(gd v, int len, d4 t) {
-  if (tj() == VC) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (4 * q + tg() < len) v[4 * q + tg()] = t[q];
-  }
-}
 __device__ inline d4 sel(bool c, d4 a) { return c ? a : zero4(); }
 
 // Stage blocks in memory hold only the entries a tile can have nonzero (the
-// layouts are listed with refine_block_doubles).  A map packs, for each of a
+// layouts are listed with refine_block_doubles).  For the value function a map packs, for each of a
 // lane's four tile items, the item's offset in the block (in doubles, 8 bits
 // per item) or 255 for an item the block does not hold.  Blocks are read and
 // written with buffer instructions whose range is the block: an item mapped
@@ -334,39 +329,16 @@ __device__ inline d4 sel(bool c, d4 a) { return c ? a : zero4(); }
 // fetch issued a stage ahead thus needs no masking and stores need no
 // branches.
 constexpr uint32_t NOT_HELD = 255;
-static_assert(TS_T < 255 && TS_K < 255 && TS_L < 255 && TS_H < 255 && TS_S < 255,
-              "a stage block must end before the out-of-range offset");
+static_assert(TS_S < 255, "the block must end before the out-of-range offset");
 __device__ inline uint32_t pack_map(const int o[4]) {
   uint32_t m = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) m |= (uint32_t)o[q] << (8 * q);
   return m;
 }
-// rows x cols, row-major
-__device__ inline uint32_t map_rect(int rows, int cols) {
-  int o[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + tg(), c = tj();
-    o[q] = (r < rows && c < cols) ? r * cols + c : (int)NOT_HELD;
-  }
-  return pack_map(o);
-}
-// stage input block: the two contacts' 6 x 6 diagonal blocks and offsets
-__device__ inline uint32_t map_T() {
-  int o[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + tg(), c = tj();
-    const bool blk = r < NU && c < NU && (r / 6) == (c / 6);
-    const bool off = r < NU && c == VC;
-    o[q] = blk ? (r / 6) * 42 + (r % 6) * 6 + (c % 6)
-               : (off ? (r / 6) * 42 + 36 + (r % 6) : (int)NOT_HELD);
-  }
-  return pack_map(o);
-}
-// value function: S symmetric (13 x 13, lower triangle), s in column VC;
-// `store` selects the lower triangle only, a load reads both triangles
+// value function: S symmetric (13 x 13, lower triangle) and s; `store` selects
+// the lower triangle and column VC, a load fills both triangles, column VC and
+// row VC
 __device__ inline uint32_t map_S(bool store) {
   int o[4];
 #pragma unroll
@@ -374,8 +346,8 @@ __device__ inline uint32_t map_S(bool store) {
     const int r = 4 * q + tg(), c = tj();
     const int hi = r > c ? r : c, lo = r > c ? c : r;
     const bool sym = r < NX && c < NX && (!store || c <= r);
-    const bool vec = r < NX && c == VC;
-    o[q] = sym ? hi * (hi + 1) / 2 + lo : (vec ? NX * (NX + 1) / 2 + r : (int)NOT_HELD);
+    const bool vec = hi == VC && lo < NX && (!store || c == VC);
+    o[q] = sym ? hi * (hi + 1) / 2 + lo : (vec ? NX * (NX + 1) / 2 + lo : (int)NOT_HELD);
   }
   return pack_map(o);
 }
@@ -418,73 +390,171 @@ __device__ inline void st_map(gd base, int doubles, uint32_t map, d4 t) {
   }
 }
 
-// Stage input blocks, written in parallel over (stage, contact): each lane
-// computes one contact's 6 x 6 diagonal block and its six offsets (column VC
-// of the tile) in registers and stores them, whole, into the stage's block
-// (zero for a swing contact).
-//   equality passes: the face projector P (block diagonal) and the face
-//                    offset c of the contact;
-//   Newton steps:    the input Hessian R + G^T diag(z/s) G and the linear term
-//                    R (u - u_ref) + G^T c_rows of a stance contact (zero
-//                    for a swing contact).
-// Interior-point rows are scaled by sc (mg force rows, tau_max moment rows):
-// row weight z / (s sc^2), linear coefficient (z + (-rc + z rp) / s) / sc with
-// rp = (g u - h) / sc + s.
-__device__ void build_tiles(const Ctx& C, bool newton, gcd rcvec, int kn) {
-  const int lane = lane_id();
-  const int rs = 2 * C.n;   // stride of a row over the contact-stages
-  for (int e = lane; e < kn * 2; e += W64) {
+// ------------------------------------------------------------ stage inputs
+//
+// Written in parallel over (stage, contact) before a recursion: each lane forms
+// its contact's force block, moment diagonals and vector in registers and stores
+// them whole (18 doubles, as 16-byte pairs).
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// One contact's block: m the 3 x 3 force block, d the moment diagonals, v the
+// vector.
+struct InputBlock {
+  double m[3][3], d[3], v[6];
+};
+__device__ inline void store_block(gd base, const InputBlock& t) {
+  GMEM d2* p = (GMEM d2*)base;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    p[2 * a] = d2{t.m[a][0], t.m[a][1]};
+    p[2 * a + 1] = d2{t.m[a][2], t.v[a]};
+    p[6 + a] = d2{t.d[a], t.v[3 + a]};
+  }
+}
+
+enum class Mode { EQ, NEWTON };
+
+// Inputs of a stage that the projector removes exactly (a zero column): every
+// input of a swing contact; on an equality pass also the force of an apex face,
+// the components that the normal-force bound fixes and each moment at its bound.
+// For those, the stage system [H | Hwx | hw] has exactly e_j as row and column j,
+// and its elimination skips them (bitwise the same result).  One byte per
+// contact-stage, in LDS.
+__device__ inline uint32_t unit_bits(int code) {
+  uint32_t m = 0;
+  if ((code & 31) == FACE_APEX) m = 7;
+  else if (code & 16) m = 4u | ((code & 3) ? 1u : 0u) | ((code & 12) ? 2u : 0u);
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if (((code >> (8 + a)) & 1) || ((code >> (11 + a)) & 1)) m |= 8u << a;
+  return m;
+}
+
+// Equality passes, stages 0..kn-1: T the face projector P and point c of each
+// contact, T2 the terms P R P + I - P and P R (c - u_ref) of the stage's
+// quadratic that need no value function.
+__device__ inline void build_eq(const Ctx& C, uint8_t* unit, int kn) {
+  for (int e = lane_id(); e < kn * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
-    gd base = C.rT + (size_t)k * TS_T + i * 42;
-    double P6[6][6], c6[6];
+    InputBlock t, t2;
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-      c6[a] = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      t.d[a] = 0.0;
+      t2.d[a] = 1.0;
 #pragma unroll
-      for (int b = 0; b < 6; ++b) P6[a][b] = 0.0;
-    }
-    if (C.contact[k * 2 + i]) {
-      if (!newton) {
-        face_affine(C.faces[k * 2 + i], C, P6, c6);
-      } else {
-        double u[6];
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-          const int jj = 6 * i + a;
-          u[a] = C.ru[k * NU + jj];
-          const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
-          P6[a][a] = C.R[jj];
-          c6[a] = C.R[jj] * (u[a] - ur);
-        }
-#pragma unroll
-        for (int row = 0; row < NROW; ++row) {
-          double gr[6], h;
-          wrench_row(row, C.mu, C.fz, C.tm, gr, &h);
-          const double isc = (row < 5) ? C.img : C.itm;
-          double gu = 0.0;
-#pragma unroll
-          for (int a = 0; a < 6; ++a) gu += gr[a] * u[a];
-          const double s = C.rs[row * rs + e], z = C.rz[row * rs + e];
-          const double is = recip(s);
-          const double rp = fma(gu - h, isc, s);
-          const double w = z * is * (isc * isc);
-          const double cr = (z + (z * rp - rcvec[row * rs + e]) * is) * isc;
-#pragma unroll
-          for (int a = 0; a < 6; ++a) {
-            c6[a] += gr[a] * cr;
-#pragma unroll
-            for (int b = 0; b < 6; ++b) P6[a][b] += w * gr[a] * gr[b];
-          }
-        }
+      for (int b = 0; b < 3; ++b) {
+        t.m[a][b] = 0.0;
+        t2.m[a][b] = a == b ? 1.0 : 0.0;
       }
     }
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
+    for (int a = 0; a < 6; ++a) t.v[a] = t2.v[a] = 0.0;
+    uint32_t u = 0x3F;
+    if (C.contact[e]) {
+      const int code = C.faces[e];
+      u = unit_bits(code);
+      double P[6][6], c[6], R[6], rho[6];
+      face_affine(code, C, P, c);
 #pragma unroll
-      for (int b = 0; b < 6; ++b) base[a * 6 + b] = P6[a][b];
-      base[36 + a] = c6[a];
+      for (int a = 0; a < 6; ++a) {
+        R[a] = C.R[6 * i + a];
+        const double ur = C.u_ref ? (double)C.u_ref[k * NU + 6 * i + a] : 0.0;
+        rho[a] = R[a] * (c[a] - ur);
+        t.v[a] = c[a];
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        double v = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          t.m[a][b] = P[a][b];
+          double x = (a == b ? 1.0 : 0.0) - P[a][b];
+#pragma unroll
+          for (int l = 0; l < 3; ++l) x += P[a][l] * R[l] * P[l][b];
+          t2.m[a][b] = x;
+          v += P[a][b] * rho[b];
+        }
+        t2.v[a] = v;
+        const double p = P[3 + a][3 + a];
+        t.d[a] = p;
+        t2.d[a] = p * R[3 + a] * p + 1.0 - p;
+        t2.v[3 + a] = p * rho[3 + a];
+      }
     }
+    unit[e] = (uint8_t)u;
+    store_block(C.rT + (size_t)e * 18, t);
+    store_block(C.rT2 + (size_t)e * 18, t2);
   }
+}
+
+// Newton steps, all N stages: T the input Hessian R + G^T diag(z/s) G and the
+// linear term R (u - u_ref) + G^T c_rows of each stance contact at the affine
+// target s z (rows scaled by sc: weight z / (s sc^2), coefficient
+// (z + (-s z + z rp) / s) / sc = z rp / (s sc), rp = (g u - h) / sc + s), the
+// identity and zero for a swing contact; and the state cost gradients
+// q_k = Q (x_{k+1} - r_k).
+__device__ inline void build_newton(const Ctx& C, uint8_t* unit, int N) {
+  const int rs = 2 * C.n;
+  for (int e = lane_id(); e < N * 2; e += W64) {
+    const int k = e >> 1, i = e & 1;
+    InputBlock t;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      t.d[a] = 1.0;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) t.m[a][b] = a == b ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) t.v[a] = 0.0;
+    uint32_t ub = 0x3F;
+    if (C.contact[e]) {
+      ub = 0;
+      double u[6];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) {
+        const int jj = 6 * i + a;
+        u[a] = C.ru[k * NU + jj];
+        const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
+        if (a < 3) t.m[a][a] = C.R[jj];
+        else t.d[a - 3] = C.R[jj];
+        t.v[a] = C.R[jj] * (u[a] - ur);
+      }
+#pragma unroll
+      for (int row = 0; row < NROW; ++row) {
+        double gr[6], h;
+        wrench_row(row, C.mu, C.fz, C.tm, gr, &h);
+        const double isc = (row < 5) ? C.img : C.itm;
+        double gu = 0.0;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) gu += gr[a] * u[a];
+        const double s = C.rs[row * rs + e], z = C.rz[row * rs + e];
+        const double rp = fma(gu - h, isc, s), zs = z * recip(s);
+        const double w = zs * (isc * isc), cr = zs * rp * isc;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) t.v[a] += gr[a] * cr;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          t.d[a] += w * gr[3 + a] * gr[3 + a];
+#pragma unroll
+          for (int b = 0; b < 3; ++b) t.m[a][b] += w * gr[a] * gr[b];
+        }
+      }
+    }
+    unit[e] = (uint8_t)ub;
+    store_block(C.rT + (size_t)e * 18, t);
+  }
+  for (int e = lane_id(); e < N * NX; e += W64)
+    C.rq[e] = C.Q[e % NX] * (C.rx[NX + e] - (double)C.x_ref[e]);
+}
+
+// The stage inputs of a recursion over stages 0..kn-1, visible to every lane.
+template <Mode mode>
+__device__ inline void build(const Ctx& C, Sh& sh, int kn) {
+  gsync();
+  if constexpr (mode == Mode::EQ) build_eq(C, sh.unit, kn);
+  else build_newton(C, sh.unit, kn);
+  gsync();
 }
 
 // ------------------------------------------------------ Riccati recursion
@@ -497,56 +567,36 @@ __device__ void build_tiles(const Ctx& C, bool newton, gcd rcvec, int kn) {
 //   EQ:     the equality-constrained tracking problem of the faces
 //           (q = -Q r, rho = -R u_ref, R' = R, e from the data);
 //   NEWTON: the interior-point Newton step, x_0 = 0, e = 0,
-//           q = Q (x_{k+1} - r), R' = R + G^T diag(z/s) G,
-//           rho from the stage tile, P = stance mask, c = 0.
+//           q = Q (x_{k+1} - r), R' = R + G^T diag(z/s) G, P the stance mask,
+//           c = 0.
 // Per stage, with W = S + Q, Bp = B P and d = B c + e:
 //   H = P R' P + Bp^T W Bp + (I - P),  Hwx = Bp^T W A,
 //   hw = P (R' c + rho) + Bp^T (W d + q + s),
 //   K = -H^{-1} Hwx, kap = -H^{-1} hw,
 //   S <- A^T W A + Hwx^T K,  s <- A^T (W d + q + s) + Hwx^T kap.
-// With factor = false only the linear part is recomputed from the stored
-// H^{-1}, Hwx and K (second right-hand side of the same Newton matrix).
 // EQ keeps each stage's value function [S_k | s_k] (symmetrised, as used);
 // stage k's factors depend on the faces of stages k..N-1 only, so a pass
 // whose faces differ from the previous pass's only before stage ktop
-// rebuilds the tiles and reruns the backward recursion for stages
+// rebuilds the inputs and reruns the backward recursion for stages
 // 0..ktop-1 only, starting from the kept [S_ktop | s_ktop]; the result is
 // bitwise that of the whole recursion.
-
-enum class Mode { EQ, NEWTON };
+//
+// The tiles are homogeneous: row and column VC carry the linear terms, so that
+// the matrix products carry the vectors along.  With
+//   Wt = [[W, q + s], [(q + s)^T, 0]]   and   D1 = [Bp | 0 | d], 1 at (VC, VC)
+// D3 = Wt^T D1 holds W Bp, in row VC Bp^T (q + s) and in column VC W d + q + s;
+// then D3^T D1 + T2 = [H | 0 | hw] and D3^T A = Hwx with nothing left to add.
+// FP64 vector instructions and FP64 matrix instructions do not overlap on this
+// chip (a group of one matrix product of 64 cycles and 12 multiply-adds takes
+// 134 cycles in one wave), so a stage costs the sum of both and is made of as
+// few of either as possible: 26 (NEWTON: 23) matrix instructions.
 
 // Raw stage data.  The stage loops fetch the next stage's data a whole stage
-// ahead; the fetch only gathers (addresses clamped into the stage's arrays)
-// and the conversion and masking happen when the stage is used.  Before the
-// next fetch and the deferred stores are issued, everything the stage uses is
-// pinned in registers, so no wait on memory falls inside a stage's compute
-// (loads and stores share one counter here: waiting for any access would
-// otherwise mean waiting for all of them).
+// ahead.  All stage arrays are read and written through buffer instructions:
+// each lane's offset within a stage is fixed for the whole loop, the stage is a
+// scalar offset, and an entry that a tile does not hold has an offset past the
+// end, so it reads as zero (and its store is dropped) without masks or branches.
 __device__ inline int clampi(int v, int hi) { return v < hi ? v : hi; }
-__device__ inline void gather(gcf M, bool transposed, int rows, int cols, float m[4]) {
-  const int g = tg(), j = tj();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + g;
-    m[q] = transposed ? M[clampi(j, rows - 1) * cols + clampi(r, cols - 1)]
-                      : M[clampi(r, rows - 1) * cols + clampi(j, cols - 1)];
-  }
-}
-__device__ inline void gatherv(gcf v, int len, float m[4]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) m[q] = v[clampi(4 * q + tg(), len - 1)];
-}
-__device__ inline d4 cook(const float m[4], bool transposed, int rows, int cols) {
-  const int g = tg(), j = tj();
-  d4 t;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + g;
-    const bool ok = transposed ? (j < rows && r < cols) : (r < rows && j < cols);
-    t[q] = ok ? (double)m[q] : 0.0;
-  }
-  return t;
-}
 __device__ inline void pin(const d4& t) {
   asm volatile("" ::"v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
 }
@@ -563,45 +613,431 @@ __device__ inline T uni(T p) {
   return (T)(((uint64_t)hi << 32) | lo);
 }
 
-// Stance mask tile (identity on the inputs of stance contacts).
-__device__ inline d4 mask_tile(int stance) {
-  const int g = tg(), j = tj();
-  const double m = (j < NU && stance) ? 1.0 : 0.0;
-  d4 p;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) p[q] = (4 * q + g == j) ? m : 0.0;
-  return p;
+typedef unsigned int u3 __attribute__((ext_vector_type(3)));
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+constexpr int OOB = 0x40000000;   // an offset past the end of every array
+template <class P>
+__device__ inline __amdgpu_buffer_rsrc_t rsrc(P base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+}
+__device__ inline float ldf(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
+}
+__device__ inline double ldd(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+  const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+  double v;
+  __builtin_memcpy(&v, &w, 8);
+  return v;
+}
+__device__ inline void ldf3(__amdgpu_buffer_rsrc_t r, int off, int soff, float v[3]) {
+  const u3 w = __builtin_amdgcn_raw_buffer_load_b96(r, off, soff, 0);
+  __builtin_memcpy(v, &w, 12);
+}
+__device__ inline void ldf4(__amdgpu_buffer_rsrc_t r, int off, int soff, float v[4]) {
+  const u4 w = __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0);
+  __builtin_memcpy(v, &w, 16);
+}
+__device__ inline void ldd2(__amdgpu_buffer_rsrc_t r, int off, int soff, double v[2]) {
+  const u4 w = __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0);
+  __builtin_memcpy(v, &w, 16);
+}
+__device__ inline void std1(__amdgpu_buffer_rsrc_t r, int off, int soff, double v) {
+  u2 w;
+  __builtin_memcpy(&w, &v, 8);
+  __builtin_amdgcn_raw_buffer_store_b64(w, r, off, soff, 0);
 }
 
-struct BackRaw {
-  float a[4], bt[4], xr[4], ev[4], ur[4];
-  double xn[4];
-  d4 T, HI, HX;
-  int ct;
-  int c0, c1, f0, f1;   // the stage's contact flags and face codes (uniform)
+// Byte offset of tile entry (r, c) in an input block T, or OOB.
+__device__ inline int t_offset(int r, int c) {
+  const int i = r / 6, a = r % 6, b = c % 6;
+  int o = -1;
+  if (r < NU && c < NU && c / 6 == i) {
+    if (a < 3 && b < 3) o = 4 * a + b;
+    else if (a >= 3 && a == b) o = 12 + 2 * (a - 3);
+  } else if (r < NU && c == VC) {
+    o = a < 3 ? 4 * a + 3 : 13 + 2 * (a - 3);
+  }
+  return o < 0 ? OOB : (i * 18 + o) * 8;
+}
+
+template <Mode mode>
+struct BackRaw;
+template <>
+struct BackRaw<Mode::EQ> {
+  float a[4], b[3], xr[4], ev[4];
+  double T[3], T2[3];
+};
+template <>
+struct BackRaw<Mode::NEWTON> {
+  float a[4], b[4];
+  double q[4], T[3];
 };
 
-// Inputs of a stage that the projector P_k removes exactly (P_k's column is
-// zero): every input of a swing contact; on an equality pass also the force of
-// an apex face and each moment component fixed at its bound.  For those, the
-// stage system [H | Hwx | hw] has exactly e_j as row and column j.
-__device__ inline uint32_t null_inputs(int c0, int c1, int f0, int f1, bool newton) {
-  uint32_t m = 0;
+// Weights that make a homogeneous tile exactly symmetric from itself and its
+// transpose: the average on the 13 x 13 block, column VC as it is, row VC its
+// transpose, zero elsewhere.
+struct SymWeights {
+  d4 own, other;
+};
+__device__ inline SymWeights sym_weights() {
+  SymWeights w;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = i ? c1 : c0, f = i ? f1 : f0;
-    if (!c) {
-      m |= 0x3Fu << (6 * i);
-    } else if (!newton) {
-      if ((f & 31) == FACE_APEX) m |= 7u << (6 * i);
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        if (((f >> (8 + a)) & 1) || ((f >> (11 + a)) & 1)) m |= 1u << (6 * i + 3 + a);
-    }
+  for (int q = 0; q < 4; ++q) {
+    const int r = 4 * q + tg(), c = tj();
+    w.own[q] = (r < NX && c < NX) ? 0.5 : ((c == VC && r < NX) ? 1.0 : 0.0);
+    w.other[q] = (r < NX && c < NX) ? 0.5 : ((r == VC && c < NX) ? 1.0 : 0.0);
   }
-  return m;
+  return w;
+}
+// S so symmetrised (its rounding is not symmetric, and an asymmetric part is
+// carried back through the open-loop A and grows along the horizon).
+__device__ inline d4 symmetrize(d4 S, const SymWeights& w, double* buf) {
+  const int g = tg(), j = tj();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) buf[(4 * q + g) * 17 + j] = S[q];
+  wsync();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) S[q] = fma(w.other[q], buf[j * 17 + 4 * q + g], w.own[q] * S[q]);
+  wsync();
+  return S;
 }
 
+// c[r] += (c[r] of lane P of this 16-lane row) * s for r in [LO, HI), the
+// leading wait states as in fmac_row_bcast12.
+template <int P, int LO, int HI>
+__device__ inline void fmac_rows(double (&c)[12], double s) {
+  if constexpr (LO < HI) asm volatile("s_nop 1");
+#pragma unroll
+  for (int r = LO; r < HI; ++r)
+    asm volatile(
+        "v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "+v"(c[r])
+        : "v"(s), "i"(P));
+  // the next pivot is broadcast from row P + 1: no closer than two wait states
+  if constexpr (LO == P + 1 && HI - LO <= 2) asm volatile("s_nop 1");
+}
+
+// Gauss-Jordan elimination without pivoting of a 12-row system whose leading
+// 12 x 12 block sits in lanes 0..11 of every 16-lane row (column c in lane c of
+// each row, the rows identical) and whose right-hand sides occupy the other
+// lanes.  Bit p of the wave-uniform `unit` marks a pivot whose row and column are
+// exactly the unit vector e_p: its step changes nothing and is skipped.
+template <int p = 0>
+__device__ inline void eliminate(double (&col)[12], uint32_t unit) {
+  if constexpr (p < 12) {
+    if (!((unit >> p) & 1u)) {
+      const double t = col[p] * recip(row_bcast<p>(col[p]));
+      fmac_rows<p, 0, p>(col, -t);
+      fmac_rows<p, p + 1, 12>(col, -t);
+      col[p] = t;
+    }
+    eliminate<p + 1>(col, unit);
+  }
+}
+// The same with the system's factors kept: forward elimination only
+// (H = U^T D U, U unit upper), lane c < 12 ending with column c of U above
+// 1 / d_c; the right-hand sides hold D^-1 U^-T b.
+template <int p = 0>
+__device__ inline void factor(double (&col)[12], int hc, uint32_t unit) {
+  if constexpr (p < 12) {
+    if (!((unit >> p) & 1u)) {
+      const double rd = recip(row_bcast<p>(col[p]));
+      const double t = col[p] * rd;
+      fmac_rows<p, p + 1, 12>(col, -t);
+      col[p] = hc == p ? rd : t;
+    }
+    factor<p + 1>(col, hc, unit);
+  }
+}
+// ... and back substitution of the right-hand sides by U (the factor's lanes
+// take a zero factor and keep their entries).
+template <int p = 11>
+__device__ inline void back_substitute(double (&col)[12], bool is_h, uint32_t unit) {
+  if constexpr (p > 0) {
+    if (!((unit >> p) & 1u)) fmac_rows<p, 0, p>(col, is_h ? 0.0 : -col[p]);
+    back_substitute<p - 1>(col, is_h, unit);
+  }
+}
+
+// Backward recursion over stages k_hi - 1 down to k_lo from the value
+// function Ss of x_{k_hi} (S in rows and columns 0..12, s in row and column
+// VC); returns the value function of x_{k_lo}.  It stores each stage's gains
+// and feedforward (and, for equality passes, its value function; for Newton
+// steps the factors of H).
+// ELEM: the chunk summary of the associative scan instead (see below): the
+// recursion starts from a zero value at x_{k_hi}, stores nothing and also
+// composes the closed-loop affine map TE (transposed, offset in row 13,
+// (13, 13) = 1) and the reachability term CE of the chunk.
+template <Mode mode, bool ELEM>
+__device__ __attribute__((always_inline)) inline d4 backward(const Ctx& C, ShR& sr,
+                                                             const uint8_t* unit, int k_lo,
+                                                             int k_hi, d4 Ss, d4* TEo, d4* CEo) {
+  const int lane = lane_id(), g = tg(), j = tj();
+  constexpr bool newton = (mode == Mode::NEWTON);
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rX = rsrc(uni(C.x_ref), N * NX * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
+  const auto rQ = rsrc(uni(C.rq), N * NX * 8);
+  const auto rT = rsrc(uni(C.rT), N * TS_T * 8), rT2 = rsrc(uni(C.rT2), N * TS_T * 8);
+  const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rF = rsrc(uni(C.rF), N * TS_F * 8);
+  const gd prS = uni(C.rS);
+  // this lane's offsets within a stage: rows 4q + g of A and B^T (EQ) or B,
+  // of column VC (and, as item 3 of group 1, row VC) of the vectors, of T, K, F
+  const int oA = j < NX ? (g * NX + j) * 4 : OOB;
+  const int oA3 = (g == 0 && j < NX) ? (12 * NX + j) * 4 : OOB;
+  const int oB = newton ? (j < NU ? (g * NU + j) * 4 : OOB) : (j < NX ? (j * NU + g) * 4 : OOB);
+  const int oB3 = (newton && g == 0 && j < NU) ? (12 * NU + j) * 4 : OOB;
+  const int oV = j == VC ? g : OOB / 8;
+  const int oV3 = (g == 0 && j == VC) ? 12 : ((g == 1 && j < NX) ? j : OOB / 8);
+  const int oE3 = (g == 0 && j == VC) ? 48 : OOB;
+  int oT[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) oT[q] = t_offset(4 * q + g, j);
+  const int oK = j <= VC ? (g * (NX + 1) + j) * 8 : OOB;
+  const int oF = j < NU ? (g * NU + j) * 8 : OOB;
+  const uint32_t mS = map_S(true);
+  // Q on the diagonal, and where q = -Q r lies (column and row VC)
+  d4 Qd, Qv;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = 4 * q + g;
+    Qd[q] = (r == j && j < NX) ? C.Q[clampi(j, NX - 1)] : 0.0;
+    Qv[q] = (j == VC && r < NX) ? C.Q[clampi(r, NX - 1)]
+                                : ((r == VC && j < NX) ? C.Q[clampi(j, NX - 1)] : 0.0);
+  }
+  const SymWeights sw = sym_weights();
+  const double one = (g == 1 && j == VC) ? 1.0 : 0.0;   // (VC, VC) as item 3
+  auto fetch = [&](int k, BackRaw<mode>& s) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.a[q] = ldf(rA, oA + q * 4 * NX * 4, k * (NX * NX * 4));
+    s.a[3] = ldf(rA, oA3, k * (NX * NX * 4));
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      s.b[q] = ldf(rB, oB + q * (newton ? 4 * NU * 4 : 16), k * (NX * NU * 4));
+    if constexpr (newton) {
+      s.b[3] = ldf(rB, oB3, k * (NX * NU * 4));
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s.q[q] = ldd(rQ, oV * 8 + q * 32, k * (NX * 8));
+      s.q[3] = ldd(rQ, oV3 * 8, k * (NX * 8));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        s.xr[q] = ldf(rX, oV * 4 + q * 16, k * (NX * 4));
+        s.ev[q] = ldf(rE, oV * 4 + q * 16, k * (NX * 4));
+        s.T2[q] = ldd(rT2, oT[q], k * (TS_T * 8));
+      }
+      s.xr[3] = ldf(rX, oV3 * 4, k * (NX * 4));
+      s.ev[3] = ldf(rE, oE3, k * (NX * 4));
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.T[q] = ldd(rT, oT[q], k * (TS_T * 8));
+  };
+
+  BackRaw<mode> raw;
+  fetch(k_hi > k_lo ? k_hi - 1 : k_lo, raw);
+  d4 TE = zero4(), CE = zero4();
+  if constexpr (ELEM) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) TE[q] = (4 * q + g == j && j <= VC) ? 1.0 : 0.0;
+  }
+  for (int k = k_hi - 1; k >= k_lo; --k) {
+    // this stage's data
+    d4 At, D1, Wt, H0 = zero4();   // H0: the part of [H | hw] without W
+#pragma unroll
+    for (int q = 0; q < 4; ++q) At[q] = (double)raw.a[q];
+    uint32_t ub;
+    {
+      const uint32_t u0 = unit[2 * k], u1 = unit[2 * k + 1];
+      ub = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u0 | (u1 << 6)));
+    }
+    if constexpr (newton) {
+      // B with the swing contacts' columns zero
+      const bool keep = j < NU && !((ub >> j) & 1u);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        D1[q] = keep ? (double)raw.b[q] : 0.0;
+        Wt[q] = Ss[q] + (Qd[q] + raw.q[q]);
+      }
+      D1[3] += one;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) H0[q] = raw.T[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        D1[q] = (double)raw.ev[q];
+        Wt[q] = Ss[q] + fma(-Qv[q], (double)raw.xr[q], Qd[q]);
+      }
+      D1[3] += one;
+      // [B P | 0 | B c + e]
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        D1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)raw.b[q], raw.T[q], D1, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) H0[q] = raw.T2[q];
+    }
+    if constexpr (ELEM) {
+      if (k == k_hi - 1) Wt = zero4();   // a zero value at x_{k_hi}
+    }
+    pin(At); pin(D1); pin(Wt); pin(H0);
+    pin_memory();
+    if (k > k_lo) fetch(k - 1, raw);
+
+    const d4 D3 = mmT<4>(Wt, D1, zero4());   // [W Bp | 0 | W d + q + s], row VC Bp^T (q + s)
+    const d4 D4 = mmT<4>(D3, D1, H0);        // [H | 0 | hw]
+    const d4 D5 = mmT<4>(D3, At, zero4());   // Hwx
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g;
+      if (j < NU) sr.G[j * GC + r] = D4[q];
+      sr.G[(NU + j) * GC + r] = -(j == VC ? D4[q] : D5[q]);
+    }
+    // A^T [W A | W d + q + s], the part of the value function without gains
+    d4 D2 = mmT<4>(Wt, At, zero4());
+#pragma unroll
+    for (int q = 0; q < 4; ++q) D2[q] = j == VC ? D3[q] : D2[q];
+    const d4 SA = mmT<4>(At, D2, zero4());
+    wsync();
+    // Elimination of [H | -Hwx | -hw] (H is SPD: no pivoting): lane 16 R + c
+    // holds column c of H (c < NU, the same in every row R) or right-hand side
+    // 4 R + c - NU; afterwards the right-hand sides are [K | kap].  Newton steps
+    // keep the factors of H for the corrector instead of reducing H to I.
+    static_assert(NU == 12, "row elimination is written for 12 inputs");
+    const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU;
+    const bool is_h = hc < NU;
+    double col[NU];
+    double* gc = sr.G + (is_h ? hc : NU + rhs) * GC;
+#pragma unroll
+    for (int r = 0; r < NU; ++r) col[r] = gc[r];
+    wsync();
+    if constexpr (ELEM) {
+      double icol[NU];
+#pragma unroll
+      for (int r = 0; r < NU; ++r) icol[r] = is_h ? col[r] : ((r == rhs) ? 1.0 : 0.0);
+      gj_rows2(col, icol, ub);
+      if (!is_h && rhs < NU) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) sr.HI[rhs * GC + r] = icol[r];
+      }
+    } else if constexpr (newton) {
+      factor(col, hc, ub);
+      back_substitute(col, is_h, ub);
+    } else {
+      eliminate(col, ub);
+    }
+    if (newton ? (!is_h || lane < NU) : !is_h) {
+#pragma unroll
+      for (int r = 0; r < NU; ++r) gc[r] = col[r];
+    }
+    wsync();
+    d4 KK = zero4();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) KK[q] = sr.G[(NU + j) * GC + 4 * q + g];   // [K | kap]
+    if constexpr (!ELEM) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) std1(rK, oK + q * 4 * (NX + 1) * 8, k * (TS_K * 8), KK[q]);
+      if constexpr (newton) {
+        // U above and below the diagonal, 1 / d on it
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const int r = 4 * q + g, c = clampi(j, NU - 1);
+          const int hi = r > c ? r : c, lo = r > c ? c : r;
+          std1(rF, oF + q * 4 * NU * 8, k * (TS_F * 8), sr.G[hi * GC + lo]);
+        }
+      }
+    } else {
+      d4 HI = zero4(), BpT = zero4(), Ah;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sr.ST[(4 * q + g) * 17 + j] = D1[q];
+      wsync();
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int r = 4 * q + g;
+        HI[q] = (j < NU) ? sr.HI[clampi(j, NU - 1) * GC + r] : 0.0;
+        BpT[q] = sr.ST[j * 17 + r];
+      }
+      wsync();
+      // the stage's closed-loop map [A + Bp K | d + Bp kap] with a 1 at
+      // (13, 13), composed after the chunk's map; the reachability term
+      // grows by A_E Bp H^-1 Bp^T A_E^T (A_E before the composition)
+      const d4 LK = mmT<3>(BpT, KK, zero4());    // [Bp K | Bp kap]
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        Ah[q] = (j < NX) ? At[q] + LK[q] : ((j == VC) ? LK[q] + D1[q] : 0.0);
+      const d4 ZT = mmT<4>(D1, TE, zero4());     // (A_E Bp)^T in rows 0..11
+      const d4 Y = mmT<3>(HI, ZT, zero4());      // H^-1 (A_E Bp)^T
+      CE = mmT<3>(ZT, Y, CE);
+      TE = mmT<4>(Ah, TE, zero4());
+    }
+    // S = A^T W A + Hwx^T K, s = A^T (W d + q + s) + Hwx^T kap
+    Ss = symmetrize(mmT<3>(D5, KK, SA), sw, sr.ST);
+    if constexpr (mode == Mode::EQ && !ELEM) st_map(prS + (size_t)k * TS_S, TS_S, mS, Ss);
+  }
+  if constexpr (ELEM) {
+    *TEo = TE;
+    *CEo = CE;
+  }
+  return Ss;
+}
+
+// --------------------------------------------------- chains over the horizon
+//
+// The rollout, the costates and the corrector's vector recursion are chains of
+// 13-vector products y = M x, one stage after the other.  Every 16-lane row g
+// holds the whole vector (entry j in lane j, the rows identical) and takes the
+// entries 3g .. 3g + 3 of the contraction (3g + 1 .. 3g + 3 for g > 0): lane j
+// of row g holds those of M's row j, so a stage loads each matrix entry once
+// into the wave, as one wide load where they are consecutive (a matrix row held
+// by every lane was 13 loads, each served four times over: the loads, about 15
+// cycles each in the one address unit of 8 waves, then bound the chains).  The
+// row's vector entries reach its lanes by DPP broadcast from a copy of x turned
+// by 3g lanes, and the partial sums of the four rows meet through the row and
+// half-wave swaps.
+
+// Row g's lanes turned by 3 g: lane i takes lane i + 3 g of its row.
+__device__ inline double turn_rows(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  uint32_t w[2] = {(uint32_t)b, (uint32_t)(b >> 32)};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int x = (int)w[h];
+    int r = __builtin_amdgcn_update_dpp(x, x, 0x103, 0x2, 0xF, false);   // row_shl:3, row 1
+    r = __builtin_amdgcn_update_dpp(r, x, 0x106, 0x4, 0xF, false);       // row_shl:6, row 2
+    r = __builtin_amdgcn_update_dpp(r, x, 0x109, 0x8, 0xF, false);       // row_shl:9, row 3
+    w[h] = (uint32_t)r;
+  }
+  return __builtin_bit_cast(double, ((uint64_t)w[1] << 32) | w[0]);
+}
+// s + sum_q (turned vector's lane q of the row) * m[q], q = 0..3 (0..2).  The
+// leading wait states separate the DPP reads from the vector write of t.
+__device__ inline double dot4(double t, const double (&m)[4], double s) {
+  asm volatile("s_nop 1\n"
+               "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               : "+v"(s)
+               : "v"(t), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]));
+  return s;
+}
+__device__ inline double dot3(double t, const double (&m)[3], double s) {
+  asm volatile("s_nop 1\n"
+               "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               : "+v"(s)
+               : "v"(t), "v"(m[0]), "v"(m[1]), "v"(m[2]));
+  return s;
+}
+// The four rows' partial sums, added in every lane.
+__device__ inline double row_total(double s) {
+  double a, b;
+  swap_rows<false>(s, a, b);
+  s = a + b;
+  swap_rows<true>(s, a, b);
+  return a + b;
+}
 // s + sum_r (v of lane r of this 16-lane row) * a[r], r = 0..12, over four
 // interleaved accumulators: the DPP row broadcast of v rides in each fused
 // multiply-add.  The leading two wait states separate the block's DPP reads
@@ -623,588 +1059,207 @@ __device__ inline double dot_row_bcast13(double v, const double (&a)[13], double
   return (s + s1) + (s2 + s3);
 }
 
-// s + sum_r (v of lane r of this 16-lane row) * a[r], r = 0..11, likewise.
-__device__ inline double dot_row_bcast12(double v, const double (&a)[12], double s) {
-  double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#define PINMPC_DOT(acc, r, ai) \
-  "v_fmac_f64_dpp %" #acc ", %4, %" #ai " row_newbcast:" #r " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
-  asm volatile("s_nop 1\n"
-               PINMPC_DOT(0, 0, 5) PINMPC_DOT(1, 1, 6) PINMPC_DOT(2, 2, 7) PINMPC_DOT(3, 3, 8)
-               PINMPC_DOT(0, 4, 9) PINMPC_DOT(1, 5, 10) PINMPC_DOT(2, 6, 11) PINMPC_DOT(3, 7, 12)
-               PINMPC_DOT(0, 8, 13) PINMPC_DOT(1, 9, 14) PINMPC_DOT(2, 10, 15)
-               PINMPC_DOT(3, 11, 16)
-               : "+v"(s), "+v"(s1), "+v"(s2), "+v"(s3)
-               : "v"(v), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]),
-                 "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]), "v"(a[10]), "v"(a[11]));
-#undef PINMPC_DOT
-  return (s + s1) + (s2 + s3);
-}
-
-// Backward recursion over stages k_hi - 1 down to k_lo from the value
-// function Ss of x_{k_hi} (S in columns 0..12, s in VC); returns the value
-// function of x_{k_lo}.  It stores each stage's gains and feedforward (and,
-// for equality passes, its value function; for Newton steps H^-1 and Hwx).
-// ELEM: the chunk summary of the associative scan instead (see below): the
-// recursion starts from a zero value at x_{k_hi}, stores nothing and also
-// composes the closed-loop affine map TE (transposed, offset in row 13,
-// (13, 13) = 1) and the reachability term CE of the chunk.
-template <Mode mode, bool factor, bool LONG, bool ELEM>
-__device__ __attribute__((always_inline)) inline d4 backward(const Ctx& C, ShR& sr, int k_lo,
-                                                             int k_hi, d4 Ss, d4* TEo, d4* CEo) {
-  static_assert(!ELEM || factor, "a chunk summary factors every stage");
+// Forward rollout after the backward recursion (all N stages): w = K x + kap,
+// x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w = w to
+// rounding: the gains lie in the range of the projector.)  VECK: kap_k from GV
+// (a corrector's) instead of the stored gains.  Stage data is fetched a ring of
+// stages ahead (unconditionally, so every path back to the loop head has issued
+// the same loads).
+template <Mode mode, bool LONG, bool VECK>
+__device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& sh) {
+  gsync();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
   const int lane = lane_id(), g = tg(), j = tj();
   constexpr bool newton = (mode == Mode::NEWTON);
-  const gcf pA = uni(C.A), pB = uni(C.B), pxr = uni(C.x_ref), pe = uni(C.e), pur = uni(C.u_ref);
-  const GMEM uint8_t* pct = uni(C.contact);
-  const GMEM int32_t* pfc = uni(C.faces);
-  const gd prT = uni(C.rT), prK = uni(C.rK), prL = uni(C.rL), prH = uni(C.rHwx), prS = uni(C.rS);
-  const gd prkap = uni(C.rkap), prx = uni(C.rx), pru = uni(C.ru), prdx = uni(C.rdx),
-           prdu = uni(C.rdu);
-  // the diagonal weights where this lane uses them
-  const double Qj = C.Q[clampi(j, NX - 1)];
-  d4 Qr, Rr;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    Qr[q] = C.Q[clampi(4 * q + g, NX - 1)];
-    Rr[q] = C.R[clampi(4 * q + g, NU - 1)];
-  }
-  // maps of the stage blocks this variant moves
-  const uint32_t mT = map_T();
-  const uint32_t mS = map_S(true);
-  const uint32_t mL = map_rect(NU, NU), mH = map_rect(NU, NX);
-  auto fetch = [&](int k, BackRaw& s) {
-    gather(pA + (size_t)k * NX * NX, false, NX, NX, s.a);
-    gather(pB + (size_t)k * NX * NU, true, NX, NU, s.bt);
-    gatherv(pxr + (size_t)k * NX, NX, s.xr);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      s.ev[q] = 0.f;
-      s.ur[q] = 0.f;
-      s.xn[q] = 0.0;
-    }
-    if (!newton && pe) gatherv(pe + (size_t)k * NX, NX, s.ev);
-    if (!newton && pur) gatherv(pur + (size_t)k * NU, NU, s.ur);
-    if (newton) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s.xn[q] = prx[(size_t)(k + 1) * NX + clampi(4 * q + g, NX - 1)];
-    }
-    s.T = ld_map(prT + (size_t)k * TS_T, TS_T, mT);
-    if (newton && !factor) {
-      s.HI = ld_map(prL + (size_t)k * TS_L, TS_L, mL);
-      s.HX = ld_map(prH + (size_t)k * TS_H, TS_H, mH);
-    } else {
-      s.HI = s.HX = zero4();
-    }
-    s.ct = newton ? (int)pct[k * 2 + (j < NU ? j / 6 : 0)] : 0;
-    s.c0 = __builtin_amdgcn_readfirstlane((int)pct[k * 2]);
-    s.c1 = __builtin_amdgcn_readfirstlane((int)pct[k * 2 + 1]);
-    s.f0 = newton ? 0 : __builtin_amdgcn_readfirstlane(pfc[k * 2]);
-    s.f1 = newton ? 0 : __builtin_amdgcn_readfirstlane(pfc[k * 2 + 1]);
-  };
-
-  BackRaw raw;
-  fetch(k_hi > k_lo ? k_hi - 1 : k_lo, raw);
-  d4 TE = zero4(), CE = zero4();
-  if constexpr (ELEM) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) TE[q] = (4 * q + g == j && j <= VC) ? 1.0 : 0.0;
-  }
-  for (int k = k_hi - 1; k >= k_lo; --k) {
-    // this stage's data
-    const d4 At = cook(raw.a, false, NX, NX);
-    const d4 BT = cook(raw.bt, true, NX, NU);
-    const d4 T = raw.T, HIs = raw.HI, HXs = raw.HX;
-    d4 om, ev, ur;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = 4 * q + g;
-      const bool vr = (j == VC && r < NX);
-      const double xr = (double)raw.xr[q];
-      om[q] = vr ? (newton ? Qr[q] * (raw.xn[q] - xr) : -Qr[q] * xr) : 0.0;
-      ev[q] = vr ? (double)raw.ev[q] : 0.0;
-      ur[q] = (j == VC && r < NU) ? (double)raw.ur[q] : 0.0;
-    }
-    if (ELEM && k == k_hi - 1) {
-      // a zero value at x_{k_hi}: S = -Q and s = -q make W = S + Q and
-      // q + s vanish at the chunk's last stage
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        Ss[q] = (j < NX && 4 * q + g == j) ? -Qj : ((j == VC) ? -om[q] : 0.0);
-    }
-    const d4 Pt = newton ? mask_tile(raw.ct) : sel(j < NU, T);
-    const uint32_t unit = null_inputs(raw.c0, raw.c1, raw.f0, raw.f1, newton);
-    pin(At); pin(BT); pin(T); pin(om); pin(ev); pin(ur); pin(Pt);
-    if (newton && !factor) { pin(HIs); pin(HXs); }
-    pin_memory();
-    if (k > k_lo) fetch(k - 1, raw);
-
-    // [Bp | 0 | d] = B [P | 0 | c] + [0 | 0 | e]
-    const d4 yc = (!newton && j == VC) ? T : Pt;
-    d4 D1 = mmT<3>(BT, yc, ev);
-    d4 PRP = zero4();
-    if (!newton && factor) {
-      d4 RP;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) RP[q] = (j < NU && 4 * q + g < NU) ? Rr[q] * T[q] : 0.0;
-      const d4 Py = (j < NU) ? T : sel(j == VC, T - ur);
-      PRP = mmT<3>(RP, Py, zero4());
-    }
-    const d4 Bp = sel(j < NU, D1);
-    d4 Sn;
-    if (factor) {
-      d4 Wt;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        Wt[q] = (j < NX) ? Ss[q] + ((4 * q + g == j) ? Qj : 0.0) : 0.0;
-      const d4 yA = (j < NX) ? At : sel(j == VC, D1);
-      d4 D2 = mmT<4>(Wt, yA, zero4());      // [W A | W d]
-      if (j == VC) D2 += om + Ss;            // [W A | W d + q + s]
-      const d4 D3 = mmT<4>(Wt, Bp, zero4()); // W Bp
-      d4 D4 = mmT<4>(Bp, D3, zero4());       // Bp^T W Bp
-      const d4 D5 = mmT<4>(Bp, D2, zero4()); // [Hwx | Bp^T (W d + q + s)]
-      if (newton) {
-        // P R' P and P rho straight from the stage tile (P a mask there)
-        D4 += sel(j < NU || j == VC, T);
-      } else {
-        // P R P and P R (c - u_ref) = P (R c + rho), independent of the chain
-        // above (its instructions overlap it)
-        D4 += PRP;
-      }
-      // A^T [W A | W d + q + s]: the part of S that needs no gains, issued
-      // before the elimination
-      const d4 SA = mmT<4>(At, D2, zero4());
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int r = 4 * q + g;
-        if (j < NU) sr.G[r * GS + j] = D4[q] + ((r == j) ? 1.0 : 0.0) - Pt[q];
-        if (j < NX) sr.G[r * GS + NU + j] = D5[q];
-        if (j == VC) sr.G[r * GS + NU + NX] = D5[q] + D4[q];
-      }
-      wsync();
-      // Gauss-Jordan elimination (H is SPD: no pivoting) of [H | Hwx | hw]
-      // (and, for Newton steps, which keep H^-1, of [H | I] beside it): lane
-      // 16 R + c holds column c of H (c < NU, the same in every row R) or
-      // right-hand side 4 R + c - NU (Hwx columns 0..12, hw as 13 = VC;
-      // identity columns 0..11); afterwards the right-hand sides are
-      // H^-1 Hwx, H^-1 hw (and H^-1).
-      static_assert(NU == 12, "row elimination is written for 12 inputs");
-      const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU;
-      const bool is_h = hc < NU;
-      double col[NU];
-#pragma unroll
-      for (int r = 0; r < NU; ++r)
-        col[r] = (is_h || rhs <= NX) ? sr.G[r * GS + (is_h ? hc : NU + rhs)] : 0.0;
-      if constexpr (!newton && !ELEM) {
-        gj_rows(col, unit);
-      } else {
-        double icol[NU];
-#pragma unroll
-        for (int r = 0; r < NU; ++r) icol[r] = is_h ? col[r] : ((r == rhs) ? 1.0 : 0.0);
-        gj_rows2(col, icol, unit);
-        if (!is_h && rhs < NU) {
-#pragma unroll
-          for (int r = 0; r < NU; ++r) sr.HI[r * 16 + rhs] = icol[r];
-        }
-      }
-      if (!is_h && rhs <= NX) {
-#pragma unroll
-        for (int r = 0; r < NU; ++r) sr.KK[r * 16 + rhs] = -col[r];
-      }
-      wsync();
-      d4 KK;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = 4 * q + g;
-        KK[q] = (r < NU && (j < NX || j == VC)) ? sr.KK[r * 16 + j] : 0.0;   // [K | kap]
-      }
-      if constexpr (!ELEM) {
-        // K row-major (row r at NX r) for the rollout; rows 4q + g, q < 3, are
-        // the 12 input rows (kap goes to its own vector)
-        if (j < NX) {
-#pragma unroll
-          for (int q = 0; q < 3; ++q) prK[(size_t)k * TS_K + (4 * q + g) * NX + j] = KK[q];
-        }
-        vec_store(prkap + (size_t)k * NU, NU, KK);
-        if (newton) {
-          d4 HI;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int r = 4 * q + g;
-            HI[q] = (r < NU && j < NU) ? sr.HI[r * 16 + j] : 0.0;
-          }
-          st_map(prL + (size_t)k * TS_L, TS_L, mL, HI);
-          st_map(prH + (size_t)k * TS_H, TS_H, mH, D5);
-        }
-      } else {
-        d4 HI;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * q + g;
-          HI[q] = (r < NU && j < NU) ? sr.HI[r * 16 + j] : 0.0;
-        }
-        // the stage's closed-loop map [A + Bp K | d + Bp kap] with a 1 at
-        // (13, 13), composed after the chunk's map; the reachability term
-        // grows by A_E Bp H^-1 Bp^T A_E^T (A_E before the composition)
-        const d4 BpT = mmT<3>(Pt, BT, zero4());    // (B P)^T = P B^T
-        const d4 LK = mmT<3>(BpT, KK, zero4());    // [Bp K | Bp kap]
-        d4 Ah;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * q + g;
-          Ah[q] = (j < NX) ? At[q] + LK[q]
-                           : ((j == VC) ? ((r < NX) ? LK[q] + D1[q] : (r == VC ? 1.0 : 0.0)) : 0.0);
-        }
-        const d4 ZT = mmT<4>(Bp, TE, zero4());     // (A_E Bp)^T
-        const d4 Y = mmT<3>(HI, ZT, zero4());      // H^-1 (A_E Bp)^T
-        CE = mmT<3>(ZT, Y, CE);
-        TE = mmT<4>(Ah, TE, zero4());
-      }
-      // S = A^T W A + Hwx^T K, s = A^T (W d + q + s) + Hwx^T kap
-      Sn = mmT<3>(sel(j < NX, D5), KK, SA);
-      // keep S exactly symmetric: its rounding is not, and an asymmetric part
-      // is carried back through the open-loop A and grows along the horizon
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sr.ST[(4 * q + g) * 17 + j] = Sn[q];
-      wsync();
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = 4 * q + g;
-        if (r < NX && j < NX) Sn[q] = 0.5 * (Sn[q] + sr.ST[j * 17 + r]);
-      }
-      if (mode == Mode::EQ && !ELEM) st_map(prS + (size_t)k * TS_S, TS_S, mS, Sn);
-      wsync();
-    } else {
-      // second right-hand side of the stored Newton matrix (d = 0, so
-      // W d + q + s = q + s)
-      const d4 wv = sel(j == VC, om + Ss);
-      d4 hw = mmT<4>(Bp, wv, zero4());
-      hw += sel(j == VC, T);
-      const d4 kap = -mmT<3>(HIs, hw, zero4());
-      vec_store(prkap + (size_t)k * NU, NU, kap);
-      Sn = mmT<4>(At, wv, zero4());
-      Sn = mmT<3>(HXs, kap, Sn);
-    }
-    Ss = Sn;
-  }
-  if constexpr (ELEM) {
-    *TEo = TE;
-    *CEo = CE;
-  }
-  return Ss;
-}
-
-// Forward rollout after the backward recursion (all N stages).
-template <Mode mode, bool LONG>
-__device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& sh) {
-  const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id();
-  constexpr bool newton = (mode == Mode::NEWTON);
-  const gcf pA = uni(C.A), pB = uni(C.B), pe = uni(C.e);
-  const GMEM uint8_t* pct = uni(C.contact);
-  const gd prT = uni(C.rT), prK = uni(C.rK), prkap = uni(C.rkap), prx = uni(C.rx),
-           pru = uni(C.ru), prdx = uni(C.rdx), prdu = uni(C.rdu);
-  // forward rollout: w = K x + kap, u = P^T w + c (P from the stage tile;
-  // the stance mask for Newton steps), x' = A x + B u + e.  It is a chain of
-  // 13-vector products, so it runs on the vector units: lane i of every
-  // 16-lane row holds x_i, w_i, u_i (the rows identical) with row i of K, A,
-  // B and column i of P, and each product is a block of fused multiply-adds
-  // whose vector factor arrives by DPP row broadcast.  The stage data is
-  // fetched a stage ahead (unconditionally, so every path back to the loop
-  // head has issued the same loads); u_k and x_{k+1} collect in LDS (the
-  // costate buffers, free here) and are copied out after the loop.
-  gd xout = newton ? prdx : prx;
-  gd uout = newton ? prdu : pru;
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
+  const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rT = rsrc(uni(C.rT), N * TS_T * 8);
   const StageBufs<LONG> sb(sh, C);
-  const int fi = lane & 15;
-  const int ix = clampi(fi, NX - 1), iu = clampi(fi, NU - 1);
-  const gcf pev = pe ? pe : pA;   // a valid address when there is no e
+  const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB, oB = j < NX ? (j * NU + 3 * g) * 4 : OOB;
+  const int oK = j < NU ? (j * (NX + 1) + 3 * g) * 8 : OOB;
+  const int oKap = (g == 0 && j < NU) ? (j * (NX + 1) + NX) * 8 : OOB;
+  const int oE = (g == 0 && j < NX) ? j * 4 : OOB;
+  const int oC = j < NU ? t_offset(clampi(j, NU - 1), VC) : OOB;
   struct FwdRaw {
-    double kr[NX];   // K[i][0..12]
-    double p6[6];    // P[6 (i / 6) + a][i], a = 0..5 (equality passes)
-    double c, kap;
-    float a[NX], b[NU], e;
-    int ct;
+    double k[4], kap, c;
+    float a[4], b[3], e;
   };
   auto ffetch = [&](int k, FwdRaw& s) {
-    const gcd kr = prK + (size_t)k * TS_K + iu * NX;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) s.kr[r] = kr[r];
-    s.kap = prkap[(size_t)k * NU + iu];
-    if (!newton) {
-      // column iu of P is nonzero only inside its contact's block
-      const gcd tt = prT + (size_t)k * TS_T + (iu / 6) * 42;
-#pragma unroll
-      for (int a = 0; a < 6; ++a) s.p6[a] = tt[a * 6 + iu % 6];
-      s.c = tt[36 + iu % 6];
-    }
-    const gcf ar = pA + (size_t)k * NX * NX + ix * NX;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) s.a[r] = ar[r];
-    const gcf br = pB + (size_t)k * NX * NU + ix * NU;
-#pragma unroll
-    for (int r = 0; r < NU; ++r) s.b[r] = br[r];
-    s.e = pev[pe ? (size_t)k * NX + ix : 0];
-    s.ct = newton ? (int)pct[k * 2 + iu / 6] : 0;
+    ldd2(rK, oK, k * (TS_K * 8), s.k);
+    ldd2(rK, oK + 16, k * (TS_K * 8), s.k + 2);
+    s.kap = VECK ? 0.0 : ldd(rK, oKap, k * (TS_K * 8));
+    s.c = newton ? 0.0 : ldd(rT, oC, k * (TS_T * 8));
+    ldf4(rA, oA, k * (NX * NX * 4), s.a);
+    ldf3(rB, oB, k * (NX * NU * 4), s.b);
+    s.e = newton ? 0.f : ldf(rE, oE, k * (NX * 4));
   };
-  double xv = 0.0;   // x_k, entry fi
-  if (!newton) xv = (double)uni(C.x0)[ix];
-  FwdRaw fr;
-  ffetch(0, fr);
-  pin_memory();
-  for (int k = 0; k < N; ++k) {
-    double kr[NX], pc[NU], a[NX], b[NU];
+  constexpr int FD = 3;
+  FwdRaw ring[FD];
 #pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      kr[r] = fr.kr[r];
-      a[r] = (double)fr.a[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NU; ++r) {
-      pc[r] = (newton || r / 6 != iu / 6) ? 0.0 : fr.p6[r % 6];
-      b[r] = (double)fr.b[r];
-    }
-    const double kap = fr.kap, cc = newton ? 0.0 : fr.c;
-    const double ee = (!newton && pe) ? (double)fr.e : 0.0;
-    const bool stance = fr.ct != 0;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      pin(kr[r]);
-      pin(a[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < NU; ++r) {
-      pin(pc[r]);
-      pin(b[r]);
-    }
+  for (int d = 0; d < FD; ++d) {
+    ffetch(d < N ? d : N - 1, ring[d]);
     pin_memory();
-    ffetch(k + 1 < N ? k + 1 : k, fr);
-    const double w = dot_row_bcast13(xv, kr, kap);
-    const double u = newton ? (stance ? w : 0.0) : dot_row_bcast12(w, pc, cc);
-    double xn = dot_row_bcast13(xv, a, ee);
-    xn = dot_row_bcast12(u, b, xn);
-    if (lane < NU) sb.GV[k * 16 + fi] = u;
-    if (lane < NX) sb.PV[k * 16 + fi] = xn;
-    xv = xn;
+  }
+  double xv = 0.0;   // x_k, entry j
+  if (!newton) xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;
+  auto step = [&](int k, FwdRaw& r) __attribute__((always_inline)) {
+    double km[4], a[4], b[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      km[q] = (q == 0 && g) ? 0.0 : r.k[q];
+      a[q] = (q == 0 && g) ? 0.0 : (double)r.a[q];
+      pin(km[q]);
+      pin(a[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      b[q] = (double)r.b[q];
+      pin(b[q]);
+    }
+    double kap = r.kap;
+    const double cc = r.c, ee = (double)r.e;
+    pin(kap); pin(cc); pin(ee);
+    pin_memory();
+    ffetch(k + FD < N ? k + FD : N - 1, r);
+    if constexpr (VECK) kap = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
+    const double xt = turn_rows(xv);
+    const double w = row_total(dot4(xt, km, kap));
+    const double ax = dot4(xt, a, ee);
+    xv = row_total(dot3(turn_rows(newton ? w : w + cc), b, ax));
+    if (lane < NU) sb.GV[k * 16 + j] = w;
+    if (lane < NX) sb.PV[k * 16 + j] = xv;
+  };
+  static_assert(FD == 3, "one line below per ring slot");
+  for (int k = 0;; k += FD) {
+    if (!(k < N)) break;
+    step(k, ring[0]);
+    if (!(k + 1 < N)) break;
+    step(k + 1, ring[1]);
+    if (!(k + 2 < N)) break;
+    step(k + 2, ring[2]);
   }
   bufsync<LONG>();
-  if (lane < NX) xout[lane] = newton ? 0.0 : (double)uni(C.x0)[lane];
-  for (int e = lane; e < N * NU; e += W64) uout[e] = sb.GV[(e / NU) * 16 + e % NU];
-  for (int e = lane; e < N * NX; e += W64) xout[NX + e] = sb.PV[(e / NX) * 16 + e % NX];
-  gsync();
 }
 
 // The sequential recursion over the whole horizon (one wave), then the
-// rollout.  Its stage loop is the one `backward` runs, written out here once
-// more: compiled through the shared function, this hot loop took about 230
-// more register moves per stage and its launch about 4 % longer.
-template <Mode mode, bool factor, bool LONG>
-__device__ __attribute__((noinline)) void riccati_t(const Ctx& C, Sh& sh, gcd rcvec, int ktop) {
+// rollout.
+template <Mode mode, bool LONG>
+__device__ __attribute__((noinline)) void riccati_t(const Ctx& C, Sh& sh, int ktop) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
-  gsync();
-  build_tiles(C, mode == Mode::NEWTON, rcvec, ktop);
-  gsync();
+  build<mode>(C, sh, ktop);
+  const d4 Vk =
+      (ktop < N) ? ld_map(uni(C.rS) + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
+  backward<mode, false>(C, sh.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
+  forward<mode, LONG, false>(C, sh);
+}
+
+// Second right-hand side of a Newton step with the stored factors: rho_k (in
+// GV) to kap_k (in GV).  With wv = q + s, hw = Bp^T wv + rho, the recursion of
+// the linear part is s <- A^T wv + K^T hw (Hwx^T kap = K^T hw), a chain; the
+// feedforwards kap = -H^{-1} hw then follow for all stages in parallel, four
+// stages at a time (one per 16-lane row), by the two triangular solves.
+template <bool LONG>
+__device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
   const int lane = lane_id(), g = tg(), j = tj();
-  constexpr bool newton = (mode == Mode::NEWTON);
-  const gcf pA = uni(C.A), pB = uni(C.B), pxr = uni(C.x_ref), pe = uni(C.e), pur = uni(C.u_ref);
-  const GMEM uint8_t* pct = uni(C.contact);
-  const GMEM int32_t* pfc = uni(C.faces);
-  const gd prT = uni(C.rT), prK = uni(C.rK), prL = uni(C.rL), prH = uni(C.rHwx), prS = uni(C.rS);
-  const gd prkap = uni(C.rkap), prx = uni(C.rx), pru = uni(C.ru), prdx = uni(C.rdx),
-           prdu = uni(C.rdu);
-  // the diagonal weights where this lane uses them
-  const double Qj = C.Q[clampi(j, NX - 1)];
-  d4 Qr, Rr;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    Qr[q] = C.Q[clampi(4 * q + g, NX - 1)];
-    Rr[q] = C.R[clampi(4 * q + g, NU - 1)];
-  }
-  // maps of the stage blocks this variant moves
-  const uint32_t mT = map_T();
-  const uint32_t mS = map_S(true);
-  const uint32_t mL = map_rect(NU, NU), mH = map_rect(NU, NX);
-  auto fetch = [&](int k, BackRaw& s) {
-    gather(pA + (size_t)k * NX * NX, false, NX, NX, s.a);
-    gather(pB + (size_t)k * NX * NU, true, NX, NU, s.bt);
-    gatherv(pxr + (size_t)k * NX, NX, s.xr);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      s.ev[q] = 0.f;
-      s.ur[q] = 0.f;
-      s.xn[q] = 0.0;
-    }
-    if (!newton && pe) gatherv(pe + (size_t)k * NX, NX, s.ev);
-    if (!newton && pur) gatherv(pur + (size_t)k * NU, NU, s.ur);
-    if (newton) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s.xn[q] = prx[(size_t)(k + 1) * NX + clampi(4 * q + g, NX - 1)];
-    }
-    s.T = ld_map(prT + (size_t)k * TS_T, TS_T, mT);
-    if (newton && !factor) {
-      s.HI = ld_map(prL + (size_t)k * TS_L, TS_L, mL);
-      s.HX = ld_map(prH + (size_t)k * TS_H, TS_H, mH);
-    } else {
-      s.HI = s.HX = zero4();
-    }
-    s.ct = newton ? (int)pct[k * 2 + (j < NU ? j / 6 : 0)] : 0;
-    s.c0 = __builtin_amdgcn_readfirstlane((int)pct[k * 2]);
-    s.c1 = __builtin_amdgcn_readfirstlane((int)pct[k * 2 + 1]);
-    s.f0 = newton ? 0 : __builtin_amdgcn_readfirstlane(pfc[k * 2]);
-    s.f1 = newton ? 0 : __builtin_amdgcn_readfirstlane(pfc[k * 2 + 1]);
+  const StageBufs<LONG> sb(sh, C);
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rQ = rsrc(uni(C.rq), N * NX * 8);
+  const auto rF = rsrc(uni(C.rF), N * TS_F * 8);
+  const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
+  const int oB = j < NU ? (3 * g * NU + j) * 4 : OOB, oB0 = (g == 0 && j < NU) ? j * 4 : OOB;
+  const int oK = j < NX ? (3 * g * (NX + 1) + j) * 8 : OOB, oQ = j < NX ? j * 8 : OOB;
+  struct VecRaw {
+    float a[4], b[4];
+    double k[3], q;
   };
-
-  // value function of x_{k+1}: S in columns 0..12, s in VC
-  d4 Ss = (ktop < N) ? ld_map(prS + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
-  BackRaw raw;
-  fetch(ktop > 0 ? ktop - 1 : 0, raw);
-  for (int k = ktop - 1; k >= 0; --k) {
-    // this stage's data
-    const d4 At = cook(raw.a, false, NX, NX);
-    const d4 BT = cook(raw.bt, true, NX, NU);
-    const d4 T = raw.T, HIs = raw.HI, HXs = raw.HX;
-    d4 om, ev, ur;
+  auto vfetch = [&](int k, VecRaw& s) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r = 4 * q + g;
-      const bool vr = (j == VC && r < NX);
-      const double xr = (double)raw.xr[q];
-      om[q] = vr ? (newton ? Qr[q] * (raw.xn[q] - xr) : -Qr[q] * xr) : 0.0;
-      ev[q] = vr ? (double)raw.ev[q] : 0.0;
-      ur[q] = (j == VC && r < NU) ? (double)raw.ur[q] : 0.0;
+      s.a[q] = ldf(rA, q == 0 ? oA0 : oA + q * NX * 4, k * (NX * NX * 4));
+      s.b[q] = ldf(rB, q == 0 ? oB0 : oB + q * NU * 4, k * (NX * NU * 4));
     }
-    const d4 Pt = newton ? mask_tile(raw.ct) : sel(j < NU, T);
-    const uint32_t unit = null_inputs(raw.c0, raw.c1, raw.f0, raw.f1, newton);
-    pin(At); pin(BT); pin(T); pin(om); pin(ev); pin(ur); pin(Pt);
-    if (newton && !factor) { pin(HIs); pin(HXs); }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.k[q] = ldd(rK, oK + q * (NX + 1) * 8, k * (TS_K * 8));
+    s.q = ldd(rQ, oQ, k * (NX * 8));
+  };
+  constexpr int VD = 3;
+  VecRaw ring[VD];
+#pragma unroll
+  for (int d = 0; d < VD; ++d) {
+    vfetch(N - 1 - d >= 0 ? N - 1 - d : 0, ring[d]);
     pin_memory();
-    if (k > 0) fetch(k - 1, raw);
-
-    // [Bp | 0 | d] = B [P | 0 | c] + [0 | 0 | e]
-    const d4 yc = (!newton && j == VC) ? T : Pt;
-    d4 D1 = mmT<3>(BT, yc, ev);
-    d4 PRP = zero4();
-    if (!newton && factor) {
-      d4 RP;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) RP[q] = (j < NU && 4 * q + g < NU) ? Rr[q] * T[q] : 0.0;
-      const d4 Py = (j < NU) ? T : sel(j == VC, T - ur);
-      PRP = mmT<3>(RP, Py, zero4());
-    }
-    const d4 Bp = sel(j < NU, D1);
-    d4 Sn;
-    if (factor) {
-      d4 Wt;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        Wt[q] = (j < NX) ? Ss[q] + ((4 * q + g == j) ? Qj : 0.0) : 0.0;
-      const d4 yA = (j < NX) ? At : sel(j == VC, D1);
-      d4 D2 = mmT<4>(Wt, yA, zero4());      // [W A | W d]
-      if (j == VC) D2 += om + Ss;            // [W A | W d + q + s]
-      const d4 D3 = mmT<4>(Wt, Bp, zero4()); // W Bp
-      d4 D4 = mmT<4>(Bp, D3, zero4());       // Bp^T W Bp
-      const d4 D5 = mmT<4>(Bp, D2, zero4()); // [Hwx | Bp^T (W d + q + s)]
-      if (newton) {
-        // P R' P and P rho straight from the stage tile (P a mask there)
-        D4 += sel(j < NU || j == VC, T);
-      } else {
-        // P R P and P R (c - u_ref) = P (R c + rho), independent of the chain
-        // above (its instructions overlap it)
-        D4 += PRP;
-      }
-      // A^T [W A | W d + q + s]: the part of S that needs no gains, issued
-      // before the elimination
-      const d4 SA = mmT<4>(At, D2, zero4());
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int r = 4 * q + g;
-        if (j < NU) sh.r.G[r * GS + j] = D4[q] + ((r == j) ? 1.0 : 0.0) - Pt[q];
-        if (j < NX) sh.r.G[r * GS + NU + j] = D5[q];
-        if (j == VC) sh.r.G[r * GS + NU + NX] = D5[q] + D4[q];
-      }
-      wsync();
-      // Gauss-Jordan elimination (H is SPD: no pivoting) of [H | Hwx | hw]
-      // (and, for Newton steps, which keep H^-1, of [H | I] beside it): lane
-      // 16 R + c holds column c of H (c < NU, the same in every row R) or
-      // right-hand side 4 R + c - NU (Hwx columns 0..12, hw as 13 = VC;
-      // identity columns 0..11); afterwards the right-hand sides are
-      // H^-1 Hwx, H^-1 hw (and H^-1).
-      static_assert(NU == 12, "row elimination is written for 12 inputs");
-      const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU;
-      const bool is_h = hc < NU;
-      double col[NU];
-#pragma unroll
-      for (int r = 0; r < NU; ++r)
-        col[r] = (is_h || rhs <= NX) ? sh.r.G[r * GS + (is_h ? hc : NU + rhs)] : 0.0;
-      if constexpr (!newton) {
-        gj_rows(col, unit);
-      } else {
-        double icol[NU];
-#pragma unroll
-        for (int r = 0; r < NU; ++r) icol[r] = is_h ? col[r] : ((r == rhs) ? 1.0 : 0.0);
-        gj_rows2(col, icol, unit);
-        if (!is_h && rhs < NU) {
-#pragma unroll
-          for (int r = 0; r < NU; ++r) sh.r.HI[r * 16 + rhs] = icol[r];
-        }
-      }
-      if (!is_h && rhs <= NX) {
-#pragma unroll
-        for (int r = 0; r < NU; ++r) sh.r.KK[r * 16 + rhs] = -col[r];
-      }
-      wsync();
-      d4 KK;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = 4 * q + g;
-        KK[q] = (r < NU && (j < NX || j == VC)) ? sh.r.KK[r * 16 + j] : 0.0;   // [K | kap]
-      }
-      // K row-major (row r at NX r) for the rollout; rows 4q + g, q < 3, are
-      // the 12 input rows (kap goes to its own vector)
-      if (j < NX) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) prK[(size_t)k * TS_K + (4 * q + g) * NX + j] = KK[q];
-      }
-      vec_store(prkap + (size_t)k * NU, NU, KK);
-      if (newton) {
-        d4 HI;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = 4 * q + g;
-          HI[q] = (r < NU && j < NU) ? sh.r.HI[r * 16 + j] : 0.0;
-        }
-        st_map(prL + (size_t)k * TS_L, TS_L, mL, HI);
-        st_map(prH + (size_t)k * TS_H, TS_H, mH, D5);
-      }
-      // S = A^T W A + Hwx^T K, s = A^T (W d + q + s) + Hwx^T kap
-      Sn = mmT<3>(sel(j < NX, D5), KK, SA);
-      // keep S exactly symmetric: its rounding is not, and an asymmetric part
-      // is carried back through the open-loop A and grows along the horizon
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sh.r.ST[(4 * q + g) * 17 + j] = Sn[q];
-      wsync();
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = 4 * q + g;
-        if (r < NX && j < NX) Sn[q] = 0.5 * (Sn[q] + sh.r.ST[j * 17 + r]);
-      }
-      if (mode == Mode::EQ) st_map(prS + (size_t)k * TS_S, TS_S, mS, Sn);
-      wsync();
-    } else {
-      // second right-hand side of the stored Newton matrix (d = 0, so
-      // W d + q + s = q + s)
-      const d4 wv = sel(j == VC, om + Ss);
-      d4 hw = mmT<4>(Bp, wv, zero4());
-      hw += sel(j == VC, T);
-      const d4 kap = -mmT<3>(HIs, hw, zero4());
-      vec_store(prkap + (size_t)k * NU, NU, kap);
-      Sn = mmT<4>(At, wv, zero4());
-      Sn = mmT<3>(HXs, kap, Sn);
-    }
-    Ss = Sn;
   }
-
-  forward<mode, LONG>(C, sh);
+  double s = 0.0;   // value function's linear part, entry j
+  auto step = [&](int k, VecRaw& r) __attribute__((always_inline)) {
+    double a[4], b[4], km[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (double)r.a[q];
+      b[q] = (double)r.b[q];
+      pin(a[q]);
+      pin(b[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      km[q] = r.k[q];
+      pin(km[q]);
+    }
+    const double qk = r.q;
+    pin(qk);
+    pin_memory();
+    vfetch(k - VD >= 0 ? k - VD : 0, r);
+    const double rho = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
+    const double wt = turn_rows(qk + s);
+    const double hw = row_total(dot4(wt, b, rho));
+    const double aw = dot4(wt, a, 0.0);
+    s = row_total(dot3(turn_rows(hw), km, aw));
+    if (lane < NU) sb.GV[k * 16 + j] = hw;
+  };
+  static_assert(VD == 3, "one line below per ring slot");
+  for (int k = N - 1;; k -= VD) {
+    if (!(k >= 0)) break;
+    step(k, ring[0]);
+    if (!(k - 1 >= 0)) break;
+    step(k - 1, ring[1]);
+    if (!(k - 2 >= 0)) break;
+    step(k - 2, ring[2]);
+  }
+  bufsync<LONG>();
+  const int oF = j < NU ? (g * TS_F + j * NU) * 8 : OOB;
+  const int oD = j < NU ? (g * TS_F + j * (NU + 1)) * 8 : OOB;
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    const int k = k0 + g;
+    const bool on = j < NU && k < N;
+    double f[NU];
+#pragma unroll
+    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8, k0 * (TS_F * 8), f + p);
+    const double rd = ldd(rF, oD, k0 * (TS_F * 8));
+    double y = 0.0;
+    if (on && C.contact[2 * k + j / 6]) y = sb.GV[k * 16 + j];
+    // y <- U^-T y, then D^-1, then U^-1
+#define PINMPC_TRI(p, use)                                                                      \
+  {                                                                                             \
+    const double m = (use) ? -f[p] : 0.0;                                                       \
+    asm volatile(                                                                               \
+        "s_nop 1\n"                                                                             \
+        "v_fmac_f64_dpp %0, %0, %1 row_newbcast:" #p " row_mask:0xf bank_mask:0xf bound_ctrl:1" \
+        : "+v"(y)                                                                               \
+        : "v"(m));                                                                              \
+  }
+    PINMPC_TRI(0, j > 0) PINMPC_TRI(1, j > 1) PINMPC_TRI(2, j > 2) PINMPC_TRI(3, j > 3)
+    PINMPC_TRI(4, j > 4) PINMPC_TRI(5, j > 5) PINMPC_TRI(6, j > 6) PINMPC_TRI(7, j > 7)
+    PINMPC_TRI(8, j > 8) PINMPC_TRI(9, j > 9) PINMPC_TRI(10, j > 10)
+    y *= rd;
+    PINMPC_TRI(11, j < 11) PINMPC_TRI(10, j < 10) PINMPC_TRI(9, j < 9) PINMPC_TRI(8, j < 8)
+    PINMPC_TRI(7, j < 7) PINMPC_TRI(6, j < 6) PINMPC_TRI(5, j < 5) PINMPC_TRI(4, j < 4)
+    PINMPC_TRI(3, j < 3) PINMPC_TRI(2, j < 2) PINMPC_TRI(1, j < 1)
+#undef PINMPC_TRI
+    if (on) sb.GV[k * 16 + j] = -y;
+  }
+  bufsync<LONG>();
 }
 
 // ---------------------------------------- associative scan over the horizon
@@ -1317,21 +1372,6 @@ __device__ d4 inv13(const d4& M, double* buf) {
   return R;
 }
 
-// S exactly symmetric on its 13 x 13 block (the average with its transpose).
-__device__ inline d4 symmetrize(d4 S, double* buf) {
-  const int g = tg(), j = tj();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) buf[(4 * q + g) * 17 + j] = S[q];
-  wsync();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + g;
-    if (r < NX && j < NX) S[q] = 0.5 * (S[q] + buf[j * 17 + r]);
-  }
-  wsync();
-  return S;
-}
-
 // Value function [S_0 | s_0] at x_{k0} of a chunk with summary (TE, CE, SE)
 // for the value V = [S | s] at x_{k1}; om holds q_{k1-1} in column VC.
 __device__ d4 combine_value(const d4& TE, const d4& CE, const d4& SE, const d4& V, const d4& om,
@@ -1370,19 +1410,17 @@ __device__ d4 combine_value(const d4& TE, const d4& CE, const d4& SE, const d4& 
   const d4 GA = mmT<4>(G, AE, zero4());
   d4 S0 = mmT<4>(AE, GA, SE);                     // [A^T G A + S_E | s_E]
   S0 -= sel(j == VC, mmT<4>(AE, u, zero4()));     // s_E - A^T u
-  return symmetrize(S0, buf);
+  return symmetrize(S0, sym_weights(), buf);
 }
 
 // The backward recursion as a scan over the horizon (the problem's first
 // wave; the helpers run scan_helper).  Falls back to the sequential recursion
 // when the horizon is too short to cut.
 template <Mode mode, bool LONG>
-__device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, gcd rcvec, int ktop) {
+__device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, int ktop) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
-  gsync();
-  build_tiles(C, mode == Mode::NEWTON, rcvec, ktop);
-  gsync();
+  build<mode>(C, sh, ktop);
   constexpr bool newton = (mode == Mode::NEWTON);
   const int lane = lane_id(), g = tg(), j = tj();
   const int W = (int)(blockDim.x >> 6);
@@ -1390,8 +1428,8 @@ __device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, gcd
       ktop / SCAN_MIN_CHUNK < W ? ktop / SCAN_MIN_CHUNK : W);
   const d4 Vk = (ktop < N) ? ld_map(uni(C.rS) + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
   if (nch < 2) {
-    backward<mode, true, LONG, false>(C, sh.r, 0, ktop, Vk, nullptr, nullptr);
-    forward<mode, LONG>(C, sh);
+    backward<mode, false>(C, sh.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
+    forward<mode, LONG, false>(C, sh);
     return;
   }
   const ScanLds L = scan_lds(W);
@@ -1405,7 +1443,7 @@ __device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, gcd
   // boundary values, from the last chunk back to the first (the first chunk's
   // summary is not needed: its recursion starts from the boundary value)
   const gcf pxr = uni(C.x_ref);
-  const gd prx = uni(C.rx);
+  const gd prq = uni(C.rq);
   const double Qj = C.Q[clampi(j, NX - 1)];
   double* buf = L.exch;   // the first chunk's summary slot, free
   d4 V = Vk;
@@ -1417,10 +1455,9 @@ __device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, gcd
     for (int q = 0; q < 4; ++q) {
       const int r = 4 * q + g;
       const int rc = clampi(r, NX - 1);
-      const double xr = (double)pxr[(size_t)(k1 - 1) * NX + rc];
-      const double Qr = C.Q[rc];
-      om[q] = (j == VC && r < NX) ? (newton ? Qr * (prx[(size_t)k1 * NX + rc] - xr) : -Qr * xr)
-                                  : 0.0;
+      const size_t at = (size_t)(k1 - 1) * NX + rc;
+      const double v = newton ? prq[at] : -C.Q[rc] * (double)pxr[at];
+      om[q] = (j == VC && r < NX) ? v : 0.0;
     }
     const double* ex = L.exch + (size_t)w * 3 * TILE_D;
     V = combine_value(ld_tile_lds(ex), ld_tile_lds(ex + TILE_D), ld_tile_lds(ex + 2 * TILE_D), V,
@@ -1428,15 +1465,14 @@ __device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, gcd
     st_tile_lds(L.bnd + (size_t)(w - 1) * TILE_D, V);
   }
   __syncthreads();   // the boundary values reach the helpers
-  backward<mode, true, LONG, false>(C, sh.r, 0, (int)(ktop / nch), V, nullptr, nullptr);
+  backward<mode, false>(C, sh.r, sh.unit, 0, (int)(ktop / nch), V, nullptr, nullptr);
   __syncthreads();   // every chunk's gains and values are stored
-  forward<mode, LONG>(C, sh);
+  forward<mode, LONG, false>(C, sh);
 }
 
 // A helper wave of a scanning workgroup: summary and recursion of its chunk
 // for every scan command, until the first wave releases it.
-template <bool LONG>
-__device__ __attribute__((noinline)) void scan_helper(const Ctx& C) {
+__device__ __attribute__((noinline)) void scan_helper(const Ctx& C, const uint8_t* unit) {
   const int wave = (int)(threadIdx.x >> 6), W = (int)(blockDim.x >> 6);
   const ScanLds L = scan_lds(W);
   ShR& sr = L.shr[wave - 1];
@@ -1451,9 +1487,9 @@ __device__ __attribute__((noinline)) void scan_helper(const Ctx& C) {
     if (mine) {
       d4 TE, CE, SE;
       if (op == SCAN_EQ)
-        SE = backward<Mode::EQ, true, LONG, true>(C, sr, k0, k1, zero4(), &TE, &CE);
+        SE = backward<Mode::EQ, true>(C, sr, unit, k0, k1, zero4(), &TE, &CE);
       else
-        SE = backward<Mode::NEWTON, true, LONG, true>(C, sr, k0, k1, zero4(), &TE, &CE);
+        SE = backward<Mode::NEWTON, true>(C, sr, unit, k0, k1, zero4(), &TE, &CE);
       double* ex = L.exch + (size_t)wave * 3 * TILE_D;
       st_tile_lds(ex, TE);
       st_tile_lds(ex + TILE_D, CE);
@@ -1464,9 +1500,9 @@ __device__ __attribute__((noinline)) void scan_helper(const Ctx& C) {
     if (mine) {
       const d4 V = ld_tile_lds(L.bnd + (size_t)wave * TILE_D);
       if (op == SCAN_EQ)
-        backward<Mode::EQ, true, LONG, false>(C, sr, k0, k1, V, nullptr, nullptr);
+        backward<Mode::EQ, false>(C, sr, unit, k0, k1, V, nullptr, nullptr);
       else
-        backward<Mode::NEWTON, true, LONG, false>(C, sr, k0, k1, V, nullptr, nullptr);
+        backward<Mode::NEWTON, false>(C, sr, unit, k0, k1, V, nullptr, nullptr);
     }
     __syncthreads();   // chunk recursions done
   }
@@ -1477,106 +1513,238 @@ __device__ inline void scan_release() {
   if (lane_id() == 0) scan_ctl.op = SCAN_EXIT;
   __syncthreads();
 }
-template <bool LONG>
-__device__ void riccati(const Ctx& C, Sh& sh, Mode mode, bool factor, gcd rcvec, int ktop) {
-  if (blockDim.x > W64 && factor) {   // a scanning workgroup
-    if (mode == Mode::EQ) riccati_scan<Mode::EQ, LONG>(C, sh, rcvec, ktop);
-    else riccati_scan<Mode::NEWTON, LONG>(C, sh, rcvec, ktop);
-    return;
-  }
-  if (mode == Mode::EQ) riccati_t<Mode::EQ, true, LONG>(C, sh, rcvec, ktop);
-  else if (factor) riccati_t<Mode::NEWTON, true, LONG>(C, sh, rcvec, ktop);
-  else riccati_t<Mode::NEWTON, false, LONG>(C, sh, rcvec, ktop);
+template <Mode mode, bool LONG>
+__device__ inline void riccati(const Ctx& C, Sh& sh, int ktop) {
+  if (blockDim.x > W64) riccati_scan<mode, LONG>(C, sh, ktop);   // a scanning workgroup
+  else riccati_t<mode, LONG>(C, sh, ktop);
 }
 
-// Costates p_{k+1} = Q (x_{k+1} - r_k) + A_{k+1}^T p_{k+2} and the reduced
-// gradient g_k = R (u_k - u_ref_k) + B_k^T p_{k+1}.  The terms that need no
-// costate are formed first, in parallel, into LDS.  The recursion is a chain
-// of 13-vector products, so it runs on the vector units rather than the
-// matrix cores (where a 16 x 16 tile product per stage would carry one useful
-// column): lane i of every 16-lane row holds entry i of p (the rows
-// identical) and column i of A_{k+1} and B_k, and each product is 13 fused
-// multiply-adds whose other factor, p_r, arrives by row broadcast.  Columns
-// are fetched two stages ahead (unconditionally, stage index clamped, loop
-// left as a whole, no global store inside: each stage waits for its own
-// loads only); p and g stay in LDS until the chain is done.  Returns the
-// state-side magnitude max |Q (x_{k+1} - r_k)|, |p|, |p - Q (x_{k+1} - r_k)|
-// (= |A^T p_{k+2}|) over all stages, which the KKT scaling needs.
+// The equality pass's point from its rollout (w_k in GV, x_{k+1} in PV): inputs
+// u = P w + c of the faces (closed form, exactly on each face), states, and what
+// the costates start from, Q (x_{k+1} - r_k) in PV and R (u_k - u_ref_k) in GV.
 template <bool LONG>
-__device__ __attribute__((noinline)) double costates_grad(const Ctx& C, Sh& sh) {
-  gsync();
+__device__ __attribute__((always_inline)) inline void eq_point(const Ctx& C, Sh& sh) {
+  const int lane = lane_id(), N = C.N;
   const StageBufs<LONG> sb(sh, C);
-  const int lane = lane_id();
-  const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const gcf pA = uni(C.A), pB = uni(C.B), pxr = uni(C.x_ref), pur = uni(C.u_ref);
-  const gd prx = uni(C.rx), pru = uni(C.ru), prlam = uni(C.rlam), prg = uni(C.rg);
+  for (int e = lane; e < N * 2; e += W64) {
+    const int k = e >> 1, i = e & 1;
+    double u[6] = {0, 0, 0, 0, 0, 0};
+    if (C.contact[e]) {
+      const int code = C.faces[e];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) u[a] = sb.GV[k * 16 + 6 * i + a];
+      if (face_apex(code)) {
+        u[0] = u[1] = u[2] = 0.0;
+      } else {
+        const ForceFace f = force_face(code);
+        const double m = C.mu;
+        if (f.top) {
+          if (f.sx != 0.0) u[0] = f.sx * m * C.fz;
+          if (f.sy != 0.0) u[1] = f.sy * m * C.fz;
+          u[2] = C.fz;
+        } else if (f.sx != 0.0 && f.sy != 0.0) {
+          const double t = (m * (f.sx * u[0] + f.sy * u[1]) + u[2]) * C.i2;
+          u[0] = f.sx * m * t;
+          u[1] = f.sy * m * t;
+          u[2] = t;
+        } else if (f.sx != 0.0 || f.sy != 0.0) {
+          const double t = (f.sx * u[0] + f.sy * u[1] - m * u[2]) * C.i1;
+          u[0] -= f.sx * t;
+          u[1] -= f.sy * t;
+          u[2] += m * t;
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (code >> (8 + a) & 1) u[3 + a] = C.tm;
+        else if (code >> (11 + a) & 1) u[3 + a] = -C.tm;
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+      const int jj = 6 * i + a;
+      const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
+      C.ru[k * NU + jj] = u[a];
+      sb.GV[k * 16 + jj] = C.R[jj] * (u[a] - ur);
+    }
+  }
   for (int e = lane; e < N * NX; e += W64) {
     const int k = e / NX, i = e % NX;
-    sb.PV[k * 16 + i] = C.Q[i] * (prx[(size_t)(k + 1) * NX + i] - (double)pxr[(size_t)k * NX + i]);
+    const double x = sb.PV[k * 16 + i];
+    C.rx[NX + e] = x;
+    sb.PV[k * 16 + i] = C.Q[i] * (x - (double)C.x_ref[e]);
   }
+  if (lane < NX) C.rx[lane] = (double)C.x0[lane];
+  bufsync<LONG>();
+}
+
+// The same stage vectors from a point (ru, rx) in memory.
+template <bool LONG>
+__device__ inline void load_point(const Ctx& C, Sh& sh) {
+  gsync();
+  const int lane = lane_id(), N = C.N;
+  const StageBufs<LONG> sb(sh, C);
+  for (int e = lane; e < N * NX; e += W64)
+    sb.PV[(e / NX) * 16 + e % NX] = C.Q[e % NX] * (C.rx[NX + e] - (double)C.x_ref[e]);
   for (int e = lane; e < N * NU; e += W64) {
-    const int k = e / NU, i = e % NU;
-    const double ur = pur ? (double)pur[(size_t)k * NU + i] : 0.0;
-    sb.GV[k * 16 + i] = C.R[i] * (pru[(size_t)k * NU + i] - ur);
+    const double ur = C.u_ref ? (double)C.u_ref[e] : 0.0;
+    sb.GV[(e / NU) * 16 + e % NU] = C.R[e % NU] * (C.ru[e] - ur);
   }
   bufsync<LONG>();
-  const int i = lane & 15;
-  const int ia = clampi(i, NX - 1), ib = clampi(i, NU - 1);
-  struct ColRaw {
-    float a[NX], b[NX];   // A_{k+1}[r][i], B_k[r][i]
-  };
-  // stage k needs A_{k+1} (for p_{k+1}) and B_k (for g_k); at k = N - 1 the
-  // clamped A_N multiplies p_{N+1} = 0
-  auto cfetch = [&](int k, ColRaw& s) {
-    const gcf Ak = pA + (size_t)clampi(k + 1, N - 1) * NX * NX;
-    const gcf Bk = pB + (size_t)k * NX * NU;
+}
+
+// Costates p_{k+1} = Q (x_{k+1} - r_k) + A_{k+1}^T p_{k+2} (a chain, its data
+// fetched CD stages ahead) and the reduced gradient g_k = R (u_k - u_ref_k) +
+// B_k^T p_{k+1} (then, four stages at a time, one per 16-lane row), from and into
+// the stage buffers.  Returns the state-side magnitude max |Q (x_{k+1} - r_k)|,
+// |p|, |A^T p| over all stages, which the KKT scaling needs.
+template <bool LONG>
+__device__ __attribute__((always_inline)) inline double costates_grad(const Ctx& C, Sh& sh) {
+  const StageBufs<LONG> sb(sh, C);
+  const int lane = lane_id(), g = tg(), j = tj();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
+  // stage k needs A_{k+1}; at k = N - 1 the clamped stage multiplies p_{N+1} = 0
+  auto cfetch = [&](int k, float (&s)[4]) {
+    const int at = clampi(k + 1, N - 1) * (NX * NX * 4);
+    s[0] = ldf(rA, oA0, at);
 #pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      s.a[r] = Ak[r * NX + ia];
-      s.b[r] = Bk[r * NU + ib];
-    }
+    for (int q = 1; q < 4; ++q) s[q] = ldf(rA, oA + q * NX * 4, at);
   };
-  constexpr int CD = 2;
-  ColRaw ring[CD];
+  constexpr int CD = 6;
+  float ring[CD][4];
 #pragma unroll
   for (int d = 0; d < CD; ++d) {
     cfetch(N - 1 - d >= 0 ? N - 1 - d : 0, ring[d]);
     pin_memory();   // issued in ring order, as the loop issues them
   }
-  double p = 0.0;   // p_{k+2}, entry i
+  double p = 0.0;   // p_{k+2}, entry j
   double tstate = 0.0;
-  for (int k = N - 1;;) {
+  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+    double a[4];
 #pragma unroll
-    for (int d = 0; d < CD; ++d, --k) {
-      if (k < 0) goto chain_done;
-      double a[NX], b[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        a[r] = (double)ring[d].a[r];
-        b[r] = (double)ring[d].b[r];
-      }
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        pin(a[r]);
-        pin(b[r]);
-      }
-      pin_memory();
-      cfetch(k - CD >= 0 ? k - CD : 0, ring[d]);
-      const double qx = (i < NX) ? sb.PV[k * 16 + i] : 0.0;
-      const double rg = (i < NU) ? sb.GV[k * 16 + i] : 0.0;
-      p = dot_row_bcast13(p, a, qx);          // p_{k+1}
-      const double gk = dot_row_bcast13(p, b, rg);
-      if (i < NX) tstate = fmax(tstate, fmax(fabs(qx), fmax(fabs(p), fabs(p - qx))));
-      if (lane < NX) sb.PV[k * 16 + i] = p;
-      if (lane < NU) sb.GV[k * 16 + i] = gk;
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (double)r[q];
+      pin(a[q]);
     }
+    pin_memory();
+    cfetch(k - CD >= 0 ? k - CD : 0, r);
+    const double qx = j < NX ? sb.PV[k * 16 + j] : 0.0;
+    const double ap = row_total(dot4(turn_rows(p), a, 0.0));
+    p = qx + ap;
+    tstate = fmax(tstate, fmax(fabs(qx), fmax(fabs(p), fabs(ap))));
+    if (lane < NX) sb.PV[k * 16 + j] = p;
+  };
+  static_assert(CD == 6, "one line below per ring slot");
+  for (int k = N - 1;; k -= CD) {
+    if (!(k >= 0)) break;
+    step(k, ring[0]);
+    if (!(k - 1 >= 0)) break;
+    step(k - 1, ring[1]);
+    if (!(k - 2 >= 0)) break;
+    step(k - 2, ring[2]);
+    if (!(k - 3 >= 0)) break;
+    step(k - 3, ring[3]);
+    if (!(k - 4 >= 0)) break;
+    step(k - 4, ring[4]);
+    if (!(k - 5 >= 0)) break;
+    step(k - 5, ring[5]);
   }
-chain_done:
   bufsync<LONG>();
-  for (int e = lane; e < N * NX; e += W64) prlam[e] = sb.PV[(e / NX) * 16 + e % NX];
-  for (int e = lane; e < N * NU; e += W64) prg[e] = sb.GV[(e / NU) * 16 + e % NU];
-  gsync();
+  const int oB = j < NU ? (g * NX * NU + j) * 4 : OOB;
+  auto bfetch = [&](int k0, float (&s)[NX]) {
+#pragma unroll
+    for (int r = 0; r < NX; ++r) s[r] = ldf(rB, oB + r * NU * 4, k0 * (NX * NU * 4));
+  };
+  float bn[NX];
+  bfetch(0, bn);
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    const int k = k0 + g;
+    double b[NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      b[r] = (double)bn[r];
+      pin(b[r]);
+    }
+    pin_memory();
+    bfetch(k0 + 4 < N ? k0 + 4 : k0, bn);
+    const bool on = j < NU && k < N;
+    const double pk = (j < NX && k < N) ? sb.PV[k * 16 + j] : 0.0;
+    const double ru = on ? sb.GV[k * 16 + j] : 0.0;
+    const double gk = dot_row_bcast13(pk, b, ru);
+    if (on) sb.GV[k * 16 + j] = gk;
+  }
+  bufsync<LONG>();
   return wave_max(tstate);
+}
+
+// x = rollout of ru from x0, in FP64, into rx: the stage terms B u + e for four
+// stages at a time, then the chain.
+template <bool LONG>
+__device__ __attribute__((noinline)) void rollout_ru(const Ctx& C, Sh& sh) {
+  gsync();
+  const StageBufs<LONG> sb(sh, C);
+  const int lane = lane_id(), g = tg(), j = tj();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0), rU = rsrc(uni(C.ru), N * NU * 8);
+  const int oB = j < NX ? (g * NX + j) * NU * 4 : OOB;
+  const int oE = j < NX ? (g * NX + j) * 4 : OOB, oU = j < NU ? (g * NU + j) * 8 : OOB;
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    float b[NU];
+#pragma unroll
+    for (int l = 0; l < NU; l += 4) ldf4(rB, oB + l * 4, k0 * (NX * NU * 4), b + l);
+    double bd[NX];
+#pragma unroll
+    for (int l = 0; l < NX; ++l) bd[l] = l < NU ? (double)b[l < NU ? l : 0] : 0.0;
+    const double u = ldd(rU, oU, k0 * (NU * 8)), e = (double)ldf(rE, oE, k0 * (NX * 4));
+    const double d = dot_row_bcast13(u, bd, e);
+    if (j < NX && k0 + g < N) sb.PV[(k0 + g) * 16 + j] = d;
+  }
+  bufsync<LONG>();
+  const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB;
+  constexpr int RD = 6;
+  float ring[RD][4];
+#pragma unroll
+  for (int d = 0; d < RD; ++d) {
+    ldf4(rA, oA, (d < N ? d : N - 1) * (NX * NX * 4), ring[d]);
+    pin_memory();
+  }
+  double xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;
+  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+    double a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (q == 0 && g) ? 0.0 : (double)r[q];
+      pin(a[q]);
+    }
+    pin_memory();
+    ldf4(rA, oA, (k + RD < N ? k + RD : N - 1) * (NX * NX * 4), r);
+    const double t = j < NX ? sb.PV[k * 16 + j] : 0.0;
+    xv = row_total(dot4(turn_rows(xv), a, 0.0)) + t;
+    if (lane < NX) sb.PV[k * 16 + j] = xv;
+  };
+  static_assert(RD == 6, "one line below per ring slot");
+  for (int k = 0;; k += RD) {
+    if (!(k < N)) break;
+    step(k, ring[0]);
+    if (!(k + 1 < N)) break;
+    step(k + 1, ring[1]);
+    if (!(k + 2 < N)) break;
+    step(k + 2, ring[2]);
+    if (!(k + 3 < N)) break;
+    step(k + 3, ring[3]);
+    if (!(k + 4 < N)) break;
+    step(k + 4, ring[4]);
+    if (!(k + 5 < N)) break;
+    step(k + 5, ring[5]);
+  }
+  bufsync<LONG>();
+  if (lane < NX) C.rx[lane] = (double)C.x0[lane];
+  for (int e = lane; e < N * NX; e += W64) C.rx[NX + e] = sb.PV[(e / NX) * 16 + e % NX];
+  gsync();
 }
 
 // Row data of one stance contact-stage (k, i) in registers: a lane owns a
@@ -1632,9 +1800,11 @@ struct FaceUpdate {
 // The force multipliers solve G_A^T mu_A = -g_f on the face's rows (least
 // squares); the Gram systems of the eight faces that are not the apex are solved
 // in closed form (see face_affine).
-__device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, double res[PINMPC_NRES],
+template <bool LONG>
+__device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh,
+                                                           double res[PINMPC_NRES],
                                                            double term_state, FaceUpdate* upd) {
-  gsync();
+  const StageBufs<LONG> sb(sh, C);
   const int lane = lane_id();
   double r_ineq = 0.0, stat = 0.0, term = term_state, comp = 0.0, mumax = 0.0, neg = 0.0;
   uint64_t hsh = 0;
@@ -1649,7 +1819,8 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, double
     if (!C.contact[e]) {
       for (int a = 0; a < 6; ++a) r_ineq = fmax(r_ineq, fabs(u[a]) * C.img);
     } else {
-      load_u6(C.rg, k, i, g);
+#pragma unroll
+      for (int a = 0; a < 6; ++a) g[a] = sb.GV[k * 16 + 6 * i + a];
 #pragma unroll
       for (int r = 0; r < NROW; ++r) mu[r] = 0.0;
 #pragma unroll
@@ -1790,14 +1961,16 @@ __device__ __attribute__((noinline)) double dyn_residual(const Ctx& C) {
   double r = 0.0;
   for (int e = lane; e < C.N * NX; e += W64) {
     const int k = e / NX, i = e % NX;
-    const int st = k;
     gcd x = C.rx + k * NX;
-    gcf A = C.A + st * NX * NX + i * NX;
-    gcf B = C.B + st * NX * NU + i * NU;
+    gcd u = C.ru + k * NU;
+    gcf A = C.A + k * NX * NX + i * NX;
+    gcf B = C.B + k * NX * NU + i * NU;
     double ax = 0.0, bu = 0.0;
+#pragma unroll
     for (int l = 0; l < NX; ++l) ax += (double)A[l] * x[l];
-    for (int l = 0; l < NU; ++l) bu += (double)B[l] * C.ru[st * NU + l];
-    const double ee = C.e ? (double)C.e[st * NX + i] : 0.0;
+#pragma unroll
+    for (int l = 0; l < NU; ++l) bu += (double)B[l] * u[l];
+    const double ee = C.e ? (double)C.e[k * NX + i] : 0.0;
     const double d = x[NX + i] - ax - bu - ee;
     const double den = 1.0 + fmax(fabs(x[NX + i]), fmax(fabs(ax), fabs(bu)));
     r = fmax(r, fabs(d) / den);
@@ -1839,9 +2012,10 @@ __device__ __attribute__((noinline)) void faces_from_u(const Ctx& C, gcd u_src, 
 template <bool LONG>
 __device__ __attribute__((noinline)) double eq_pass(const Ctx& C, Sh& sh, double res[PINMPC_NRES],
                                                    int ktop, FaceUpdate* upd) {
-  riccati<LONG>(C, sh, Mode::EQ, true, nullptr, ktop);
+  riccati<Mode::EQ, LONG>(C, sh, ktop);
+  eq_point<LONG>(C, sh);
   const double ts = costates_grad<LONG>(C, sh);
-  return multipliers_kkt(C, res, ts, upd);
+  return multipliers_kkt<LONG>(C, sh, res, ts, upd);
 }
 
 // Faces from the interior-point iterate (row active where z > s); returns an
@@ -1879,12 +2053,12 @@ struct Counts {
   int eq, ipm, stf;
 };
 
-// Least centring weight of the corrector.  Mehrotra's (mu_aff / mu)^3 alone lets
-// a few products run far ahead of the others on degenerate problems, and the
-// steps then stay short for tens of iterations: over 64 problems of 100 to 400
-// stages the iterations fall from at most 130 to at most 102 (mean 48.4 to
-// 45.2); at 20 and 10..60 stages they are the same (mean 8.3 and 10.5) with
-// and without it.
+// Least centring weight of the corrector after SIGMA_FROM iterations.
+// Mehrotra's (mu_aff / mu)^3 alone lets a few products run far ahead of the
+// others on degenerate problems, and the steps then stay short for tens of
+// iterations: 64 problems of 100 to 400 stages took up to 130.  Few problems up
+// to 64 stages reach that many.
+constexpr int SIGMA_FROM = 40;
 constexpr double SIGMA_MIN = 0.05;
 
 // Interior-point fallback.  Rows scaled by mg (force rows) and tau_max
@@ -1907,7 +2081,8 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
     if (C.contact[(e >> 1) * 2 + (e & 1)]) mloc += NROW;
   const double m = wave_sum((double)mloc);
   if (m == 0.0) return 0;
-  gd rc = C.rdz;   // complementarity target
+  const gd rc = C.rrc;   // complementarity target of the corrector
+  const StageBufs<LONG> sb(sh, C);
   // initial point: the current ru (the ADMM point) and its rollout in rx,
   // slacks at least 1, multipliers 1 (a start from the last active-set pass,
   // its slacks and multipliers floored at 1e-1 .. 1e-3, took as long or
@@ -1918,7 +2093,7 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
   for (int e = lane; e < N * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
     if (!C.contact[e]) continue;
-    double u[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
+    double u[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW];
     load_u6(C.ru, k, i, u);
     rows_of(C, u, gu, hh, isc);
 #pragma unroll
@@ -1927,11 +2102,9 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
       zv[r] = 1.0;
       rpn = fmax(rpn, fabs(fma(gu[r] - hh[r], isc[r], sv[r])));
       smz += sv[r] * zv[r];
-      cv[r] = sv[r] * zv[r];
     }
     store_r(C.rs, rs, e, sv);
     store_r(C.rz, rs, e, zv);
-    store_r(rc, rs, e, cv);
   }
   int it = 0;
   uint64_t hprev = 0;
@@ -1939,8 +2112,8 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
     const double sz = wave_sum(smz), muv = sz / m;
     rpn = wave_max(rpn);
     if (muv <= 1e-10 && rpn <= 1e-9) break;
-    // predictor (affine target rc = s z)
-    riccati<LONG>(C, sh, Mode::NEWTON, true, rc, C.N);
+    // predictor (affine target s z)
+    riccati<Mode::NEWTON, LONG>(C, sh, N);
     // its row steps, the largest step to the boundary, and the sums that give
     // the complementarity after any step: s z + a (s dz + z ds) + a^2 ds dz
     double amax_s = 1.0, amax_z = 1.0, sm1 = 0.0, sm2 = 0.0;
@@ -1949,7 +2122,8 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
       if (!C.contact[e]) continue;
       double u[6], du[6], gu[NROW], gdu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW];
       load_u6(C.ru, k, i, u);
-      load_u6(C.rdu, k, i, du);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
       load_r(C.rs, rs, e, sv);
       load_r(C.rz, rs, e, zv);
       rows_of(C, u, gu, hh, isc);
@@ -1970,18 +2144,46 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
     }
     const double aa = fmin(wave_min(amax_s), wave_min(amax_z));
     const double mu_aff = fmax(fma(aa, fma(aa, wave_sum(sm2), wave_sum(sm1)), sz), 0.0) / m;
-    const double ratio = mu_aff / muv, smu = fmax(ratio * ratio * ratio, SIGMA_MIN) * muv;
-    // corrector target: s z + ds_aff dz_aff - sigma mu
+    const double ratio = mu_aff / muv, cube = ratio * ratio * ratio,
+                 smu = (it < SIGMA_FROM ? cube : fmax(cube, SIGMA_MIN)) * muv;
+    // corrector target s z + ds_aff dz_aff - sigma mu: its linear term per input
+    // into the stage buffers, then the recursion's vector part and the rollout
+    // with the predictor's factors
     for (int e = lane; e < N * 2; e += W64) {
-      if (!C.contact[e]) continue;
-      double cv[NROW];
-      load_r(rc, rs, e, cv);
+      const int k = e >> 1, i = e & 1;
+      double rho[6] = {0, 0, 0, 0, 0, 0};
+      if (C.contact[e]) {
+        double u[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
+        load_u6(C.ru, k, i, u);
+        load_r(C.rs, rs, e, sv);
+        load_r(C.rz, rs, e, zv);
+        load_r(rc, rs, e, cv);
+        rows_of(C, u, gu, hh, isc);
 #pragma unroll
-      for (int r = 0; r < NROW; ++r) cv[r] -= smu;
-      store_r(rc, rs, e, cv);
+        for (int r = 0; r < NROW; ++r) cv[r] -= smu;
+        store_r(rc, rs, e, cv);
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+          const int jj = 6 * i + a;
+          const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
+          rho[a] = C.R[jj] * (u[a] - ur);
+        }
+#pragma unroll
+        for (int r = 0; r < NROW; ++r) {
+          const double rp = fma(gu[r] - hh[r], isc[r], sv[r]);
+          const double cr = (zv[r] + (zv[r] * rp - cv[r]) * recip(sv[r])) * isc[r];
+          double g[6], h;
+          wrench_row(r, C.mu, C.fz, C.tm, g, &h);
+#pragma unroll
+          for (int a = 0; a < 6; ++a) rho[a] += g[a] * cr;
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 6; ++a) sb.GV[k * 16 + 6 * i + a] = rho[a];
     }
-    // corrector: same matrix, new right-hand side
-    riccati<LONG>(C, sh, Mode::NEWTON, false, rc, C.N);
+    bufsync<LONG>();
+    newton_vector<LONG>(C, sh);
+    forward<Mode::NEWTON, LONG, true>(C, sh);
     amax_s = 1.0;
     amax_z = 1.0;
     for (int e = lane; e < N * 2; e += W64) {
@@ -1989,7 +2191,8 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
       if (!C.contact[e]) continue;
       double u[6], du[6], gu[NROW], gdu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
       load_u6(C.ru, k, i, u);
-      load_u6(C.rdu, k, i, du);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
       load_r(C.rs, rs, e, sv);
       load_r(C.rz, rs, e, zv);
       load_r(rc, rs, e, cv);
@@ -2005,7 +2208,7 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
         if (dzv[r] < 0) amax_z = fmin(amax_z, -zv[r] * recip(dzv[r]));
       }
       store_r(C.rds, rs, e, dsv);
-      store_r(C.rmu, rs, e, dzv);
+      store_r(C.rdz, rs, e, dzv);
     }
     const double a = fmin(1.0, 0.99 * fmin(wave_min(amax_s), wave_min(amax_z)));
     // step, and the residuals and affine target of the new point; a lane
@@ -2015,14 +2218,14 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
     for (int e = lane; e < N * 2; e += W64) {
       const int k = e >> 1, i = e & 1;
       if (!C.contact[e]) continue;
-      double u[6], du[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW],
-          cv[NROW];
+      double u[6], du[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW];
       load_u6(C.ru, k, i, u);
-      load_u6(C.rdu, k, i, du);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
       load_r(C.rs, rs, e, sv);
       load_r(C.rz, rs, e, zv);
       load_r(C.rds, rs, e, dsv);
-      load_r(C.rmu, rs, e, dzv);
+      load_r(C.rdz, rs, e, dzv);
 #pragma unroll
       for (int t = 0; t < 6; ++t) {
         u[t] += a * du[t];
@@ -2035,25 +2238,22 @@ __device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, do
         zv[r] += a * dzv[r];
         rpn = fmax(rpn, fabs(fma(gu[r] - hh[r], isc[r], sv[r])));
         smz += sv[r] * zv[r];
-        cv[r] = sv[r] * zv[r];
       }
       store_r(C.rs, rs, e, sv);
       store_r(C.rz, rs, e, zv);
-      store_r(rc, rs, e, cv);
     }
-    // states: loads of a group first, then its stores
-    for (int e0 = lane; e0 < (N + 1) * NX; e0 += 4 * W64) {
-      double xv[4], dv[4];
+    // states (x_0 is fixed): loads of a group first, then its stores
+    for (int e0 = lane; e0 < N * NX; e0 += 4 * W64) {
+      double xv[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int e = e0 + t * W64;
-        xv[t] = (e < (N + 1) * NX) ? C.rx[e] : 0.0;
-        dv[t] = (e < (N + 1) * NX) ? C.rdx[e] : 0.0;
+        xv[t] = (e < N * NX) ? C.rx[NX + e] : 0.0;
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int e = e0 + t * W64;
-        if (e < (N + 1) * NX) C.rx[e] = xv[t] + a * dv[t];
+        if (e < N * NX) C.rx[NX + e] = xv[t] + a * sb.PV[(e / NX) * 16 + e % NX];
       }
     }
     wsync();
@@ -2111,29 +2311,6 @@ __device__ bool active_set_loop(const Ctx& C, Sh& sh, int maxp, double tol, Coun
     ++nh;
   }
   return false;
-}
-
-__device__ __attribute__((noinline)) void rollout_ru(const Ctx& C, Sh& sh) {
-  gsync();
-  // x = rollout of ru from x0, in FP64, into rx
-  const int lane = lane_id();
-  if (lane < NX) sh.xv[lane] = (double)C.x0[lane];
-  wsync();
-  if (lane < NX) C.rx[lane] = sh.xv[lane];
-  for (int k = 0; k < C.N; ++k) {
-    if (lane < NX) {
-      double acc = C.e ? (double)C.e[k * NX + lane] : 0.0;
-      for (int l = 0; l < NX; ++l) acc += (double)C.A[k * NX * NX + lane * NX + l] * sh.xv[l];
-      for (int l = 0; l < NU; ++l) acc += (double)C.B[k * NX * NU + lane * NU + l] * C.ru[k * NU + l];
-      sh.xn[lane] = acc;
-    }
-    wsync();
-    if (lane < NX) {
-      sh.xv[lane] = sh.xn[lane];
-      C.rx[(k + 1) * NX + lane] = sh.xn[lane];
-    }
-    wsync();
-  }
 }
 
 // The ADMM's input iterate, unscaled, into ru (swing inputs exactly 0).
@@ -2201,7 +2378,7 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     // with the horizon scan the workgroup holds one wave per chunk: all but
     // the first take the scan's commands until the first releases them
     if (threadIdx.x >= W64) {
-      scan_helper<LONG>(C);
+      scan_helper(C, sh.unit);
       return;
     }
   }
@@ -2233,20 +2410,19 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     const int n = C.n;
     gd blk = (gd)(ws.rblk + (size_t)C.b * refine_block_doubles(n));
     C.rT = blk;                       blk += (size_t)n * TS_T;
+    C.rT2 = blk;                      blk += (size_t)n * TS_T;
     C.rK = blk;                       blk += (size_t)n * TS_K;
-    C.rL = blk;                       blk += (size_t)n * TS_L;
-    C.rHwx = blk;                     blk += (size_t)n * TS_H;
+    C.rF = blk;                       blk += (size_t)n * TS_F;
     C.rS = blk;                       blk += (size_t)n * TS_S;
-    C.rkap = blk;                     blk += (size_t)n * NU;
     C.ru = blk;                       blk += (size_t)n * NU;
-    C.rlam = blk;                     blk += (size_t)n * NX;
-    C.rg = blk;                       blk += (size_t)n * NU;
-    C.rmu = blk;                      blk += (size_t)n * 2 * NROW;
+    C.rq = blk;                       blk += (size_t)n * NX;
     C.rs = blk;                       blk += (size_t)n * 2 * NROW;
     C.rz = blk;                       blk += (size_t)n * 2 * NROW;
     C.rds = blk;                      blk += (size_t)n * 2 * NROW;
     C.rdz = blk;                      blk += (size_t)n * 2 * NROW;
+    C.rrc = blk;                      blk += (size_t)n * 2 * NROW;
     C.rdu = blk;                      blk += (size_t)n * NU;
+    blk += (size_t)n * TS_PAD;
     C.rx = blk;                       blk += (size_t)(n + 1) * NX;
     C.rdx = blk;                      blk += (size_t)(n + 1) * NX;
     C.rPV = blk;                      blk += (size_t)n * 16;
@@ -2338,7 +2514,7 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
       if (!ok && ipm_max > 0) {
         // interior point from the ADMM point
         admm_point(C, zsrc, sf, tsc);
-        rollout_ru(C, sh);
+        rollout_ru<LONG>(C, sh);
         cnt.ipm = ipm<LONG>(C, sh, ipm_max, tol, &cnt, res, &kkt, &ok);
         if (!ok) ok = active_set_loop<LONG>(C, sh, pass_c, tol, &cnt, res, &kkt);
       }
@@ -2350,9 +2526,10 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
   } else {
     // the ADMM point as it is: rollout, faces from slack, residuals
     faces_from_u(C, C.ru, 1e-5);
-    rollout_ru(C, sh);
+    rollout_ru<LONG>(C, sh);
+    load_point<LONG>(C, sh);
     const double ts = costates_grad<LONG>(C, sh);
-    kkt = multipliers_kkt(C, res, ts, nullptr);
+    kkt = multipliers_kkt<LONG>(C, sh, res, ts, nullptr);
     res[0] = dyn_residual(C);
   }
 
