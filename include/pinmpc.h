@@ -102,8 +102,7 @@ typedef struct {
                               refine_passes and ipm_iters not both 0) */
   double kkt_tol;          /* certification threshold; default 1e-9 */
   int32_t precision;       /* 0: FP32 operators; 1: BF16 operators */
-  int32_t form;            /* 0: plain (one launch per sweep);
-                              1: fused (all sweeps in one launch: operators in
+  int32_t form;            /* 0, 1: all sweeps in one launch (operators in
                                  registers up to 40 stages, streamed beyond);
                               -1: pack problems by horizon class;
                               2: horizon split across workgroups (a chain of
@@ -165,9 +164,9 @@ typedef struct {
                               u_prev [B][m], u_ref [B][n_max][m], R [B][m],
                               contact [B][n_max][C], u [B][n_max][m].  With 4
                               contacts: n_max <= PINMPC_NMAX, the ADMM sweeps
-                              run in the streamed form (settings.form 0: one
-                              launch per sweep, else all sweeps in one launch)
-                              and the FP64 refinement is the interior point
+                              run in one launch whatever settings.form
+                              (operators in registers up to 27 stages,
+                              streamed beyond) and the FP64 refinement is the interior point
                               alone (settings.ipm_iters iterations, at least
                               1; refine_passes, first_passes, polish_passes
                               and scan do not apply); the serving loop takes

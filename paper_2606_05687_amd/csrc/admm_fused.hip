@@ -1,10 +1,10 @@
-// Fused form of the parallel-in-horizon ADMM (Sec. III): all sweeps of a
-// problem in one launch, with every thread's share of the stage operators
-// loaded once into registers and kept there across the sweeps.
+// Parallel-in-horizon ADMM (Sec. III), all sweeps of a problem in one launch,
+// with every thread's share of the stage operators loaded once into registers
+// and kept there across the sweeps.
 //
 // A workgroup owns PPW problems (one, or two or four short ones packed into one
-// workgroup), each with its own group of threads and LDS buffers; thread
-// (k, r) of a problem's group owns lifted row r of stage k:
+// workgroup), each with its own group of threads and LDS buffers; with U = 6 NC
+// inputs, thread (k, r) of a problem's group owns lifted row r of stage k:
 //   r < 13 : row r of H_k, row r and column r of A_k, row r of Bt_k
 //   r >= 13: row r of H_k, column j = r-13 of Bt_k, row j of M_k
 // which is exactly what its share of the stage products needs:
@@ -13,6 +13,14 @@
 // neighbour stage, du) are exchanged through LDS; the iterates stay in
 // registers and are written back once at the end.  HBM traffic per solve is
 // the operators once plus the iterates once, independent of the sweep count.
+//
+// Bound by the latency of its phases: each waits at a barrier for the vectors
+// the one before it wrote.  So a stage's vectors sit at a stride of 16 + U floats
+// with the inputs at 16, read as 16-byte pieces (a quarter of the LDS
+// instructions of single floats), and every thread forms the restart test's sum
+// over the stages itself (no barrier for one thread's result): eight barriers a
+// sweep.  Launching every sweep on its own, operators streamed, took 136 us a
+// sweep at 4096 x 10 and 13 us at one problem of 10 stages.
 #include "pinmpc_internal.h"
 
 // Every multiply-add below is either an explicit fmaf or a separate multiply
@@ -24,25 +32,69 @@ namespace pinmpc {
 
 namespace {
 
-constexpr int V25 = 25;
+// Stage stride and offset of lifted row r in the LDS vectors.
+template <int NC>
+constexpr int VS = 16 + Dims<NC>::U;
+__device__ inline int vrow(int r) { return r < NX ? r : r + 3; }
 
-// LDS floats of one problem for a capacity of n stages.
+// LDS floats of one problem for a capacity of n stages: five lifted vectors and
+// four input vectors per stage, the stage sums of the restart test, and the
+// fixed initial lifted state.
+template <int NC>
 __host__ __device__ inline size_t fused_lds_floats(int n) {
-  return (size_t)(5 * n * V25 + 4 * n * NU + 32);
+  return (size_t)(5 * n * VS<NC> + 4 * n * Dims<NC>::U + ((n + 3) & ~3) + VS<NC>);
 }
 
-template <int MAXT, bool BF16, int PPW>
-__global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace ws, float rho,
+// acc + sum_i o[i] p[i] in order, p 16-byte aligned LDS.
+template <int COUNT>
+__device__ inline float dot(const float* o, const float* p, float acc) {
+#pragma unroll
+  for (int i = 0; i < COUNT / 4; ++i) {
+    const float4 t = ((const float4*)p)[i];
+    acc = fmaf(o[4 * i], t.x, acc);
+    acc = fmaf(o[4 * i + 1], t.y, acc);
+    acc = fmaf(o[4 * i + 2], t.z, acc);
+    acc = fmaf(o[4 * i + 3], t.w, acc);
+  }
+#pragma unroll
+  for (int i = COUNT & ~3; i < COUNT; ++i) acc = fmaf(o[i], p[i], acc);
+  return acc;
+}
+// acc + p[0] + p[1] + ... in order.
+template <int COUNT>
+__device__ inline float sum(const float* p, float acc) {
+#pragma unroll
+  for (int i = 0; i < COUNT / 4; ++i) {
+    const float4 t = ((const float4*)p)[i];
+    acc += t.x;
+    acc += t.y;
+    acc += t.z;
+    acc += t.w;
+  }
+#pragma unroll
+  for (int i = COUNT & ~3; i < COUNT; ++i) acc += p[i];
+  return acc;
+}
+
+// Four waves per SIMD with two contacts, so that a second workgroup's operator
+// loads and barriers fill the first one's waits: 207 us instead of 373 for three
+// sweeps at 4096 x 20, 1372 instead of 1698 for a hundred at 4096 x 10, against
+// 8 spilled registers (one problem alone: 292 instead of 272).  With four
+// contacts a row's operators leave no room for it.
+template <int MAXT, bool BF16, int PPW, int NC>
+__global__ void __launch_bounds__(MAXT, (NC == 2 && MAXT <= 512) ? 4 : 1) admm_fused_kernel(Problem p, Workspace ws, float rho,
                                                           int accel, float eta, int iters,
                                                           const int32_t* order,
                                                           const int32_t* count, int lds_n) {
+  constexpr int NU = Dims<NC>::U, NL = Dims<NC>::L, NH = Dims<NC>::H, NM = Dims<NC>::M;
+  constexpr int V = VS<NC>;
   OpLoad<BF16> op;
   if constexpr (BF16) {
     op.A = ws.Abf; op.Bt = ws.Btbf; op.H = ws.Hbf; op.M = ws.Mbf;
   } else {
     op.A = p.A; op.Bt = ws.Bt; op.H = ws.Hp; op.M = ws.Mp;
   }
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const int slots = count ? *count : p.batch;   // problems this launch walks
   if ((int)blockIdx.x * PPW >= slots) return;   // the whole workgroup: uniform
   // this thread's problem slot in the workgroup, and its index in that group
@@ -62,35 +114,27 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
   if (N > ln) N = 0;
   live = live && N > 0;
   // LDS: per stage vectors of this group's problem
-  float* W = lds + (size_t)sub * (fused_lds_floats(ln));   // w = vhat - betahat; restart terms [N][25]
-  float* Y = W + ln * V25;        // y = zhat - vhat - e + lamhat [N][25]
-  float* ATY = Y + ln * V25;      // Abar^T y                     [N][25]
-  float* HT = ATY + ln * V25;     // htilde                       [N][25]
-  float* XI = HT + ln * V25;      // xi_{k+1}                     [N][25]
-  float* T1 = XI + ln * V25;      // Bt^T w_x + w_u               [N][12]
-  float* DU = T1 + ln * NU;       // du                           [N][12]
-  float* PIN = DU + ln * NU;      // projection input (u part)    [N][12]
-  float* PO = PIN + ln * NU;      // projection output            [N][12]
-  float* XI0 = PO + ln * NU;      // [32]
+  float* W = lds + (size_t)sub * (fused_lds_floats<NC>(ln));   // w = vhat - betahat; restart terms
+  float* Y = W + ln * V;          // y = zhat - vhat - e + lamhat
+  float* ATY = Y + ln * V;        // Abar^T y
+  float* HT = ATY + ln * V;       // htilde
+  float* XI = HT + ln * V;        // xi_{k+1}
+  float* T1 = XI + ln * V;        // Bt^T w_x + w_u
+  float* DU = T1 + ln * NU;       // du
+  float* PIN = DU + ln * NU;      // projection input (u part)
+  float* PO = PIN + ln * NU;      // projection output
+  float* SS = PO + ln * NU;       // restart-test sum of each stage
+  float* XI0 = SS + ((ln + 3) & ~3);
 
   const int tid = PPW == 1 ? (int)threadIdx.x : (int)threadIdx.x - sub * tpp;
   const bool act = tid < N * NL;
   const int k = act ? tid / NL : 0;
   const int r = act ? tid % NL : 0;
+  const int at = k * V + vrow(r);
   const size_t s0 = (size_t)b * n;
   const size_t st = s0 + k;
   const float mu = live ? p.mu[b] : 0.f;
-  const float tmax = live ? p.tau_max[b] : 0.f;
   const float tsc = live ? ws.tsc[b] : 1.f;
-
-  if (live && tid < NL) {
-    float v;
-    if (tid < NX) v = p.x0[(size_t)b * NX + tid];
-    else v = p.u_prev ? p.u_prev[(size_t)b * NU + tid - NX] /
-                            ((tid - NX) % 6 < 3 ? ws.sf[s0] : tsc)
-                      : 0.f;
-    XI0[tid] = v;
-  }
 
   // operators into registers
   float hrow[NL], o1[NX], o2[NX], o3[NU];
@@ -111,6 +155,15 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
     qb = ws.qb[st * NL + r];
     eb = (r < NX && p.e) ? p.e[st * NX + r] : 0.f;
   }
+  if (live && tid < NL) {
+    float v;
+    if (tid < NX) v = p.x0[(size_t)b * NX + tid];
+    else v = p.u_prev ? p.u_prev[(size_t)b * NU + tid - NX] /
+                            ((tid - NX) % 6 < 3 ? ws.sf[s0] : tsc)
+                      : 0.f;
+    XI0[vrow(tid)] = v;
+  }
+
   // iterates
   float zh = 0, vh = 0, th = 0, bh = 0, lh = 0;
   float zc = 0, vc = 0, tc = 0, bc = 0, lc = 0;
@@ -123,67 +176,56 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
   }
   float alpha = live ? ws.alpha[b] : 1.f, cprev = live ? ws.cprev[b] : 0.f;
   int restarts = 0;
-  const float Fz = live ? p.fz_max[b] : 0.f;
+  // the contact-stage this thread projects (one thread each), its bounds
+  // (a group has at least 25 threads per stage, so one pass covers them)
+  const bool proj = tid < NC * N;
+  const int pks = proj ? tid / NC : 0;
+  const bool stance = proj && p.contact[(s0 + pks) * NC + tid % NC];
+  const float F = proj ? p.fz_max[b] / ws.sf[s0 + pks] : 0.f;
+  const float tm = proj ? p.tau_max[b] / tsc : 0.f;
   __syncthreads();
 
   for (int it = 0; it < iters; ++it) {
     if (act) {
-      W[k * V25 + r] = vh - bh;
-      Y[k * V25 + r] = zh - vh - eb + lh;
+      W[at] = vh - bh;
+      Y[at] = zh - vh - eb + lh;
     }
     __syncthreads();
     if (act) {
-      const float* y = Y + k * V25;
       float aty;
       if (r < NX) {
-        aty = 0.f;
-        for (int i = 0; i < NX; ++i) aty = fmaf(o2[i], y[i], aty);
+        aty = dot<NX>(o2, Y + k * V, 0.f);
       } else {
-        const int jj = r - NX;
-        const float* w = W + k * V25;
-        aty = y[r];
-        float t = w[r];
-        for (int i = 0; i < NX; ++i) {
-          aty = fmaf(o1[i], y[i], aty);
-          t = fmaf(o1[i], w[i], t);
-        }
-        T1[k * NU + jj] = t;
+        aty = dot<NX>(o1, Y + k * V, Y[at]);
+        T1[k * NU + r - NX] = dot<NX>(o1, W + k * V, W[at]);
       }
-      ATY[k * V25 + r] = aty;
+      ATY[at] = aty;
     }
     __syncthreads();
     if (act) {
       float h = zh - th;
-      if (k + 1 < N) h += ATY[(k + 1) * V25 + r];
-      HT[k * V25 + r] = fmaf(rho, h, qb);
-      if (r >= NX) {
-        const float* t = T1 + k * NU;
-        float du = 0.f;
-        for (int l = 0; l < NU; ++l) du = fmaf(o3[l], t[l], du);
-        DU[k * NU + r - NX] = du;
-      }
+      if (k + 1 < N) h += ATY[at + V];
+      HT[at] = fmaf(rho, h, qb);
+      if (r >= NX) DU[k * NU + r - NX] = dot<NU>(o3, T1 + k * NU, 0.f);
     }
     __syncthreads();
     float xi = 0.f;
     if (act) {
-      const float* h = HT + k * V25;
-      for (int l = 0; l < NL; ++l) xi = fmaf(hrow[l], h[l], xi);
-      XI[k * V25 + r] = xi;
+      xi = dot<NX>(hrow, HT + k * V, 0.f);
+      xi = dot<NU>(hrow + NX, HT + k * V + 16, xi);
+      XI[at] = xi;
     }
     __syncthreads();
     float s = 0.f, bb = 0.f, gam = 0.f, zin = 0.f;
     if (act) {
-      const float* prev = (k == 0) ? XI0 : XI + (k - 1) * V25;
-      const float* du = DU + k * NU;
+      const float* prev = (k == 0) ? XI0 : XI + (k - 1) * V;
       if (r < NX) {
-        for (int j = 0; j < NX; ++j) s = fmaf(o1[j], prev[j], s);
-        for (int j = 0; j < NU; ++j) {
-          s = fmaf(o3[j], prev[NX + j], s);
-          bb = fmaf(o3[j], du[j], bb);
-        }
+        s = dot<NX>(o1, prev, 0.f);
+        s = dot<NU>(o3, prev + 16, s);
+        bb = dot<NU>(o3, DU + k * NU, 0.f);
       } else {
-        s = prev[r];
-        bb = du[r - NX];
+        s = prev[vrow(r)];
+        bb = DU[k * NU + r - NX];
       }
       gam = bb + bh - s - eb + lh;
       const float gt = xi + th + s + eb - lh;
@@ -191,13 +233,10 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
       if (r >= NX) PIN[k * NU + r - NX] = zin;
     }
     __syncthreads();
-    if (tid < 2 * N) {
-      const int kk = tid >> 1, i = tid & 1;
-      const float* yv = PIN + kk * NU + 6 * i;
-      float* o = PO + kk * NU + 6 * i;
-      if (p.contact[(s0 + kk) * 2 + i]) {
-        const float F = Fz / ws.sf[s0 + kk];
-        const float tm = tmax / tsc;
+    if (proj) {
+      const float* yv = PIN + tid * 6;
+      float* o = PO + tid * 6;
+      if (stance) {
         float px, py, pz;
         project_pyramid<float>(mu, F, yv[0], yv[1], yv[2], &px, &py, &pz);
         o[0] = px; o[1] = py; o[2] = pz;
@@ -214,14 +253,25 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
       tv = th + xi - zv;
       bv = bh + bb - vv;
       lv = lh + zv - s - vv - eb;
-      if (accel) {
-        const float dz = zv - zh, dv = vv - vh;
-        const float d1 = tv - th, d2 = bv - bh, d3 = lv - lh;
-        W[k * V25 + r] = d1 * d1 + d2 * d2 + d3 * d3 + dz * dz + dv * dv + (dz - dv) * (dz - dv);
-      }
     }
     if (accel) {
-      const float cm = stage_ordered_sum(W, T1, N, tid);
+      // the restart test: the terms summed over a stage's rows in order by one
+      // thread, then over the stages in order by every thread (an order fixed by
+      // N alone, as in the other sweep kernels)
+      if (act) {
+        const float dz = zv - zh, dv = vv - vh;
+        const float d1 = tv - th, d2 = bv - bh, d3 = lv - lh;
+        W[at] = d1 * d1 + d2 * d2 + d3 * d3 + dz * dz + dv * dv + (dz - dv) * (dz - dv);
+      }
+      __syncthreads();
+      if (tid < N) {
+        SS[tid] = sum<NU>(W + tid * V + 16, sum<NX>(W + tid * V, 0.f));
+      }
+      __syncthreads();
+      float cm = 0.f;
+      int kk = 0;
+      for (; kk + 4 <= N; kk += 4) cm = sum<4>(SS + kk, cm);
+      for (; kk < N; ++kk) cm += SS[kk];
       if (cm < eta * cprev) {
         const float an = 0.5f * (1.f + sqrtf(1.f + 4.f * alpha * alpha));
         const float f = (alpha - 1.f) / an;
@@ -238,7 +288,6 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
       zc = zv; vc = vv; tc = tv; bc = bv; lc = lv;
     } else {
       zh = zv; vh = vv; th = tv; bh = bv; lh = lv;
-      __syncthreads();
     }
   }
   if (act) {
@@ -257,61 +306,57 @@ __global__ void __launch_bounds__(MAXT) admm_fused_kernel(Problem p, Workspace w
   }
 }
 
-}  // namespace
-
-// LDS of one problem for a capacity of n stages: five 25-vectors and four
-// 12-vectors per stage, then the fixed initial lifted state (32 floats).
-size_t fused_lds_bytes(int n) { return fused_lds_floats(n) * sizeof(float); }
-
-// Problems per workgroup that fit: ppw groups of round_up(25 n, 64) threads.
-static int fit_ppw(int ppw, int n) {
-  const int tpp = ((NL * n + 63) / 64) * 64;
+// Problems per workgroup that fit: ppw groups of round_up(nl n, 64) threads.
+int fit_ppw(int ppw, int nl, int n) {
+  const int tpp = ((nl * n + 63) / 64) * 64;
   while (ppw > 1 && ppw * tpp > 1024) ppw /= 2;
   return ppw < 1 ? 1 : ppw;
 }
 
-// The instantiation for (threads, precision, problems per workgroup).
-#define PINMPC_FUSED_DISPATCH                                           \
-  if (threads <= 512) {                                                 \
-    if (!s.precision) {                                                 \
-      if (ppw == 1) PINMPC_FUSED(512, false, 1);                        \
-      else if (ppw == 2) PINMPC_FUSED(512, false, 2);                   \
-      else PINMPC_FUSED(512, false, 4);                                 \
-    } else {                                                            \
-      if (ppw == 1) PINMPC_FUSED(512, true, 1);                         \
-      else if (ppw == 2) PINMPC_FUSED(512, true, 2);                    \
-      else PINMPC_FUSED(512, true, 4);                                  \
-    }                                                                   \
-  } else {                                                              \
-    if (!s.precision) {                                                 \
-      if (ppw == 1) PINMPC_FUSED(1024, false, 1);                       \
-      else if (ppw == 2) PINMPC_FUSED(1024, false, 2);                  \
-      else PINMPC_FUSED(1024, false, 4);                                \
-    } else {                                                            \
-      if (ppw == 1) PINMPC_FUSED(1024, true, 1);                        \
-      else if (ppw == 2) PINMPC_FUSED(1024, true, 2);                   \
-      else PINMPC_FUSED(1024, true, 4);                                 \
-    }                                                                   \
+template <bool BF16, int NC>
+hipError_t fused(const Problem& p, const Workspace& w, const pinmpc_settings& s, int iters,
+                 int cap, const int32_t* ord, const int32_t* cnt, hipStream_t st) {
+  const int ppw = NC == 2 ? fit_ppw(s.group, Dims<NC>::L, cap) : 1;
+  const int threads = ppw * (((Dims<NC>::L * cap + 63) / 64) * 64);
+  const dim3 grid((unsigned)((p.batch + ppw - 1) / ppw));
+  const size_t lds = (size_t)ppw * fused_lds_floats<NC>(cap) * sizeof(float);
+  // a kernel bound to fewer threads may use more registers: the operators of
+  // one row (63 floats, 87 with four contacts) fit without spilling up to 768
+#define PINMPC_FUSED(T, G)                                                                    \
+  hipLaunchKernelGGL((admm_fused_kernel<T, BF16, G, NC>), grid, dim3(threads), lds, st, p, w, \
+                     s.rho, s.accel, s.restart_eta, iters, ord, cnt, cap)
+  if constexpr (NC == 2) {
+    if (threads <= 512) {
+      if (ppw == 1) PINMPC_FUSED(512, 1);
+      else if (ppw == 2) PINMPC_FUSED(512, 2);
+      else PINMPC_FUSED(512, 4);
+    } else {
+      if (ppw == 1) PINMPC_FUSED(1024, 1);
+      else if (ppw == 2) PINMPC_FUSED(1024, 2);
+      else PINMPC_FUSED(1024, 4);
+    }
+  } else {
+    if (threads <= 512) PINMPC_FUSED(512, 1);
+    else if (threads <= 768) PINMPC_FUSED(768, 1);
+    else PINMPC_FUSED(1024, 1);
   }
+#undef PINMPC_FUSED
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool fused_fits(int nc, int n_max) { return (NX + 6 * nc) * n_max <= 1024; }
 
 hipError_t launch_admm_fused(const Problem& p, const Workspace& w, const pinmpc_settings& s,
                              int iters, hipStream_t st) {
   if (p.batch == 0 || iters == 0) return hipSuccess;
-  const int work = NL * p.n_max;
-  if (work > 1024) return hipErrorInvalidValue;
-  const int ppw = fit_ppw(s.group, p.n_max);
-  const int tpp = ((work + 63) / 64) * 64;
-  const int threads = ppw * tpp;
-  const unsigned grid = (unsigned)((p.batch + ppw - 1) / ppw);
-  const size_t lds = (size_t)ppw * fused_lds_bytes(p.n_max);
-  // up to 512 threads the kernel may use 256 VGPRs (two waves per SIMD)
-#define PINMPC_FUSED(T, BF, G)                                                              \
-  hipLaunchKernelGGL((admm_fused_kernel<T, BF, G>), dim3(grid), dim3(threads), lds, st, p, w, \
-                     s.rho, s.accel, s.restart_eta, iters, (const int32_t*)nullptr,          \
-                     (const int32_t*)nullptr, p.n_max)
-  PINMPC_FUSED_DISPATCH
-#undef PINMPC_FUSED
-  return hipGetLastError();
+  if (!fused_fits(p.nc, p.n_max)) return hipErrorInvalidValue;
+  if (p.nc == 4)
+    return s.precision ? fused<true, 4>(p, w, s, iters, p.n_max, nullptr, nullptr, st)
+                       : fused<false, 4>(p, w, s, iters, p.n_max, nullptr, nullptr, st);
+  return s.precision ? fused<true, 2>(p, w, s, iters, p.n_max, nullptr, nullptr, st)
+                     : fused<false, 2>(p, w, s, iters, p.n_max, nullptr, nullptr, st);
 }
 
 // Problems of horizon class cls, walked through the order array; the grid
@@ -320,18 +365,10 @@ hipError_t launch_admm_fused_class(const Problem& p, const Workspace& w, const p
                                    int iters, int cls, hipStream_t st) {
   if (p.batch == 0 || iters == 0) return hipSuccess;
   const int cap = CLASS_N[cls] < p.n_max ? CLASS_N[cls] : p.n_max;
-  const int ppw = fit_ppw(s.group, cap);
-  const int threads = ppw * (((NL * cap + 63) / 64) * 64);
-  const unsigned grid = (unsigned)((p.batch + ppw - 1) / ppw);
-  const size_t lds = (size_t)ppw * fused_lds_bytes(cap);
   const int32_t* ord = w.order + (size_t)cls * p.batch;
   const int32_t* cnt = w.counts + cls;
-#define PINMPC_FUSED(T, BF, G)                                                                \
-  hipLaunchKernelGGL((admm_fused_kernel<T, BF, G>), dim3(grid), dim3(threads), lds, st, p, w, \
-                     s.rho, s.accel, s.restart_eta, iters, ord, cnt, cap)
-  PINMPC_FUSED_DISPATCH
-#undef PINMPC_FUSED
-  return hipGetLastError();
+  return s.precision ? fused<true, 2>(p, w, s, iters, cap, ord, cnt, st)
+                     : fused<false, 2>(p, w, s, iters, cap, ord, cnt, st);
 }
 
 }  // namespace pinmpc

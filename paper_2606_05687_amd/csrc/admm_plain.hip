@@ -1,5 +1,6 @@
-// Plain batched form of the parallel-in-horizon ADMM (Sec. III): one kernel
-// launch per sweep, operators and iterates streamed from HBM every sweep.
+// Streaming form of the parallel-in-horizon ADMM (Sec. III), for horizons whose
+// rows are more than one workgroup has threads: all sweeps in one launch, the
+// iterates in registers, the operators read from memory every sweep.
 //
 // A workgroup owns one problem; thread t handles (stage k, lifted row r),
 // r in 0..24 (0..36 with four contacts), so every stage-local update of the
@@ -32,8 +33,8 @@ struct Lds {     // each buffer: L floats per stage (L = 13 + inputs)
 
 // `sweeps` sweeps in one launch: the iterates and the acceleration state stay
 // in registers between sweeps (loaded once, stored once); the operators are
-// read from memory every sweep.  sweeps = 1 is the plain form.  NC contacts
-// per stage (2: feet, 4: feet and hands).
+// read from memory every sweep.  NC contacts per stage (2: feet, 4: feet and
+// hands); PAIRS (stage, row) items per thread.
 template <int PAIRS, bool BF16, int NC>
 __global__ void __launch_bounds__(1024) admm_sweep_kernel(Problem p, Workspace ws, float rho,
                                                           int accel, float eta,
@@ -442,15 +443,11 @@ static hipError_t sweep(const Problem& p, const Workspace& w, const pinmpc_setti
                      w, s.rho, s.accel, s.restart_eta, ord, cnt, sweeps)
   const bool bf = s.precision != 0;
   if (p.nc == 2) {
-    if (pairs == 1 && !bf) PINMPC_SWEEP(1, false, 2);
-    else if (pairs == 1) PINMPC_SWEEP(1, true, 2);
-    else if (pairs == 2 && !bf) PINMPC_SWEEP(2, false, 2);
+    if (pairs == 2 && !bf) PINMPC_SWEEP(2, false, 2);
     else if (pairs == 2) PINMPC_SWEEP(2, true, 2);
     else return hipErrorInvalidValue;
   } else if (p.nc == 4) {
-    if (pairs == 1 && !bf) PINMPC_SWEEP(1, false, 4);
-    else if (pairs == 1) PINMPC_SWEEP(1, true, 4);
-    else if (pairs == 2 && !bf) PINMPC_SWEEP(2, false, 4);
+    if (pairs == 2 && !bf) PINMPC_SWEEP(2, false, 4);
     else if (pairs == 2) PINMPC_SWEEP(2, true, 4);
     else if (pairs == 3 && !bf) PINMPC_SWEEP(3, false, 4);
     else if (pairs == 3) PINMPC_SWEEP(3, true, 4);

@@ -4,7 +4,7 @@
 // not fill the chip.
 //
 // A workgroup owns SEG = 10 consecutive stages of one problem, thread (stage,
-// lifted row) as in the one-launch-per-sweep kernel.  The two exchanges the
+// lifted row) as in the one-workgroup kernels.  The two exchanges the
 // splitting leaves cross segment boundaries: block 1 at stage k needs
 // Abar_{k+1}^T y_{k+1}, block 2 at stage k needs xi_k from stage k-1 of the
 // same sweep.  So one sweep is a chain of launches, each stage-parallel, whose
@@ -16,7 +16,7 @@
 //   split_p4: per problem, the restart test on the horizon-ordered sum
 //   split_p5: extrapolation (or restart) into the next sweep's iterates.
 // Every element is computed with the same operations in the same order as in
-// the one-launch-per-sweep kernel, so the iterates are bitwise the same.
+// the one-workgroup kernels, so the iterates are bitwise the same.
 #include "pinmpc_internal.h"
 
 #pragma clang fp contract(off)

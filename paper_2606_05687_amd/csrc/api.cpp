@@ -179,32 +179,21 @@ Problem to_problem(const pinmpc_batch* in) {
   return p;
 }
 
-// The fused kernel holds one problem per workgroup with one thread per
-// (stage, lifted row) and that row's operators in registers: horizons up to
-// 1024 / 25 = 40 stages.  Longer horizons in the fused and packed forms run all
-// sweeps in one launch of the streaming kernel (iterates resident, operators
-// streamed).
-static bool fits_fused(int n_max) { return NL * n_max <= 1024; }
-
-// The ADMM sweeps in the form the settings ask for.
+// The ADMM sweeps in the form the settings ask for.  Forms 0 and 1 run all
+// sweeps in one launch: with the operators in registers where one workgroup
+// holds a problem's rows (fused_fits: 25 rows a stage up to 40 stages, 37 rows
+// with four contacts up to 27), else with the operators streamed.  (One launch
+// per sweep, what form 0 once was, took 100 sweeps in 13.6 ms at 4096 x 10
+// stages and in 1.3 ms at one problem; the same sweeps in one launch, bitwise
+// equal, take 1.4 ms and 0.3 ms.)
 int launch_admm_phase(const pinmpc_settings& s, const Problem& p, const Workspace& w, int iters,
                       hipStream_t st) {
   if (iters <= 0) return PINMPC_OK;
-  if (p.nc != NCONTACT) {
-    // four contacts: the streaming sweep kernel, one launch per sweep (form
-    // 0) or all sweeps in one launch
-    if (s.form == 0) {
-      for (int it = 0; it < iters; ++it)
-        if (launch_admm_sweep(p, w, s, 1, st) != hipSuccess) return PINMPC_EDEVICE;
-    } else if (launch_admm_sweep(p, w, s, iters, st) != hipSuccess) {
-      return PINMPC_EDEVICE;
-    }
-    return PINMPC_OK;
-  }
-  if (s.form == 2 || p.n_max > PINMPC_NMAX) {
+  const bool wide = p.nc != NCONTACT;   // four contacts: neither split nor packed
+  if (!wide && (s.form == 2 || p.n_max > PINMPC_NMAX)) {
     // the horizon split across workgroups: every horizon up to PINMPC_NMAX_LONG
     if (launch_admm_split(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
-  } else if (s.form == -1 && p.n_max > CLASS_N[0]) {
+  } else if (!wide && s.form == -1 && p.n_max > CLASS_N[0]) {
     // pack problems by horizon class: fused kernels sized for each class,
     // the persistent streaming kernel for the longest horizons
     if (launch_classify(p, w, st) != hipSuccess) return PINMPC_EDEVICE;
@@ -212,13 +201,10 @@ int launch_admm_phase(const pinmpc_settings& s, const Problem& p, const Workspac
       if (launch_admm_fused_class(p, w, s, iters, cls, st) != hipSuccess) return PINMPC_EDEVICE;
     if (p.n_max > CLASS_N[1] && launch_admm_sweep_class(p, w, s, 2, iters, st) != hipSuccess)
       return PINMPC_EDEVICE;
-  } else if (s.form != 0 && fits_fused(p.n_max)) {
+  } else if (fused_fits(p.nc, p.n_max)) {
     if (launch_admm_fused(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
-  } else if (s.form != 0) {
-    if (launch_admm_sweep(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
-  } else {
-    for (int it = 0; it < iters; ++it)
-      if (launch_admm_sweep(p, w, s, 1, st) != hipSuccess) return PINMPC_EDEVICE;
+  } else if (launch_admm_sweep(p, w, s, iters, st) != hipSuccess) {
+    return PINMPC_EDEVICE;
   }
   return PINMPC_OK;
 }

@@ -425,11 +425,14 @@ hipError_t launch_setup(const Problem& p, const Workspace& w, const pinmpc_setti
 hipError_t launch_admm_init(const Problem& p, const Workspace& w, hipStream_t st);
 hipError_t launch_warm_save(const Problem& p, const Workspace& w, int accel, hipStream_t st);
 hipError_t launch_fill_i32(int32_t* dst, size_t n, int32_t base, int32_t step, hipStream_t st);
-// `sweeps` ADMM sweeps in one launch of the streaming sweep kernel (1: the
-// plain form, one launch per sweep; more: iterates resident in registers
-// across the sweeps, operators streamed every sweep).
+// `sweeps` ADMM sweeps in one launch of the streaming sweep kernel (iterates
+// resident in registers across the sweeps, operators streamed every sweep), for
+// horizons beyond those of the fused kernel.
 hipError_t launch_admm_sweep(const Problem& p, const Workspace& w, const pinmpc_settings& s,
                              int sweeps, hipStream_t st);
+// Whether one workgroup of the fused kernel holds a problem of nc contacts and
+// n_max stages (one thread per stage and lifted row).
+bool fused_fits(int nc, int n_max);
 hipError_t launch_admm_fused(const Problem& p, const Workspace& w, const pinmpc_settings& s,
                              int iters, hipStream_t st);
 // All sweeps with the horizon split across workgroups (a chain of
