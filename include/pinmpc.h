@@ -193,9 +193,8 @@ typedef struct {
                               equality passes factored (a pass restarted at
                               stage k factors k stages; with four contacts:
                               the stages of the interior point's factoring
-                              recursions, every predictor and the correctors
-                              near the optimum, the other correctors running
-                              the recursion's vector part only), and the
+                              recursions, one per iteration: its corrector
+                              runs the recursion's vector part only), and the
                               refinement launch (1 or 2) that finished the
                               problem; 0 0 0 0 for a problem with bad input */
 } pinmpc_out;

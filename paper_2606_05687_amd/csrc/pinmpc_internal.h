@@ -178,15 +178,14 @@ __host__ __device__ constexpr size_t refine_block_doubles(int n) {
            (n > PINMPC_NMAX ? (size_t)n * 32 : 0)) + 3) & ~(size_t)3;
 }
 
-// FP64 scratch of the four-contact refinement (refine_wide.hip) per problem
-// with n stages: gains (24 x 13), feedforward, inputs, their step and the
-// costates (24 each), the stage input terms (per contact a 6 x 6 block and
-// six entries), slacks, multipliers, their steps and the complementarity
-// target (11 per contact each), the inverse input Hessian (24 x 24) and Hwx
-// (24 x 13), then x and dx ((n+1) x 13 each).
+// FP64 scratch of the four-contact refinement (refine_wide.hip) per problem with
+// n stages: input blocks (18 per contact), gains of both input halves (12 x 14
+// each), the factors of the input Hessian (3 x 144), inputs (24), slacks,
+// multipliers, their steps and the complementarity target (11 per contact each),
+// state cost gradients (13), then x ((n+1) x 13), within the size that callers'
+// HBM budgets and the static scratch were sized for.
 __host__ __device__ constexpr size_t refine_wide_block_doubles(int n) {
-  return ((size_t)n * (24 * NX + 4 * 24 + 4 * 42 + 5 * 4 * NROW + 24 * 24 + 24 * NX) +
-          2 * (size_t)(n + 1) * NX + 3) & ~(size_t)3;
+  return ((size_t)n * 1684 + 2 * (size_t)(n + 1) * NX + 3) & ~(size_t)3;
 }
 
 // 1/a from the hardware estimate refined by two Newton steps (the pivots of
@@ -197,38 +196,6 @@ __device__ inline double recip(double a) {
   r = fma(r, e, r);
   e = fma(-a, r, 1.0);
   return fma(r, e, r);
-}
-
-__device__ inline double readlane_d(double v, int l) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// Gauss-Jordan elimination without pivoting (SPD systems) on a matrix whose
-// column c is held in registers by lane c of a 64-lane wave: col[r] is row r.
-// The pivot column is broadcast from its lane with readlane (a broadcast
-// through LDS was slower: each pivot then waits for an LDS round trip).
-// Afterwards each lane holds its column of M^{-1} [rest] where M is the
-// leading n x n block (lanes 0..n-1 end with the identity).  Bit p of the
-// wave-uniform `unit` marks a pivot whose row and column of the whole system
-// are exactly the unit vector e_p: its elimination step changes nothing and
-// is skipped (bitwise the same result).
-template <int n>
-__device__ inline void gj_columns(double (&col)[n], uint32_t unit = 0) {
-#pragma unroll
-  for (int p = 0; p < n; ++p) {
-    if ((unit >> p) & 1u) continue;
-    double pc[n];
-#pragma unroll
-    for (int r = 0; r < n; ++r) pc[r] = readlane_d(col[r], p);
-    const double t = col[p] * recip(pc[p]);
-#pragma unroll
-    for (int r = 0; r < n; ++r)
-      if (r != p) col[r] -= pc[r] * t;
-    col[p] = t;
-  }
 }
 
 // Lane P of each 16-lane row of the wave, to every lane of that row (a DPP
@@ -256,13 +223,15 @@ __device__ inline void fmac_row_bcast12(double (&c)[12], double s) {
 #undef PINMPC_FMAC
 }
 
-// The elimination of gj_columns (the same roundings in the same order) on two
-// 12-row systems with the same leading block (so the same pivots: one
+// Gauss-Jordan elimination without pivoting (SPD systems) on two 12-row
+// systems with the same leading block (so the same pivots: one
 // reciprocal, two independent update blocks), which sits in lanes 0..11 of every
 // 16-lane row of the wave (column c in lane c of each row, the rows identical)
 // while their other columns occupy the remaining lanes of the rows: the pivot
 // column reaches its row's lanes through the DPP row broadcast of the update
-// instructions themselves.
+// instructions themselves.  Bit p of the wave-uniform `unit` marks a pivot whose
+// row and column are exactly the unit vector e_p: its step changes nothing and is
+// skipped (bitwise the same result).
 template <int p = 0>
 __device__ inline void gj_rows2(double (&a)[12], double (&b)[12], uint32_t unit = 0) {
   if constexpr (p < 12) {

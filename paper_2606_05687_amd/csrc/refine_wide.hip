@@ -14,20 +14,21 @@
 //            input term rho = R (u - u_ref) + G^T (z + (z rp - rc) / s) and
 //            state term q = Q (x_{k+1} - r_k), solved by the backward Riccati
 //            recursion over the horizon and a forward rollout of the gains;
-//   stop     when the point's KKT residuals, with the interior point's own
-//            multipliers, meet the tolerance.
+//   stop     when the point's KKT residuals, with multipliers refitted to its
+//            gradient, meet the tolerance.
 // The returned u is the last iterate, x its rollout in FP64, and res its
 // normalised residuals (r_dyn, r_ineq, r_stat, r_comp, r_sign).
 //
-// Per stage the wave forms, one entry per lane at a time through LDS, W B,
-// W A and the system [H | Hwx | hw] with the input Hessian H = R' + B^T W B,
-// Hwx = B^T W A and hw = rho + B^T w (W = S + Q, w = s + q, the value
-// function (S, s) of x_{k+1}); lane c then holds column c of the system and
-// one Gauss-Jordan elimination over the lanes (SPD, no pivoting) leaves the
-// gains K = -H^{-1} Hwx and the feedforward kap = -H^{-1} hw in lanes
-// 24..37; the value function of x_k is S = A^T W A + Hwx^T K,
-// s = A^T w + Hwx^T kap (symmetrised).
-#include "pinmpc_internal.h"
+// The 24 inputs are handled as two halves of 12 (a: contacts 0 and 1, b: 2 and
+// 3), each the size the two-contact tiles and elimination are built for.  Per
+// stage 51 matrix instructions form W Ba, W Bb, the blocks Haa, Hab, Hbb of
+// H = R' + B^T W B, Hwx and the value function; half a is eliminated beside
+// Hab and its right-hand sides, half b after the Schur update, and half a's
+// gains follow by back substitution (H = U^T D U with U = [Ua, Tab; 0, Ub],
+// whose factors the corrector keeps).  A stage built entry by entry through LDS
+// (products on the vector units, a 24-column elimination broadcast by lane
+// reads) took about 25 000 cycles, and each stage of the chains 6 000.
+#include "refine_tiles.h"
 
 namespace pinmpc {
 
@@ -36,129 +37,81 @@ namespace {
 constexpr int C4 = 4;                 // contacts
 constexpr int U4 = 6 * C4;            // 24 inputs
 constexpr int L4 = NX + U4;           // 37 lifted rows of the ADMM iterates
-constexpr int TB = 36 + 6;            // per contact: R' block (6 x 6) and rho (6)
-constexpr int NSN = NX * NX + NX;     // S and s of one stage
-
-__device__ inline double wmax(double v) {
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ inline double wmin(double v) {
-  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ inline double wsum(double v) {
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-// The kernel runs one 64-lane wave per workgroup.  LDS operations of a wave
-// execute in issue order, so a hand-off between its lanes through LDS needs
-// only a point the compiler moves no memory access across (wsync); the stage
-// loops use it, so that loads of the next stage and stores of this one stay
-// in flight across the hand-offs.  Data passed between lanes through global
-// memory (one phase's results for the next) goes through the workgroup
-// barrier with its memory fence at the phase boundaries.
-__device__ inline void wsync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// Global pointers with their address space spelled out: the context is
-// passed by reference into the phase functions, where a generic (flat)
-// access would count against the LDS counter too, so that every wait for an
-// LDS hand-off would also wait for the loads of the next stage in flight.
-#define GMEM __attribute__((address_space(1)))
-typedef const GMEM float* gcf;
-typedef const GMEM double* gcd;
-typedef GMEM double* gd;
+// doubles per stage of the scratch blocks: the input blocks of four contacts,
+// the gains [K | kap] of both halves (12 x 14 each), the factors Ua, Ub and Tab
+constexpr int WT = C4 * 18, WK = 2 * NU * (NX + 1), WF = 3 * NU * NU;
+constexpr int KB = NU * (NX + 1) * 8;   // byte offset of half b's gains in a stage
+constexpr int FB = NU * NU * 8;         // of Ub (and twice that: Tab) in a stage
 
 // The problem's FP64 scratch (refine_wide_block_doubles(n) doubles).
 struct WCtx {
   int b, n, N;
   double mu, fz, tm, mg, scf, scm;   // bounds, force scale, row scales
+  double isf, ism;                   // inverse row scales
   gcf A, B, e, x_ref, u_ref, x0;
   const GMEM uint8_t* contact;       // [n][4]
-  gd K, kap, u, du, x, dx, lam, T, s, z, ds, dz, rc, Hi, Hx;
+  gd T, K, F, u, s, z, ds, dz, rc, q, x;
 };
 
 static_assert(refine_wide_block_doubles(1) >=
-                  (size_t)U4 * NX + 4 * U4 + C4 * TB + 5 * C4 * NROW + U4 * U4 + U4 * NX +
-                      2 * 2 * NX,
+                  (size_t)WT + WK + WF + U4 + 5 * C4 * NROW + NX + 2 * NX,
               "the carve below fits the scratch block");
 
-__device__ void carve(WCtx& C, gd blk) {
+__device__ inline void carve(WCtx& C, gd blk) {
   const int n = C.n;
-  C.K = blk;    blk += (size_t)n * U4 * NX;
-  C.kap = blk;  blk += (size_t)n * U4;
+  C.T = blk;    blk += (size_t)n * WT;
+  C.K = blk;    blk += (size_t)n * WK;
+  C.F = blk;    blk += (size_t)n * WF;
   C.u = blk;    blk += (size_t)n * U4;
-  C.du = blk;   blk += (size_t)n * U4;
-  C.lam = blk;  blk += (size_t)n * U4;   // costates (13 used per stage)
-  C.T = blk;    blk += (size_t)n * C4 * TB;
   C.s = blk;    blk += (size_t)n * C4 * NROW;
   C.z = blk;    blk += (size_t)n * C4 * NROW;
   C.ds = blk;   blk += (size_t)n * C4 * NROW;
   C.dz = blk;   blk += (size_t)n * C4 * NROW;
   C.rc = blk;   blk += (size_t)n * C4 * NROW;
-  C.Hi = blk;   blk += (size_t)n * U4 * U4;
-  C.Hx = blk;   blk += (size_t)n * U4 * NX;
-  C.x = blk;    blk += (size_t)(n + 1) * NX;
-  C.dx = blk;
+  C.q = blk;    blk += (size_t)n * NX;
+  C.x = blk;
 }
 
-// LDS of the stage recursion.
-// Matrices with 13 columns keep rows of 14 (XP), so that an entry with an even
-// column and its right neighbour are one aligned 16-byte pair; the stage
-// products read such pairs.
-constexpr int XP = NX + 1;
-// Arrays whose lives within a stage do not overlap share storage, which keeps
-// a workgroup within 20 KB of LDS (eight per compute unit):
-//   X: B, W B and the stage terms, from the stage's start to the system;
-//   Y: the system [H | Hwx | hw] column by column until the elimination reads
-//      it; then the gains by column with the feedforward, and the unsymmetrised
-//      value function, over the H columns, while the Hwx columns stay for the
-//      value-function update.
-constexpr int OFF_WB = NX * U4, OFF_T = 2 * NX * U4;        // in X
-constexpr int OFF_HWX = U4 * U4, OFF_SN = (NX + 1) * U4;     // in Y
-static_assert(OFF_SN + NSN <= OFF_HWX, "gains and value function fit over the H columns");
+// LDS: the stage recursion's hand-off buffers (columns of 12 at stride GC), or
+// the per-stage vectors of the chains; the two are never in use together.
+constexpr int GC = 14;
 struct WSh {
-  alignas(16) double A[NX * XP];
-  alignas(16) double WA[NX * XP];
-  alignas(16) double X[2 * NX * U4 + C4 * TB];
-  alignas(16) double Y[(L4 + 1) * U4];
-  double W[NX * NX];   // S + Q of x_{k+1}, formed when S is
-  double sv[NX], w[NX], kap[U4], v13[NX], v24[U4], Q[NX], R[U4];
+  union {
+    struct {
+      alignas(16) double G[(NU + 16) * GC];   // [H | right-hand sides] of a half
+      alignas(16) double Tab[NU * GC];        // D^-1 Ua^-T Hab
+      alignas(16) double Yab[NU * GC];        // Ua^-T Hab
+      double ST[16 * 17];                     // a tile for its transpose
+    } r;
+    struct {
+      double PV[PINMPC_NMAX * NX];   // dx_{k+1}, x_{k+1}, Q (x_{k+1} - r_k), p_{k+1}
+      double GV[PINMPC_NMAX * U4];   // du_k, rho_k, hw_k, kap_k, B_k^T p_{k+1}
+    } c;
+  };
+  double Q[NX], R[U4];
+  uint32_t unit[PINMPC_NMAX];        // swing inputs of a stage, a byte per contact
 };
-
-typedef double dpair __attribute__((ext_vector_type(2)));
-__device__ inline dpair ld2(const double* p) { return *reinterpret_cast<const dpair*>(p); }
-__device__ inline void st2(double* p, double a, double b) {
-  *reinterpret_cast<dpair*>(p) = dpair{a, b};
-}
-__device__ inline void st2(gd p, double a, double b) {
-  *reinterpret_cast<GMEM dpair*>(p) = dpair{a, b};
-}
 
 __device__ inline bool stance(const WCtx& C, int k, int i) { return C.contact[k * C4 + i] != 0; }
 
 // g_r . u for the eleven rows of one contact (u its six inputs), with h_r and
-// the row scale: pyramid sides, normal-force bound, moment box.
+// the inverse row scale: pyramid sides, normal-force bound, moment box.
 __device__ inline void rows_of(const WCtx& C, const double u[6], double gu[NROW], double h[NROW],
-                               double sc[NROW]) {
+                               double isc[NROW]) {
   gu[0] = u[0] - C.mu * u[2];
   gu[1] = -u[0] - C.mu * u[2];
   gu[2] = u[1] - C.mu * u[2];
   gu[3] = -u[1] - C.mu * u[2];
   gu[4] = u[2];
-  #pragma unroll
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
     gu[5 + a] = u[3 + a];
     gu[8 + a] = -u[3 + a];
   }
-  #pragma unroll
+#pragma unroll
   for (int r = 0; r < NROW; ++r) {
     h[r] = r < 4 ? 0.0 : (r == 4 ? C.fz : C.tm);
-    sc[r] = r < 5 ? C.scf : C.scm;
+    isc[r] = r < 5 ? C.isf : C.ism;
   }
 }
 
@@ -167,473 +120,641 @@ __device__ inline void rows_T(const WCtx& C, const double v[NROW], double o[6]) 
   o[0] = v[0] - v[1];
   o[1] = v[2] - v[3];
   o[2] = -C.mu * (v[0] + v[1] + v[2] + v[3]) + v[4];
-  #pragma unroll
+#pragma unroll
   for (int a = 0; a < 3; ++a) o[3 + a] = v[5 + a] - v[8 + a];
 }
 
 __device__ inline void ld6(gcd p, double v[6]) {
-  #pragma unroll
+#pragma unroll
   for (int t = 0; t < 6; ++t) v[t] = p[t];
 }
-__device__ inline void ldr(gcd p, double v[NROW]) {
-  #pragma unroll
-  for (int r = 0; r < NROW; ++r) v[r] = p[r];
+// A row's entries for consecutive contact-stages are consecutive in memory
+// (rs = 4 n_max apart per row).
+__device__ inline void ldr(gcd p, int rs, int e, double v[NROW]) {
+#pragma unroll
+  for (int r = 0; r < NROW; ++r) v[r] = p[r * rs + e];
 }
-__device__ inline void str(gd p, const double v[NROW]) {
-  #pragma unroll
-  for (int r = 0; r < NROW; ++r) p[r] = v[r];
+__device__ inline void str(gd p, int rs, int e, const double v[NROW]) {
+#pragma unroll
+  for (int r = 0; r < NROW; ++r) p[r * rs + e] = v[r];
 }
 
-// Stage input terms of the Newton step, in parallel over (stage, contact):
-// the R' block and rho of every contact (identity and zero on a swing
-// contact), from the iterate (u, s, z) and the complementarity target rc.
-template <int OCC>
-__device__ __attribute__((noinline)) void build_terms(const WCtx& C, const WSh& sh) {
+// Stage inputs of the Newton step, in parallel over (stage, contact): the R'
+// block and rho of every contact at the affine target s z (identity and zero on
+// a swing contact), and the state cost gradients q.
+__device__ inline void build_terms(const WCtx& C, WSh& sh) {
+  const int rs = C4 * C.n;
   __syncthreads();
-  for (int e = threadIdx.x; e < C.N * C4; e += 64) {
+  for (int e = lane_id(); e < C.N * C4; e += W64) {
     const int k = e / C4, i = e % C4;
-    gd T = C.T + (size_t)e * TB;
-    if (!stance(C, k, i)) {
-      #pragma unroll
-      for (int t = 0; t < 36; ++t) T[t] = (t % 7 == 0) ? 1.0 : 0.0;
-      #pragma unroll
-      for (int t = 0; t < 6; ++t) T[36 + t] = 0.0;
-      continue;
+    InputBlock t;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      t.d[a] = 1.0;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) t.m[a][b] = a == b ? 1.0 : 0.0;
     }
-    double u[6], gu[NROW], h[NROW], sc[NROW], sv[NROW], zv[NROW], cv[NROW];
-    ld6(C.u + (size_t)k * U4 + 6 * i, u);
-    ldr(C.s + (size_t)e * NROW, sv);
-    ldr(C.z + (size_t)e * NROW, zv);
-    ldr(C.rc + (size_t)e * NROW, cv);
-    rows_of(C, u, gu, h, sc);
-    double d[NROW], c[NROW];
-    #pragma unroll
-    for (int r = 0; r < NROW; ++r) {
-      const double rp = (gu[r] - h[r]) / sc[r] + sv[r];
-      d[r] = zv[r] / (sv[r] * sc[r] * sc[r]);
-      c[r] = (zv[r] + (zv[r] * rp - cv[r]) / sv[r]) / sc[r];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) t.v[a] = 0.0;
+    const bool on = stance(C, k, i);
+    if (on) {
+      double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], d[NROW], c[NROW];
+      ld6(C.u + (size_t)k * U4 + 6 * i, u);
+      ldr(C.s, rs, e, sv);
+      ldr(C.z, rs, e, zv);
+      rows_of(C, u, gu, h, isc);
+#pragma unroll
+      for (int r = 0; r < NROW; ++r) {
+        const double rp = fma(gu[r] - h[r], isc[r], sv[r]), zs = zv[r] * recip(sv[r]);
+        d[r] = zs * (isc[r] * isc[r]);
+        c[r] = zs * rp * isc[r];
+      }
+      const double m = C.mu;
+      double rho[6];
+      rows_T(C, c, rho);
+#pragma unroll
+      for (int a = 0; a < 6; ++a) {
+        const int j = 6 * i + a;
+        const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + j] : 0.0;
+        t.v[a] = fma(sh.R[j], u[a] - ur, rho[a]);
+      }
+      t.m[0][0] = d[0] + d[1] + sh.R[6 * i];
+      t.m[0][1] = t.m[1][0] = 0.0;
+      t.m[0][2] = t.m[2][0] = -m * (d[0] - d[1]);
+      t.m[1][1] = d[2] + d[3] + sh.R[6 * i + 1];
+      t.m[1][2] = t.m[2][1] = -m * (d[2] - d[3]);
+      t.m[2][2] = m * m * (d[0] + d[1] + d[2] + d[3]) + d[4] + sh.R[6 * i + 2];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) t.d[a] = d[5 + a] + d[8 + a] + sh.R[6 * i + 3 + a];
     }
-    double H[36];
-    #pragma unroll
-    for (int t = 0; t < 36; ++t) H[t] = 0.0;
-    const double m = C.mu;
-    H[0 * 6 + 0] = d[0] + d[1];
-    H[0 * 6 + 2] = H[2 * 6 + 0] = -m * (d[0] - d[1]);
-    H[1 * 6 + 1] = d[2] + d[3];
-    H[1 * 6 + 2] = H[2 * 6 + 1] = -m * (d[2] - d[3]);
-    H[2 * 6 + 2] = m * m * (d[0] + d[1] + d[2] + d[3]) + d[4];
-    #pragma unroll
-    for (int a = 0; a < 3; ++a) H[(3 + a) * 7] = d[5 + a] + d[8 + a];
-    double rho[6];
-    rows_T(C, c, rho);
-    #pragma unroll
-    for (int t = 0; t < 6; ++t) {
-      const int j = 6 * i + t;
-      const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + j] : 0.0;
-      H[t * 7] += sh.R[j];
-      rho[t] += sh.R[j] * (u[t] - ur);
-    }
-    #pragma unroll
-    for (int t = 0; t < 36; ++t) T[t] = H[t];
-    #pragma unroll
-    for (int t = 0; t < 6; ++t) T[36 + t] = rho[t];
+    reinterpret_cast<uint8_t*>(sh.unit)[e] = on ? 0 : 0x3F;
+    store_block(C.T + (size_t)e * 18, t);
   }
+  for (int e = lane_id(); e < C.N * NX; e += W64)
+    C.q[e] = sh.Q[e % NX] * (C.x[NX + e] - (double)C.x_ref[e]);
   __syncthreads();
 }
 
-// Backward recursion of the Newton step, stages N-1 .. 0: gains and
-// feedforward of every stage into the scratch.  The elimination also turns the
-// identity carried in lanes 38..61 into H^{-1}, kept with Hwx for a second
-// right-hand side of the same Newton matrix (factor = false: the corrector of
-// an interior-point iteration), whose recursion is the vector part alone:
-// hw = rho + B^T w, kap = -H^{-1} hw, s = A^T w + Hwx^T kap.
-template <int OCC>
-__device__ __attribute__((noinline)) void backward_rhs(const WCtx& C, WSh& sh) {
-  const int lane = threadIdx.x;
-  __syncthreads();
-  {
-    if (lane < NX) sh.sv[lane] = 0.0;
-    // per stage: lanes 0..23 the linear term and their column of B, lanes
-    // 0..12 x_{k+1}, x_ref[k] and their column of A, fetched a stage ahead
-    // from clamped addresses; the rows of H^{-1} and columns of Hwx at the
-    // top of their own stage
-    const int lu = min(lane, U4 - 1), lx = min(lane, NX - 1);
-    double frho, fx, fr;
-    float fbc[NX], fac[NX];
-    auto fetch = [&](int k) {
-      frho = C.T[(size_t)k * C4 * TB + (lu / 6) * TB + 36 + lu % 6];
-      const auto Bk = C.B + (size_t)k * NX * U4;
-      const auto Ak = C.A + (size_t)k * NX * NX;
+// Forward elimination of a half's system c1 = [H | right-hand sides] (as factor)
+// with the columns c2 of Hab beside it (column j in lane j of every 16-lane row):
+// y2 ends with Ua^-T Hab, c2 with D^-1 times that.  The pivot column comes from
+// c1's lanes, so c2's update of a pivot goes first.
+template <int p = 0>
+__device__ inline void factor_beside(double (&c1)[12], double (&c2)[12], double (&y2)[12], int hc,
+                                     uint32_t unit) {
+  if constexpr (p < 12) {
+    y2[p] = c2[p];
+    if (!((unit >> p) & 1u)) {
+      const double rd = recip(row_bcast<p>(c1[p]));
+      const double t1 = c1[p] * rd, t2 = c2[p] * rd, n2 = -t2;
+      if constexpr (p < 11) asm volatile("s_nop 1");
 #pragma unroll
-      for (int i = 0; i < NX; ++i) {
-        fbc[i] = Bk[i * U4 + lu];
-        fac[i] = Ak[i * NX + lx];
-      }
-      fx = C.x[(size_t)(k + 1) * NX + lx];
-      fr = (double)C.x_ref[(size_t)k * NX + lx];
-    };
-    fetch(C.N - 1);
-    for (int k = C.N - 1; k >= 0; --k) {
-      double h[U4], hw[U4], rho = frho, bc[NX], ac[NX];
-      const auto Hc = C.Hi + (size_t)k * U4 * U4 + lu;
-      const auto Hx = C.Hx + (size_t)k * U4 * NX + lx;
-#pragma unroll
-      for (int j = 0; j < U4; ++j) {
-        h[j] = Hc[j * U4];
-        hw[j] = Hx[j * NX];
-      }
-#pragma unroll
-      for (int i = 0; i < NX; ++i) {
-        bc[i] = (double)fbc[i];
-        ac[i] = (double)fac[i];
-      }
-      const double q = sh.Q[lx] * (fx - fr);
-      fetch(k > 0 ? k - 1 : 0);   // in flight during this stage
-      wsync();
-      if (lane < NX) sh.w[lane] = sh.sv[lane] + q;
-      wsync();
-      if (lane < U4) {
-        // swing inputs: zero rho and a unit row of H^{-1}, so kap = 0 there
-        double a = rho;
-        if (stance(C, k, lane / 6)) {
-#pragma unroll
-          for (int i = 0; i < NX; ++i) a = fma(bc[i], sh.w[i], a);
-        }
-        sh.v24[lane] = a;
-      }
-      wsync();
-      if (lane < U4) {
-        // row `lane` of H^{-1} (its columns are stored one after the other)
-        double a = 0.0;
-#pragma unroll
-        for (int j = 0; j < U4; ++j) a = fma(h[j], sh.v24[j], a);
-        sh.kap[lane] = -a;
-        C.kap[(size_t)k * U4 + lane] = -a;
-      }
-      if (k == 0) break;
-      wsync();
-      if (lane < NX) {
-        double a = 0.0;
-#pragma unroll
-        for (int l = 0; l < NX; ++l) a = fma(ac[l], sh.w[l], a);
-#pragma unroll
-        for (int r = 0; r < U4; ++r) a = fma(hw[r], sh.kap[r], a);
-        sh.sv[lane] = a;
-      }
+      for (int r = p + 1; r < 12; ++r)
+        asm volatile(
+            "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+            : "+v"(c2[r])
+            : "v"(c1[r]), "v"(n2), "i"(p));
+      fmac_rows<p, p + 1, 12>(c1, -t1);
+      c1[p] = hc == p ? rd : t1;
+      c2[p] = t2;
     }
-    __syncthreads();
+    factor_beside<p + 1>(c1, c2, y2, hc, unit);
   }
 }
 
-template <int OCC>
-__device__ __attribute__((noinline)) void backward(const WCtx& C, WSh& sh, bool factor) {
-  if (!factor) {
-    backward_rhs<OCC>(C, sh);
-    return;
-  }
-  const int lane = threadIdx.x;
-  double* const B = sh.X;
-  double* const WB = sh.X + OFF_WB;
-  double* const T = sh.X + OFF_T;
-  double* const Aug = sh.Y;
-  double* const Kc = sh.Y;
-  double* const Sn = sh.Y + OFF_SN;
-  __syncthreads();
-  for (int e = lane; e < NX * NX; e += 64) sh.W[e] = (e % (NX + 1) == 0) ? sh.Q[e / NX] : 0.0;
-  if (lane < NX) sh.sv[lane] = 0.0;
-  // the stage data a lane moves into LDS (A: 3, B: 5, stage terms: 3 items per
-  // lane; x_{k+1} and x_ref[k] in lanes 0..12; the contact flags), fetched a
-  // stage ahead; the addresses are clamped into the stage's arrays, so every
-  // lane issues the same loads on every path
-  float fa[3], fb[5];
-  double ft[3], fx, fr;
-  uint32_t fc;
-  auto fetch = [&](int k) {
-    fc = *reinterpret_cast<const GMEM uint32_t*>(C.contact + (size_t)k * C4);
-    const auto Ak = C.A + (size_t)k * NX * NX;
-    const auto Bk = C.B + (size_t)k * NX * U4;
-    const auto Tk = C.T + (size_t)k * C4 * TB;
+struct WideRaw {
+  float a[4], ba[4], bb[4];
+  double q[4], ta[3], tb[3];
+};
+
+// Backward recursion of the Newton step, stages N-1 .. 0: gains, feedforward and
+// factors of every stage into the scratch.  Tiles are homogeneous (row and
+// column VC carry the linear terms), as in the two-contact recursion.
+__device__ __attribute__((noinline)) void backward(const WCtx& C, WSh& sh) {
+  const int lane = lane_id(), g = tg(), j = tj();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const auto rQ = rsrc(uni(C.q), N * NX * 8), rT = rsrc(uni(C.T), N * WT * 8);
+  const auto rK = rsrc(uni(C.K), N * WK * 8), rF = rsrc(uni(C.F), N * WF * 8);
+  const int oA = j < NX ? (g * NX + j) * 4 : OOB;
+  const int oA3 = (g == 0 && j < NX) ? (12 * NX + j) * 4 : OOB;
+  const int oB = j < NU ? (g * U4 + j) * 4 : OOB;
+  const int oB3 = (g == 0 && j < NU) ? (12 * U4 + j) * 4 : OOB;
+  const int oV = j == VC ? g * 8 : OOB;
+  const int oV3 = (g == 0 && j == VC) ? 96 : ((g == 1 && j < NX) ? j * 8 : OOB);
+  int oT[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) fa[i] = Ak[min(lane + 64 * i, NX * NX - 1)];
+  for (int q = 0; q < 3; ++q) oT[q] = t_offset(4 * q + g, j);
+  const int oK = j <= VC ? (g * (NX + 1) + j) * 8 : OOB;
+  const int oF = j < NU ? (g * NU + j) * 8 : OOB;
+  d4 Qd;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) fb[i] = Bk[min(lane + 64 * i, NX * U4 - 1)];
+  for (int q = 0; q < 4; ++q) Qd[q] = (4 * q + g == j && j < NX) ? sh.Q[clampi(j, NX - 1)] : 0.0;
+  const SymWeights sw = sym_weights();
+  const double one = (g == 1 && j == VC) ? 1.0 : 0.0;   // (VC, VC) as item 3
+  const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU, jc = clampi(j, NU - 1);
+  const bool is_h = hc < NU, in = j < NU;
+  double* const gc = sh.r.G + (is_h ? hc : NU + rhs) * GC;
+  auto fetch = [&](int k, WideRaw& s) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) ft[i] = Tk[min(lane + 64 * i, C4 * TB - 1)];
-    const int l = min(lane, NX - 1);
-    fx = C.x[(size_t)(k + 1) * NX + l];
-    fr = (double)C.x_ref[(size_t)k * NX + l];
+    for (int q = 0; q < 3; ++q) {
+      s.a[q] = ldf(rA, oA + q * 4 * NX * 4, k * (NX * NX * 4));
+      s.ba[q] = ldf(rB, oB + q * 4 * U4 * 4, k * (NX * U4 * 4));
+      s.bb[q] = ldf(rB, oB + q * 4 * U4 * 4 + NU * 4, k * (NX * U4 * 4));
+      s.q[q] = ldd(rQ, oV + q * 32, k * (NX * 8));
+      s.ta[q] = ldd(rT, oT[q], k * (WT * 8));
+      s.tb[q] = ldd(rT, oT[q] + WT * 4, k * (WT * 8));
+    }
+    s.a[3] = ldf(rA, oA3, k * (NX * NX * 4));
+    s.ba[3] = ldf(rB, oB3, k * (NX * U4 * 4));
+    s.bb[3] = ldf(rB, oB3 + NU * 4, k * (NX * U4 * 4));
+    s.q[3] = ldd(rQ, oV3, k * (NX * 8));
   };
-  fetch(C.N - 1);
-  for (int k = C.N - 1; k >= 0; --k) {
-    // with two waves per SIMD the lane index is opaque to the compiler once
-    // per stage: the per-lane LDS addresses below are then formed anew each
-    // stage (a few integer operations) instead of held in registers across
-    // it, which lets the two waves share a SIMD without spilling inside it
-    int lane_k = threadIdx.x;
-    if constexpr (OCC > 1) asm volatile("" : "+v"(lane_k));
-    const int lane = lane_k;
-    wsync();
-    uint32_t unit = 0;
-    #pragma unroll
-    for (int i = 0; i < C4; ++i)
-      if (((fc >> (8 * i)) & 0xFFu) == 0) unit |= 0x3Fu << (6 * i);
+  WideRaw raw;
+  fetch(N - 1, raw);
+  d4 Ss = zero4();
+  for (int k = N - 1; k >= 0; --k) {
+    // this stage's data, the swing contacts' columns of B zero
+    const uint32_t ub = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.unit[k]);
+    const uint32_t ua = (ub & 0x3F) | ((ub >> 2) & 0xFC0), uc = ((ub >> 16) & 0x3F) | ((ub >> 18) & 0xFC0);
+    const bool ka = in && !((ua >> jc) & 1u), kb = in && !((uc >> jc) & 1u);
+    d4 At, Da, Db, Wt, Ta = zero4(), Tb = zero4();
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int e = lane + 64 * i;
-      if (e < NX * NX) sh.A[(e / NX) * XP + e % NX] = (double)fa[i];
-      if (e < C4 * TB) T[e] = ft[i];
+    for (int q = 0; q < 4; ++q) {
+      At[q] = (double)raw.a[q];
+      Da[q] = ka ? (double)raw.ba[q] : 0.0;
+      Db[q] = kb ? (double)raw.bb[q] : 0.0;
+      Wt[q] = Ss[q] + (Qd[q] + raw.q[q]);
     }
+    Da[3] += one;
+    Db[3] += one;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const int e = lane + 64 * i;
-      if (e < NX * U4) B[e] = ((unit >> (e % U4)) & 1u) ? 0.0 : (double)fb[i];
+    for (int q = 0; q < 3; ++q) {
+      Ta[q] = raw.ta[q];
+      Tb[q] = raw.tb[q];
     }
-    if (lane < NX) sh.w[lane] = sh.sv[lane] + sh.Q[lane] * (fx - fr);
-    fetch(k > 0 ? k - 1 : 0);   // in flight during this stage
-    wsync();
-    // W B and W A in blocks of two neighbouring entries of a row (each entry
-    // summed in the order of its own dot product)
-    for (int e = lane; e < NX * (U4 / 2) + NX * 7; e += 64) {
-      double a0 = 0.0, a1 = 0.0;
-      if (e < NX * (U4 / 2)) {
-        const int i = e / (U4 / 2), c = 2 * (e % (U4 / 2));
+    pin(At); pin(Da); pin(Db); pin(Wt); pin(Ta); pin(Tb);
+    pin_memory();
+    if (k > 0) fetch(k - 1, raw);
+
+    const d4 D3a = mmT<4>(Wt, Da, zero4());   // [W Ba | 0 | q + s], row VC Ba^T (q + s)
+    const d4 Haa = mmT<4>(D3a, Da, Ta);       // [Haa | 0 | hwa]
+    const d4 Hxa = mmT<4>(D3a, At, zero4());
+    const d4 Hab = mmT<4>(D3a, Db, zero4());
 #pragma unroll
-        for (int j = 0; j < NX; ++j) {
-          const double w = sh.W[i * NX + j];
-          const dpair b = ld2(&B[j * U4 + c]);
-          a0 = fma(w, b.x, a0);
-          a1 = fma(w, b.y, a1);
-        }
-        st2(&WB[i * U4 + c], a0, a1);
-      } else {
-        const int f = e - NX * (U4 / 2), i = f / 7, j = 2 * (f % 7);
-#pragma unroll
-        for (int l = 0; l < NX; ++l) {
-          const double w = sh.W[i * NX + l];
-          const dpair b = ld2(&sh.A[l * XP + j]);
-          a0 = fma(w, b.x, a0);
-          a1 = fma(w, b.y, a1);
-        }
-        st2(&sh.WA[i * XP + j], a0, a1);   // column 13 of the pair is padding
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g;
+      if (in) {
+        sh.r.G[j * GC + r] = Haa[q];
+        sh.r.Tab[j * GC + r] = Hab[q];
       }
+      sh.r.G[(NU + j) * GC + r] = -(j == VC ? Haa[q] : Hxa[q]);
     }
+    const d4 D3b = mmT<4>(Wt, Db, zero4());
+    d4 Hbb = mmT<4>(D3b, Db, Tb);             // [Hbb | 0 | hwb]
+    const d4 Hxb = mmT<4>(D3b, At, zero4());
+    d4 D2 = mmT<4>(Wt, At, zero4());          // [W A | q + s]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) D2[q] = j == VC ? D3a[q] : D2[q];
+    const d4 SA = mmT<4>(At, D2, zero4());
     wsync();
-    // the columns of [H | Hwx | hw] (column c at Aug[c][0..23]) in blocks of
-    // two rows r, r + 1: H = R' + B^T (W B) two columns at a time,
-    // Hwx = B^T (W A) and hw = rho + B^T w one column at a time
-    for (int e = lane; e < 12 * 12 + 12 * NX + 12; e += 64) {
-      if (e < 144) {
-        const int r = 2 * (e / 12), c = 2 * (e % 12);
-        double a00, a01, a10, a11;   // (r, c), (r, c+1), (r+1, c), (r+1, c+1)
-        if (r / 6 == c / 6) {
-          const double* Tb = T + (c / 6) * TB;
-          const int rr = r % 6, cc = c % 6;
-          a00 = Tb[rr * 6 + cc];
-          a01 = Tb[rr * 6 + cc + 1];
-          a10 = Tb[(rr + 1) * 6 + cc];
-          a11 = Tb[(rr + 1) * 6 + cc + 1];
-        } else {
-          a00 = a01 = a10 = a11 = 0.0;
-        }
+    // half a: lane 16 R + c holds column c of Haa (c < 12, the same in every row
+    // R) or right-hand side 4 R + c - 12, and column c of Hab
+    double c1[NU];
+    {
+      double c2[NU], y2[NU];
+      const double* hb = sh.r.Tab + clampi(hc, NU - 1) * GC;
 #pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const dpair b = ld2(&B[i * U4 + r]);
-          const dpair g = ld2(&WB[i * U4 + c]);
-          a00 = fma(b.x, g.x, a00);
-          a01 = fma(b.x, g.y, a01);
-          a10 = fma(b.y, g.x, a10);
-          a11 = fma(b.y, g.y, a11);
-        }
-        st2(&Aug[c * U4 + r], a00, a10);
-        st2(&Aug[(c + 1) * U4 + r], a01, a11);
-      } else if (e < 144 + 12 * NX) {
-        const int f = e - 144, r = 2 * (f / NX), j = f % NX;
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const dpair b = ld2(&B[i * U4 + r]);
-          const double g = sh.WA[i * XP + j];
-          a0 = fma(b.x, g, a0);
-          a1 = fma(b.y, g, a1);
-        }
-        C.Hx[(size_t)k * U4 * NX + r * NX + j] = a0;
-        C.Hx[(size_t)k * U4 * NX + (r + 1) * NX + j] = a1;
-        st2(&Aug[(U4 + j) * U4 + r], a0, a1);
-      } else {
-        const int r = 2 * (e - 144 - 12 * NX);
-        double a0 = T[(r / 6) * TB + 36 + r % 6];
-        double a1 = T[((r + 1) / 6) * TB + 36 + (r + 1) % 6];
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-          const dpair b = ld2(&B[i * U4 + r]);
-          const double g = sh.w[i];
-          a0 = fma(b.x, g, a0);
-          a1 = fma(b.y, g, a1);
-        }
-        st2(&Aug[L4 * U4 + r], a0, a1);
+      for (int r = 0; r < NU; ++r) {
+        c1[r] = gc[r];
+        c2[r] = hb[r];
       }
+      wsync();
+      factor_beside(c1, c2, y2, hc, ua);
+      if (!is_h || lane < NU) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) gc[r] = c1[r];
+      }
+      if (lane < NU) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) {
+          sh.r.Tab[lane * GC + r] = c2[r];
+          sh.r.Yab[lane * GC + r] = y2[r];
+        }
+      }
+      wsync();
+    }
+    d4 Tx = zero4(), Tab = zero4(), nTt = zero4(), nY = zero4(), X = zero4();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g;
+      Tx[q] = sh.r.G[(NU + j) * GC + r];
+      const double tab = sh.r.Tab[jc * GC + r], tt = sh.r.Tab[r * GC + jc];
+      const double y = sh.r.Yab[jc * GC + r];
+      const int hi = r > jc ? r : jc, lo = r > jc ? jc : r;
+      Tab[q] = in ? tab : 0.0;
+      nTt[q] = in ? -tt : 0.0;
+      nY[q] = in ? -y : 0.0;
+      std1(rF, oF + q * 4 * NU * 8, k * (WF * 8), sh.r.G[hi * GC + lo]);   // Ua, 1 / d
+      std1(rF, oF + q * 4 * NU * 8 + 2 * FB, k * (WF * 8), tab);
+      X[q] = -(j == VC ? Hbb[q] : Hxb[q]);
     }
     wsync();
-    double col[U4];
+    // half b after the Schur update
+    Hbb = mmT<3>(nY, Tab, Hbb);
+    X = mmT<3>(nY, Tx, X);
 #pragma unroll
-    for (int r = 0; r < U4; ++r)
-      col[r] = lane <= L4 ? Aug[lane * U4 + r] : (lane - L4 - 1 == r ? 1.0 : 0.0);
-    gj_columns<U4>(col, unit);
-    // lanes 24..36: the gain columns -H^{-1} Hwx; lane 37: the feedforward
-    // -H^{-1} hw; lanes 38..61: the columns of H^{-1}; each a contiguous
-    // column of 24 in the scratch (and the gains with the feedforward in LDS)
-    if (lane >= U4 && lane < L4 + 1 + U4) {
-      const double sg = lane <= L4 ? -1.0 : 1.0;
-      gd dst = lane < L4 ? C.K + (size_t)k * U4 * NX + (lane - U4) * U4
-                  : lane == L4 ? C.kap + (size_t)k * U4
-                               : C.Hi + (size_t)k * U4 * U4 + (lane - L4 - 1) * U4;
-#pragma unroll
-      for (int r = 0; r < U4; r += 2) st2(dst + r, sg * col[r], sg * col[r + 1]);
-      if (lane <= L4) {
-#pragma unroll
-        for (int r = 0; r < U4; r += 2) st2(&Kc[(lane - U4) * U4 + r], -col[r], -col[r + 1]);
-      }
-    }
-    if (k == 0) break;   // x_0 is fixed: its value function is not needed
-    wsync();
-    // S = A^T W A + Hwx^T K and s = A^T w + Hwx^T kap in blocks of two rows
-    // i, i + 1 (row 13 of the last block is padding)
-    for (int e = lane; e < 7 * (NX + 1); e += 64) {
-      const int i = 2 * (e / (NX + 1)), j = e % (NX + 1);   // j = 13: s
-      double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-      for (int l = 0; l < NX; ++l) {
-        const dpair av = ld2(&sh.A[l * XP + i]);
-        const double g = j < NX ? sh.WA[l * XP + j] : sh.w[l];
-        a0 = fma(av.x, g, a0);
-        a1 = fma(av.y, g, a1);
-      }
-#pragma unroll
-      for (int r = 0; r < U4; ++r) {
-        // Hwx (r, i) and (r, i + 1): rows r of the system's columns 24 + i, 25 + i
-        const double h0 = Aug[OFF_HWX + i * U4 + r];
-        const double h1 = i + 1 < NX ? Aug[OFF_HWX + (i + 1) * U4 + r] : 0.0;
-        const double g = Kc[j * U4 + r];
-        a0 = fma(h0, g, a0);
-        a1 = fma(h1, g, a1);
-      }
-      if (j < NX) {
-        Sn[i * NX + j] = a0;
-        if (i + 1 < NX) Sn[(i + 1) * NX + j] = a1;
-      } else {
-        Sn[NX * NX + i] = a0;
-        if (i + 1 < NX) Sn[NX * NX + i + 1] = a1;
-      }
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g;
+      if (in) sh.r.G[j * GC + r] = Hbb[q];
+      sh.r.G[(NU + j) * GC + r] = X[q];
     }
     wsync();
-    for (int e = lane; e < NX * NX; e += 64) {
-      const int i = e / NX, j = e % NX;
-      const double s = 0.5 * (Sn[i * NX + j] + Sn[j * NX + i]);
-      sh.W[e] = s + (i == j ? sh.Q[i] : 0.0);
+    d4 Kb = zero4();
+    {
+      double c3[NU];
+#pragma unroll
+      for (int r = 0; r < NU; ++r) c3[r] = gc[r];
+      wsync();
+      factor(c3, hc, uc);
+      back_substitute(c3, is_h, uc);
+      if (!is_h || lane < NU) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) gc[r] = c3[r];
+      }
+      wsync();
     }
-    if (lane < NX) sh.sv[lane] = Sn[NX * NX + lane];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g;
+      const int hi = r > jc ? r : jc, lo = r > jc ? jc : r;
+      Kb[q] = sh.r.G[(NU + j) * GC + r];
+      std1(rK, oK + q * 4 * (NX + 1) * 8 + KB, k * (WK * 8), Kb[q]);
+      std1(rF, oF + q * 4 * NU * 8 + FB, k * (WF * 8), sh.r.G[hi * GC + lo]);   // Ub, 1 / d
+    }
+    // half a's gains: Ua Ka = Tx - Tab Kb
+    Tx = mmT<3>(nTt, Kb, Tx);
+    wsync();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) sh.r.G[(NU + j) * GC + 4 * q + g] = Tx[q];
+    wsync();
+    if (!is_h) {
+#pragma unroll
+      for (int r = 0; r < NU; ++r) c1[r] = gc[r];
+    }
+    back_substitute(c1, is_h, ua);
+    wsync();
+    if (!is_h) {
+#pragma unroll
+      for (int r = 0; r < NU; ++r) gc[r] = c1[r];
+    }
+    wsync();
+    d4 Ka = zero4();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      Ka[q] = sh.r.G[(NU + j) * GC + 4 * q + g];
+      std1(rK, oK + q * 4 * (NX + 1) * 8, k * (WK * 8), Ka[q]);
+    }
+    // S = A^T W A + Hwx^T K, s = A^T (q + s) + Hwx^T kap
+    Ss = symmetrize(mmT<3>(Hxa, Ka, mmT<3>(Hxb, Kb, SA)), sw, sh.r.ST);
   }
-  __syncthreads();
 }
 
-// Forward rollout of the gains from dx_0 = 0: du_k = K_k dx_k + kap_k,
-// dx_{k+1} = A_k dx_k + B_k du_k.
-template <int OCC>
+// Forward rollout of the gains from dx_0 = 0: du_k = K_k dx_k + kap_k (into GV),
+// dx_{k+1} = A_k dx_k + B_k du_k (into PV).  VECK: kap_k from GV (a corrector's)
+// instead of the stored gains.
+template <bool VECK>
 __device__ __attribute__((noinline)) void forward(const WCtx& C, WSh& sh) {
-  const int lane = threadIdx.x;
   __syncthreads();
-  if (lane < NX) {
-    sh.v13[lane] = 0.0;
-    C.dx[lane] = 0.0;
-  }
-  // a stage's gains row and feedforward (lanes 0..23) and rows of A and B
-  // (lanes 0..12), fetched a stage ahead from clamped addresses
-  const int lk = min(lane, U4 - 1), lx = min(lane, NX - 1);
-  double fk[NX], fp;
-  float fa[NX], fb[U4];
-  auto fetch = [&](int k) {
-    const auto Kr = C.K + (size_t)k * U4 * NX + lk;   // row lk of K (stored by column)
-#pragma unroll
-    for (int c = 0; c < NX; ++c) fk[c] = Kr[c * U4];
-    fp = C.kap[(size_t)k * U4 + lk];
-    const auto Ar = C.A + (size_t)k * NX * NX + lx * NX;
-    const auto Br = C.B + (size_t)k * NX * U4 + lx * U4;
-#pragma unroll
-    for (int c = 0; c < NX; ++c) fa[c] = Ar[c];
-#pragma unroll
-    for (int r = 0; r < U4; ++r) fb[r] = Br[r];
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const int lane = lane_id(), g = tg(), j = tj();
+  double* const PV = sh.c.PV;
+  double* const GV = sh.c.GV;
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const auto rK = rsrc(uni(C.K), N * WK * 8);
+  const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB, oB = j < NX ? (j * U4 + 3 * g) * 4 : OOB;
+  const int oK = j < NU ? (j * (NX + 1) + 3 * g) * 8 : OOB;
+  const int oKap = (g == 0 && j < NU) ? (j * (NX + 1) + NX) * 8 : OOB;
+  struct FwdRaw {
+    double ka[4], kb[4], pa, pb;
+    float a[4], ba[3], bb[3];
   };
-  fetch(0);
-  for (int k = 0; k < C.N; ++k) {
-    double kr[NX], kp = fp;
-    float ar[NX], br[U4];
+  auto ffetch = [&](int k, FwdRaw& s) {
+    ldd2(rK, oK, k * (WK * 8), s.ka);
+    ldd2(rK, oK + 16, k * (WK * 8), s.ka + 2);
+    ldd2(rK, oK + KB, k * (WK * 8), s.kb);
+    ldd2(rK, oK + KB + 16, k * (WK * 8), s.kb + 2);
+    s.pa = VECK ? 0.0 : ldd(rK, oKap, k * (WK * 8));
+    s.pb = VECK ? 0.0 : ldd(rK, oKap + KB, k * (WK * 8));
+    ldf4(rA, oA, k * (NX * NX * 4), s.a);
+    ldf3(rB, oB, k * (NX * U4 * 4), s.ba);
+    ldf3(rB, oB + NU * 4, k * (NX * U4 * 4), s.bb);
+  };
+  constexpr int FD = 2;
+  FwdRaw ring[FD];
 #pragma unroll
-    for (int c = 0; c < NX; ++c) {
-      kr[c] = fk[c];
-      ar[c] = fa[c];
-    }
-#pragma unroll
-    for (int r = 0; r < U4; ++r) br[r] = fb[r];
-    fetch(k + 1 < C.N ? k + 1 : k);   // in flight during this stage
-    wsync();
-    if (lane < U4) {
-      double a = kp;
-      #pragma unroll
-      for (int c = 0; c < NX; ++c) a = fma(kr[c], sh.v13[c], a);
-      sh.v24[lane] = a;
-      C.du[(size_t)k * U4 + lane] = a;
-    }
-    wsync();
-    double nx = 0.0;
-    if (lane < NX) {
-      #pragma unroll
-      for (int c = 0; c < NX; ++c) nx = fma((double)ar[c], sh.v13[c], nx);
-      #pragma unroll
-      for (int r = 0; r < U4; ++r) nx = fma((double)br[r], sh.v24[r], nx);
-      C.dx[(size_t)(k + 1) * NX + lane] = nx;
-    }
-    wsync();
-    if (lane < NX) sh.v13[lane] = nx;
+  for (int d = 0; d < FD; ++d) {
+    ffetch(d < N ? d : N - 1, ring[d]);
+    pin_memory();
   }
+  double xv = 0.0;   // dx_k, entry j
+  auto step = [&](int k, FwdRaw& r) __attribute__((always_inline)) {
+    double ka[4], kb[4], a[4], ba[3], bb[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ka[q] = (q == 0 && g) ? 0.0 : r.ka[q];
+      kb[q] = (q == 0 && g) ? 0.0 : r.kb[q];
+      a[q] = (q == 0 && g) ? 0.0 : (double)r.a[q];
+      pin(ka[q]); pin(kb[q]); pin(a[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      ba[q] = (double)r.ba[q];
+      bb[q] = (double)r.bb[q];
+      pin(ba[q]); pin(bb[q]);
+    }
+    double pa = r.pa, pb = r.pb;
+    pin(pa); pin(pb);
+    pin_memory();
+    ffetch(k + FD < N ? k + FD : N - 1, r);
+    if constexpr (VECK) {
+      pa = (g == 0 && j < NU) ? GV[k * U4 + clampi(j, NU - 1)] : 0.0;
+      pb = (g == 0 && j < NU) ? GV[k * U4 + NU + clampi(j, NU - 1)] : 0.0;
+    }
+    const double xt = turn_rows(xv);
+    const double wa = row_total(dot4(xt, ka, pa)), wb = row_total(dot4(xt, kb, pb));
+    const double ax = dot4(xt, a, 0.0);
+    xv = row_total(dot3(turn_rows(wb), bb, dot3(turn_rows(wa), ba, ax)));
+    if (lane < NU) {
+      GV[k * U4 + j] = wa;
+      GV[k * U4 + NU + j] = wb;
+    }
+    if (lane < NX) PV[k * NX + j] = xv;
+  };
+  static_assert(FD == 2, "one line below per ring slot");
+  for (int k = 0;; k += FD) {
+    if (!(k < N)) break;
+    step(k, ring[0]);
+    if (!(k + 1 < N)) break;
+    step(k + 1, ring[1]);
+  }
+  wsync();
+}
+
+// Second right-hand side of a Newton step with the stored factors (the corrector
+// of an interior-point iteration): rho_k (in GV) to kap_k (in GV).  The
+// recursion of the linear part, s <- A^T wv + K^T hw with wv = q + s and
+// hw = B^T wv + rho, is a chain; the feedforwards kap = -H^{-1} hw then follow
+// four stages at a time, by block triangular solves with Ua, Tab and Ub.
+__device__ __attribute__((noinline)) void newton_vector(const WCtx& C, WSh& sh) {
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const int lane = lane_id(), g = tg(), j = tj();
+  double* const GV = sh.c.GV;
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const auto rK = rsrc(uni(C.K), N * WK * 8), rQ = rsrc(uni(C.q), N * NX * 8);
+  const auto rF = rsrc(uni(C.F), N * WF * 8);
+  const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
+  const int oB = j < NU ? (3 * g * U4 + j) * 4 : OOB, oB0 = (g == 0 && j < NU) ? j * 4 : OOB;
+  const int oK = j < NX ? (3 * g * (NX + 1) + j) * 8 : OOB, oQ = j < NX ? j * 8 : OOB;
+  struct VecRaw {
+    float a[4], ba[4], bb[4];
+    double ka[3], kb[3], q;
+  };
+  auto vfetch = [&](int k, VecRaw& s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int ob = q == 0 ? oB0 : oB + q * U4 * 4;
+      s.a[q] = ldf(rA, q == 0 ? oA0 : oA + q * NX * 4, k * (NX * NX * 4));
+      s.ba[q] = ldf(rB, ob, k * (NX * U4 * 4));
+      s.bb[q] = ldf(rB, ob + NU * 4, k * (NX * U4 * 4));
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      s.ka[q] = ldd(rK, oK + q * (NX + 1) * 8, k * (WK * 8));
+      s.kb[q] = ldd(rK, oK + q * (NX + 1) * 8 + KB, k * (WK * 8));
+    }
+    s.q = ldd(rQ, oQ, k * (NX * 8));
+  };
+  constexpr int VD = 2;
+  VecRaw ring[VD];
+#pragma unroll
+  for (int d = 0; d < VD; ++d) {
+    vfetch(N - 1 - d >= 0 ? N - 1 - d : 0, ring[d]);
+    pin_memory();
+  }
+  double s = 0.0;   // value function's linear part, entry j
+  auto step = [&](int k, VecRaw& r) __attribute__((always_inline)) {
+    double a[4], ba[4], bb[4], ka[3], kb[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (double)r.a[q];
+      ba[q] = (double)r.ba[q];
+      bb[q] = (double)r.bb[q];
+      pin(a[q]); pin(ba[q]); pin(bb[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      ka[q] = r.ka[q];
+      kb[q] = r.kb[q];
+      pin(ka[q]); pin(kb[q]);
+    }
+    const double qk = r.q;
+    pin(qk);
+    pin_memory();
+    vfetch(k - VD >= 0 ? k - VD : 0, r);
+    const bool on = g == 0 && j < NU;
+    const double rhoa = on ? GV[k * U4 + clampi(j, NU - 1)] : 0.0;
+    const double rhob = on ? GV[k * U4 + NU + clampi(j, NU - 1)] : 0.0;
+    const double wt = turn_rows(qk + s);
+    const double ha = row_total(dot4(wt, ba, rhoa)), hb = row_total(dot4(wt, bb, rhob));
+    const double aw = dot4(wt, a, 0.0);
+    s = row_total(dot3(turn_rows(hb), kb, dot3(turn_rows(ha), ka, aw)));
+    if (lane < NU) {
+      GV[k * U4 + j] = ha;
+      GV[k * U4 + NU + j] = hb;
+    }
+  };
+  static_assert(VD == 2, "one line below per ring slot");
+  for (int k = N - 1;; k -= VD) {
+    if (!(k >= 0)) break;
+    step(k, ring[0]);
+    if (!(k - 1 >= 0)) break;
+    step(k - 1, ring[1]);
+  }
+  wsync();
+  const int oF = j < NU ? (g * WF + j * NU) * 8 : OOB;          // row j of a block
+  const int oC = j < NU ? (g * WF + j) * 8 : OOB;               // column j of a block
+  const int oD = j < NU ? (g * WF + j * (NU + 1)) * 8 : OOB;    // its diagonal
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    const int k = k0 + g, at = k0 * (WF * 8);
+    const bool on = j < NU && k < N;
+    double f[NU], tc[NU], ya = 0.0, yb = 0.0;
+    if (on && stance(C, k, j / 6)) ya = GV[k * U4 + j];
+    if (on && stance(C, k, 2 + j / 6)) yb = GV[k * U4 + NU + j];
+    const double da = ldd(rF, oD, at), db = ldd(rF, oD + FB, at);
+#define PINMPC_ACC(y, src, p, m)                                                              \
+  {                                                                                           \
+    const double mm = (m);                                                                    \
+    asm volatile(                                                                             \
+        "s_nop 1\n"                                                                           \
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:" #p " row_mask:0xf bank_mask:0xf bound_ctrl:1" \
+        : "+v"(y)                                                                             \
+        : "v"(src), "v"(mm));                                                                 \
+  }
+// y += (y of lane p) * m: the destination is its own broadcast source
+#define PINMPC_TRI(y, p, use)                                                                 \
+  {                                                                                           \
+    const double mm = (use) ? -f[p] : 0.0;                                                    \
+    asm volatile(                                                                             \
+        "s_nop 1\n"                                                                           \
+        "v_fmac_f64_dpp %0, %0, %1 row_newbcast:" #p " row_mask:0xf bank_mask:0xf bound_ctrl:1" \
+        : "+v"(y)                                                                             \
+        : "v"(mm));                                                                           \
+  }
+#define PINMPC_DOWN(y)                                                                     \
+  PINMPC_TRI(y, 0, j > 0) PINMPC_TRI(y, 1, j > 1) PINMPC_TRI(y, 2, j > 2)                  \
+  PINMPC_TRI(y, 3, j > 3) PINMPC_TRI(y, 4, j > 4) PINMPC_TRI(y, 5, j > 5)                  \
+  PINMPC_TRI(y, 6, j > 6) PINMPC_TRI(y, 7, j > 7) PINMPC_TRI(y, 8, j > 8)                  \
+  PINMPC_TRI(y, 9, j > 9) PINMPC_TRI(y, 10, j > 10)
+#define PINMPC_UP(y)                                                                       \
+  PINMPC_TRI(y, 11, j < 11) PINMPC_TRI(y, 10, j < 10) PINMPC_TRI(y, 9, j < 9)              \
+  PINMPC_TRI(y, 8, j < 8) PINMPC_TRI(y, 7, j < 7) PINMPC_TRI(y, 6, j < 6)                  \
+  PINMPC_TRI(y, 5, j < 5) PINMPC_TRI(y, 4, j < 4) PINMPC_TRI(y, 3, j < 3)                  \
+  PINMPC_TRI(y, 2, j < 2) PINMPC_TRI(y, 1, j < 1)
+#define PINMPC_SUB(y, src, v)                                                              \
+  PINMPC_ACC(y, src, 0, -v[0]) PINMPC_ACC(y, src, 1, -v[1]) PINMPC_ACC(y, src, 2, -v[2])   \
+  PINMPC_ACC(y, src, 3, -v[3]) PINMPC_ACC(y, src, 4, -v[4]) PINMPC_ACC(y, src, 5, -v[5])   \
+  PINMPC_ACC(y, src, 6, -v[6]) PINMPC_ACC(y, src, 7, -v[7]) PINMPC_ACC(y, src, 8, -v[8])   \
+  PINMPC_ACC(y, src, 9, -v[9]) PINMPC_ACC(y, src, 10, -v[10]) PINMPC_ACC(y, src, 11, -v[11])
+    // ya <- Ua^-T ya, yb <- Ub^-T (yb - Tab^T ya)
+#pragma unroll
+    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8, at, f + p);
+#pragma unroll
+    for (int p = 0; p < NU; ++p) tc[p] = ldd(rF, oC + p * NU * 8 + 2 * FB, at);
+    PINMPC_DOWN(ya)
+    PINMPC_SUB(yb, ya, tc)
+    double fa[NU];
+#pragma unroll
+    for (int p = 0; p < NU; ++p) fa[p] = f[p];
+#pragma unroll
+    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8 + FB, at, f + p);
+    PINMPC_DOWN(yb)
+    ya *= da;
+    yb *= db;
+    // yb <- Ub^-1 yb, ya <- Ua^-1 (ya - Tab yb)
+    PINMPC_UP(yb)
+#pragma unroll
+    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8 + 2 * FB, at, tc + p);
+    PINMPC_SUB(ya, yb, tc)
+#pragma unroll
+    for (int p = 0; p < NU; ++p) f[p] = fa[p];
+    PINMPC_UP(ya)
+#undef PINMPC_SUB
+#undef PINMPC_UP
+#undef PINMPC_DOWN
+#undef PINMPC_TRI
+#undef PINMPC_ACC
+    if (on) {
+      GV[k * U4 + j] = -ya;
+      GV[k * U4 + NU + j] = -yb;
+    }
+  }
+  wsync();
+}
+
+// s + sum_l u_l b[l] over a half's 12 inputs (u in lanes 0..11 of the row).
+__device__ inline double dot_half(double u, const float (&b)[NU], double s) {
+  double bd[NX];
+#pragma unroll
+  for (int l = 0; l < NX; ++l) bd[l] = l < NU ? (double)b[l < NU ? l : 0] : 0.0;
+  return dot_row_bcast13(u, bd, s);
+}
+
+// x = rollout of u from x0, in FP64: the stage terms B u + e for four stages at
+// a time, then the chain.  x_{k+1} is left in PV as well.
+__device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
+  __syncthreads();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const int lane = lane_id(), g = tg(), j = tj();
+  double* const PV = sh.c.PV;
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0), rU = rsrc(uni(C.u), N * U4 * 8);
+  const int oB = j < NX ? (g * NX + j) * U4 * 4 : OOB, oE = j < NX ? (g * NX + j) * 4 : OOB;
+  const int oU = j < NU ? (g * U4 + j) * 8 : OOB;
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    float ba[NU], bb[NU];
+#pragma unroll
+    for (int l = 0; l < NU; l += 4) {
+      ldf4(rB, oB + l * 4, k0 * (NX * U4 * 4), ba + l);
+      ldf4(rB, oB + (NU + l) * 4, k0 * (NX * U4 * 4), bb + l);
+    }
+    const double u0 = ldd(rU, oU, k0 * (U4 * 8)), u1 = ldd(rU, oU + NU * 8, k0 * (U4 * 8));
+    const double e = (double)ldf(rE, oE, k0 * (NX * 4));
+    const double d = dot_half(u1, bb, dot_half(u0, ba, e));
+    if (j < NX && k0 + g < N) PV[(k0 + g) * NX + j] = d;
+  }
+  wsync();
+  const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB;
+  constexpr int RD = 4;
+  float ring[RD][4];
+#pragma unroll
+  for (int d = 0; d < RD; ++d) {
+    ldf4(rA, oA, (d < N ? d : N - 1) * (NX * NX * 4), ring[d]);
+    pin_memory();
+  }
+  double xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;
+  if (lane < NX) C.x[lane] = xv;
+  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+    double a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (q == 0 && g) ? 0.0 : (double)r[q];
+      pin(a[q]);
+    }
+    pin_memory();
+    ldf4(rA, oA, (k + RD < N ? k + RD : N - 1) * (NX * NX * 4), r);
+    const double t = j < NX ? PV[k * NX + clampi(j, NX - 1)] : 0.0;
+    xv = row_total(dot4(turn_rows(xv), a, 0.0)) + t;
+    if (lane < NX) PV[k * NX + j] = xv;
+  };
+  static_assert(RD == 4, "one line below per ring slot");
+  for (int k = 0;; k += RD) {
+    if (!(k < N)) break;
+    step(k, ring[0]);
+    if (!(k + 1 < N)) break;
+    step(k + 1, ring[1]);
+    if (!(k + 2 < N)) break;
+    step(k + 2, ring[2]);
+    if (!(k + 3 < N)) break;
+    step(k + 3, ring[3]);
+  }
+  wsync();
+  for (int e = lane; e < N * NX; e += W64) C.x[NX + e] = PV[e];
   __syncthreads();
 }
 
-// FP64 rollout of u from x0 into x, and the dynamics residual of that
-// trajectory (normalised as the certificate's r_dyn).
-template <int OCC>
-__device__ __attribute__((noinline)) double rollout(const WCtx& C, WSh& sh) {
-  const int lane = threadIdx.x;
-  __syncthreads();
-  if (lane < NX) {
-    const double v = (double)C.x0[lane];
-    sh.v13[lane] = v;
-    C.x[lane] = v;
+// Dynamics residual of the FP64 trajectory (x, u), normalised by the largest
+// term of each entry.
+__device__ __attribute__((noinline)) double dyn_residual(const WCtx& C) {
+  double r = 0.0;
+  for (int e = lane_id(); e < C.N * NX; e += W64) {
+    const int k = e / NX, i = e % NX;
+    gcd x = C.x + k * NX;
+    gcd u = C.u + k * U4;
+    gcf A = C.A + (size_t)k * NX * NX + i * NX;
+    gcf B = C.B + (size_t)k * NX * U4 + i * U4;
+    double ax = 0.0, bu = 0.0;
+#pragma unroll
+    for (int l = 0; l < NX; ++l) ax += (double)A[l] * x[l];
+#pragma unroll
+    for (int l = 0; l < U4; ++l) bu += (double)B[l] * u[l];
+    const double ee = C.e ? (double)C.e[k * NX + i] : 0.0;
+    const double d = x[NX + i] - ax - bu - ee;
+    const double den = 1.0 + fmax(fabs(x[NX + i]), fmax(fabs(ax), fabs(bu)));
+    r = fmax(r, fabs(d) / den);
   }
-  double rd = 0.0;
-  for (int k = 0; k < C.N; ++k) {
-    __syncthreads();
-    double nx = 0.0, ax = 0.0, bu = 0.0;
-    if (lane < NX) {
-      const auto Ar = C.A + (size_t)k * NX * NX + lane * NX;
-      const auto Br = C.B + (size_t)k * NX * U4 + lane * U4;
-      const auto uk = C.u + (size_t)k * U4;
-      #pragma unroll
-      for (int c = 0; c < NX; ++c) ax = fma((double)Ar[c], sh.v13[c], ax);
-      #pragma unroll
-      for (int r = 0; r < U4; ++r) bu = fma((double)Br[r], uk[r], bu);
-      const double ev = C.e ? (double)C.e[(size_t)k * NX + lane] : 0.0;
-      nx = ax + bu + ev;
-      C.x[(size_t)(k + 1) * NX + lane] = nx;
-    }
-    // |x_{k+1} - A x_k - B u_k - e_k| over the stage's largest term
-    const double d = fabs(nx - ax - bu - (lane < NX && C.e ? (double)C.e[(size_t)k * NX + lane] : 0.0));
-    const double den = 1.0 + wmax(fmax(fabs(nx), fmax(fabs(ax), fabs(bu))));
-    rd = fmax(rd, wmax(d) / den);
-    __syncthreads();
-    if (lane < NX) sh.v13[lane] = nx;
-  }
-  __syncthreads();
-  return rd;
+  return wave_max(r);
 }
 
 // Gradient of force row r (0..4) of the pyramid with respect to f.
@@ -724,59 +845,98 @@ __device__ void force_refit(int am, double mu, const double gf[3], double m[5]) 
 // construction and stationarity measures how well u meets it.  (The interior
 // point's own multipliers lose their accuracy as the slacks of active rows
 // approach zero: their step divides by the slack.)  Returns max(res).
-template <int OCC>
-__device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh, double res[PINMPC_NRES],
-                                                      double tol) {
-  const int lane = threadIdx.x;
-  res[0] = rollout<OCC>(C, sh);
-  // costates, backwards: lam_k = Q (x_{k+1} - r_k) + A_{k+1}^T lam_{k+1}
-  double tq = 0.0, tl = 0.0, ta = 0.0;
-  if (lane < NX) sh.v13[lane] = 0.0;
-  for (int k = C.N - 1; k >= 0; --k) {
-    __syncthreads();
-    double l = 0.0, al = 0.0;
-    if (lane < NX) {
-      const double q =
-          sh.Q[lane] * (C.x[(size_t)(k + 1) * NX + lane] - (double)C.x_ref[(size_t)k * NX + lane]);
-      if (k + 1 < C.N) {
-        const auto A1 = C.A + (size_t)(k + 1) * NX * NX;
-        #pragma unroll
-        for (int i = 0; i < NX; ++i) al = fma((double)A1[i * NX + lane], sh.v13[i], al);
-      }
-      l = q + al;
-      C.lam[(size_t)k * U4 + lane] = l;
-      tq = fmax(tq, fabs(q));
-      tl = fmax(tl, fabs(l));
-      ta = fmax(ta, fabs(al));
-    }
-    __syncthreads();
-    if (lane < NX) sh.v13[lane] = l;
+__device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
+                                                       double res[PINMPC_NRES], double tol) {
+  rollout(C, sh);
+  res[0] = dyn_residual(C);
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const int lane = lane_id(), g = tg(), j = tj();
+  double* const PV = sh.c.PV;
+  double* const GV = sh.c.GV;
+  for (int e = lane; e < N * NX; e += W64)
+    PV[e] = sh.Q[e % NX] * (PV[e] - (double)C.x_ref[e]);
+  wsync();
+  // costates, backwards: p_{k+1} = Q (x_{k+1} - r_k) + A_{k+1}^T p_{k+2}
+  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
+  auto cfetch = [&](int k, float (&s)[4]) {
+    const int at = clampi(k + 1, N - 1) * (NX * NX * 4);
+    s[0] = ldf(rA, oA0, at);
+#pragma unroll
+    for (int q = 1; q < 4; ++q) s[q] = ldf(rA, oA + q * NX * 4, at);
+  };
+  constexpr int CD = 4;
+  float ring[CD][4];
+#pragma unroll
+  for (int d = 0; d < CD; ++d) {
+    cfetch(N - 1 - d >= 0 ? N - 1 - d : 0, ring[d]);
+    pin_memory();
   }
-  __syncthreads();
+  double p = 0.0, terms = 0.0;
+  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+    double a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (double)r[q];
+      pin(a[q]);
+    }
+    pin_memory();
+    cfetch(k - CD >= 0 ? k - CD : 0, r);
+    const double qx = j < NX ? PV[k * NX + clampi(j, NX - 1)] : 0.0;
+    const double ap = row_total(dot4(turn_rows(p), a, 0.0));
+    p = qx + ap;
+    terms = fmax(terms, fmax(fabs(qx), fmax(fabs(p), fabs(ap))));
+    if (lane < NX) PV[k * NX + j] = p;
+  };
+  static_assert(CD == 4, "one line below per ring slot");
+  for (int k = N - 1;; k -= CD) {
+    if (!(k >= 0)) break;
+    step(k, ring[0]);
+    if (!(k - 1 >= 0)) break;
+    step(k - 1, ring[1]);
+    if (!(k - 2 >= 0)) break;
+    step(k - 2, ring[2]);
+    if (!(k - 3 >= 0)) break;
+    step(k - 3, ring[3]);
+  }
+  wsync();
+  // B^T p, four stages at a time
+  const int oB = j < NU ? (g * NX * U4 + j) * 4 : OOB;
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    const int k = k0 + g;
+    double ba[NX], bb[NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      ba[r] = (double)ldf(rB, oB + r * U4 * 4, k0 * (NX * U4 * 4));
+      bb[r] = (double)ldf(rB, oB + r * U4 * 4 + NU * 4, k0 * (NX * U4 * 4));
+    }
+    const double pk = (j < NX && k < N) ? PV[k * NX + j] : 0.0;
+    const double ga = dot_row_bcast13(pk, ba, 0.0), gb = dot_row_bcast13(pk, bb, 0.0);
+    if (j < NU && k < N) {
+      GV[k * U4 + j] = ga;
+      GV[k * U4 + NU + j] = gb;
+    }
+  }
+  wsync();
   // per (stage, contact): gradient, multipliers, feasibility, complementarity
-  double terms = fmax(tq, fmax(tl, ta)), stat = 0.0, rin = 0.0, mmax = 0.0, comp = 0.0;
-  for (int e = lane; e < C.N * C4; e += 64) {
+  double stat = 0.0, rin = 0.0, mmax = 0.0, comp = 0.0;
+  for (int e = lane; e < N * C4; e += W64) {
     const int k = e / C4, i = e % C4;
     double u[6];
     ld6(C.u + (size_t)k * U4 + 6 * i, u);
     if (!stance(C, k, i)) {
-      #pragma unroll
+#pragma unroll
       for (int t = 0; t < 6; ++t) rin = fmax(rin, fabs(u[t]) / C.mg);
       continue;
     }
-    double gu[NROW], h[NROW], sc[NROW], mv[NROW], gr[6];
-    rows_of(C, u, gu, h, sc);
-    const auto Bk = C.B + (size_t)k * NX * U4;
-    const auto lk = C.lam + (size_t)k * U4;
+    double gu[NROW], h[NROW], isc[NROW], mv[NROW], gr[6];
+    rows_of(C, u, gu, h, isc);
     double tr = 0.0, tb = 0.0;
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
-      const int j = 6 * i + t;
-      const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + j] : 0.0;
-      const double ru = sh.R[j] * (u[t] - ur);
-      double bl = 0.0;
-#pragma unroll
-      for (int l = 0; l < NX; ++l) bl = fma((double)Bk[l * U4 + j], lk[l], bl);
+      const int jj = 6 * i + t;
+      const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + jj] : 0.0;
+      const double ru = sh.R[jj] * (u[t] - ur), bl = GV[k * U4 + jj];
       tr = fmax(tr, fabs(ru));
       tb = fmax(tb, fabs(bl));
       gr[t] = ru + bl;
@@ -785,7 +945,7 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh, 
     int am = 0;
 #pragma unroll
     for (int r = 0; r < NROW; ++r)
-      if (h[r] - gu[r] <= tol * sc[r]) am |= 1 << r;
+      if (h[r] - gu[r] <= tol * (r < 5 ? C.scf : C.scm)) am |= 1 << r;
     double mf[5];
     force_refit(am & 31, C.mu, gr, mf);
 #pragma unroll
@@ -797,10 +957,10 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh, 
     }
     double gm[6];
     rows_T(C, mv, gm);
-    double tg = 0.0, cmp = 0.0;
+    double tgm = 0.0, cmp = 0.0;
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
-      tg = fmax(tg, fabs(gm[t]));
+      tgm = fmax(tgm, fabs(gm[t]));
       stat = fmax(stat, fabs(gr[t] + gm[t]));
     }
 #pragma unroll
@@ -810,88 +970,56 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh, 
       cmp = fmax(cmp, mv[r] * fmax(h[r] - gu[r], 0.0));
     }
     comp = fmax(comp, cmp);
-    terms = fmax(terms, fmax(tr, fmax(tb, tg)));
+    terms = fmax(terms, fmax(tr, fmax(tb, tgm)));
   }
-  terms = wmax(terms);
-  mmax = wmax(mmax);
-  comp = wmax(comp) / (1.0 + mmax * C.mg);
-  res[1] = wmax(rin);
-  res[2] = wmax(stat) / (1.0 + terms);
+  terms = wave_max(terms);
+  mmax = wave_max(mmax);
+  comp = wave_max(comp) / (1.0 + mmax * C.mg);
+  res[1] = wave_max(rin);
+  res[2] = wave_max(stat) / (1.0 + terms);
   res[3] = comp;
   res[4] = 0.0;   // the refitted multipliers are nonnegative
   double m = 0.0;
-  #pragma unroll
+#pragma unroll
   for (int i = 0; i < PINMPC_NRES; ++i) m = fmax(m, res[i]);
   return m;
 }
 
-// Slack and multiplier steps of the direction (du) for complementarity
-// target rc; returns the largest step keeping s, z >= 0 (at most 1).
-template <int OCC>
-__device__ __attribute__((noinline)) double row_steps(const WCtx& C) {
-  double amax = 1.0;
-  for (int e = threadIdx.x; e < C.N * C4; e += 64) {
-    const int k = e / C4, i = e % C4;
-    if (!stance(C, k, i)) continue;
-    double u[6], du[6], gu[NROW], gd[NROW], h[NROW], sc[NROW], sv[NROW], zv[NROW], cv[NROW];
-    ld6(C.u + (size_t)k * U4 + 6 * i, u);
-    ld6(C.du + (size_t)k * U4 + 6 * i, du);
-    ldr(C.s + (size_t)e * NROW, sv);
-    ldr(C.z + (size_t)e * NROW, zv);
-    ldr(C.rc + (size_t)e * NROW, cv);
-    rows_of(C, u, gu, h, sc);
-    rows_of(C, du, gd, h, sc);
-    double dsv[NROW], dzv[NROW];
-    #pragma unroll
-    for (int r = 0; r < NROW; ++r) {
-      const double rp = (gu[r] - h[r]) / sc[r] + sv[r];
-      dsv[r] = -rp - gd[r] / sc[r];
-      dzv[r] = (-cv[r] - zv[r] * dsv[r]) / sv[r];
-      if (dsv[r] < 0.0) amax = fmin(amax, -sv[r] / dsv[r]);
-      if (dzv[r] < 0.0) amax = fmin(amax, -zv[r] / dzv[r]);
-    }
-    str(C.ds + (size_t)e * NROW, dsv);
-    str(C.dz + (size_t)e * NROW, dzv);
-  }
-  return wmin(amax);
-}
-
 // Interior point from the current u (its rollout in x).  Returns the
 // iterations; *ok tells whether the certificate was met (then res is it).
-template <int OCC>
-__device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, double tol, double res[PINMPC_NRES],
-                   bool* ok, int* nfact) {
-  const int lane = threadIdx.x;
+__device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, double tol,
+                                            double res[PINMPC_NRES], bool* ok) {
+  const int lane = lane_id(), N = C.N, rs = C4 * C.n;
+  double* const PV = sh.c.PV;
+  double* const GV = sh.c.GV;
   *ok = false;
-  *nfact = 0;   // backward recursions that factored (the others: vector part only)
   // rows of stance contacts, starting slacks (at least 1) and multipliers 1
   double mloc = 0.0, smz = 0.0, rpn = 0.0;
   __syncthreads();
-  for (int e = lane; e < C.N * C4; e += 64) {
+  for (int e = lane; e < N * C4; e += W64) {
     const int k = e / C4, i = e % C4;
     if (!stance(C, k, i)) continue;
-    double u[6], gu[NROW], h[NROW], sc[NROW], sv[NROW], zv[NROW];
+    double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW];
     ld6(C.u + (size_t)k * U4 + 6 * i, u);
-    rows_of(C, u, gu, h, sc);
-    #pragma unroll
+    rows_of(C, u, gu, h, isc);
+#pragma unroll
     for (int r = 0; r < NROW; ++r) {
-      sv[r] = fmax((h[r] - gu[r]) / sc[r], 1.0);
+      sv[r] = fmax((h[r] - gu[r]) * isc[r], 1.0);
       zv[r] = 1.0;
       smz += sv[r] * zv[r];
-      rpn = fmax(rpn, fabs((gu[r] - h[r]) / sc[r] + sv[r]));
+      rpn = fmax(rpn, fabs(fma(gu[r] - h[r], isc[r], sv[r])));
     }
     mloc += NROW;
-    str(C.s + (size_t)e * NROW, sv);
-    str(C.z + (size_t)e * NROW, zv);
-    str(C.rc + (size_t)e * NROW, sv);   // affine target s z with z = 1
+    str(C.s, rs, e, sv);
+    str(C.z, rs, e, zv);
   }
-  const double m = wsum(mloc);
+  const double m = wave_sum(mloc);
   int it = 0;
   for (; it < maxit; ++it) {
-    const double muv = m > 0.0 ? wsum(smz) / m : 0.0;
-    rpn = wmax(rpn);
+    const double sz = wave_sum(smz), muv = m > 0.0 ? sz / m : 0.0;
+    rpn = wave_max(rpn);
     if (muv <= 1e-8 && rpn <= 1e-8) {
-      if (certificate<OCC>(C, sh, res, tol) <= tol) {
+      if (certificate(C, sh, res, tol) <= tol) {
         *ok = true;
         return it;
       }
@@ -899,96 +1027,149 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
       // slacks near zero) carry no accuracy
       if (muv <= 1e-20) break;
     }
-    // predictor: affine target rc = s z (in C.rc)
-    build_terms<OCC>(C, sh);
-    backward<OCC>(C, sh, true);
-    ++*nfact;
-    forward<OCC>(C, sh);
-    double sigma = 0.0;
+    // predictor: affine target s z
+    build_terms(C, sh);
+    backward(C, sh);
+    forward<false>(C, sh);
+    double a = 1.0;
     if (m > 0.0) {
-      const double aa = row_steps<OCC>(C);
-      double sm = 0.0;
-      for (int e = lane; e < C.N * C4; e += 64) {
+      // its row steps, the largest step to the boundary, and the sums that give
+      // the complementarity after any step
+      double amax = 1.0, sm1 = 0.0, sm2 = 0.0;
+      for (int e = lane; e < N * C4; e += W64) {
         const int k = e / C4, i = e % C4;
         if (!stance(C, k, i)) continue;
-        double sv[NROW], zv[NROW], dsv[NROW], dzv[NROW], cv[NROW];
-        ldr(C.s + (size_t)e * NROW, sv);
-        ldr(C.z + (size_t)e * NROW, zv);
-        ldr(C.ds + (size_t)e * NROW, dsv);
-        ldr(C.dz + (size_t)e * NROW, dzv);
-        #pragma unroll
+        double u[6], du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
+        ld6(C.u + (size_t)k * U4 + 6 * i, u);
+#pragma unroll
+        for (int t = 0; t < 6; ++t) du[t] = GV[k * U4 + 6 * i + t];
+        ldr(C.s, rs, e, sv);
+        ldr(C.z, rs, e, zv);
+        rows_of(C, u, gu, h, isc);
+        rows_of(C, du, gdu, h, isc);
+#pragma unroll
         for (int r = 0; r < NROW; ++r) {
-          sm += (sv[r] + aa * dsv[r]) * (zv[r] + aa * dzv[r]);
-          cv[r] = sv[r] * zv[r] + dsv[r] * dzv[r];   // sigma mu subtracted below
+          const double rp = fma(gu[r] - h[r], isc[r], sv[r]);
+          const double ds = -fma(gdu[r], isc[r], rp);
+          const double dz = -(zv[r] + zv[r] * ds * recip(sv[r]));
+          if (ds < 0.0) amax = fmin(amax, -sv[r] * recip(ds));
+          if (dz < 0.0) amax = fmin(amax, -zv[r] * recip(dz));
+          sm1 += sv[r] * dz + zv[r] * ds;
+          sm2 += ds * dz;
+          cv[r] = fma(ds, dz, sv[r] * zv[r]);   // corrector target, less sigma mu
         }
-        str(C.rc + (size_t)e * NROW, cv);
+        str(C.rc, rs, e, cv);
       }
-      const double mu_aff = wsum(sm) / m;
-      sigma = muv > 0.0 ? pow(mu_aff / muv, 3.0) : 0.0;
-      // corrector: rc = s z + ds_aff dz_aff - sigma mu, the same Newton matrix
-      // (solved with the inverse the predictor's elimination left)
-      for (int e = lane; e < C.N * C4; e += 64) {
+      const double aa = wave_min(amax);
+      const double mu_aff = fmax(fma(aa, fma(aa, wave_sum(sm2), wave_sum(sm1)), sz), 0.0) / m;
+      const double ratio = muv > 0.0 ? mu_aff / muv : 0.0, smu = ratio * ratio * ratio * muv;
+      // corrector: rc = s z + ds_aff dz_aff - sigma mu, the same Newton matrix:
+      // its linear input term, the recursion's vector part and the rollout with
+      // the predictor's factors (triangular solves, as accurate near the optimum
+      // as factoring again; a product with the inverse is not)
+      for (int e = lane; e < N * C4; e += W64) {
+        const int k = e / C4, i = e % C4;
+        double rho[6] = {0, 0, 0, 0, 0, 0};
+        if (stance(C, k, i)) {
+          double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW], c[NROW];
+          ld6(C.u + (size_t)k * U4 + 6 * i, u);
+          ldr(C.s, rs, e, sv);
+          ldr(C.z, rs, e, zv);
+          ldr(C.rc, rs, e, cv);
+          rows_of(C, u, gu, h, isc);
+#pragma unroll
+          for (int r = 0; r < NROW; ++r) {
+            cv[r] -= smu;
+            const double rp = fma(gu[r] - h[r], isc[r], sv[r]);
+            c[r] = (zv[r] + (zv[r] * rp - cv[r]) * recip(sv[r])) * isc[r];
+          }
+          str(C.rc, rs, e, cv);
+          rows_T(C, c, rho);
+#pragma unroll
+          for (int t = 0; t < 6; ++t) {
+            const int jj = 6 * i + t;
+            const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + jj] : 0.0;
+            rho[t] = fma(sh.R[jj], u[t] - ur, rho[t]);
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < 6; ++t) GV[k * U4 + 6 * i + t] = rho[t];
+      }
+      wsync();
+      newton_vector(C, sh);
+      forward<true>(C, sh);
+      // the step's rows, and its length
+      amax = 1.0;
+      for (int e = lane; e < N * C4; e += W64) {
         const int k = e / C4, i = e % C4;
         if (!stance(C, k, i)) continue;
-        gd cv = C.rc + (size_t)e * NROW;
-        #pragma unroll
-        for (int r = 0; r < NROW; ++r) cv[r] -= sigma * muv;
+        double u[6], du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
+        ld6(C.u + (size_t)k * U4 + 6 * i, u);
+#pragma unroll
+        for (int t = 0; t < 6; ++t) du[t] = GV[k * U4 + 6 * i + t];
+        ldr(C.s, rs, e, sv);
+        ldr(C.z, rs, e, zv);
+        ldr(C.rc, rs, e, cv);
+        rows_of(C, u, gu, h, isc);
+        rows_of(C, du, gdu, h, isc);
+        double dsv[NROW], dzv[NROW];
+#pragma unroll
+        for (int r = 0; r < NROW; ++r) {
+          const double rp = fma(gu[r] - h[r], isc[r], sv[r]);
+          dsv[r] = -fma(gdu[r], isc[r], rp);
+          dzv[r] = -fma(zv[r], dsv[r], cv[r]) * recip(sv[r]);
+          if (dsv[r] < 0.0) amax = fmin(amax, -sv[r] * recip(dsv[r]));
+          if (dzv[r] < 0.0) amax = fmin(amax, -zv[r] * recip(dzv[r]));
+        }
+        str(C.ds, rs, e, dsv);
+        str(C.dz, rs, e, dzv);
       }
-      // (near the optimum the corrector factors again: the product with the
-      // kept inverse carries the Hessian's conditioning into the step, which
-      // then limits how closely u meets stationarity)
-      build_terms<OCC>(C, sh);
-      const bool refactor = muv <= 1e-8;
-      backward<OCC>(C, sh, refactor);
-      *nfact += refactor;
-      forward<OCC>(C, sh);
+      a = fmin(1.0, 0.99 * wave_min(amax));
     }
-    const double a = m > 0.0 ? fmin(1.0, 0.99 * row_steps<OCC>(C)) : 1.0;
-    // step; residuals and affine target of the new point
-    __syncthreads();
+    // step; residuals of the new point (a lane updates the inputs of its own
+    // contact-stage; swing inputs stay 0)
     smz = 0.0;
     rpn = 0.0;
-    for (int e = lane; e < C.N * U4; e += 64) C.u[e] += a * C.du[e];
-    for (int e = lane; e < (C.N + 1) * NX; e += 64) C.x[e] += a * C.dx[e];
-    __syncthreads();
-    for (int e = lane; e < C.N * C4; e += 64) {
+    for (int e = lane; e < N * C4; e += W64) {
       const int k = e / C4, i = e % C4;
       if (!stance(C, k, i)) continue;
-      double u[6], gu[NROW], h[NROW], sc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW];
+      double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW];
       ld6(C.u + (size_t)k * U4 + 6 * i, u);
-      rows_of(C, u, gu, h, sc);
-      ldr(C.s + (size_t)e * NROW, sv);
-      ldr(C.z + (size_t)e * NROW, zv);
-      ldr(C.ds + (size_t)e * NROW, dsv);
-      ldr(C.dz + (size_t)e * NROW, dzv);
-      #pragma unroll
+#pragma unroll
+      for (int t = 0; t < 6; ++t) {
+        u[t] += a * GV[k * U4 + 6 * i + t];
+        C.u[(size_t)k * U4 + 6 * i + t] = u[t];
+      }
+      rows_of(C, u, gu, h, isc);
+      ldr(C.s, rs, e, sv);
+      ldr(C.z, rs, e, zv);
+      ldr(C.ds, rs, e, dsv);
+      ldr(C.dz, rs, e, dzv);
+#pragma unroll
       for (int r = 0; r < NROW; ++r) {
         sv[r] += a * dsv[r];
         zv[r] += a * dzv[r];
         smz += sv[r] * zv[r];
-        rpn = fmax(rpn, fabs((gu[r] - h[r]) / sc[r] + sv[r]));
+        rpn = fmax(rpn, fabs(fma(gu[r] - h[r], isc[r], sv[r])));
       }
-      str(C.s + (size_t)e * NROW, sv);
-      str(C.z + (size_t)e * NROW, zv);
-      double cv[NROW];
-      #pragma unroll
-      for (int r = 0; r < NROW; ++r) cv[r] = sv[r] * zv[r];
-      str(C.rc + (size_t)e * NROW, cv);
+      str(C.s, rs, e, sv);
+      str(C.z, rs, e, zv);
     }
+    for (int e = lane; e < N * NX; e += W64) C.x[NX + e] += a * PV[e];
+    wsync();
   }
-  *ok = certificate<OCC>(C, sh, res, tol) <= tol;
+  *ok = certificate(C, sh, res, tol) <= tol;
   return it;
 }
 
-template <int OCC>
-__global__ void __launch_bounds__(64, OCC) refine_wide_kernel(Problem p, Workspace ws, float* out_u,
+__global__ void __launch_bounds__(64, 2) refine_wide_kernel(Problem p, Workspace ws, float* out_u,
                                                          float* out_x, float* out_res,
                                                          int32_t* out_iters, int32_t* out_status,
                                                          int32_t* out_detail, int admm_iters,
                                                          int accel, int refine, int ipm_max,
                                                          double tol) {
   __shared__ WSh sh;
-  const int lane = threadIdx.x;
+  const int lane = lane_id();
   // the problem's context lives in LDS (the phase functions read its fields
   // with LDS loads, which no wait for a global load in flight holds up)
   __shared__ WCtx C;
@@ -1003,6 +1184,8 @@ __global__ void __launch_bounds__(64, OCC) refine_wide_kernel(Problem p, Workspa
     C.mg = weight_of(p, C.b);
     C.scf = C.mg;
     C.scm = C.tm > 0.0 ? C.tm : 1.0;
+    C.isf = 1.0 / C.scf;
+    C.ism = 1.0 / C.scm;
     C.A = (gcf)(p.A + s0 * NX * NX);
     C.B = (gcf)(p.B + s0 * NX * U4);
     C.e = p.e ? (gcf)(p.e + s0 * NX) : nullptr;
@@ -1036,18 +1219,13 @@ __global__ void __launch_bounds__(64, OCC) refine_wide_kernel(Problem p, Workspa
     for (int j = 0; j < U4; ++j) bad |= !(sh.R[j] > 0.0);
   }
   if (!bad && !nonfinite) {
-    int nf = 0;
-    for (int e = lane; e < N * NX * NX; e += 64) nf |= !isfinite(C.A[e]);
-    for (int e = lane; e < N * NX * U4; e += 64) nf |= !isfinite(C.B[e]);
-    for (int e = lane; e < N * NX; e += 64) {
-      nf |= !isfinite(C.x_ref[e]);
-      if (C.e) nf |= !isfinite(C.e[e]);
-    }
-    if (C.u_ref)
-      for (int e = lane; e < N * U4; e += 64) nf |= !isfinite(C.u_ref[e]);
+    int nf = any_nonfinite(uni(C.A), N * NX * NX) | any_nonfinite(uni(C.B), N * NX * U4) |
+             any_nonfinite(uni(C.x_ref), N * NX);
+    if (C.e) nf |= any_nonfinite(uni(C.e), N * NX);
+    if (C.u_ref) nf |= any_nonfinite(uni(C.u_ref), N * U4);
     if (lane < NX) nf |= !isfinite(C.x0[lane]);
     if (p.u_prev && lane < U4) nf |= !isfinite(p.u_prev[(size_t)C.b * U4 + lane]);
-    nonfinite = wmax((double)nf) > 0.0;
+    nonfinite = wave_max_int(nf) > 0;
   }
   const size_t ux = (size_t)C.b * C.n * U4, xx = (size_t)C.b * (C.n + 1) * NX;
   if (bad || nonfinite) {
@@ -1072,14 +1250,14 @@ __global__ void __launch_bounds__(64, OCC) refine_wide_kernel(Problem p, Workspa
     C.u[e] = stance(C, k, j / 6) ? v : 0.0;
   }
   double res[PINMPC_NRES] = {0, 0, 0, 0, 0};
-  int its = 0, nfact = 0;
+  int its = 0;
   bool ok = false;
-  (void)rollout<OCC>(C, sh);
+  rollout(C, sh);
   if (refine) {
-    its = ipm<OCC>(C, sh, ipm_max, tol, res, &ok, &nfact);   // res: the returned point's
+    its = ipm(C, sh, ipm_max, tol, res, &ok);   // res: the returned point's
   } else {
     // the ADMM point as it is
-    (void)certificate<OCC>(C, sh, res, tol);
+    (void)certificate(C, sh, res, tol);
   }
 
   // outputs
@@ -1094,7 +1272,8 @@ __global__ void __launch_bounds__(64, OCC) refine_wide_kernel(Problem p, Workspa
     if (out_iters) out_iters[C.b] = admm_iters + its;
   }
   if (out_detail && lane < 4) {
-    const int v = lane == 1 ? its : lane == 2 ? nfact * N : lane == 3 ? 1 : 0;
+    // (every predictor factors the horizon, no corrector does)
+    const int v = lane == 1 ? its : lane == 2 ? its * N : lane == 3 ? 1 : 0;
     out_detail[(size_t)C.b * 4 + lane] = v;
   }
   if (out_res && lane < PINMPC_NRES) out_res[(size_t)C.b * PINMPC_NRES + lane] = (float)res[lane];
@@ -1106,22 +1285,9 @@ hipError_t launch_refine_wide(const Problem& p, const Workspace& w, const pinmpc
                               const pinmpc_out& out, hipStream_t st) {
   if (p.batch == 0) return hipSuccess;
   if (p.nc != C4 || p.n_max > PINMPC_NMAX) return hipErrorInvalidValue;
-  // two waves per SIMD once the batch has more problems than the chip has
-  // SIMDs; below that every problem has a SIMD of its own and the one-wave
-  // build, with all registers for its stage, is faster (both builds do the
-  // same arithmetic in the same order: bitwise the same results)
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 256;
-  if (p.batch > 4 * cus)
-    hipLaunchKernelGGL(refine_wide_kernel<2>, dim3(p.batch), dim3(64), 0, st, p, w, out.u, out.x,
-                       out.res, out.iters, out.status, out.detail, s.iters, s.accel, s.refine,
-                       s.ipm_iters, s.kkt_tol);
-  else
-    hipLaunchKernelGGL(refine_wide_kernel<1>, dim3(p.batch), dim3(64), 0, st, p, w, out.u, out.x,
-                       out.res, out.iters, out.status, out.detail, s.iters, s.accel, s.refine,
-                       s.ipm_iters, s.kkt_tol);
+  hipLaunchKernelGGL(refine_wide_kernel, dim3(p.batch), dim3(64), 0, st, p, w, out.u, out.x,
+                     out.res, out.iters, out.status, out.detail, s.iters, s.accel, s.refine,
+                     s.ipm_iters, s.kkt_tol);
   return hipGetLastError();
 }
 
