@@ -24,13 +24,20 @@ namespace pinmpc {
 
 namespace {
 
+// Every function is part of its kernel: with a call, a recursion that takes all
+// 256 registers saves and restores up to a hundred of the caller's through scratch
+// memory (about a tenth of an equality pass at full occupancy).
+#define INLINE __attribute__((always_inline)) inline
+
 // One problem's view: its inputs and its FP64 scratch block, all as
 // pointers to the problem's own first stage, so stage k is plain k.
-struct Ctx {
-  int b, N, n;
+struct Scalars {
   double mu, fz, tm, mg;
   double i1, i2;          // 1 / (1 + mu^2), 1 / (1 + 2 mu^2): the pyramid's Gram inverses
   double img, itm;        // 1 / mg, 1 / tm: the interior point's row scales
+};
+struct Ctx : Scalars {
+  int b, N, n;
   const LMEM double* Q;   // LDS copies of the diagonal weights
   const LMEM double* R;
   gcf A, B, e, x_ref, u_ref, x0;
@@ -43,27 +50,56 @@ struct Ctx {
 
 // ------------------------------------------------------------ small helpers
 
-// Row i (0..10) of one stance contact's wrench constraints on (f, tau).
-__device__ inline void wrench_row(int i, double mu, double fz, double tm, double g[6],
-                                  double* h) {
-  for (int a = 0; a < 6; ++a) g[a] = 0.0;
-  switch (i) {
-    case 0: g[0] = 1; g[2] = -mu; *h = 0; break;
-    case 1: g[0] = -1; g[2] = -mu; *h = 0; break;
-    case 2: g[1] = 1; g[2] = -mu; *h = 0; break;
-    case 3: g[1] = -1; g[2] = -mu; *h = 0; break;
-    case 4: g[2] = 1; *h = fz; break;
-    default: {
-      const int a = (i - 5) % 3;
-      g[3 + a] = (i < 8) ? 1.0 : -1.0;
-      *h = tm;
-    }
+// A copy of the scalars in scalar registers.
+__device__ inline Scalars scalars(const Ctx& C) {
+  return {uni(C.mu), uni(C.fz), uni(C.tm), uni(C.mg), uni(C.i1), uni(C.i2), uni(C.img), uni(C.itm)};
+}
+
+// The 11 rows of one stance contact's wrench constraints G (f, tau) <= h: the
+// pyramid's sides f_x - mu f_z, -f_x - mu f_z, f_y - mu f_z, -f_y - mu f_z <= 0,
+// f_z <= fz_max, then tau_a <= tau_max and -tau_a <= tau_max.  The products skip
+// G's zeros (a dense row is six multiply-adds, and the compiler keeps those with
+// a zero).  G u:
+__device__ inline void rows_of(const Scalars& C, const double u[6], double gu[NROW]) {
+  gu[0] = fma(-C.mu, u[2], u[0]);
+  gu[1] = fma(-C.mu, u[2], -u[0]);
+  gu[2] = fma(-C.mu, u[2], u[1]);
+  gu[3] = fma(-C.mu, u[2], -u[1]);
+  gu[4] = u[2];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    gu[5 + a] = u[3 + a];
+    gu[8 + a] = -u[3 + a];
   }
 }
+// o + G^T v
+__device__ inline void rows_T(const Scalars& C, const double v[NROW], double o[6]) {
+  o[0] += v[0] - v[1];
+  o[1] += v[2] - v[3];
+  o[2] += fma(-C.mu, (v[0] + v[1]) + (v[2] + v[3]), v[4]);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) o[3 + a] += v[5 + a] - v[8 + a];
+}
+// h_r, the row's scale and the interior point's inverse scale (r a constant)
+__device__ inline double row_h(const Scalars& C, int r) { return r < 4 ? 0.0 : (r == 4 ? C.fz : C.tm); }
+__device__ inline double row_scale(const Scalars& C, int r) { return r < 5 ? C.mg : C.tm; }
+__device__ inline double row_isc(const Scalars& C, int r) { return r < 5 ? C.img : C.itm; }
+// face bit of row r
+__device__ inline int row_bit(int r) { return r < 5 ? (1 << r) : (1 << (8 + (r - 5))); }
 
 __device__ inline bool face_apex(int code) {
   const int f = code & 31;
   return ((f & 3) == 3) || ((f & 12) == 12);
+}
+
+// The face of a set of active rows: all of an apex's force rows, and only the
+// upper of two opposite moment rows.
+__device__ inline int settle_face(int code) {
+  if (face_apex(code)) code = (code & ~31) | FACE_APEX;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if ((code >> (8 + a) & 1) && (code >> (11 + a) & 1)) code &= ~(1 << (11 + a));
+  return code;
 }
 
 // The force part of a face that is not the apex: the active side rows along x
@@ -88,7 +124,7 @@ __device__ inline ForceFace force_face(int code) {
 // (the side rows are [s_x, 0, -mu], [0, s_y, -mu]): at the normal-force bound
 // f_z and every component with an active side row are fixed; otherwise one
 // side row leaves its plane, two the line along [s_x mu, s_y mu, 1].
-__device__ inline void face_affine(int code, const Ctx& C, double P[6][6], double c[6]) {
+__device__ inline void face_affine(int code, const Scalars& C, double P[6][6], double c[6]) {
 #pragma unroll
   for (int a = 0; a < 6; ++a) {
     c[a] = 0.0;
@@ -119,6 +155,63 @@ __device__ inline void face_affine(int code, const Ctx& C, double P[6][6], doubl
     if (code >> (8 + a) & 1) c[3 + a] = C.tm;
     else if (code >> (11 + a) & 1) c[3 + a] = -C.tm;
     else P[3 + a][3 + a] = 1.0;
+  }
+}
+
+// ------------------------------------------------- a contact-stage's data
+//
+// The passes over the rows run one lane per contact-stage.  With a few waves per
+// SIMD each trip to memory costs 2000 to 4000 cycles and the arithmetic of a pass
+// about as much, so a pass loads all it needs at once, before any branch on it
+// (a load under `if (u_ref)` or `if (contact)` is one more trip: six of them,
+// one per component of u_ref, made a pass over 20 stages 30 to 50 thousand
+// cycles), through buffer instructions: scalar bases, one offset per lane.
+
+typedef __amdgpu_buffer_rsrc_t Buf;
+// inputs of contact-stage e (6 of 12 per stage: 48 bytes each)
+__device__ inline void ld6(Buf r, int e, double v[6]) {
+#pragma unroll
+  for (int t = 0; t < 6; t += 2) ldd2(r, e * 48 + t * 8, 0, v + t);
+}
+__device__ inline void st6(Buf r, int e, const double v[6]) {
+#pragma unroll
+  for (int t = 0; t < 6; t += 2) std2(r, e * 48 + t * 8, 0, v[t], v[t + 1]);
+}
+// the reference inputs (an empty buffer where there are none: zeros)
+__device__ inline Buf uref_buf(const Ctx& C) {
+  const gcf p = uni(C.u_ref);
+  return rsrc(p ? p : uni(C.A), p ? C.N * NU * 4 : 0);
+}
+__device__ inline void ldu6(Buf r, int e, float v[6]) {
+  ldf3(r, e * 24, 0, v);
+  ldf3(r, e * 24 + 12, 0, v + 3);
+}
+// A row's entries for consecutive contact-stages e are consecutive in memory,
+// `step` bytes apart per row: the lanes of a pass load and store whole lines.
+__device__ inline Buf row_buf(const Ctx& C, gd p) { return rsrc(uni(p), 2 * C.n * NROW * 8); }
+__device__ inline void load_r(Buf r, int step, int e, double x[NROW]) {
+#pragma unroll
+  for (int q = 0; q < NROW; ++q) x[q] = ldd(r, e * 8, q * step);
+}
+__device__ inline void store_r(Buf r, int step, int e, const double x[NROW]) {
+#pragma unroll
+  for (int q = 0; q < NROW; ++q) std1(r, e * 8, q * step, x[q]);
+}
+template <int M, class T>
+__device__ inline void pin_all(const T (&v)[M]) {
+#pragma unroll
+  for (int t = 0; t < M; ++t) asm volatile("" ::"v"(v[t]));
+}
+__device__ inline void copy_doubles(gd dst, gd src, int count) {
+  const Buf r = rsrc(uni(src), count * 8);
+  for (int e0 = lane_id(); e0 < count; e0 += 8 * W64) {
+    double v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = ldd(r, (e0 + t * W64) * 8, 0);
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (e0 + t * W64 < count) dst[e0 + t * W64] = v[t];
   }
 }
 
@@ -271,9 +364,20 @@ __device__ inline uint32_t unit_bits(int code) {
 // Equality passes, stages 0..kn-1: T the face projector P and point c of each
 // contact, T2 the terms P R P + I - P and P R (c - u_ref) of the stage's
 // quadratic that need no value function.
-__device__ inline void build_eq(const Ctx& C, uint8_t* unit, int kn) {
+__device__ inline void build_eq(const Ctx& C, const double* Rd, uint8_t* unit, int kn) {
+  const Scalars sc = scalars(C);
+  const Buf rR = uref_buf(C);
+  const auto ct = uni(C.contact);
+  const auto fc = uni(C.faces);
+  const gd pT = uni(C.rT), pT2 = uni(C.rT2);
   for (int e = lane_id(); e < kn * 2; e += W64) {
-    const int k = e >> 1, i = e & 1;
+    const int i = e & 1;
+    float ur[6];
+    const int code = fc[e];
+    const bool on = ct[e];
+    ldu6(rR, e, ur);
+    pin_all(ur);
+    pin_memory();
     InputBlock t, t2;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -288,16 +392,14 @@ __device__ inline void build_eq(const Ctx& C, uint8_t* unit, int kn) {
 #pragma unroll
     for (int a = 0; a < 6; ++a) t.v[a] = t2.v[a] = 0.0;
     uint32_t u = 0x3F;
-    if (C.contact[e]) {
-      const int code = C.faces[e];
+    if (on) {
       u = unit_bits(code);
       double P[6][6], c[6], R[6], rho[6];
-      face_affine(code, C, P, c);
+      face_affine(code, sc, P, c);
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
-        R[a] = C.R[6 * i + a];
-        const double ur = C.u_ref ? (double)C.u_ref[k * NU + 6 * i + a] : 0.0;
-        rho[a] = R[a] * (c[a] - ur);
+        R[a] = Rd[6 * i + a];
+        rho[a] = R[a] * (c[a] - (double)ur[a]);
         t.v[a] = c[a];
       }
 #pragma unroll
@@ -320,78 +422,52 @@ __device__ inline void build_eq(const Ctx& C, uint8_t* unit, int kn) {
       }
     }
     unit[e] = (uint8_t)u;
-    store_block(C.rT + (size_t)e * 18, t);
-    store_block(C.rT2 + (size_t)e * 18, t2);
+    store_block(pT + (size_t)e * 18, t);
+    store_block(pT2 + (size_t)e * 18, t2);
   }
 }
 
-// Newton steps, all N stages: T the input Hessian R + G^T diag(z/s) G and the
-// linear term R (u - u_ref) + G^T c_rows of each stance contact at the affine
-// target s z (rows scaled by sc: weight z / (s sc^2), coefficient
-// (z + (-s z + z rp) / s) / sc = z rp / (s sc), rp = (g u - h) / sc + s), the
-// identity and zero for a swing contact; and the state cost gradients
-// q_k = Q (x_{k+1} - r_k).
-__device__ inline void build_newton(const Ctx& C, uint8_t* unit, int N) {
-  const int rs = 2 * C.n;
-  for (int e = lane_id(); e < N * 2; e += W64) {
-    const int k = e >> 1, i = e & 1;
-    InputBlock t;
+// Newton steps: the input block of stance contact-stage e at (u, s, z), the
+// input Hessian R + G^T diag(z/s) G and the linear term R (u - u_ref) +
+// G^T c_rows at the affine target s z (rows scaled by sc: weight z / (s sc^2),
+// coefficient (z + (-s z + z rp) / s) / sc = z rp / (s sc), rp = (g u - h) / sc
+// + s).
+__device__ inline void newton_block(const Scalars& C, const double* R, gd T, int e,
+                                    const double u[6], const float ur[6], const double sv[NROW],
+                                    const double zv[NROW]) {
+  double gu[NROW], d[NROW], c[NROW];
+  InputBlock t;
+  rows_of(C, u, gu);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      t.d[a] = 1.0;
-#pragma unroll
-      for (int b = 0; b < 3; ++b) t.m[a][b] = a == b ? 1.0 : 0.0;
-    }
-#pragma unroll
-    for (int a = 0; a < 6; ++a) t.v[a] = 0.0;
-    uint32_t ub = 0x3F;
-    if (C.contact[e]) {
-      ub = 0;
-      double u[6];
-#pragma unroll
-      for (int a = 0; a < 6; ++a) {
-        const int jj = 6 * i + a;
-        u[a] = C.ru[k * NU + jj];
-        const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
-        if (a < 3) t.m[a][a] = C.R[jj];
-        else t.d[a - 3] = C.R[jj];
-        t.v[a] = C.R[jj] * (u[a] - ur);
-      }
-#pragma unroll
-      for (int row = 0; row < NROW; ++row) {
-        double gr[6], h;
-        wrench_row(row, C.mu, C.fz, C.tm, gr, &h);
-        const double isc = (row < 5) ? C.img : C.itm;
-        double gu = 0.0;
-#pragma unroll
-        for (int a = 0; a < 6; ++a) gu += gr[a] * u[a];
-        const double s = C.rs[row * rs + e], z = C.rz[row * rs + e];
-        const double rp = fma(gu - h, isc, s), zs = z * recip(s);
-        const double w = zs * (isc * isc), cr = zs * rp * isc;
-#pragma unroll
-        for (int a = 0; a < 6; ++a) t.v[a] += gr[a] * cr;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          t.d[a] += w * gr[3 + a] * gr[3 + a];
-#pragma unroll
-          for (int b = 0; b < 3; ++b) t.m[a][b] += w * gr[a] * gr[b];
-        }
-      }
-    }
-    unit[e] = (uint8_t)ub;
-    store_block(C.rT + (size_t)e * 18, t);
+  for (int r = 0; r < NROW; ++r) {
+    const double isc = row_isc(C, r);
+    const double rp = fma(gu[r] - row_h(C, r), isc, sv[r]), zs = zv[r] * recip(sv[r]);
+    d[r] = zs * (isc * isc);
+    c[r] = zs * rp * isc;
   }
-  for (int e = lane_id(); e < N * NX; e += W64)
-    C.rq[e] = C.Q[e % NX] * (C.rx[NX + e] - (double)C.x_ref[e]);
+#pragma unroll
+  for (int a = 0; a < 6; ++a) t.v[a] = R[a] * (u[a] - (double)ur[a]);
+  rows_T(C, c, t.v);
+  t.m[0][0] = R[0] + (d[0] + d[1]);
+  t.m[1][1] = R[1] + (d[2] + d[3]);
+  t.m[2][2] = R[2] + fma(C.mu * C.mu, (d[0] + d[1]) + (d[2] + d[3]), d[4]);
+  t.m[0][1] = t.m[1][0] = 0.0;
+  t.m[0][2] = t.m[2][0] = -C.mu * (d[0] - d[1]);
+  t.m[1][2] = t.m[2][1] = -C.mu * (d[2] - d[3]);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) t.d[a] = R[3 + a] + (d[5 + a] + d[8 + a]);
+  store_block(T + (size_t)e * 18, t);
 }
 
-// The stage inputs of a recursion over stages 0..kn-1, visible to every lane.
+// The stage inputs of a recursion over stages 0..kn-1, visible to every lane
+// (a Newton step's are written by the interior point as it moves its iterate).
 template <Mode mode>
 __device__ inline void build(const Ctx& C, Sh& sh, int kn) {
   gsync();
-  if constexpr (mode == Mode::EQ) build_eq(C, sh.unit, kn);
-  else build_newton(C, sh.unit, kn);
-  gsync();
+  if constexpr (mode == Mode::EQ) {
+    build_eq(C, sh.Rd, sh.unit, kn);
+    gsync();
+  }
 }
 
 // ------------------------------------------------------ Riccati recursion
@@ -468,7 +544,7 @@ __device__ inline void eliminate(double (&col)[12], uint32_t unit) {
 // composes the closed-loop affine map TE (transposed, offset in row 13,
 // (13, 13) = 1) and the reachability term CE of the chunk.
 template <Mode mode, bool ELEM>
-__device__ __attribute__((always_inline)) inline d4 backward(const Ctx& C, ShR& sr,
+__device__ INLINE d4 backward(const Ctx& C, ShR& sr,
                                                              const uint8_t* unit, int k_lo,
                                                              int k_hi, d4 Ss, d4* TEo, d4* CEo) {
   const int lane = lane_id(), g = tg(), j = tj();
@@ -698,10 +774,10 @@ __device__ __attribute__((always_inline)) inline d4 backward(const Ctx& C, ShR& 
 // x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w = w to
 // rounding: the gains lie in the range of the projector.)  VECK: kap_k from GV
 // (a corrector's) instead of the stored gains.  Stage data is fetched a ring of
-// stages ahead (unconditionally, so every path back to the loop head has issued
+// six stages ahead, about 3000 cycles, as a trip to memory takes (unconditionally, so every path back to the loop head has issued
 // the same loads).
 template <Mode mode, bool LONG, bool VECK>
-__device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& sh) {
+__device__ INLINE void forward(const Ctx& C, Sh& sh) {
   gsync();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const int lane = lane_id(), g = tg(), j = tj();
@@ -723,13 +799,14 @@ __device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& 
   auto ffetch = [&](int k, FwdRaw& s) {
     ldd2(rK, oK, k * (TS_K * 8), s.k);
     ldd2(rK, oK + 16, k * (TS_K * 8), s.k + 2);
-    s.kap = VECK ? 0.0 : ldd(rK, oKap, k * (TS_K * 8));
+    if constexpr (VECK) s.kap = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
+    else s.kap = ldd(rK, oKap, k * (TS_K * 8));
     s.c = newton ? 0.0 : ldd(rT, oC, k * (TS_T * 8));
     ldf4(rA, oA, k * (NX * NX * 4), s.a);
     ldf3(rB, oB, k * (NX * NU * 4), s.b);
     s.e = newton ? 0.f : ldf(rE, oE, k * (NX * 4));
   };
-  constexpr int FD = 3;
+  constexpr int FD = 6;
   FwdRaw ring[FD];
 #pragma unroll
   for (int d = 0; d < FD; ++d) {
@@ -752,12 +829,10 @@ __device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& 
       b[q] = (double)r.b[q];
       pin(b[q]);
     }
-    double kap = r.kap;
-    const double cc = r.c, ee = (double)r.e;
+    const double kap = r.kap, cc = r.c, ee = (double)r.e;
     pin(kap); pin(cc); pin(ee);
     pin_memory();
     ffetch(k + FD < N ? k + FD : N - 1, r);
-    if constexpr (VECK) kap = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
     const double xt = turn_rows(xv);
     const double w = row_total(dot4(xt, km, kap));
     const double ax = dot4(xt, a, ee);
@@ -765,7 +840,7 @@ __device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& 
     if (lane < NU) sb.GV[k * 16 + j] = w;
     if (lane < NX) sb.PV[k * 16 + j] = xv;
   };
-  static_assert(FD == 3, "one line below per ring slot");
+  static_assert(FD == 6, "one line below per ring slot");
   for (int k = 0;; k += FD) {
     if (!(k < N)) break;
     step(k, ring[0]);
@@ -773,6 +848,12 @@ __device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& 
     step(k + 1, ring[1]);
     if (!(k + 2 < N)) break;
     step(k + 2, ring[2]);
+    if (!(k + 3 < N)) break;
+    step(k + 3, ring[3]);
+    if (!(k + 4 < N)) break;
+    step(k + 4, ring[4]);
+    if (!(k + 5 < N)) break;
+    step(k + 5, ring[5]);
   }
   bufsync<LONG>();
 }
@@ -780,7 +861,7 @@ __device__ __attribute__((always_inline)) inline void forward(const Ctx& C, Sh& 
 // The sequential recursion over the whole horizon (one wave), then the
 // rollout.
 template <Mode mode, bool LONG>
-__device__ __attribute__((noinline)) void riccati_t(const Ctx& C, Sh& sh, int ktop) {
+__device__ INLINE void riccati_t(const Ctx& C, Sh& sh, int ktop) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
   build<mode>(C, sh, ktop);
@@ -790,13 +871,13 @@ __device__ __attribute__((noinline)) void riccati_t(const Ctx& C, Sh& sh, int kt
   forward<mode, LONG, false>(C, sh);
 }
 
-// Second right-hand side of a Newton step with the stored factors: rho_k (in
-// GV) to kap_k (in GV).  With wv = q + s, hw = Bp^T wv + rho, the recursion of
-// the linear part is s <- A^T wv + K^T hw (Hwx^T kap = K^T hw), a chain; the
-// feedforwards kap = -H^{-1} hw then follow for all stages in parallel, four
-// stages at a time (one per 16-lane row), by the two triangular solves.
+// Second right-hand side of a Newton step with the stored factors: its linear
+// term rho_k = GV + smu PV to kap_k (in GV).  With wv = q + s, hw = Bp^T wv + rho,
+// the recursion of the linear part is s <- A^T wv + K^T hw (Hwx^T kap = K^T hw), a
+// chain; the feedforwards kap = -H^{-1} hw then follow for all stages in parallel,
+// four stages at a time (one per 16-lane row), by the two triangular solves.
 template <bool LONG>
-__device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
+__device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const int lane = lane_id(), g = tg(), j = tj();
   const StageBufs<LONG> sb(sh, C);
@@ -808,7 +889,7 @@ __device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
   const int oK = j < NX ? (3 * g * (NX + 1) + j) * 8 : OOB, oQ = j < NX ? j * 8 : OOB;
   struct VecRaw {
     float a[4], b[4];
-    double k[3], q;
+    double k[3], q, ra, rb;
   };
   auto vfetch = [&](int k, VecRaw& s) {
 #pragma unroll
@@ -819,8 +900,11 @@ __device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) s.k[q] = ldd(rK, oK + q * (NX + 1) * 8, k * (TS_K * 8));
     s.q = ldd(rQ, oQ, k * (NX * 8));
+    const bool on = g == 0 && j < NU;
+    s.ra = on ? sb.GV[k * 16 + j] : 0.0;
+    s.rb = on ? sb.PV[k * 16 + j] : 0.0;
   };
-  constexpr int VD = 3;
+  constexpr int VD = 6;
   VecRaw ring[VD];
 #pragma unroll
   for (int d = 0; d < VD; ++d) {
@@ -842,18 +926,18 @@ __device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
       km[q] = r.k[q];
       pin(km[q]);
     }
-    const double qk = r.q;
+    const double qk = r.q, rho = fma(smu, r.rb, r.ra);
     pin(qk);
+    pin(rho);
     pin_memory();
     vfetch(k - VD >= 0 ? k - VD : 0, r);
-    const double rho = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
     const double wt = turn_rows(qk + s);
     const double hw = row_total(dot4(wt, b, rho));
     const double aw = dot4(wt, a, 0.0);
     s = row_total(dot3(turn_rows(hw), km, aw));
     if (lane < NU) sb.GV[k * 16 + j] = hw;
   };
-  static_assert(VD == 3, "one line below per ring slot");
+  static_assert(VD == 6, "one line below per ring slot");
   for (int k = N - 1;; k -= VD) {
     if (!(k >= 0)) break;
     step(k, ring[0]);
@@ -861,19 +945,46 @@ __device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
     step(k - 1, ring[1]);
     if (!(k - 2 >= 0)) break;
     step(k - 2, ring[2]);
+    if (!(k - 3 >= 0)) break;
+    step(k - 3, ring[3]);
+    if (!(k - 4 >= 0)) break;
+    step(k - 4, ring[4]);
+    if (!(k - 5 >= 0)) break;
+    step(k - 5, ring[5]);
   }
   bufsync<LONG>();
   const int oF = j < NU ? (g * TS_F + j * NU) * 8 : OOB;
-  const int oD = j < NU ? (g * TS_F + j * (NU + 1)) * 8 : OOB;
-  for (int k0 = 0; k0 < N; k0 += 4) {
+  struct TriRaw {
+    double f[NU], rd, hw;
+  };
+  auto tfetch = [&](int k0, TriRaw& s) {
+    const int k = k0 + g;
+#pragma unroll
+    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8, k0 * (TS_F * 8), s.f + p);
+    s.rd = ldd(rF, oF + j * 8, k0 * (TS_F * 8));
+    s.hw = (j < NU && k < N) ? sb.GV[k * 16 + j] : 0.0;
+  };
+  constexpr int TD = 3;
+  TriRaw tri[TD];
+#pragma unroll
+  for (int d = 0; d < TD; ++d) {
+    tfetch(4 * d < N ? 4 * d : 0, tri[d]);
+    pin_memory();
+  }
+  auto solve = [&](int k0, TriRaw& r) __attribute__((always_inline)) {
     const int k = k0 + g;
     const bool on = j < NU && k < N;
-    double f[NU];
+    double f[NU], rd = r.rd, y = r.hw;
 #pragma unroll
-    for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8, k0 * (TS_F * 8), f + p);
-    const double rd = ldd(rF, oD, k0 * (TS_F * 8));
-    double y = 0.0;
-    if (on && C.contact[2 * k + j / 6]) y = sb.GV[k * 16 + j];
+    for (int p = 0; p < NU; ++p) {
+      f[p] = r.f[p];
+      pin(f[p]);
+    }
+    pin(rd);
+    pin(y);
+    pin_memory();
+    tfetch(k0 + 4 * TD < N ? k0 + 4 * TD : k0, r);
+    if (!on || sh.unit[2 * k + j / 6]) y = 0.0;   // a swing contact's inputs
     // y <- U^-T y, then D^-1, then U^-1
 #define PINMPC_TRI(p, use)                                                                      \
   {                                                                                             \
@@ -893,6 +1004,15 @@ __device__ __attribute__((noinline)) void newton_vector(const Ctx& C, Sh& sh) {
     PINMPC_TRI(3, j < 3) PINMPC_TRI(2, j < 2) PINMPC_TRI(1, j < 1)
 #undef PINMPC_TRI
     if (on) sb.GV[k * 16 + j] = -y;
+  };
+  static_assert(TD == 3, "one line below per ring slot");
+  for (int k0 = 0;; k0 += 4 * TD) {
+    if (!(k0 < N)) break;
+    solve(k0, tri[0]);
+    if (!(k0 + 4 < N)) break;
+    solve(k0 + 4, tri[1]);
+    if (!(k0 + 8 < N)) break;
+    solve(k0 + 8, tri[2]);
   }
   bufsync<LONG>();
 }
@@ -970,7 +1090,7 @@ __device__ inline double readlane_d(double v, int l) {
 // without pivoting: lane c < 13 holds column c of the matrix, lane 16 + c
 // column c of the identity; each pivot's column reaches every lane by lane
 // reads.  buf: 256 doubles of LDS.
-__device__ d4 inv13(const d4& M, double* buf) {
+__device__ INLINE d4 inv13(const d4& M, double* buf) {
   const int lane = lane_id(), g = tg(), j = tj();
 #pragma unroll
   for (int q = 0; q < 4; ++q) buf[(4 * q + g) * 16 + j] = M[q];
@@ -1009,7 +1129,7 @@ __device__ d4 inv13(const d4& M, double* buf) {
 
 // Value function [S_0 | s_0] at x_{k0} of a chunk with summary (TE, CE, SE)
 // for the value V = [S | s] at x_{k1}; om holds q_{k1-1} in column VC.
-__device__ d4 combine_value(const d4& TE, const d4& CE, const d4& SE, const d4& V, const d4& om,
+__device__ INLINE d4 combine_value(const d4& TE, const d4& CE, const d4& SE, const d4& V, const d4& om,
                             double Qj, double* buf) {
   const int g = tg(), j = tj();
   d4 J, eta, E13;
@@ -1052,7 +1172,7 @@ __device__ d4 combine_value(const d4& TE, const d4& CE, const d4& SE, const d4& 
 // wave; the helpers run scan_helper).  Falls back to the sequential recursion
 // when the horizon is too short to cut.
 template <Mode mode, bool LONG>
-__device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, int ktop) {
+__device__ INLINE void riccati_scan(const Ctx& C, Sh& sh, int ktop) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
   build<mode>(C, sh, ktop);
@@ -1107,7 +1227,7 @@ __device__ __attribute__((noinline)) void riccati_scan(const Ctx& C, Sh& sh, int
 
 // A helper wave of a scanning workgroup: summary and recursion of its chunk
 // for every scan command, until the first wave releases it.
-__device__ __attribute__((noinline)) void scan_helper(const Ctx& C, const uint8_t* unit) {
+__device__ INLINE void scan_helper(const Ctx& C, const uint8_t* unit) {
   const int wave = (int)(threadIdx.x >> 6), W = (int)(blockDim.x >> 6);
   const ScanLds L = scan_lds(W);
   ShR& sr = L.shr[wave - 1];
@@ -1148,9 +1268,9 @@ __device__ inline void scan_release() {
   if (lane_id() == 0) scan_ctl.op = SCAN_EXIT;
   __syncthreads();
 }
-template <Mode mode, bool LONG>
-__device__ inline void riccati(const Ctx& C, Sh& sh, int ktop) {
-  if (blockDim.x > W64) riccati_scan<mode, LONG>(C, sh, ktop);   // a scanning workgroup
+template <Mode mode, bool LONG, bool SCAN>
+__device__ INLINE void riccati(const Ctx& C, Sh& sh, int ktop) {
+  if constexpr (SCAN) riccati_scan<mode, LONG>(C, sh, ktop);
   else riccati_t<mode, LONG>(C, sh, ktop);
 }
 
@@ -1158,32 +1278,42 @@ __device__ inline void riccati(const Ctx& C, Sh& sh, int ktop) {
 // u = P w + c of the faces (closed form, exactly on each face), states, and what
 // the costates start from, Q (x_{k+1} - r_k) in PV and R (u_k - u_ref_k) in GV.
 template <bool LONG>
-__device__ __attribute__((always_inline)) inline void eq_point(const Ctx& C, Sh& sh) {
-  const int lane = lane_id(), N = C.N;
+__device__ INLINE void eq_point(const Ctx& C, Sh& sh) {
+  const int lane = lane_id(), N = __builtin_amdgcn_readfirstlane(C.N);
   const StageBufs<LONG> sb(sh, C);
+  const Scalars sc = scalars(C);
+  const Buf rR = uref_buf(C), rU = rsrc(uni(C.ru), N * NU * 8);
+  const auto ct = uni(C.contact);
+  const auto fc = uni(C.faces);
   for (int e = lane; e < N * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
-    double u[6] = {0, 0, 0, 0, 0, 0};
-    if (C.contact[e]) {
-      const int code = C.faces[e];
+    float ur[6];
+    const int code = fc[e];
+    const bool on = ct[e];
+    ldu6(rR, e, ur);
+    double u[6];
 #pragma unroll
-      for (int a = 0; a < 6; ++a) u[a] = sb.GV[k * 16 + 6 * i + a];
+    for (int a = 0; a < 6; ++a) u[a] = sb.GV[k * 16 + 6 * i + a];
+    pin_all(ur);
+    pin_all(u);
+    pin_memory();
+    if (on) {
       if (face_apex(code)) {
         u[0] = u[1] = u[2] = 0.0;
       } else {
         const ForceFace f = force_face(code);
-        const double m = C.mu;
+        const double m = sc.mu;
         if (f.top) {
-          if (f.sx != 0.0) u[0] = f.sx * m * C.fz;
-          if (f.sy != 0.0) u[1] = f.sy * m * C.fz;
-          u[2] = C.fz;
+          if (f.sx != 0.0) u[0] = f.sx * m * sc.fz;
+          if (f.sy != 0.0) u[1] = f.sy * m * sc.fz;
+          u[2] = sc.fz;
         } else if (f.sx != 0.0 && f.sy != 0.0) {
-          const double t = (m * (f.sx * u[0] + f.sy * u[1]) + u[2]) * C.i2;
+          const double t = (m * (f.sx * u[0] + f.sy * u[1]) + u[2]) * sc.i2;
           u[0] = f.sx * m * t;
           u[1] = f.sy * m * t;
           u[2] = t;
         } else if (f.sx != 0.0 || f.sy != 0.0) {
-          const double t = (f.sx * u[0] + f.sy * u[1] - m * u[2]) * C.i1;
+          const double t = (f.sx * u[0] + f.sy * u[1] - m * u[2]) * sc.i1;
           u[0] -= f.sx * t;
           u[1] -= f.sy * t;
           u[2] += m * t;
@@ -1191,25 +1321,39 @@ __device__ __attribute__((always_inline)) inline void eq_point(const Ctx& C, Sh&
       }
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        if (code >> (8 + a) & 1) u[3 + a] = C.tm;
-        else if (code >> (11 + a) & 1) u[3 + a] = -C.tm;
+        if (code >> (8 + a) & 1) u[3 + a] = sc.tm;
+        else if (code >> (11 + a) & 1) u[3 + a] = -sc.tm;
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < 6; ++a) u[a] = 0.0;
+    }
+    st6(rU, e, u);
+#pragma unroll
+    for (int a = 0; a < 6; ++a)
+      sb.GV[k * 16 + 6 * i + a] = sh.Rd[6 * i + a] * (u[a] - (double)ur[a]);
+  }
+  const Buf rX = rsrc(uni(C.x_ref), N * NX * 4);
+  const gd px = uni(C.rx);
+  for (int e0 = lane; e0 < N * NX; e0 += 8 * W64) {
+    double x[8], xr[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * W64, ec = e < N * NX ? e : e0;
+      xr[t] = (double)ldf(rX, e * 4, 0);
+      x[t] = sb.PV[(ec / NX) * 16 + ec % NX];
+    }
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * W64;
+      if (e < N * NX) {
+        px[NX + e] = x[t];
+        sb.PV[(e / NX) * 16 + e % NX] = sh.Qd[e % NX] * (x[t] - xr[t]);
       }
     }
-#pragma unroll
-    for (int a = 0; a < 6; ++a) {
-      const int jj = 6 * i + a;
-      const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
-      C.ru[k * NU + jj] = u[a];
-      sb.GV[k * 16 + jj] = C.R[jj] * (u[a] - ur);
-    }
   }
-  for (int e = lane; e < N * NX; e += W64) {
-    const int k = e / NX, i = e % NX;
-    const double x = sb.PV[k * 16 + i];
-    C.rx[NX + e] = x;
-    sb.PV[k * 16 + i] = C.Q[i] * (x - (double)C.x_ref[e]);
-  }
-  if (lane < NX) C.rx[lane] = (double)C.x0[lane];
+  if (lane < NX) px[lane] = (double)uni(C.x0)[lane];
   bufsync<LONG>();
 }
 
@@ -1234,21 +1378,26 @@ __device__ inline void load_point(const Ctx& C, Sh& sh) {
 // the stage buffers.  Returns the state-side magnitude max |Q (x_{k+1} - r_k)|,
 // |p|, |A^T p| over all stages, which the KKT scaling needs.
 template <bool LONG>
-__device__ __attribute__((always_inline)) inline double costates_grad(const Ctx& C, Sh& sh) {
+__device__ INLINE double costates_grad(const Ctx& C, Sh& sh) {
   const StageBufs<LONG> sb(sh, C);
   const int lane = lane_id(), g = tg(), j = tj();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
   const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
   // stage k needs A_{k+1}; at k = N - 1 the clamped stage multiplies p_{N+1} = 0
-  auto cfetch = [&](int k, float (&s)[4]) {
-    const int at = clampi(k + 1, N - 1) * (NX * NX * 4);
-    s[0] = ldf(rA, oA0, at);
-#pragma unroll
-    for (int q = 1; q < 4; ++q) s[q] = ldf(rA, oA + q * NX * 4, at);
+  struct CosRaw {
+    float a[4];
+    double q;
   };
-  constexpr int CD = 6;
-  float ring[CD][4];
+  auto cfetch = [&](int k, CosRaw& s) {
+    const int at = clampi(k + 1, N - 1) * (NX * NX * 4);
+    s.a[0] = ldf(rA, oA0, at);
+#pragma unroll
+    for (int q = 1; q < 4; ++q) s.a[q] = ldf(rA, oA + q * NX * 4, at);
+    s.q = j < NX ? sb.PV[k * 16 + j] : 0.0;
+  };
+  constexpr int CD = 12;
+  CosRaw ring[CD];
 #pragma unroll
   for (int d = 0; d < CD; ++d) {
     cfetch(N - 1 - d >= 0 ? N - 1 - d : 0, ring[d]);
@@ -1256,22 +1405,23 @@ __device__ __attribute__((always_inline)) inline double costates_grad(const Ctx&
   }
   double p = 0.0;   // p_{k+2}, entry j
   double tstate = 0.0;
-  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+  auto step = [&](int k, CosRaw& r) __attribute__((always_inline)) {
     double a[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      a[q] = (double)r[q];
+      a[q] = (double)r.a[q];
       pin(a[q]);
     }
+    const double qx = r.q;
+    pin(qx);
     pin_memory();
     cfetch(k - CD >= 0 ? k - CD : 0, r);
-    const double qx = j < NX ? sb.PV[k * 16 + j] : 0.0;
     const double ap = row_total(dot4(turn_rows(p), a, 0.0));
     p = qx + ap;
     tstate = fmax(tstate, fmax(fabs(qx), fmax(fabs(p), fabs(ap))));
     if (lane < NX) sb.PV[k * 16 + j] = p;
   };
-  static_assert(CD == 6, "one line below per ring slot");
+  static_assert(CD == 12, "one line below per ring slot");
   for (int k = N - 1;; k -= CD) {
     if (!(k >= 0)) break;
     step(k, ring[0]);
@@ -1285,6 +1435,18 @@ __device__ __attribute__((always_inline)) inline double costates_grad(const Ctx&
     step(k - 4, ring[4]);
     if (!(k - 5 >= 0)) break;
     step(k - 5, ring[5]);
+    if (!(k - 6 >= 0)) break;
+    step(k - 6, ring[6]);
+    if (!(k - 7 >= 0)) break;
+    step(k - 7, ring[7]);
+    if (!(k - 8 >= 0)) break;
+    step(k - 8, ring[8]);
+    if (!(k - 9 >= 0)) break;
+    step(k - 9, ring[9]);
+    if (!(k - 10 >= 0)) break;
+    step(k - 10, ring[10]);
+    if (!(k - 11 >= 0)) break;
+    step(k - 11, ring[11]);
   }
   bufsync<LONG>();
   const int oB = j < NU ? (g * NX * NU + j) * 4 : OOB;
@@ -1292,23 +1454,39 @@ __device__ __attribute__((always_inline)) inline double costates_grad(const Ctx&
 #pragma unroll
     for (int r = 0; r < NX; ++r) s[r] = ldf(rB, oB + r * NU * 4, k0 * (NX * NU * 4));
   };
-  float bn[NX];
-  bfetch(0, bn);
-  for (int k0 = 0; k0 < N; k0 += 4) {
+  constexpr int GD = 4;
+  float br[GD][NX];
+#pragma unroll
+  for (int d = 0; d < GD; ++d) {
+    bfetch(4 * d < N ? 4 * d : 0, br[d]);
+    pin_memory();
+  }
+  auto grad = [&](int k0, float (&r)[NX]) __attribute__((always_inline)) {
     const int k = k0 + g;
     double b[NX];
 #pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      b[r] = (double)bn[r];
-      pin(b[r]);
+    for (int l = 0; l < NX; ++l) {
+      b[l] = (double)r[l];
+      pin(b[l]);
     }
     pin_memory();
-    bfetch(k0 + 4 < N ? k0 + 4 : k0, bn);
+    bfetch(k0 + 4 * GD < N ? k0 + 4 * GD : k0, r);
     const bool on = j < NU && k < N;
     const double pk = (j < NX && k < N) ? sb.PV[k * 16 + j] : 0.0;
     const double ru = on ? sb.GV[k * 16 + j] : 0.0;
     const double gk = dot_row_bcast13(pk, b, ru);
     if (on) sb.GV[k * 16 + j] = gk;
+  };
+  static_assert(GD == 4, "one line below per ring slot");
+  for (int k0 = 0;; k0 += 4 * GD) {
+    if (!(k0 < N)) break;
+    grad(k0, br[0]);
+    if (!(k0 + 4 < N)) break;
+    grad(k0 + 4, br[1]);
+    if (!(k0 + 8 < N)) break;
+    grad(k0 + 8, br[2]);
+    if (!(k0 + 12 < N)) break;
+    grad(k0 + 12, br[3]);
   }
   bufsync<LONG>();
   return wave_max(tstate);
@@ -1317,7 +1495,7 @@ __device__ __attribute__((always_inline)) inline double costates_grad(const Ctx&
 // x = rollout of ru from x0, in FP64, into rx: the stage terms B u + e for four
 // stages at a time, then the chain.
 template <bool LONG>
-__device__ __attribute__((noinline)) void rollout_ru(const Ctx& C, Sh& sh) {
+__device__ INLINE void rollout_ru(const Ctx& C, Sh& sh) {
   gsync();
   const StageBufs<LONG> sb(sh, C);
   const int lane = lane_id(), g = tg(), j = tj();
@@ -1340,28 +1518,37 @@ __device__ __attribute__((noinline)) void rollout_ru(const Ctx& C, Sh& sh) {
   }
   bufsync<LONG>();
   const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB;
-  constexpr int RD = 6;
-  float ring[RD][4];
+  struct RollRaw {
+    float a[4];
+    double t;
+  };
+  auto rfetch = [&](int k, RollRaw& s) {
+    ldf4(rA, oA, k * (NX * NX * 4), s.a);
+    s.t = j < NX ? sb.PV[k * 16 + j] : 0.0;
+  };
+  constexpr int RD = 12;
+  RollRaw ring[RD];
 #pragma unroll
   for (int d = 0; d < RD; ++d) {
-    ldf4(rA, oA, (d < N ? d : N - 1) * (NX * NX * 4), ring[d]);
+    rfetch(d < N ? d : N - 1, ring[d]);
     pin_memory();
   }
   double xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;
-  auto step = [&](int k, float (&r)[4]) __attribute__((always_inline)) {
+  auto step = [&](int k, RollRaw& r) __attribute__((always_inline)) {
     double a[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      a[q] = (q == 0 && g) ? 0.0 : (double)r[q];
+      a[q] = (q == 0 && g) ? 0.0 : (double)r.a[q];
       pin(a[q]);
     }
+    const double t = r.t;
+    pin(t);
     pin_memory();
-    ldf4(rA, oA, (k + RD < N ? k + RD : N - 1) * (NX * NX * 4), r);
-    const double t = j < NX ? sb.PV[k * 16 + j] : 0.0;
+    rfetch(k + RD < N ? k + RD : N - 1, r);
     xv = row_total(dot4(turn_rows(xv), a, 0.0)) + t;
     if (lane < NX) sb.PV[k * 16 + j] = xv;
   };
-  static_assert(RD == 6, "one line below per ring slot");
+  static_assert(RD == 12, "one line below per ring slot");
   for (int k = 0;; k += RD) {
     if (!(k < N)) break;
     step(k, ring[0]);
@@ -1375,43 +1562,23 @@ __device__ __attribute__((noinline)) void rollout_ru(const Ctx& C, Sh& sh) {
     step(k + 4, ring[4]);
     if (!(k + 5 < N)) break;
     step(k + 5, ring[5]);
+    if (!(k + 6 < N)) break;
+    step(k + 6, ring[6]);
+    if (!(k + 7 < N)) break;
+    step(k + 7, ring[7]);
+    if (!(k + 8 < N)) break;
+    step(k + 8, ring[8]);
+    if (!(k + 9 < N)) break;
+    step(k + 9, ring[9]);
+    if (!(k + 10 < N)) break;
+    step(k + 10, ring[10]);
+    if (!(k + 11 < N)) break;
+    step(k + 11, ring[11]);
   }
   bufsync<LONG>();
   if (lane < NX) C.rx[lane] = (double)C.x0[lane];
   for (int e = lane; e < N * NX; e += W64) C.rx[NX + e] = sb.PV[(e / NX) * 16 + e % NX];
   gsync();
-}
-
-// Row data of one stance contact-stage (k, i) in registers: a lane owns a
-// contact-stage and its 11 rows, so each row pass over the horizon issues its
-// loads together and stores once (no store-then-load chains between rows).
-__device__ inline void load_u6(gcd v, int k, int i, double x[6]) {
-#pragma unroll
-  for (int a = 0; a < 6; ++a) x[a] = v[k * NU + 6 * i + a];
-}
-// (a row's entries for consecutive contact-stages e are consecutive in memory,
-// rs = 2 n_max apart per row: the lanes of a pass load and store whole lines)
-__device__ inline void load_r(gcd v, int rs, int e, double x[NROW]) {
-#pragma unroll
-  for (int r = 0; r < NROW; ++r) x[r] = v[r * rs + e];
-}
-__device__ inline void store_r(gd v, int rs, int e, const double x[NROW]) {
-#pragma unroll
-  for (int r = 0; r < NROW; ++r) v[r * rs + e] = x[r];
-}
-// g_r u, h_r and the inverse row scale of the contact's 11 rows
-__device__ inline void rows_of(const Ctx& C, const double u[6], double gu[NROW], double hh[NROW],
-                               double isc[NROW]) {
-#pragma unroll
-  for (int r = 0; r < NROW; ++r) {
-    double g[6];
-    wrench_row(r, C.mu, C.fz, C.tm, g, &hh[r]);
-    double acc = 0.0;
-#pragma unroll
-    for (int a = 0; a < 6; ++a) acc += g[a] * u[a];
-    gu[r] = acc;
-    isc[r] = (r < 5) ? C.img : C.itm;
-  }
 }
 
 // Order-independent hash term of contact-stage e's face code.
@@ -1430,38 +1597,48 @@ struct FaceUpdate {
 
 // Row multipliers of each stance contact from its face and the gradient, and
 // the normalised KKT residuals of the current (u, x, p, mu).  Returns KKT.
-// With upd, also the primal-dual active-set update of the faces (row active iff
+// With update, also the primal-dual active-set update of the faces (row active iff
 // mu_r s_r + (G_r u - h_r) > 0): the multipliers it needs are in registers here.
 // The force multipliers solve G_A^T mu_A = -g_f on the face's rows (least
 // squares); the Gram systems of the eight faces that are not the apex are solved
 // in closed form (see face_affine).
 template <bool LONG>
-__device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh,
-                                                           double res[PINMPC_NRES],
-                                                           double term_state, FaceUpdate* upd) {
+__device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC_NRES],
+                                 double term_state, bool update, FaceUpdate* upd) {
   const StageBufs<LONG> sb(sh, C);
   const int lane = lane_id();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const Scalars sc = scalars(C);
+  const Buf rR = uref_buf(C), rU = rsrc(uni(C.ru), N * NU * 8);
+  const auto ct = uni(C.contact);
+  const auto fc = uni(C.faces);
   double r_ineq = 0.0, stat = 0.0, term = term_state, comp = 0.0, mumax = 0.0, neg = 0.0;
   uint64_t hsh = 0;
   int kch = 0;
-  for (int e = lane; e < C.N * 2; e += W64) {
+  for (int e = lane; e < N * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
     // the contact-stage's inputs, gradient and multipliers in registers
     double u[6], g[6], mu[NROW];
-    load_u6(C.ru, k, i, u);
-    const int code = C.faces[e];
-    int fresh = 0;
-    if (!C.contact[e]) {
-      for (int a = 0; a < 6; ++a) r_ineq = fmax(r_ineq, fabs(u[a]) * C.img);
-    } else {
+    float ur[6];
+    const int code = fc[e];
+    const bool on = ct[e];
+    ld6(rU, e, u);
+    ldu6(rR, e, ur);
 #pragma unroll
-      for (int a = 0; a < 6; ++a) g[a] = sb.GV[k * 16 + 6 * i + a];
+    for (int a = 0; a < 6; ++a) g[a] = sb.GV[k * 16 + 6 * i + a];
+    pin_all(u);
+    pin_all(ur);
+    pin_all(g);
+    pin_memory();
+    int fresh = 0;
+    if (!on) {
+      for (int a = 0; a < 6; ++a) r_ineq = fmax(r_ineq, fabs(u[a]) * sc.img);
+    } else {
 #pragma unroll
       for (int r = 0; r < NROW; ++r) mu[r] = 0.0;
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
-        const double ur = C.u_ref ? (double)C.u_ref[k * NU + 6 * i + a] : 0.0;
-        const double ru = C.R[6 * i + a] * (u[a] - ur);
+        const double ru = sh.Rd[6 * i + a] * (u[a] - (double)ur[a]);
         term = fmax(term, fmax(fabs(ru), fabs(g[a] - ru)));
       }
       if (face_apex(code)) {
@@ -1472,7 +1649,7 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh
         // S = -b_z / mu the three-row systems are
         //   mu0 - mu1 = b_x,  mu2 - mu3 = b_y,  mu0 + mu1 + mu2 + mu3 = S
         // with the dropped multiplier zero, solved in closed form
-        const double bx = -g[0], by = -g[1], S = g[2] / C.mu;
+        const double bx = -g[0], by = -g[1], S = g[2] / sc.mu;
         double cand[4][4];
         cand[0][0] = 0.0;                    cand[0][1] = -bx;
         cand[0][2] = 0.5 * (S + bx + by);    cand[0][3] = 0.5 * (S + bx - by);
@@ -1504,7 +1681,7 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh
         }
       } else {
         const ForceFace f = force_face(code);
-        const double m = C.mu;
+        const double m = sc.mu;
         double mx, my, mt = 0.0;
         if (f.top) {
           // the bound fixes f_z: each side row alone holds its component
@@ -1515,7 +1692,7 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh
           const double rx = f.sx != 0.0 ? m * g[2] - f.sx * g[0] : 0.0;
           const double ry = f.sy != 0.0 ? m * g[2] - f.sy * g[1] : 0.0;
           const bool two = f.sx != 0.0 && f.sy != 0.0;
-          const double w = two ? C.i2 : C.i1, d = two ? m * m * (rx - ry) : 0.0;
+          const double w = two ? sc.i2 : sc.i1, d = two ? m * m * (rx - ry) : 0.0;
           mx = (rx + d) * w;
           my = (ry - d) * w;
         }
@@ -1531,43 +1708,34 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh
         else if (code >> (11 + a) & 1) mu[8 + a] = g[3 + a];
       }
       // residual pieces, and the updated face
-      double gm[6] = {0, 0, 0, 0, 0, 0};
+      double gu[NROW], gm[6] = {0, 0, 0, 0, 0, 0};
+      rows_of(sc, u, gu);
+      rows_T(sc, mu, gm);
 #pragma unroll
       for (int r = 0; r < NROW; ++r) {
-        double gg[6], hh;
-        wrench_row(r, C.mu, C.fz, C.tm, gg, &hh);
-        double gu = 0.0;
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-          gu += gg[a] * u[a];
-          gm[a] += gg[a] * mu[r];
-        }
-        r_ineq = fmax(r_ineq, fmax(0.0, gu - hh) * C.img);
-        comp = fmax(comp, mu[r] * fmax(0.0, hh - gu));
+        const double d = gu[r] - row_h(sc, r);
+        r_ineq = fmax(r_ineq, fmax(0.0, d) * sc.img);
+        comp = fmax(comp, mu[r] * fmax(0.0, -d));
         mumax = fmax(mumax, mu[r]);
         neg = fmax(neg, -mu[r]);
-        const double sc = (r < 5) ? C.mg : C.tm;
-        if (mu[r] * sc + (gu - hh) > 0.0) fresh |= (r < 5) ? (1 << r) : (1 << (8 + (r - 5)));
+        if (fma(mu[r], row_scale(sc, r), d) > 0.0) fresh |= row_bit(r);
       }
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
         term = fmax(term, fabs(gm[a]));
         stat = fmax(stat, fabs(g[a] + gm[a]));
       }
-      if (face_apex(fresh)) fresh = (fresh & ~31) | FACE_APEX;
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        if ((fresh >> (8 + a) & 1) && (fresh >> (11 + a) & 1)) fresh &= ~(1 << (11 + a));
+      fresh = settle_face(fresh);
     }
-    if (upd) {
+    if (update) {
       if (code != fresh) {
         kch = k + 1;
-        C.faces[e] = fresh;
+        fc[e] = fresh;
       }
       hsh ^= face_hash(fresh, e);
     }
   }
-  if (upd) {
+  if (update) {
     upd->ktop = wave_max_int(kch);
     upd->hash = wave_xor(hsh);
   }
@@ -1582,102 +1750,137 @@ __device__ __attribute__((noinline)) double multipliers_kkt(const Ctx& C, Sh& sh
   res[0] = 0.0;   // r_dyn: filled by the caller from the rollout
   res[1] = r_ineq;
   res[2] = stat / (1.0 + term);
-  res[3] = comp / (1.0 + mumax * C.mg);
+  res[3] = comp / (1.0 + mumax * sc.mg);
   res[4] = fmax(0.0, neg) / (1.0 + term);
   double kkt = 0.0;
   for (int i = 1; i < PINMPC_NRES; ++i) kkt = fmax(kkt, res[i]);
   return kkt;
 }
 
-// Dynamics residual of the FP64 trajectory (rx, ru).
-__device__ __attribute__((noinline)) double dyn_residual(const Ctx& C) {
+// Dynamics residual of the FP64 trajectory (rx, ru), four stages at a time (one
+// per 16-lane row, state j in lane j).
+__device__ INLINE double dyn_residual(const Ctx& C) {
   gsync();
-  const int lane = lane_id();
-  double r = 0.0;
-  for (int e = lane; e < C.N * NX; e += W64) {
-    const int k = e / NX, i = e % NX;
-    gcd x = C.rx + k * NX;
-    gcd u = C.ru + k * NU;
-    gcf A = C.A + k * NX * NX + i * NX;
-    gcf B = C.B + k * NX * NU + i * NU;
-    double ax = 0.0, bu = 0.0;
+  const int g = tg(), j = tj();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
+  const auto rU = rsrc(uni(C.ru), N * NU * 8), rX = rsrc(uni(C.rx), (N + 1) * NX * 8);
+  const int oA = j < NX ? (g * NX + j) * NX * 4 : OOB, oB = j < NX ? (g * NX + j) * NU * 4 : OOB;
+  const int oX = j < NX ? (g * NX + j) * 8 : OOB, oU = j < NU ? (g * NU + j) * 8 : OOB;
+  const int oE = j < NX ? (g * NX + j) * 4 : OOB;
+  struct DynRaw {
+    float a[NX], b[NU], e;
+    double x, xn, u;
+  };
+  auto fetch = [&](int k0, DynRaw& s) {
 #pragma unroll
-    for (int l = 0; l < NX; ++l) ax += (double)A[l] * x[l];
+    for (int l = 0; l < NU; l += 4) {
+      ldf4(rA, oA + l * 4, k0 * (NX * NX * 4), s.a + l);
+      ldf4(rB, oB + l * 4, k0 * (NX * NU * 4), s.b + l);
+    }
+    s.a[NU] = ldf(rA, oA + NU * 4, k0 * (NX * NX * 4));
+    s.e = ldf(rE, oE, k0 * (NX * 4));
+    s.x = ldd(rX, oX, k0 * (NX * 8));
+    s.xn = ldd(rX, oX + NX * 8, k0 * (NX * 8));
+    s.u = ldd(rU, oU, k0 * (NU * 8));
+  };
+  constexpr int DD = 3;
+  DynRaw ring[DD];
 #pragma unroll
-    for (int l = 0; l < NU; ++l) bu += (double)B[l] * u[l];
-    const double ee = C.e ? (double)C.e[k * NX + i] : 0.0;
-    const double d = x[NX + i] - ax - bu - ee;
-    const double den = 1.0 + fmax(fabs(x[NX + i]), fmax(fabs(ax), fabs(bu)));
-    r = fmax(r, fabs(d) / den);
+  for (int d = 0; d < DD; ++d) {
+    fetch(4 * d < N ? 4 * d : 0, ring[d]);
+    pin_memory();
   }
-  return wave_max(r);
+  double res = 0.0;
+  auto step = [&](int k0, DynRaw& r) __attribute__((always_inline)) {
+    double a[NX], b[NX];
+#pragma unroll
+    for (int l = 0; l < NX; ++l) {
+      a[l] = (double)r.a[l];
+      b[l] = l < NU ? (double)r.b[l < NU ? l : 0] : 0.0;
+      pin(a[l]);
+      pin(b[l]);
+    }
+    const double x = r.x, xn = r.xn, u = r.u, ee = (double)r.e;
+    pin(x); pin(xn); pin(u); pin(ee);
+    pin_memory();
+    fetch(k0 + 4 * DD < N ? k0 + 4 * DD : k0, r);
+    const double ax = dot_row_bcast13(x, a, 0.0), bu = dot_row_bcast13(u, b, 0.0);
+    const double d = xn - ax - bu - ee;
+    const double den = 1.0 + fmax(fabs(xn), fmax(fabs(ax), fabs(bu)));
+    if (j < NX && k0 + g < N) res = fmax(res, fabs(d) / den);
+  };
+  static_assert(DD == 3, "one line below per ring slot");
+  for (int k0 = 0;; k0 += 4 * DD) {
+    if (!(k0 < N)) break;
+    step(k0, ring[0]);
+    if (!(k0 + 4 < N)) break;
+    step(k0 + 4, ring[1]);
+    if (!(k0 + 8 < N)) break;
+    step(k0 + 8, ring[2]);
+  }
+  return wave_max(res);
 }
 
 // Faces from slack: rows whose slack is below tol * row scale.
-__device__ __attribute__((noinline)) void faces_from_u(const Ctx& C, gcd u_src, double tol) {
+__device__ INLINE void faces_from_u(const Ctx& C, double tol) {
   gsync();
-  const int lane = lane_id();
-  for (int e = lane; e < C.N * 2; e += W64) {
-    const int k = e >> 1, i = e & 1;
-    const int st = k;
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const Scalars sc = scalars(C);
+  const Buf rU = rsrc(uni(C.ru), N * NU * 8);
+  for (int e = lane_id(); e < N * 2; e += W64) {
+    double u[6], gu[NROW];
+    const bool on = uni(C.contact)[e];
+    ld6(rU, e, u);
+    rows_of(sc, u, gu);
     int code = 0;
-    if (C.contact[st * 2 + i]) {
-      gcd u = u_src + st * NU + 6 * i;
-      for (int r = 0; r < NROW; ++r) {
-        double gg[6], hh;
-        wrench_row(r, C.mu, C.fz, C.tm, gg, &hh);
-        double gu = 0.0;
-        for (int a = 0; a < 6; ++a) gu += gg[a] * u[a];
-        const double sc = (r < 5) ? C.mg : C.tm;
-        if ((hh - gu) / sc <= tol) code |= (r < 5) ? (1 << r) : (1 << (8 + (r - 5)));
-      }
-      if (face_apex(code)) code = (code & ~31) | FACE_APEX;
-    }
-    C.faces[st * 2 + i] = code;
-  }
-  wsync();
-}
-
-// One active-set pass: equality-constrained solve on the current faces,
-// costates, multipliers and residuals.  `ktop` < N: the faces of stages
-// ktop..N-1 are those of the previous equality-constrained solve, whose tiles
-// and factors are still in the scratch block.
-// The pass's x is the FP64 rollout of its u, so its dynamics residual is
-// rounding only: it is checked once, on the final trajectory, by the caller.
-template <bool LONG>
-__device__ __attribute__((noinline)) double eq_pass(const Ctx& C, Sh& sh, double res[PINMPC_NRES],
-                                                   int ktop, FaceUpdate* upd) {
-  riccati<Mode::EQ, LONG>(C, sh, ktop);
-  eq_point<LONG>(C, sh);
-  const double ts = costates_grad<LONG>(C, sh);
-  return multipliers_kkt<LONG>(C, sh, res, ts, upd);
-}
-
-// Faces from the interior-point iterate (row active where z > s); returns an
-// order-independent hash of the face set.
-__device__ __attribute__((noinline)) uint64_t faces_from_zs(const Ctx& C) {
-  gsync();
-  const int lane = lane_id();
-  uint64_t hsh = 0;
-  for (int e = lane; e < C.N * 2; e += W64) {
-    const int k = e >> 1, i = e & 1;
-    int code = 0;
-    if (C.contact[k * 2 + i]) {
-      double zv[NROW], sv[NROW];
-      load_r(C.rz, 2 * C.n, e, zv);
-      load_r(C.rs, 2 * C.n, e, sv);
 #pragma unroll
-      for (int r = 0; r < NROW; ++r)
-        if (zv[r] > sv[r]) code |= (r < 5) ? (1 << r) : (1 << (8 + (r - 5)));
-      if (face_apex(code)) code = (code & ~31) | FACE_APEX;
-      for (int a = 0; a < 3; ++a)
-        if ((code >> (8 + a) & 1) && (code >> (11 + a) & 1)) code &= ~(1 << (11 + a));
-    }
-    C.faces[k * 2 + i] = code;
-    hsh ^= face_hash(code, e);
+    for (int r = 0; r < NROW; ++r)
+      if ((row_h(sc, r) - gu[r]) / row_scale(sc, r) <= tol) code |= row_bit(r);
+    if (face_apex(code)) code = (code & ~31) | FACE_APEX;
+    uni(C.faces)[e] = on ? code : 0;
   }
   wsync();
-  return wave_xor(hsh);
+}
+
+// One active-set pass: equality-constrained solve on the current faces (`solve`;
+// else the point in memory is taken as it is), costates, multipliers and
+// residuals.  `ktop` < N: the faces of stages ktop..N-1 are those of the previous
+// equality-constrained solve, whose tiles and factors are still in the scratch
+// block.  The pass's x is the FP64 rollout of its u, so its dynamics residual is
+// rounding only: it is checked once, on the final trajectory, by the caller.
+template <bool LONG, bool SCAN>
+__device__ INLINE double eq_pass(const Ctx& C, Sh& sh, double res[PINMPC_NRES], bool solve,
+                                 int ktop, bool update, FaceUpdate* upd) {
+  if (solve) {
+    riccati<Mode::EQ, LONG, SCAN>(C, sh, ktop);
+    eq_point<LONG>(C, sh);
+  } else {
+    load_point<LONG>(C, sh);
+  }
+  const double ts = costates_grad<LONG>(C, sh);
+  return multipliers_kkt<LONG>(C, sh, res, ts, update, upd);
+}
+
+// Faces of the interior point's iterate: row active iff z > s.
+__device__ INLINE void faces_from_zs(const Ctx& C) {
+  gsync();
+  const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
+  const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
+  for (int e = lane_id(); e < N * 2; e += W64) {
+    double zv[NROW], sv[NROW];
+    const bool on = uni(C.contact)[e];
+    load_r(rZ, step, e, zv);
+    load_r(rS, step, e, sv);
+    int code = 0;
+#pragma unroll
+    for (int r = 0; r < NROW; ++r)
+      if (zv[r] > sv[r]) code |= row_bit(r);
+    uni(C.faces)[e] = on ? settle_face(code) : 0;
+  }
+  wsync();
 }
 
 // Work done by the refinement of one problem: equality-constrained passes
@@ -1696,268 +1899,365 @@ struct Counts {
 constexpr int SIGMA_FROM = 40;
 constexpr double SIGMA_MIN = 0.05;
 
+// The input blocks and pivot masks of every contact-stage from the iterate
+// (u, s, z) in memory: the identity and zero for a swing contact.
+__device__ INLINE void newton_blocks(const Ctx& C, Sh& sh) {
+  gsync();
+  const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
+  const Scalars sc = scalars(C);
+  const Buf rU = rsrc(uni(C.ru), N * NU * 8), rR = uref_buf(C);
+  const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
+  const gd pT = uni(C.rT);
+  for (int e = lane_id(); e < N * 2; e += W64) {
+    double u[6], sv[NROW], zv[NROW];
+    float ur[6];
+    const bool on = uni(C.contact)[e];
+    ld6(rU, e, u);
+    ldu6(rR, e, ur);
+    load_r(rS, step, e, sv);
+    load_r(rZ, step, e, zv);
+    pin_all(u);
+    pin_all(ur);
+    pin_all(sv);
+    pin_all(zv);
+    pin_memory();
+    sh.unit[e] = on ? 0 : 0x3F;
+    if (on) {
+      newton_block(sc, sh.Rd + 6 * (e & 1), pT, e, u, ur, sv, zv);
+    } else {
+      InputBlock t;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        t.d[a] = 1.0;
+        t.v[a] = t.v[3 + a] = 0.0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) t.m[a][b] = a == b ? 1.0 : 0.0;
+      }
+      store_block(pT + (size_t)e * 18, t);
+    }
+  }
+}
+
+// A contact-stage's iterate and step, in the registers of the lane that owns it.
+struct RowState {
+  double u[6], s[NROW], z[NROW], ds[NROW], dz[NROW];
+  float ur[6];
+};
+
 // Interior-point fallback.  Rows scaled by mg (force rows) and tau_max
 // (moment rows).  Crossover: once the face guess z > s is the same after two
 // consecutive iterations, one equality-constrained pass on those faces is
-// tried (the iterate is kept aside and restored if it does not certify).
-// Returns the number of iterations; *certified tells whether a crossover pass
-// certified (then ru, rx, res and *kkt are that pass's), else the faces from
-// z > s are left for the polish passes.
+// tried (the iterate is kept aside and restored if it does not certify).  ipm_run
+// iterates until it wants such a pass (true: the iterate is kept aside) or is
+// done (false: the faces from z > s are left for the polish passes).
+//
+// Besides the recursions an iteration passes three times over its rows, one lane
+// per contact-stage: the predictor's steps and the corrector's linear term, the
+// corrector's steps, and the move to the new iterate with its faces and its next
+// input blocks.  The few problems that come here leave the chip nearly empty
+// (about 430 waves on its 1024 SIMDs with 4096 problems of 20 stages), so a pass
+// costs its latency: the trip to memory, the reciprocals and the reductions.
+// Ratios therefore share the reciprocal of a product and are reduced as one
+// maximum of step over distance, and the last two passes keep a contact-stage's
+// rows in registers while every lane has only one.
+struct IpmState {
+  int it;
+  uint64_t hprev;
+  double m, smz, rpn;   // stance rows; this lane's share of s z, largest row residual
+};
 template <bool LONG>
-__device__ __attribute__((noinline)) int ipm(const Ctx& C, Sh& sh, int maxit, double tol, Counts* cnt,
-                   double res[PINMPC_NRES], double* kkt_out, bool* certified) {
-  *certified = false;
+__device__ INLINE void ipm_start(const Ctx& C, Sh& sh, IpmState& st) {
   gsync();
   const int lane = lane_id();
-  const int N = C.N;
+  const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
+  const auto ct = uni(C.contact);
   // number of stance rows
   int mloc = 0;
   for (int e = lane; e < N * 2; e += W64)
-    if (C.contact[(e >> 1) * 2 + (e & 1)]) mloc += NROW;
-  const double m = wave_sum((double)mloc);
-  if (m == 0.0) return 0;
-  const gd rc = C.rrc;   // complementarity target of the corrector
-  const StageBufs<LONG> sb(sh, C);
+    if (ct[e]) mloc += NROW;
+  st = {0, 0, wave_sum((double)mloc), 0.0, 0.0};
   // initial point: the current ru (the ADMM point) and its rollout in rx,
   // slacks at least 1, multipliers 1 (a start from the last active-set pass,
   // its slacks and multipliers floored at 1e-1 .. 1e-3, took as long or
   // longer: the early steps near the boundary are short); and the residuals
   // of that point
-  double smz = 0.0, rpn = 0.0;
-  const int rs = 2 * C.n;   // stride of a row over the contact-stages
-  for (int e = lane; e < N * 2; e += W64) {
-    const int k = e >> 1, i = e & 1;
-    if (!C.contact[e]) continue;
-    double u[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW];
-    load_u6(C.ru, k, i, u);
-    rows_of(C, u, gu, hh, isc);
-#pragma unroll
-    for (int r = 0; r < NROW; ++r) {
-      sv[r] = fmax((hh[r] - gu[r]) * isc[r], 1.0);
-      zv[r] = 1.0;
-      rpn = fmax(rpn, fabs(fma(gu[r] - hh[r], isc[r], sv[r])));
-      smz += sv[r] * zv[r];
-    }
-    store_r(C.rs, rs, e, sv);
-    store_r(C.rz, rs, e, zv);
-  }
-  int it = 0;
-  uint64_t hprev = 0;
-  for (; it < maxit; ++it) {
-    const double sz = wave_sum(smz), muv = sz / m;
-    rpn = wave_max(rpn);
-    if (muv <= 1e-10 && rpn <= 1e-9) break;
-    // predictor (affine target s z)
-    riccati<Mode::NEWTON, LONG>(C, sh, N);
-    // its row steps, the largest step to the boundary, and the sums that give
-    // the complementarity after any step: s z + a (s dz + z ds) + a^2 ds dz
-    double amax_s = 1.0, amax_z = 1.0, sm1 = 0.0, sm2 = 0.0;
+  {
+    const Scalars sc = scalars(C);
+    const Buf rU = rsrc(uni(C.ru), N * NU * 8), rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
     for (int e = lane; e < N * 2; e += W64) {
-      const int k = e >> 1, i = e & 1;
-      if (!C.contact[e]) continue;
-      double u[6], du[6], gu[NROW], gdu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW];
-      load_u6(C.ru, k, i, u);
-#pragma unroll
-      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
-      load_r(C.rs, rs, e, sv);
-      load_r(C.rz, rs, e, zv);
-      rows_of(C, u, gu, hh, isc);
-      rows_of(C, du, gdu, hh, isc);
-      double cv[NROW];
+      double u[6], gu[NROW], sv[NROW], zv[NROW];
+      const bool on = ct[e];
+      ld6(rU, e, u);
+      rows_of(sc, u, gu);
 #pragma unroll
       for (int r = 0; r < NROW; ++r) {
-        const double rp = fma(gu[r] - hh[r], isc[r], sv[r]);
-        const double ds = -fma(gdu[r], isc[r], rp);
-        const double dz = -(zv[r] + zv[r] * ds * recip(sv[r]));
-        if (ds < 0) amax_s = fmin(amax_s, -sv[r] * recip(ds));
-        if (dz < 0) amax_z = fmin(amax_z, -zv[r] * recip(dz));
-        sm1 += sv[r] * dz + zv[r] * ds;
-        sm2 += ds * dz;
-        cv[r] = fma(ds, dz, sv[r] * zv[r]);   // corrector target, less sigma mu
+        const double d = gu[r] - row_h(sc, r), isc = row_isc(sc, r);
+        sv[r] = fmax(-d * isc, 1.0);
+        zv[r] = 1.0;
+        if (on) {
+          st.rpn = fmax(st.rpn, fabs(fma(d, isc, sv[r])));
+          st.smz += sv[r] * zv[r];
+        }
       }
-      store_r(rc, rs, e, cv);
+      store_r(rS, step, e, sv);
+      store_r(rZ, step, e, zv);
     }
-    const double aa = fmin(wave_min(amax_s), wave_min(amax_z));
-    const double mu_aff = fmax(fma(aa, fma(aa, wave_sum(sm2), wave_sum(sm1)), sz), 0.0) / m;
-    const double ratio = mu_aff / muv, cube = ratio * ratio * ratio,
-                 smu = (it < SIGMA_FROM ? cube : fmax(cube, SIGMA_MIN)) * muv;
-    // corrector target s z + ds_aff dz_aff - sigma mu: its linear term per input
-    // into the stage buffers, then the recursion's vector part and the rollout
-    // with the predictor's factors
+  }
+  {
+    const Buf rX = rsrc(uni(C.rx), (N + 1) * NX * 8), rXr = rsrc(uni(C.x_ref), N * NX * 4);
+    const gd pq = uni(C.rq);
+    for (int e0 = lane; e0 < N * NX; e0 += 4 * W64) {
+      double x[4], xr[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        x[t] = ldd(rX, (NX + e0 + t * W64) * 8, 0);
+        xr[t] = (double)ldf(rXr, (e0 + t * W64) * 4, 0);
+      }
+      pin_memory();
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int e = e0 + t * W64;
+        if (e < N * NX) pq[e] = sh.Qd[e % NX] * (x[t] - xr[t]);
+      }
+    }
+  }
+}
+template <bool LONG, bool SCAN>
+__device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
+  if (st.m == 0.0) return false;
+  const int lane = lane_id();
+  const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
+  const auto ct = uni(C.contact);
+  const StageBufs<LONG> sb(sh, C);
+  const bool one_each = 2 * N <= W64;   // every lane owns at most one contact-stage
+  newton_blocks(C, sh);   // (an equality pass leaves its own blocks)
+  for (; st.it < maxit; ++st.it) {
+    const int it = st.it;
+    const double sz = wave_sum(st.smz), muv = sz / st.m;
+    if (scalar(muv <= 1e-10 && wave_max(st.rpn) <= 1e-9)) break;
+    // predictor (affine target s z)
+    riccati<Mode::NEWTON, LONG, SCAN>(C, sh, N);
+    const Scalars sc = scalars(C);
+    const Buf rU = rsrc(uni(C.ru), N * NU * 8), rR = uref_buf(C);
+    const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
+    const Buf rC = row_buf(C, C.rrc);   // complementarity target, less sigma mu
+    // its row steps; the largest step to the boundary, as 1 / max(1, step over
+    // distance); the sums that give the complementarity after any step,
+    // s z + a (s dz + z ds) + a^2 ds dz; and the corrector's linear term per
+    // input for the target s z + ds dz - sigma mu, whose part in sigma mu goes
+    // to PV and the rest to GV
+    double over = 1.0, sm1 = 0.0, sm2 = 0.0;
     for (int e = lane; e < N * 2; e += W64) {
       const int k = e >> 1, i = e & 1;
-      double rho[6] = {0, 0, 0, 0, 0, 0};
-      if (C.contact[e]) {
-        double u[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
-        load_u6(C.ru, k, i, u);
-        load_r(C.rs, rs, e, sv);
-        load_r(C.rz, rs, e, zv);
-        load_r(rc, rs, e, cv);
-        rows_of(C, u, gu, hh, isc);
+      double u[6], du[6], sv[NROW], zv[NROW];
+      float ur[6];
+      const bool on = ct[e];
+      ld6(rU, e, u);
+      ldu6(rR, e, ur);
+      load_r(rS, step, e, sv);
+      load_r(rZ, step, e, zv);
 #pragma unroll
-        for (int r = 0; r < NROW; ++r) cv[r] -= smu;
-        store_r(rc, rs, e, cv);
+      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
+      pin_all(u);
+      pin_all(ur);
+      pin_all(sv);
+      pin_all(zv);
+      pin_all(du);
+      pin_memory();
+      double ra[6] = {0, 0, 0, 0, 0, 0}, rb[6] = {0, 0, 0, 0, 0, 0};
+      if (on) {
+        double gu[NROW], gdu[NROW], cv[NROW], ca[NROW], cb[NROW];
 #pragma unroll
-        for (int a = 0; a < 6; ++a) {
-          const int jj = 6 * i + a;
-          const double ur = C.u_ref ? (double)C.u_ref[k * NU + jj] : 0.0;
-          rho[a] = C.R[jj] * (u[a] - ur);
-        }
+        for (int t = 0; t < 6; ++t) ra[t] = sh.Rd[6 * i + t] * (u[t] - (double)ur[t]);
+        rows_of(sc, u, gu);
+        rows_of(sc, du, gdu);
 #pragma unroll
         for (int r = 0; r < NROW; ++r) {
-          const double rp = fma(gu[r] - hh[r], isc[r], sv[r]);
-          const double cr = (zv[r] + (zv[r] * rp - cv[r]) * recip(sv[r])) * isc[r];
-          double g[6], h;
-          wrench_row(r, C.mu, C.fz, C.tm, g, &h);
-#pragma unroll
-          for (int a = 0; a < 6; ++a) rho[a] += g[a] * cr;
+          const double isc = row_isc(sc, r), is = recip(sv[r]);
+          const double rp = fma(gu[r] - row_h(sc, r), isc, sv[r]);
+          const double ds = -fma(gdu[r], isc, rp);
+          const double t = ds * is, dz = -fma(zv[r], t, zv[r]);
+          over = fmax(over, fmax(-t, 1.0 + t));
+          sm1 += sv[r] * dz + zv[r] * ds;
+          sm2 += ds * dz;
+          cv[r] = fma(ds, dz, sv[r] * zv[r]);
+          ca[r] = fma(fma(zv[r], rp, -cv[r]), is, zv[r]) * isc;
+          cb[r] = is * isc;
         }
+        store_r(rC, step, e, cv);
+        rows_T(sc, ca, ra);
+        rows_T(sc, cb, rb);
       }
-#pragma unroll
-      for (int a = 0; a < 6; ++a) sb.GV[k * 16 + 6 * i + a] = rho[a];
-    }
-    bufsync<LONG>();
-    newton_vector<LONG>(C, sh);
-    forward<Mode::NEWTON, LONG, true>(C, sh);
-    amax_s = 1.0;
-    amax_z = 1.0;
-    for (int e = lane; e < N * 2; e += W64) {
-      const int k = e >> 1, i = e & 1;
-      if (!C.contact[e]) continue;
-      double u[6], du[6], gu[NROW], gdu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
-      load_u6(C.ru, k, i, u);
-#pragma unroll
-      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
-      load_r(C.rs, rs, e, sv);
-      load_r(C.rz, rs, e, zv);
-      load_r(rc, rs, e, cv);
-      rows_of(C, u, gu, hh, isc);
-      rows_of(C, du, gdu, hh, isc);
-      double dsv[NROW], dzv[NROW];
-#pragma unroll
-      for (int r = 0; r < NROW; ++r) {
-        const double rp = fma(gu[r] - hh[r], isc[r], sv[r]);
-        dsv[r] = -fma(gdu[r], isc[r], rp);
-        dzv[r] = -fma(zv[r], dsv[r], cv[r]) * recip(sv[r]);
-        if (dsv[r] < 0) amax_s = fmin(amax_s, -sv[r] * recip(dsv[r]));
-        if (dzv[r] < 0) amax_z = fmin(amax_z, -zv[r] * recip(dzv[r]));
-      }
-      store_r(C.rds, rs, e, dsv);
-      store_r(C.rdz, rs, e, dzv);
-    }
-    const double a = fmin(1.0, 0.99 * fmin(wave_min(amax_s), wave_min(amax_z)));
-    // step, and the residuals and affine target of the new point; a lane
-    // updates the inputs of its own contact-stage (swing inputs stay 0)
-    smz = 0.0;
-    rpn = 0.0;
-    for (int e = lane; e < N * 2; e += W64) {
-      const int k = e >> 1, i = e & 1;
-      if (!C.contact[e]) continue;
-      double u[6], du[6], gu[NROW], hh[NROW], isc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW];
-      load_u6(C.ru, k, i, u);
-#pragma unroll
-      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
-      load_r(C.rs, rs, e, sv);
-      load_r(C.rz, rs, e, zv);
-      load_r(C.rds, rs, e, dsv);
-      load_r(C.rdz, rs, e, dzv);
 #pragma unroll
       for (int t = 0; t < 6; ++t) {
-        u[t] += a * du[t];
-        C.ru[k * NU + 6 * i + t] = u[t];
+        sb.GV[k * 16 + 6 * i + t] = ra[t];
+        sb.PV[k * 16 + 6 * i + t] = rb[t];
       }
-      rows_of(C, u, gu, hh, isc);
+    }
+    const double aa = recip(wave_max(over));
+    const double mu_aff = fmax(fma(aa, fma(aa, wave_sum(sm2), wave_sum(sm1)), sz), 0.0) / st.m;
+    const double ratio = mu_aff / muv, cube = ratio * ratio * ratio,
+                 smu = (it < SIGMA_FROM ? cube : fmax(cube, SIGMA_MIN)) * muv;
+    // corrector: the recursion's vector part and the rollout with the
+    // predictor's factors
+    bufsync<LONG>();
+    newton_vector<LONG>(C, sh, smu);
+    forward<Mode::NEWTON, LONG, true>(C, sh);
+    // its row steps, and the largest step over distance
+    over = 1.0;
+    auto row_steps = [&](int e, bool on, RowState& w) __attribute__((always_inline)) {
+      const int k = e >> 1, i = e & 1;
+      double du[6], gu[NROW], gdu[NROW], cv[NROW];
+      ld6(rU, e, w.u);
+      ldu6(rR, e, w.ur);
+      load_r(rS, step, e, w.s);
+      load_r(rZ, step, e, w.z);
+      load_r(rC, step, e, cv);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) du[t] = sb.GV[k * 16 + 6 * i + t];
+      rows_of(sc, w.u, gu);
+      rows_of(sc, du, gdu);
 #pragma unroll
       for (int r = 0; r < NROW; ++r) {
-        sv[r] += a * dsv[r];
-        zv[r] += a * dzv[r];
-        rpn = fmax(rpn, fabs(fma(gu[r] - hh[r], isc[r], sv[r])));
-        smz += sv[r] * zv[r];
+        const double isc = row_isc(sc, r);
+        const double rp = fma(gu[r] - row_h(sc, r), isc, w.s[r]);
+        const double isz = recip(w.s[r] * w.z[r]), is = w.z[r] * isz, iz = w.s[r] * isz;
+        w.ds[r] = -fma(gdu[r], isc, rp);
+        w.dz[r] = -fma(w.z[r], w.ds[r], cv[r] - smu) * is;
+        if (on) over = fmax(over, fmax(-w.ds[r] * is, -w.dz[r] * iz));
       }
-      store_r(C.rs, rs, e, sv);
-      store_r(C.rz, rs, e, zv);
-    }
-    // states (x_0 is fixed): loads of a group first, then its stores
-    for (int e0 = lane; e0 < N * NX; e0 += 4 * W64) {
-      double xv[4];
+    };
+    // the step, the residuals and affine target of the new point, its face guess
+    // and its input block; a lane moves its own contact-stage (swing inputs stay 0)
+    uint64_t hsh = 0;
+    double smz = 0.0, rpn = 0.0;
+    const gd pT = uni(C.rT);
+    const auto fc = uni(C.faces);
+    auto advance = [&](int e, RowState& w, double a) __attribute__((always_inline)) {
+      const int k = e >> 1, i = e & 1;
+      double gu[NROW];
+      int code = 0;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int e = e0 + t * W64;
-        xv[t] = (e < N * NX) ? C.rx[NX + e] : 0.0;
-      }
+      for (int t = 0; t < 6; ++t) w.u[t] += a * sb.GV[k * 16 + 6 * i + t];
+      st6(rU, e, w.u);
+      rows_of(sc, w.u, gu);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int e = e0 + t * W64;
-        if (e < N * NX) C.rx[NX + e] = xv[t] + a * sb.PV[(e / NX) * 16 + e % NX];
+      for (int r = 0; r < NROW; ++r) {
+        w.s[r] += a * w.ds[r];
+        w.z[r] += a * w.dz[r];
+        rpn = fmax(rpn, fabs(fma(gu[r] - row_h(sc, r), row_isc(sc, r), w.s[r])));
+        smz += w.s[r] * w.z[r];
+        if (w.z[r] > w.s[r]) code |= row_bit(r);
+      }
+      store_r(rS, step, e, w.s);
+      store_r(rZ, step, e, w.z);
+      code = settle_face(code);
+      fc[e] = code;
+      hsh ^= face_hash(code, e);
+      newton_block(sc, sh.Rd + 6 * i, pT, e, w.u, w.ur, w.s, w.z);
+    };
+    double a;
+    if (one_each) {
+      RowState w;
+      const int e = lane < 2 * N ? lane : 2 * N - 1;   // surplus lanes repeat the last's loads
+      const bool on = ct[e] && lane < 2 * N;
+      row_steps(e, on, w);
+      a = 0.99 * recip(wave_max(over));
+      if (on) advance(e, w, a);
+    } else {
+      const Buf rDs = row_buf(C, C.rds), rDz = row_buf(C, C.rdz);
+      for (int e = lane; e < N * 2; e += W64) {
+        RowState w;
+        row_steps(e, ct[e], w);
+        store_r(rDs, step, e, w.ds);
+        store_r(rDz, step, e, w.dz);
+      }
+      a = 0.99 * recip(wave_max(over));
+      for (int e = lane; e < N * 2; e += W64) {
+        RowState w;
+        const bool on = ct[e];
+        ld6(rU, e, w.u);
+        ldu6(rR, e, w.ur);
+        load_r(rS, step, e, w.s);
+        load_r(rZ, step, e, w.z);
+        load_r(rDs, step, e, w.ds);
+        load_r(rDz, step, e, w.dz);
+        pin_all(w.u);
+        pin_all(w.ur);
+        pin_all(w.s);
+        pin_all(w.z);
+        pin_all(w.ds);
+        pin_all(w.dz);
+        pin_memory();
+        if (on) advance(e, w, a);
       }
     }
-    wsync();
-    const uint64_t h = faces_from_zs(C);
-    if (it >= 1 && h == hprev) {
+    // states (x_0 is fixed) and their cost gradients: loads of a group first,
+    // then its stores
+    {
+      const Buf rX = rsrc(uni(C.rx), (N + 1) * NX * 8), rXr = rsrc(uni(C.x_ref), N * NX * 4);
+      const gd px = uni(C.rx), pq = uni(C.rq);
+      for (int e0 = lane; e0 < N * NX; e0 += 8 * W64) {
+        double x[8], xr[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int e = e0 + t * W64, ec = e < N * NX ? e : e0;
+          x[t] = ldd(rX, (NX + e) * 8, 0);
+          xr[t] = (double)ldf(rXr, e * 4, 0);
+          x[t] += a * sb.PV[(ec / NX) * 16 + ec % NX];
+        }
+        pin_memory();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int e = e0 + t * W64;
+          if (e < N * NX) {
+            px[NX + e] = x[t];
+            pq[e] = sh.Qd[e % NX] * (x[t] - xr[t]);
+          }
+        }
+      }
+    }
+    st.smz = smz;
+    st.rpn = rpn;
+    const uint64_t h = wave_xor(hsh);
+    const bool cross = scalar(it >= 1 && h == st.hprev);
+    st.hprev = h;
+    if (cross) {
       // the step buffers are free between iterations: keep the iterate there
+      ++st.it;
       gsync();
-      for (int e = lane; e < N * NU; e += W64) C.rdu[e] = C.ru[e];
-      for (int e = lane; e < (N + 1) * NX; e += W64) C.rdx[e] = C.rx[e];
-      const double kkt = eq_pass<LONG>(C, sh, res, N, nullptr);
-      ++cnt->eq;
-      cnt->stf += N;
-      if (kkt <= tol) {
-        *kkt_out = kkt;
-        *certified = true;
-        return it + 1;
-      }
-      gsync();
-      for (int e = lane; e < N * NU; e += W64) C.ru[e] = C.rdu[e];
-      for (int e = lane; e < (N + 1) * NX; e += W64) C.rx[e] = C.rdx[e];
-      wsync();
+      copy_doubles(uni(C.rdu), C.ru, N * NU);
+      copy_doubles(uni(C.rdx), C.rx, (N + 1) * NX);
+      return true;
     }
-    hprev = h;
   }
   faces_from_zs(C);
-  return it;
-}
-
-// Active-set loop; returns true if certified.  cnt accumulates.
-template <bool LONG>
-__device__ bool active_set_loop(const Ctx& C, Sh& sh, int maxp, double tol, Counts* cnt,
-                                double res[PINMPC_NRES], double* kkt_out,
-                                bool* cycled = nullptr) {
-  if (cycled) *cycled = false;
-  uint64_t hist[8];
-  for (int i = 0; i < 8; ++i) hist[i] = 0;
-  int nh = 0;
-  int ktop = C.N;   // the first pass solves the whole horizon
-  for (int it = 0; it < maxp; ++it) {
-    FaceUpdate upd;
-    const double kkt = eq_pass<LONG>(C, sh, res, ktop, &upd);
-    ++cnt->eq;
-    cnt->stf += ktop < C.N ? ktop : C.N;
-    *kkt_out = kkt;
-    if (kkt <= tol) return true;
-    const uint64_t h = upd.hash;
-    ktop = upd.ktop;
-    bool seen = false;
-    for (int i = 0; i < 8; ++i) seen |= (hist[i] == h) && (i < nh || nh >= 8);
-    if (seen) {
-      if (cycled) *cycled = true;
-      return false;
-    }
-    hist[nh & 7] = h;
-    ++nh;
-  }
   return false;
 }
 
 // The ADMM's input iterate, unscaled, into ru (swing inputs exactly 0).
-__device__ __attribute__((noinline)) void admm_point(const Ctx& C, gcf zsrc, gcf sf, float tsc) {
+__device__ INLINE void admm_point(const Ctx& C, gcf zsrc, gcf sf, float tsc) {
   gsync();
-  const int lane = lane_id();
-  for (int e = lane; e < C.N * NU; e += W64) {
-    const int k = e / NU, j = e % NU;
-    const double sc = (j % 6 < 3) ? (double)sf[k] : (double)tsc;
-    double v = (double)zsrc[((size_t)k * NSTATE) * NL + NX + j] * sc;
-    if (!C.contact[k * 2 + j / 6]) v = 0.0;
-    C.ru[k * NU + j] = v;
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const auto ct = uni(C.contact);
+  const gd pu = uni(C.ru);
+  for (int e0 = lane_id(); e0 < N * NU; e0 += 4 * W64) {
+    float z[4], f[4];
+    int on[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int e = e0 + t * W64, ec = e < N * NU ? e : e0, k = ec / NU, j = ec % NU;
+      z[t] = zsrc[(k * NSTATE) * NL + NX + j];
+      f[t] = sf[k];
+      on[t] = ct[k * 2 + j / 6];
+    }
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int e = e0 + t * W64, j = e % NU;
+      const double sc = (j % 6 < 3) ? (double)f[t] : (double)tsc;
+      if (e < N * NU) pu[e] = on[t] ? (double)z[t] * sc : 0.0;
+    }
   }
   wsync();
 }
@@ -1967,6 +2267,19 @@ __device__ __attribute__((noinline)) void admm_point(const Ctx& C, gcf zsrc, gcf
 // to PHASE 2, which runs the interior point and the polish passes for the
 // listed problems only (surplus blocks exit).  The slow problems thus start
 // together instead of behind a second round of easy ones.
+// The doubles of a buffer as floats, zero past its end.
+__device__ inline void put_floats(float* out, Buf r, int count) {
+  for (int e0 = lane_id(); e0 < count; e0 += 8 * W64) {
+    double v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = ldd(r, (e0 + t * W64) * 8, 0);
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (e0 + t * W64 < count) out[e0 + t * W64] = (float)v[t];
+  }
+}
+
 // The first wave releases a scanning workgroup's helpers on every way out.
 template <bool SCAN>
 struct ScanRelease {
@@ -2098,65 +2411,98 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
   const float tsc = ws.tsc[C.b];
   if (PHASE == 1) admm_point(C, zsrc, sf, tsc);
 
+  // Passes until one certifies, the face set repeats or their number is spent;
+  // then (second launch) the interior point with its crossover passes, then polish
+  // passes again.  One loop, so that the pass is in the kernel once.  The first
+  // launch takes pass_1 passes (all pass_a when pass_1 is 0) and leaves the rest to
+  // the second.  Without refinement the ADMM point is evaluated as it is: rollout,
+  // faces from slack, residuals.
   double res[PINMPC_NRES] = {0, 0, 0, 0, 0};
-  double kkt = 1e300;
   Counts cnt = {0, 0, 0};
-  bool ok = false;
-  if (refine) {
-    // first launch: pass_1 passes (all pass_a when pass_1 is 0); the rest of
-    // the passes, the interior point and the polish in the second launch
-    const int p1 = (pass_1 > 0 && pass_1 < pass_a) ? pass_1 : pass_a;
-    if (PHASE == 1) {
-      faces_from_u(C, C.ru, 1e-5);
-      bool cycled = false;
-      ok = active_set_loop<LONG>(C, sh, p1, tol, &cnt, res, &kkt, &cycled);
-      const bool more = !cycled && p1 < pass_a;
-      if (!ok && (more || ipm_max > 0)) {
-        if (lane == 0) {
-          const int slot = atomicAdd(ws.rcount, 1);
-          ws.rlist[slot] = C.b;
-          // passes (< 2^10, settings are capped at 1000) and stages factored
-          // (< 2^20) so far, and whether active-set passes remain
-          ws.rpass[C.b] = cnt.eq | (cnt.stf << 10) | (more ? (1 << 30) : 0);
-        }
-        return;
-      }
-    } else {
-      const int rp = ws.rpass[C.b];
-      cnt.eq = rp & 1023;
-      cnt.stf = (rp >> 10) & ((1 << 20) - 1);
-      if ((rp >> 30) & 1) {
-        // resume the active-set passes from the faces the first launch left
-        ok = active_set_loop<LONG>(C, sh, pass_a - cnt.eq, tol, &cnt, res, &kkt);
-      }
-      if (!ok && ipm_max > 0) {
+  bool ok = false, cycled = false;
+  enum { PASSES, INTERIOR, POLISH } part = PASSES;
+  const int p1 = (pass_1 > 0 && pass_1 < pass_a) ? pass_1 : pass_a;
+  int left = refine ? p1 : 1;
+  if (PHASE == 1) {
+    faces_from_u(C, 1e-5);
+    if (!refine) rollout_ru<LONG>(C, sh);
+  } else {
+    // resume from the faces the first launch left
+    const int rp = __builtin_amdgcn_readfirstlane(ws.rpass[C.b]);
+    cnt.eq = rp & 1023;
+    cnt.stf = (rp >> 10) & ((1 << 20) - 1);
+    left = ((rp >> 30) & 1) ? pass_a - cnt.eq : 0;
+  }
+  IpmState ist = {0, 0, 0.0, 0.0, 0.0};
+  uint64_t hist[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // the last face sets
+  int nh = 0, ktop = N;   // the first pass solves the whole horizon
+  for (;;) {
+    bool cross = false;
+    if constexpr (PHASE == 2) {
+      if (part == PASSES && (left <= 0 || cycled)) {
+        if (ipm_max <= 0) break;
         // interior point from the ADMM point
         admm_point(C, zsrc, sf, tsc);
         rollout_ru<LONG>(C, sh);
-        cnt.ipm = ipm<LONG>(C, sh, ipm_max, tol, &cnt, res, &kkt, &ok);
-        if (!ok) ok = active_set_loop<LONG>(C, sh, pass_c, tol, &cnt, res, &kkt);
+        ipm_start<LONG>(C, sh, ist);
+        part = INTERIOR;
+      }
+      if (part == INTERIOR) {
+        cross = ipm_run<LONG, SCAN>(C, sh, ist, ipm_max);
+        if (!cross) {
+          part = POLISH;
+          left = pass_c;
+          cycled = false;
+          nh = 0;
+          ktop = N;
+        }
       }
     }
-    // the dynamics residual of the returned trajectory, checked independently
-    // of the rollout that produced it
-    res[0] = dyn_residual(C);
-    ok = ok && res[0] <= tol;
-  } else {
-    // the ADMM point as it is: rollout, faces from slack, residuals
-    faces_from_u(C, C.ru, 1e-5);
-    rollout_ru<LONG>(C, sh);
-    load_point<LONG>(C, sh);
-    const double ts = costates_grad<LONG>(C, sh);
-    kkt = multipliers_kkt<LONG>(C, sh, res, ts, nullptr);
-    res[0] = dyn_residual(C);
+    if (!cross && (left <= 0 || cycled)) break;
+    FaceUpdate upd;
+    const bool update = refine && !cross;
+    const int kt = cross || ktop > N ? N : ktop;
+    const double kkt = eq_pass<LONG, SCAN>(C, sh, res, PHASE == 2 || refine, kt, update, &upd);
+    if (PHASE == 1 && !refine) break;
+    ++cnt.eq;
+    cnt.stf += kt;
+    ok = scalar(kkt <= tol);
+    if (ok) break;
+    if (cross) {
+      gsync();
+      copy_doubles(uni(C.ru), C.rdu, N * NU);
+      copy_doubles(uni(C.rx), C.rdx, (N + 1) * NX);
+      continue;
+    }
+    ktop = __builtin_amdgcn_readfirstlane(upd.ktop);
+    for (int i = 0; i < 8; ++i) cycled |= hist[i] == upd.hash && (i < nh || nh >= 8);
+    cycled = scalar(cycled);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if ((nh & 7) == i) hist[i] = upd.hash;
+    ++nh;
+    --left;
   }
+  cnt.ipm = ist.it;
+  if (PHASE == 1 && refine && !ok && (ipm_max > 0 || (!cycled && p1 < pass_a))) {
+    if (lane == 0) {
+      const int slot = atomicAdd(ws.rcount, 1);
+      ws.rlist[slot] = C.b;
+      // passes (< 2^10, settings are capped at 1000) and stages factored
+      // (< 2^20) so far, and whether active-set passes remain
+      ws.rpass[C.b] = cnt.eq | (cnt.stf << 10) | (!cycled && p1 < pass_a ? (1 << 30) : 0);
+    }
+    return;
+  }
+  // the dynamics residual of the returned trajectory, checked independently
+  // of the rollout that produced it
+  res[0] = dyn_residual(C);
+  ok = ok && res[0] <= tol;
 
   // outputs
   gsync();
-  for (int e = lane; e < C.n * NU; e += W64)
-    out_u[ux + e] = (e < N * NU) ? (float)C.ru[e] : 0.f;
-  for (int e = lane; e < (C.n + 1) * NX; e += W64)
-    out_x[xx + e] = (e < (N + 1) * NX) ? (float)C.rx[e] : 0.f;
+  put_floats(out_u + ux, rsrc(uni(C.ru), N * NU * 8), C.n * NU);
+  put_floats(out_x + xx, rsrc(uni(C.rx), (N + 1) * NX * 8), (C.n + 1) * NX);
   if (lane == 0) {
     // the solve's refinement work (stages of every pass and iteration)
     atomicAdd(ws.work, (unsigned long long)(cnt.eq + cnt.ipm) * (unsigned long long)N);

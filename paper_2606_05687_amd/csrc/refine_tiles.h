@@ -24,26 +24,23 @@ typedef GMEM double* gd;
 // The refinement runs one 64-lane wave per workgroup.  LDS operations of a
 // wave execute in issue order, so handing data between the lanes of the wave
 // through LDS needs only a point the compiler does not move memory accesses
-// across (wsync).  Global memory written by one lane and read by another needs
-// the workgroup barrier with its memory fence (gsync); it is used where one
-// phase's global outputs feed the next phase, not inside the stage loops.
+// across (wsync).  gsync is used where one phase's global outputs feed the next
+// phase, not inside the stage loops.
 __device__ inline void wsync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-// With the associative scan of the backward recursion a problem's workgroup
-// holds several waves; the first runs the refinement and the others join it
-// only at the scan's own barriers.  There, the hand-off between lanes of the
-// first wave needs the fence alone (the waves of a workgroup share the CU's
-// caches), never the workgroup barrier.
+// Global memory written by one lane and read by another: the fence at workgroup
+// scope (it waits for the stores; the waves of a workgroup share the CU's caches).
+// No barrier: with the associative scan of the backward recursion a problem's
+// workgroup holds several waves, the others join the first only at the scan's own
+// barriers.
 __device__ inline void gsync() {
-  if (blockDim.x == W64) {
-    __syncthreads();
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_wave_barrier();
 }
+// A condition that is the same in every lane, for a scalar branch.
+__device__ inline bool scalar(bool c) { return __builtin_amdgcn_readfirstlane((int)c) != 0; }
 // lane within the wave (the workgroup may hold several waves)
 __device__ inline int lane_id() { return (int)(threadIdx.x & 63); }
 
@@ -196,6 +193,13 @@ __device__ inline T uni(T p) {
   return (T)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ inline double uni(double d) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, d);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 typedef unsigned int u3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 constexpr int OOB = 0x40000000;   // an offset past the end of every array
@@ -228,6 +232,12 @@ __device__ inline void std1(__amdgpu_buffer_rsrc_t r, int off, int soff, double 
   u2 w;
   __builtin_memcpy(&w, &v, 8);
   __builtin_amdgcn_raw_buffer_store_b64(w, r, off, soff, 0);
+}
+__device__ inline void std2(__amdgpu_buffer_rsrc_t r, int off, int soff, double a, double b) {
+  u4 w;
+  __builtin_memcpy(&w, &a, 8);
+  __builtin_memcpy((char*)&w + 8, &b, 8);
+  __builtin_amdgcn_raw_buffer_store_b128(w, r, off, soff, 0);
 }
 
 // Byte offset of tile entry (r, c) in an input block T, or OOB.
