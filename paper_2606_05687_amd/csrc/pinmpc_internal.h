@@ -157,6 +157,8 @@ struct Workspace {
 //   T2   equality passes: P R P + I - P and P R (c - u_ref) in the same layout
 //   K    gains and feedforward [K | kap], 12 x 14 row-major
 //   F    factors of the input Hessian, 12 x 12 (interior-point steps)
+//   M    closed loop [A + B K | B kap] of an interior-point step, 13 x 14
+//        row-major, over T2 and the padding
 //   S    value function: lower triangle of S (13 x 13, row by row), then s
 // Then per stage: inputs (12), state cost gradients (13), slacks, multipliers,
 // their steps and the complementarity target of the interior point (5 x 22),
@@ -169,10 +171,12 @@ struct Workspace {
 constexpr int TS_T = 2 * 18;
 constexpr int TS_K = NU * (NX + 1);
 constexpr int TS_F = NU * NU;
+constexpr int TS_M = NX * (NX + 1);
 constexpr int TS_S = NX * (NX + 1) / 2 + NX;
 constexpr int TS_STAGE = 815;
 constexpr int TS_PAD = TS_STAGE - (2 * TS_T + TS_K + TS_F + TS_S + NU + NX + 5 * 2 * NROW + NU);
 static_assert(TS_PAD >= 0, "the stage's arrays fit its share of the block");
+static_assert(TS_M <= TS_T + TS_PAD, "M's room");
 __host__ __device__ constexpr size_t refine_block_doubles(int n) {
   return (((size_t)n * TS_STAGE + 2 * (size_t)(n + 1) * NX +
            (n > PINMPC_NMAX ? (size_t)n * 32 : 0)) + 3) & ~(size_t)3;

@@ -43,6 +43,7 @@ struct Ctx : Scalars {
   gcf A, B, e, x_ref, u_ref, x0;
   const GMEM uint8_t* contact;
   gd rT, rT2, rK, rF, rS;    // per-stage compact blocks (TS_T, TS_K, ... doubles)
+  gd rM;   // closed loops of a Newton step, over T2 and the padding
   gd ru, rx, rq, rs, rz, rds, rdz, rrc, rdu, rdx;
   gd rPV, rGV;   // long horizons: the stage buffers of the rollout and costates
   GMEM int32_t* faces;
@@ -204,7 +205,7 @@ __device__ inline void pin_all(const T (&v)[M]) {
 }
 __device__ inline void copy_doubles(gd dst, gd src, int count) {
   const Buf r = rsrc(uni(src), count * 8);
-  for (int e0 = lane_id(); e0 < count; e0 += 8 * W64) {
+  for (int e0 = fresh_lane(); e0 < count; e0 += 8 * W64) {
     double v[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] = ldd(r, (e0 + t * W64) * 8, 0);
@@ -226,13 +227,18 @@ struct ShR {
   // accesses over all banks
   alignas(16) double G[(NU + 16) * GC];
   double ST[16 * 17];             // a tile for its transpose
-  alignas(16) double HI[NU * GC];             // H^{-1} by column (chunk summaries)
+  // the right-hand sides by column between the two triangular solves (Z; the last
+  // column takes what the lanes of H write), or H^{-1} by column (chunk summaries)
+  alignas(16) double Z[17 * GC];
 };
 struct Sh {
   // the Riccati recursion's hand-off buffers and the stage vectors of the
   // rollout and the costates share storage: they are never in use together
   union {
-    ShR r;
+    struct {
+      ShR r;
+      alignas(16) double G1[(NU + 16) * GC];   // a pair's second system (odd stages)
+    } p;
     struct {
       double PV[PINMPC_NMAX * 16];   // x_{k+1}, Q (x_{k+1} - r_k), p_{k+1}
       double GV[PINMPC_NMAX * 16];   // w_k, R (u_k - u_ref_k), g_k
@@ -288,10 +294,11 @@ __device__ inline uint32_t pack_map(const int o[4]) {
 // the lower triangle and column VC, a load fills both triangles, column VC and
 // row VC
 __device__ inline uint32_t map_S(bool store) {
+  const int lane = fresh_lane();
   int o[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + tg(), c = tj();
+    const int r = 4 * q + (lane >> 4), c = lane & 15;
     const int hi = r > c ? r : c, lo = r > c ? c : r;
     const bool sym = r < NX && c < NX && (!store || c <= r);
     const bool vec = hi == VC && lo < NX && (!store || c == VC);
@@ -370,7 +377,7 @@ __device__ inline void build_eq(const Ctx& C, const double* Rd, uint8_t* unit, i
   const auto ct = uni(C.contact);
   const auto fc = uni(C.faces);
   const gd pT = uni(C.rT), pT2 = uni(C.rT2);
-  for (int e = lane_id(); e < kn * 2; e += W64) {
+  for (int e = fresh_lane(); e < kn * 2; e += W64) {
     const int i = e & 1;
     float ur[6];
     const int code = fc[e];
@@ -498,7 +505,9 @@ __device__ inline void build(const Ctx& C, Sh& sh, int kn) {
 // the matrix products carry the vectors along.  With
 //   Wt = [[W, q + s], [(q + s)^T, 0]]   and   D1 = [Bp | 0 | d], 1 at (VC, VC)
 // D3 = Wt^T D1 holds W Bp, in row VC Bp^T (q + s) and in column VC W d + q + s;
-// then D3^T D1 + T2 = [H | 0 | hw] and D3^T A = Hwx with nothing left to add.
+// then D3^T D1 + T2 = [H | 0 | hw] with nothing left to add.  With [A | d] in the
+// same form (1 at (VC, VC)) D2 = Wt^T [A | d] holds W A and, in column VC, W d + q
+// + s; D1^T D2 is Hwx and A^T D2 the value function without the gains' part.
 // FP64 vector instructions and FP64 matrix instructions do not overlap on this
 // chip (a group of one matrix product of 64 cycles and 12 multiply-adds takes
 // 134 cycles in one wave), so a stage costs the sum of both and is made of as
@@ -513,7 +522,7 @@ struct BackRaw<Mode::EQ> {
 };
 template <>
 struct BackRaw<Mode::NEWTON> {
-  float a[4], b[4];
+  float a[4], b[4], bt[3];
   double q[4], T[3];
 };
 
@@ -534,6 +543,24 @@ __device__ inline void eliminate(double (&col)[12], uint32_t unit) {
     eliminate<p + 1>(col, unit);
   }
 }
+// Newton steps, which keep the factors of H for the corrector: forward elimination
+// only (lanes as above; see `factor` for the factors).  z (LDS) takes the right-hand
+// sides between the two triangular solves, z = U^-T b, and col D^-1 z: the value
+// function needs only these two, Hwx^T H^-1 Hwx = z^T D^-1 z, and the back
+// substitution to [K | kap] = U^-1 D^-1 z follows beside it.
+template <int p = 0>
+__device__ inline void forward_eliminate(double (&col)[12], double* z, int hc, uint32_t unit) {
+  if constexpr (p < 12) {
+    z[p] = col[p];
+    if (!((unit >> p) & 1u)) {
+      const double rd = recip(row_bcast<p>(col[p]));
+      const double t = col[p] * rd;
+      fmac_rows<p, p + 1, 12>(col, -t);
+      col[p] = hc == p ? rd : t;
+    }
+    forward_eliminate<p + 1>(col, z, hc, unit);
+  }
+}
 // Backward recursion over stages k_hi - 1 down to k_lo from the value
 // function Ss of x_{k_hi} (S in rows and columns 0..12, s in row and column
 // VC); returns the value function of x_{k_lo}.  It stores each stage's gains
@@ -547,7 +574,7 @@ template <Mode mode, bool ELEM>
 __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
                                                              const uint8_t* unit, int k_lo,
                                                              int k_hi, d4 Ss, d4* TEo, d4* CEo) {
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   constexpr bool newton = (mode == Mode::NEWTON);
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const gcf pe = uni(C.e), pA = uni(C.A);
@@ -558,11 +585,13 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
   const auto rT = rsrc(uni(C.rT), N * TS_T * 8), rT2 = rsrc(uni(C.rT2), N * TS_T * 8);
   const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rF = rsrc(uni(C.rF), N * TS_F * 8);
   const gd prS = uni(C.rS);
+  const auto rM = rsrc(uni(C.rM), N * TS_M * 8);
   // this lane's offsets within a stage: rows 4q + g of A and B^T (EQ) or B,
   // of column VC (and, as item 3 of group 1, row VC) of the vectors, of T, K, F
   const int oA = j < NX ? (g * NX + j) * 4 : OOB;
   const int oA3 = (g == 0 && j < NX) ? (12 * NX + j) * 4 : OOB;
-  const int oB = newton ? (j < NU ? (g * NU + j) * 4 : OOB) : (j < NX ? (j * NU + g) * 4 : OOB);
+  const int oBt = j < NX ? (j * NU + g) * 4 : OOB;
+  const int oB = newton ? (j < NU ? (g * NU + j) * 4 : OOB) : oBt;
   const int oB3 = (newton && g == 0 && j < NU) ? (12 * NU + j) * 4 : OOB;
   const int oV = j == VC ? g : OOB / 8;
   const int oV3 = (g == 0 && j == VC) ? 12 : ((g == 1 && j < NX) ? j : OOB / 8);
@@ -572,6 +601,8 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
   for (int q = 0; q < 3; ++q) oT[q] = t_offset(4 * q + g, j);
   const int oK = j <= VC ? (g * (NX + 1) + j) * 8 : OOB;
   const int oF = j < NU ? (g * NU + j) * 8 : OOB;
+  const int oM = j <= VC ? (g * (NX + 1) + j) * 8 : OOB;
+  const int oM3 = (g == 0 && j <= VC) ? (12 * (NX + 1) + j) * 8 : OOB;
   const uint32_t mS = map_S(true);
   // Q on the diagonal, and where q = -Q r lies (column and row VC)
   d4 Qd, Qv;
@@ -582,7 +613,7 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
     Qv[q] = (j == VC && r < NX) ? C.Q[clampi(r, NX - 1)]
                                 : ((r == VC && j < NX) ? C.Q[clampi(j, NX - 1)] : 0.0);
   }
-  const SymWeights sw = sym_weights();
+  const SymWeights sw = sym_weights(lane);
   const double one = (g == 1 && j == VC) ? 1.0 : 0.0;   // (VC, VC) as item 3
   auto fetch = [&](int k, BackRaw<mode>& s) {
 #pragma unroll
@@ -592,6 +623,9 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
     for (int q = 0; q < 3; ++q)
       s.b[q] = ldf(rB, oB + q * (newton ? 4 * NU * 4 : 16), k * (NX * NU * 4));
     if constexpr (newton) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        if constexpr (!ELEM) s.bt[q] = ldf(rB, oBt + q * 16, k * (NX * NU * 4));
       s.b[3] = ldf(rB, oB3, k * (NX * NU * 4));
 #pragma unroll
       for (int q = 0; q < 3; ++q) s.q[q] = ldd(rQ, oV * 8 + q * 32, k * (NX * 8));
@@ -620,6 +654,7 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
   for (int k = k_hi - 1; k >= k_lo; --k) {
     // this stage's data
     d4 At, D1, Wt, H0 = zero4();   // H0: the part of [H | hw] without W
+    d4 Bt = zero4();               // B^T
 #pragma unroll
     for (int q = 0; q < 4; ++q) At[q] = (double)raw.a[q];
     uint32_t ub;
@@ -637,7 +672,11 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
       }
       D1[3] += one;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) H0[q] = raw.T[q];
+      for (int q = 0; q < 3; ++q) {
+        H0[q] = raw.T[q];
+        if constexpr (!ELEM) Bt[q] = (double)raw.bt[q];
+      }
+      pin(Bt);
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -655,13 +694,16 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
     if constexpr (ELEM) {
       if (k == k_hi - 1) Wt = zero4();   // a zero value at x_{k_hi}
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) At[q] = j == VC ? D1[q] : At[q];   // [A | d], 1 at (VC, VC)
     pin(At); pin(D1); pin(Wt); pin(H0);
     pin_memory();
     if (k > k_lo) fetch(k - 1, raw);
 
     const d4 D3 = mmT<4>(Wt, D1, zero4());   // [W Bp | 0 | W d + q + s], row VC Bp^T (q + s)
     const d4 D4 = mmT<4>(D3, D1, H0);        // [H | 0 | hw]
-    const d4 D5 = mmT<4>(D3, At, zero4());   // Hwx
+    const d4 D2 = mmT<4>(Wt, At, zero4());   // [W A | W d + q + s]
+    const d4 D5 = mmT<4>(D1, D2, zero4());   // Hwx
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int r = 4 * q + g;
@@ -669,15 +711,8 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
       sr.G[(NU + j) * GC + r] = -(j == VC ? D4[q] : D5[q]);
     }
     // A^T [W A | W d + q + s], the part of the value function without gains
-    d4 D2 = mmT<4>(Wt, At, zero4());
-#pragma unroll
-    for (int q = 0; q < 4; ++q) D2[q] = j == VC ? D3[q] : D2[q];
     const d4 SA = mmT<4>(At, D2, zero4());
     wsync();
-    // Elimination of [H | -Hwx | -hw] (H is SPD: no pivoting): lane 16 R + c
-    // holds column c of H (c < NU, the same in every row R) or right-hand side
-    // 4 R + c - NU; afterwards the right-hand sides are [K | kap].  Newton steps
-    // keep the factors of H for the corrector instead of reducing H to I.
     static_assert(NU == 12, "row elimination is written for 12 inputs");
     const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU;
     const bool is_h = hc < NU;
@@ -686,6 +721,7 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 #pragma unroll
     for (int r = 0; r < NU; ++r) col[r] = gc[r];
     wsync();
+    d4 ZT = zero4(), YT = zero4();
     if constexpr (ELEM) {
       double icol[NU];
 #pragma unroll
@@ -693,13 +729,24 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
       gj_rows2(col, icol, ub);
       if (!is_h && rhs < NU) {
 #pragma unroll
-        for (int r = 0; r < NU; ++r) sr.HI[rhs * GC + r] = icol[r];
+        for (int r = 0; r < NU; ++r) sr.Z[rhs * GC + r] = icol[r];
       }
-    } else if constexpr (newton) {
-      factor(col, hc, ub);
-      back_substitute(col, is_h, ub);
-    } else {
+    } else if constexpr (!newton) {
       eliminate(col, ub);
+    } else {
+      forward_eliminate(col, sr.Z + (is_h ? 16 : rhs) * GC, hc, ub);
+      if (!is_h) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) gc[r] = col[r];
+      }
+      wsync();
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        ZT[q] = -sr.Z[j * GC + 4 * q + g];
+        YT[q] = sr.G[(NU + j) * GC + 4 * q + g];
+      }
+      wsync();
+      back_substitute(col, is_h, ub);
     }
     if (newton ? (!is_h || lane < NU) : !is_h) {
 #pragma unroll
@@ -729,7 +776,7 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
         const int r = 4 * q + g;
-        HI[q] = (j < NU) ? sr.HI[clampi(j, NU - 1) * GC + r] : 0.0;
+        HI[q] = (j < NU) ? sr.Z[clampi(j, NU - 1) * GC + r] : 0.0;
         BpT[q] = sr.ST[j * 17 + r];
       }
       wsync();
@@ -740,13 +787,21 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         Ah[q] = (j < NX) ? At[q] + LK[q] : ((j == VC) ? LK[q] + D1[q] : 0.0);
-      const d4 ZT = mmT<4>(D1, TE, zero4());     // (A_E Bp)^T in rows 0..11
-      const d4 Y = mmT<3>(HI, ZT, zero4());      // H^-1 (A_E Bp)^T
-      CE = mmT<3>(ZT, Y, CE);
+      const d4 RT = mmT<4>(D1, TE, zero4());     // (A_E Bp)^T in rows 0..11
+      const d4 Y = mmT<3>(HI, RT, zero4());      // H^-1 (A_E Bp)^T
+      CE = mmT<3>(RT, Y, CE);
       TE = mmT<4>(Ah, TE, zero4());
     }
-    // S = A^T W A + Hwx^T K, s = A^T (W d + q + s) + Hwx^T kap
-    Ss = symmetrize(mmT<3>(D5, KK, SA), sw, sr.ST);
+    // S = A^T W A - Hwx^T H^-1 Hwx, s = A^T (W d + q + s) - Hwx^T H^-1 hw
+    constexpr bool zy = newton && !ELEM;
+    Ss = symmetrize(zy ? mmT<3>(ZT, YT, SA) : mmT<3>(D5, KK, SA), sw, sr.ST, lane);
+    if constexpr (newton && !ELEM) {
+      // the closed loop [A + B K | B kap] for the chains
+      const d4 M = mmT<3>(Bt, KK, At);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        std1(rM, q < 3 ? oM + q * 4 * (NX + 1) * 8 : oM3, k * (TS_M * 8), M[q]);
+    }
     if constexpr (mode == Mode::EQ && !ELEM) st_map(prS + (size_t)k * TS_S, TS_S, mS, Ss);
   }
   if constexpr (ELEM) {
@@ -770,18 +825,16 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 // by 3g lanes, and the partial sums of the four rows meet through the row and
 // half-wave swaps.
 
-// Forward rollout after the backward recursion (all N stages): w = K x + kap,
+// Forward rollout of an equality pass after its recursion (all N stages): w = K x + kap,
 // x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w = w to
-// rounding: the gains lie in the range of the projector.)  VECK: kap_k from GV
-// (a corrector's) instead of the stored gains.  Stage data is fetched a ring of
+// rounding: the gains lie in the range of the projector.)  Stage data is fetched a ring of
 // six stages ahead, about 3000 cycles, as a trip to memory takes (unconditionally, so every path back to the loop head has issued
 // the same loads).
-template <Mode mode, bool LONG, bool VECK>
+template <bool LONG>
 __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   gsync();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
-  constexpr bool newton = (mode == Mode::NEWTON);
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const gcf pe = uni(C.e), pA = uni(C.A);
   const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
   const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
@@ -799,12 +852,11 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   auto ffetch = [&](int k, FwdRaw& s) {
     ldd2(rK, oK, k * (TS_K * 8), s.k);
     ldd2(rK, oK + 16, k * (TS_K * 8), s.k + 2);
-    if constexpr (VECK) s.kap = (g == 0 && j < NU) ? sb.GV[k * 16 + j] : 0.0;
-    else s.kap = ldd(rK, oKap, k * (TS_K * 8));
-    s.c = newton ? 0.0 : ldd(rT, oC, k * (TS_T * 8));
+    s.kap = ldd(rK, oKap, k * (TS_K * 8));
+    s.c = ldd(rT, oC, k * (TS_T * 8));
     ldf4(rA, oA, k * (NX * NX * 4), s.a);
     ldf3(rB, oB, k * (NX * NU * 4), s.b);
-    s.e = newton ? 0.f : ldf(rE, oE, k * (NX * 4));
+    s.e = ldf(rE, oE, k * (NX * 4));
   };
   constexpr int FD = 6;
   FwdRaw ring[FD];
@@ -813,8 +865,7 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
     ffetch(d < N ? d : N - 1, ring[d]);
     pin_memory();
   }
-  double xv = 0.0;   // x_k, entry j
-  if (!newton) xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;
+  double xv = j < NX ? (double)uni(C.x0)[clampi(j, NX - 1)] : 0.0;   // x_k, entry j
   auto step = [&](int k, FwdRaw& r) __attribute__((always_inline)) {
     double km[4], a[4], b[3];
 #pragma unroll
@@ -836,7 +887,7 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
     const double xt = turn_rows(xv);
     const double w = row_total(dot4(xt, km, kap));
     const double ax = dot4(xt, a, ee);
-    xv = row_total(dot3(turn_rows(newton ? w : w + cc), b, ax));
+    xv = row_total(dot3(turn_rows(w + cc), b, ax));
     if (lane < NU) sb.GV[k * 16 + j] = w;
     if (lane < NX) sb.PV[k * 16 + j] = xv;
   };
@@ -858,8 +909,128 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   bufsync<LONG>();
 }
 
-// The sequential recursion over the whole horizon (one wave), then the
-// rollout.
+// The rollout of a Newton step (from x = 0), by the closed loops [M | m] that its
+// recursion leaves: x' = M x + m is the chain, w = K x + kap follows for four
+// stages at a time, one per 16-lane row.  The chain has one dependent product per
+// stage instead of two and issues half the instructions (its one wave is bound by
+// their number).  VECK: kap_k comes in GV and m_k = B kap_k in PV (a corrector's)
+// instead of the stored ones.
+template <bool LONG, bool VECK>
+__device__ INLINE void forward_map(const Ctx& C, Sh& sh) {
+  gsync();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
+  const auto rK = rsrc(uni(C.rK), N * TS_K * 8);
+  const auto rM = rsrc(uni(C.rM), N * TS_M * 8);
+  const StageBufs<LONG> sb(sh, C);
+  const int oM = j < NX ? (j * (NX + 1) + 3 * g) * 8 : OOB;
+  const int oV = (g == 0 && j < NX) ? (j * (NX + 1) + NX) * 8 : OOB;
+  struct FwdRaw {
+    double m[4], v;
+  };
+  auto ffetch = [&](int k, FwdRaw& s) {
+    ldd2(rM, oM, k * (TS_M * 8), s.m);
+    ldd2(rM, oM + 16, k * (TS_M * 8), s.m + 2);
+    if constexpr (VECK) s.v = lane < NX ? sb.PV[k * 16 + j] : 0.0;
+    else s.v = ldd(rM, oV, k * (TS_M * 8));
+  };
+  constexpr int FD = 12;
+  FwdRaw ring[FD];
+#pragma unroll
+  for (int d = 0; d < FD; ++d) {
+    ffetch(d < N ? d : N - 1, ring[d]);
+    pin_memory();
+  }
+  double xv = 0.0;   // x_k, entry j
+  auto step = [&](int k, FwdRaw& r) __attribute__((always_inline)) {
+    double m[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      m[q] = (q == 0 && g) ? 0.0 : r.m[q];
+      pin(m[q]);
+    }
+    const double v = r.v;
+    pin(v);
+    pin_memory();
+    ffetch(k + FD < N ? k + FD : N - 1, r);
+    xv = row_total(dot4(turn_rows(xv), m, v));
+    if (lane < NX) sb.PV[k * 16 + j] = xv;
+  };
+  static_assert(FD == 12, "one line below per ring slot");
+  for (int k = 0;; k += FD) {
+    if (!(k < N)) break;
+    step(k, ring[0]);
+    if (!(k + 1 < N)) break;
+    step(k + 1, ring[1]);
+    if (!(k + 2 < N)) break;
+    step(k + 2, ring[2]);
+    if (!(k + 3 < N)) break;
+    step(k + 3, ring[3]);
+    if (!(k + 4 < N)) break;
+    step(k + 4, ring[4]);
+    if (!(k + 5 < N)) break;
+    step(k + 5, ring[5]);
+    if (!(k + 6 < N)) break;
+    step(k + 6, ring[6]);
+    if (!(k + 7 < N)) break;
+    step(k + 7, ring[7]);
+    if (!(k + 8 < N)) break;
+    step(k + 8, ring[8]);
+    if (!(k + 9 < N)) break;
+    step(k + 9, ring[9]);
+    if (!(k + 10 < N)) break;
+    step(k + 10, ring[10]);
+    if (!(k + 11 < N)) break;
+    step(k + 11, ring[11]);
+  }
+  bufsync<LONG>();
+  const int oK = j < NU ? (g * TS_K + j * (NX + 1)) * 8 : OOB;
+  auto kfetch = [&](int k0, double (&s)[NX + 1]) {
+#pragma unroll
+    for (int l = 0; l <= NX; l += 2) ldd2(rK, oK + l * 8, k0 * (TS_K * 8), s + l);
+  };
+  constexpr int KD = 3;
+  double kn[KD][NX + 1];
+#pragma unroll
+  for (int d = 0; d < KD; ++d) {
+    kfetch(4 * d < N ? 4 * d : 0, kn[d]);
+    pin_memory();
+  }
+  auto gain = [&](int k0, double (&r)[NX + 1]) __attribute__((always_inline)) {
+    const int k = k0 + g;
+    double km[NX], kap = r[NX];
+#pragma unroll
+    for (int l = 0; l < NX; ++l) {
+      km[l] = r[l];
+      pin(km[l]);
+    }
+    pin(kap);
+    pin_memory();
+    kfetch(k0 + 4 * KD < N ? k0 + 4 * KD : k0, r);
+    const bool on = j < NU && k < N;
+    if constexpr (VECK) kap = on ? sb.GV[k * 16 + j] : 0.0;
+    const double x = (k > 0 && j < NX && k < N) ? sb.PV[(k - 1) * 16 + j] : 0.0;
+    const double w = dot_row_bcast13(x, km, kap);
+    if (on) sb.GV[k * 16 + j] = w;
+  };
+  static_assert(KD == 3, "one line below per ring slot");
+  for (int k0 = 0;; k0 += 4 * KD) {
+    if (!(k0 < N)) break;
+    gain(k0, kn[0]);
+    if (!(k0 + 4 < N)) break;
+    gain(k0 + 4, kn[1]);
+    if (!(k0 + 8 < N)) break;
+    gain(k0 + 8, kn[2]);
+  }
+  bufsync<LONG>();
+}
+
+// The sequential recursion over the whole horizon (one wave), then the rollout.
+template <Mode mode, bool LONG>
+__device__ INLINE void rollout(const Ctx& C, Sh& sh) {
+  if constexpr (mode == Mode::EQ) forward<LONG>(C, sh);
+  else forward_map<LONG, false>(C, sh);
+}
 template <Mode mode, bool LONG>
 __device__ INLINE void riccati_t(const Ctx& C, Sh& sh, int ktop) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
@@ -867,44 +1038,79 @@ __device__ INLINE void riccati_t(const Ctx& C, Sh& sh, int ktop) {
   build<mode>(C, sh, ktop);
   const d4 Vk =
       (ktop < N) ? ld_map(uni(C.rS) + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
-  backward<mode, false>(C, sh.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
-  forward<mode, LONG, false>(C, sh);
+  backward<mode, false>(C, sh.p.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
+  rollout<mode, LONG>(C, sh);
 }
 
-// Second right-hand side of a Newton step with the stored factors: its linear
-// term rho_k = GV + smu PV to kap_k (in GV).  With wv = q + s, hw = Bp^T wv + rho,
-// the recursion of the linear part is s <- A^T wv + K^T hw (Hwx^T kap = K^T hw), a
-// chain; the feedforwards kap = -H^{-1} hw then follow for all stages in parallel,
-// four stages at a time (one per 16-lane row), by the two triangular solves.
+// Second right-hand side of a Newton step with the stored factors.  In: its
+// linear term rho_k = GV + smu PV; out: kap_k in GV and m_k = B kap_k in PV, as
+// the rollout takes them.  With wv = q + s and hw = Bp^T wv + rho the recursion of
+// the linear part is s <- A^T wv + K^T hw (Hwx^T kap = K^T hw) = M^T wv + K^T rho
+// with the closed loop M = A + Bp K: one product per stage in the chain.  K^T rho
+// comes before it and kap = -H^{-1} hw, by the two triangular solves, after it,
+// for four stages at a time (one per 16-lane row).
 template <bool LONG>
 __device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const StageBufs<LONG> sb(sh, C);
-  const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rB = rsrc(uni(C.B), N * NX * NU * 4), rM = rsrc(uni(C.rM), N * TS_M * 8);
   const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rQ = rsrc(uni(C.rq), N * NX * 8);
   const auto rF = rsrc(uni(C.rF), N * TS_F * 8);
-  const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
-  const int oB = j < NU ? (3 * g * NU + j) * 4 : OOB, oB0 = (g == 0 && j < NU) ? j * 4 : OOB;
-  const int oK = j < NX ? (3 * g * (NX + 1) + j) * 8 : OOB, oQ = j < NX ? j * 8 : OOB;
+  {
+    const int oK = j < NX ? (g * TS_K + j) * 8 : OOB;
+    auto kfetch = [&](int k0, double (&s)[NU]) {
+#pragma unroll
+      for (int r = 0; r < NU; ++r) s[r] = ldd(rK, oK + r * (NX + 1) * 8, k0 * (TS_K * 8));
+    };
+    constexpr int KD = 3;
+    double kn[KD][NU];
+#pragma unroll
+    for (int d = 0; d < KD; ++d) {
+      kfetch(4 * d < N ? 4 * d : 0, kn[d]);
+      pin_memory();
+    }
+    auto term = [&](int k0, double (&r)[NU]) __attribute__((always_inline)) {
+      const int k = k0 + g;
+      double kc[NX];
+#pragma unroll
+      for (int l = 0; l < NU; ++l) {
+        kc[l] = r[l];
+        pin(kc[l]);
+      }
+      kc[NU] = 0.0;
+      pin_memory();
+      kfetch(k0 + 4 * KD < N ? k0 + 4 * KD : k0, r);
+      const bool on = j < NU && k < N;
+      const double rho = on ? fma(smu, sb.PV[k * 16 + j], sb.GV[k * 16 + j]) : 0.0;
+      const double v = dot_row_bcast13(rho, kc, 0.0);
+      if (on) sb.GV[k * 16 + j] = rho;
+      if (j < NX && k < N) sb.PV[k * 16 + j] = v;
+    };
+    static_assert(KD == 3, "one line below per ring slot");
+    for (int k0 = 0;; k0 += 4 * KD) {
+      if (!(k0 < N)) break;
+      term(k0, kn[0]);
+      if (!(k0 + 4 < N)) break;
+      term(k0 + 4, kn[1]);
+      if (!(k0 + 8 < N)) break;
+      term(k0 + 8, kn[2]);
+    }
+  }
+  bufsync<LONG>();
+  const int oM = j < NX ? (3 * g * (NX + 1) + j) * 8 : OOB, oM0 = (g == 0 && j < NX) ? j * 8 : OOB;
+  const int oQ = j < NX ? j * 8 : OOB;
   struct VecRaw {
-    float a[4], b[4];
-    double k[3], q, ra, rb;
+    double m[4], q, v;
   };
   auto vfetch = [&](int k, VecRaw& s) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      s.a[q] = ldf(rA, q == 0 ? oA0 : oA + q * NX * 4, k * (NX * NX * 4));
-      s.b[q] = ldf(rB, q == 0 ? oB0 : oB + q * NU * 4, k * (NX * NU * 4));
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) s.k[q] = ldd(rK, oK + q * (NX + 1) * 8, k * (TS_K * 8));
+    for (int q = 0; q < 4; ++q)
+      s.m[q] = ldd(rM, q == 0 ? oM0 : oM + q * (NX + 1) * 8, k * (TS_M * 8));
     s.q = ldd(rQ, oQ, k * (NX * 8));
-    const bool on = g == 0 && j < NU;
-    s.ra = on ? sb.GV[k * 16 + j] : 0.0;
-    s.rb = on ? sb.PV[k * 16 + j] : 0.0;
+    s.v = lane < NX ? sb.PV[k * 16 + j] : 0.0;
   };
-  constexpr int VD = 6;
+  constexpr int VD = 12;
   VecRaw ring[VD];
 #pragma unroll
   for (int d = 0; d < VD; ++d) {
@@ -913,31 +1119,22 @@ __device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
   }
   double s = 0.0;   // value function's linear part, entry j
   auto step = [&](int k, VecRaw& r) __attribute__((always_inline)) {
-    double a[4], b[4], km[3];
+    double m[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      a[q] = (double)r.a[q];
-      b[q] = (double)r.b[q];
-      pin(a[q]);
-      pin(b[q]);
+      m[q] = r.m[q];
+      pin(m[q]);
     }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      km[q] = r.k[q];
-      pin(km[q]);
-    }
-    const double qk = r.q, rho = fma(smu, r.rb, r.ra);
+    const double qk = r.q, v = r.v;
     pin(qk);
-    pin(rho);
+    pin(v);
     pin_memory();
     vfetch(k - VD >= 0 ? k - VD : 0, r);
-    const double wt = turn_rows(qk + s);
-    const double hw = row_total(dot4(wt, b, rho));
-    const double aw = dot4(wt, a, 0.0);
-    s = row_total(dot3(turn_rows(hw), km, aw));
-    if (lane < NU) sb.GV[k * 16 + j] = hw;
+    const double wv = qk + s;
+    if (lane < NX) sb.PV[k * 16 + j] = wv;
+    s = row_total(dot4(turn_rows(wv), m, v));
   };
-  static_assert(VD == 6, "one line below per ring slot");
+  static_assert(VD == 12, "one line below per ring slot");
   for (int k = N - 1;; k -= VD) {
     if (!(k >= 0)) break;
     step(k, ring[0]);
@@ -951,20 +1148,37 @@ __device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
     step(k - 4, ring[4]);
     if (!(k - 5 >= 0)) break;
     step(k - 5, ring[5]);
+    if (!(k - 6 >= 0)) break;
+    step(k - 6, ring[6]);
+    if (!(k - 7 >= 0)) break;
+    step(k - 7, ring[7]);
+    if (!(k - 8 >= 0)) break;
+    step(k - 8, ring[8]);
+    if (!(k - 9 >= 0)) break;
+    step(k - 9, ring[9]);
+    if (!(k - 10 >= 0)) break;
+    step(k - 10, ring[10]);
+    if (!(k - 11 >= 0)) break;
+    step(k - 11, ring[11]);
   }
   bufsync<LONG>();
   const int oF = j < NU ? (g * TS_F + j * NU) * 8 : OOB;
+  const int oBt = j < NU ? (g * NX * NU + j) * 4 : OOB;      // B^T's row j
+  const int oB = j < NX ? (g * NX + j) * NU * 4 : OOB;       // B's row j
   struct TriRaw {
-    double f[NU], rd, hw;
+    double f[NU], rd;
+    float bt[NX], b[NU];
   };
   auto tfetch = [&](int k0, TriRaw& s) {
-    const int k = k0 + g;
+#pragma unroll
+    for (int r = 0; r < NX; ++r) s.bt[r] = ldf(rB, oBt + r * NU * 4, k0 * (NX * NU * 4));
 #pragma unroll
     for (int p = 0; p < NU; p += 2) ldd2(rF, oF + p * 8, k0 * (TS_F * 8), s.f + p);
     s.rd = ldd(rF, oF + j * 8, k0 * (TS_F * 8));
-    s.hw = (j < NU && k < N) ? sb.GV[k * 16 + j] : 0.0;
+#pragma unroll
+    for (int l = 0; l < NU; l += 4) ldf4(rB, oB + l * 4, k0 * (NX * NU * 4), s.b + l);
   };
-  constexpr int TD = 3;
+  constexpr int TD = 2;
   TriRaw tri[TD];
 #pragma unroll
   for (int d = 0; d < TD; ++d) {
@@ -974,16 +1188,24 @@ __device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
   auto solve = [&](int k0, TriRaw& r) __attribute__((always_inline)) {
     const int k = k0 + g;
     const bool on = j < NU && k < N;
-    double f[NU], rd = r.rd, y = r.hw;
+    double f[NU], rd = r.rd, bt[NX], b[NX];
 #pragma unroll
-    for (int p = 0; p < NU; ++p) {
-      f[p] = r.f[p];
-      pin(f[p]);
+    for (int p = 0; p < NX; ++p) {
+      if (p < NU) {
+        f[p < NU ? p : 0] = r.f[p < NU ? p : 0];
+        pin(f[p < NU ? p : 0]);
+      }
+      bt[p] = (double)r.bt[p];
+      b[p] = p < NU ? (double)r.b[p < NU ? p : 0] : 0.0;
+      pin(bt[p]);
+      pin(b[p]);
     }
     pin(rd);
-    pin(y);
     pin_memory();
     tfetch(k0 + 4 * TD < N ? k0 + 4 * TD : k0, r);
+    const double wv = (j < NX && k < N) ? sb.PV[k * 16 + j] : 0.0;
+    const double rho = on ? sb.GV[k * 16 + j] : 0.0;
+    double y = dot_row_bcast13(wv, bt, rho);
     if (!on || sh.unit[2 * k + j / 6]) y = 0.0;   // a swing contact's inputs
     // y <- U^-T y, then D^-1, then U^-1
 #define PINMPC_TRI(p, use)                                                                      \
@@ -1003,18 +1225,305 @@ __device__ INLINE void newton_vector(const Ctx& C, Sh& sh, double smu) {
     PINMPC_TRI(7, j < 7) PINMPC_TRI(6, j < 6) PINMPC_TRI(5, j < 5) PINMPC_TRI(4, j < 4)
     PINMPC_TRI(3, j < 3) PINMPC_TRI(2, j < 2) PINMPC_TRI(1, j < 1)
 #undef PINMPC_TRI
-    if (on) sb.GV[k * 16 + j] = -y;
+    const double kap = on ? -y : 0.0;
+    const double mk = dot_row_bcast13(kap, b, 0.0);
+    if (on) sb.GV[k * 16 + j] = kap;
+    if (j < NX && k < N) sb.PV[k * 16 + j] = mk;
   };
-  static_assert(TD == 3, "one line below per ring slot");
+  static_assert(TD == 2, "one line below per ring slot");
   for (int k0 = 0;; k0 += 4 * TD) {
     if (!(k0 < N)) break;
     solve(k0, tri[0]);
     if (!(k0 + 4 < N)) break;
     solve(k0 + 4, tri[1]);
-    if (!(k0 + 8 < N)) break;
-    solve(k0 + 8, tri[2]);
   }
   bufsync<LONG>();
+}
+
+// ------------------------------------------------------- two waves per problem
+//
+// The recursion of one problem as a pair of waves, where the chip has room for
+// both (see launch_refine).  The first forms H and hw and eliminates; the second
+// forms Hwx and the part of the value function without gains beside that and
+// finishes the value function.  Per stage three meetings in LDS: the system is
+// complete, it is eliminated, the value function is known.  While the first
+// eliminates, the second also takes the stage before through the back
+// substitution (Newton steps) and stores what the chains read (gains, factors,
+// closed loops).  A stage's chain is then 8 + 3 matrix instructions and the
+// forward elimination instead of 23 + 3 and both triangular solves; the results are bitwise those of
+// one wave.  The second wave waits at a barrier while the first does all else.
+enum { PAIR_EXIT = 0, PAIR_EQ = 1, PAIR_NEWTON = 2 };
+struct PairCtl {
+  int op, ktop;
+};
+__shared__ PairCtl pair_ctl;
+
+// LDS hand-off between the waves: what this wave wrote has arrived.  The loads
+// in flight from memory go on (the fence of __syncthreads would wait for them).
+__device__ inline void pair_meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The symmetrised value function from the raw one in LDS.
+__device__ inline d4 read_sym(const SymWeights& w, const double* buf, int lane) {
+  const int g = lane >> 4, j = lane & 15;
+  d4 S;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    S[q] = fma(w.other[q], buf[j * 17 + 4 * q + g], w.own[q] * buf[(4 * q + g) * 17 + j]);
+  return S;
+}
+
+// One wave's side of the recursion over stages ktop - 1 .. 0 (FIRST: the wave
+// that eliminates).
+template <Mode mode, bool FIRST>
+__device__ INLINE void pair_backward(const Ctx& C, Sh& sh, int ktop) {
+  ShR& sr = sh.p.r;
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
+  constexpr bool newton = (mode == Mode::NEWTON);
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
+  const auto rX = rsrc(uni(C.x_ref), N * NX * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
+  const auto rQ = rsrc(uni(C.rq), N * NX * 8);
+  const auto rT = rsrc(uni(C.rT), N * TS_T * 8), rT2 = rsrc(uni(C.rT2), N * TS_T * 8);
+  const auto rK = rsrc(uni(C.rK), N * TS_K * 8), rF = rsrc(uni(C.rF), N * TS_F * 8);
+  const auto rM = rsrc(uni(C.rM), N * TS_M * 8);
+  const gd prS = uni(C.rS);
+  const int oA = j < NX ? (g * NX + j) * 4 : OOB;
+  const int oA3 = (g == 0 && j < NX) ? (12 * NX + j) * 4 : OOB;
+  const int oBt = j < NX ? (j * NU + g) * 4 : OOB;
+  const int oB = j < NU ? (g * NU + j) * 4 : OOB;
+  const int oB3 = (g == 0 && j < NU) ? (12 * NU + j) * 4 : OOB;
+  const int oV = j == VC ? g : OOB / 8;
+  const int oV3 = (g == 0 && j == VC) ? 12 : ((g == 1 && j < NX) ? j : OOB / 8);
+  const int oE3 = (g == 0 && j == VC) ? 48 : OOB;
+  int oT[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) oT[q] = t_offset(4 * q + g, j);
+  const int oK = j <= VC ? (g * (NX + 1) + j) * 8 : OOB;
+  const int oF = j < NU ? (g * NU + j) * 8 : OOB;
+  const int oK3 = (g == 0 && j <= VC) ? (12 * (NX + 1) + j) * 8 : OOB;
+  const uint32_t mS = map_S(true);
+  d4 Qd, Qv;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = 4 * q + g;
+    Qd[q] = (r == j && j < NX) ? sh.Qd[clampi(j, NX - 1)] : 0.0;
+    Qv[q] = (j == VC && r < NX) ? sh.Qd[clampi(r, NX - 1)]
+                                : ((r == VC && j < NX) ? sh.Qd[clampi(j, NX - 1)] : 0.0);
+  }
+  const SymWeights sw = sym_weights(lane);
+  const double one = (g == 1 && j == VC) ? 1.0 : 0.0;
+  struct Raw {
+    float a[4], b[4], bt[3], xr[4], ev[4];
+    double q[4], T[3], T2[3];
+  };
+  auto fetch = [&](int k, Raw& s) {
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s.a[q] = ldf(rA, oA + q * 4 * NX * 4, k * (NX * NX * 4));
+      s.a[3] = ldf(rA, oA3, k * (NX * NX * 4));
+    }
+    if constexpr (!FIRST || !newton) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s.bt[q] = ldf(rB, oBt + q * 16, k * (NX * NU * 4));
+    }
+    if constexpr (newton) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        s.b[q] = ldf(rB, oB + q * 4 * NU * 4, k * (NX * NU * 4));
+        s.q[q] = ldd(rQ, oV * 8 + q * 32, k * (NX * 8));
+      }
+      s.b[3] = ldf(rB, oB3, k * (NX * NU * 4));
+      s.q[3] = ldd(rQ, oV3 * 8, k * (NX * 8));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        s.xr[q] = ldf(rX, oV * 4 + q * 16, k * (NX * 4));
+        s.ev[q] = ldf(rE, oV * 4 + q * 16, k * (NX * 4));
+        if constexpr (FIRST) s.T2[q] = ldd(rT2, oT[q], k * (TS_T * 8));
+      }
+      s.xr[3] = ldf(rX, oV3 * 4, k * (NX * 4));
+      s.ev[3] = ldf(rE, oE3, k * (NX * 4));
+    }
+    if constexpr (FIRST || !newton) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s.T[q] = ldd(rT, oT[q], k * (TS_T * 8));
+    }
+  };
+  Raw raw;
+  fetch(ktop > 0 ? ktop - 1 : 0, raw);
+  d4 Ss = (ktop < N) ? ld_map(prS + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
+  const int hc = lane & 15, rhs = 4 * (lane >> 4) + hc - NU;
+  const bool is_h = hc < NU;
+  // the second wave's previous stage, its gains yet to be solved for and stored
+  d4 Ap = zero4(), Bp = zero4(), KE = zero4();
+  uint32_t up = 0;
+  auto finish = [&](int k) {
+    if constexpr (!newton) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) std1(rK, oK + q * 4 * (NX + 1) * 8, k * (TS_K * 8), KE[q]);
+      return;
+    }
+    double* G = (k & 1) ? sh.p.G1 : sr.G;
+    double col[NU];
+    double* gc = G + (is_h ? hc : NU + rhs) * GC;
+#pragma unroll
+    for (int r = 0; r < NU; ++r) col[r] = gc[r];
+    back_substitute(col, is_h, up);
+    if (!is_h) {
+#pragma unroll
+      for (int r = 0; r < NU; ++r) gc[r] = col[r];
+    }
+    wsync();
+    d4 KK = zero4();   // [K | kap]
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int r = 4 * q + g, c = clampi(j, NU - 1);
+      KK[q] = G[(NU + j) * GC + r];
+      std1(rK, oK + q * 4 * (NX + 1) * 8, k * (TS_K * 8), KK[q]);
+      // U above and below the diagonal, 1 / d on it
+      std1(rF, oF + q * 4 * NU * 8, k * (TS_F * 8), G[(r > c ? r : c) * GC + (r > c ? c : r)]);
+    }
+    wsync();
+    const d4 M = mmT<3>(Bp, KK, Ap);   // [A + B K | B kap]
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      std1(rM, q < 3 ? oK + q * 4 * (NX + 1) * 8 : oK3, k * (TS_M * 8), M[q]);
+  };
+  for (int k = ktop - 1; k >= 0; --k) {
+    d4 At = zero4(), D1, Wt, H0 = zero4(), Bt = zero4();
+    uint32_t ub;
+    {
+      const uint32_t u0 = sh.unit[2 * k], u1 = sh.unit[2 * k + 1];
+      ub = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u0 | (u1 << 6)));
+    }
+    if (k < ktop - 1) Ss = read_sym(sw, sr.ST, lane);
+    if constexpr (newton) {
+      const bool keep = j < NU && !((ub >> j) & 1u);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        D1[q] = keep ? (double)raw.b[q] : 0.0;
+        Wt[q] = Ss[q] + (Qd[q] + raw.q[q]);
+      }
+      D1[3] += one;
+      if constexpr (FIRST) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) H0[q] = raw.T[q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) Bt[q] = (double)raw.bt[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        D1[q] = (double)raw.ev[q];
+        Wt[q] = Ss[q] + fma(-Qv[q], (double)raw.xr[q], Qd[q]);
+      }
+      D1[3] += one;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        Bt[q] = (double)raw.bt[q];
+        D1 = __builtin_amdgcn_mfma_f64_16x16x4f64(Bt[q], raw.T[q], D1, 0, 0, 0);
+        if constexpr (FIRST) H0[q] = raw.T2[q];
+      }
+    }
+    if constexpr (!FIRST) {
+      // [A | d] with a 1 at (VC, VC)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) At[q] = j == VC ? D1[q] : (double)raw.a[q];
+    }
+    pin(At); pin(D1); pin(Wt); pin(H0); pin(Bt);
+    pin_memory();
+    if (k > 0) fetch(k - 1, raw);
+    double* G = (k & 1) ? sh.p.G1 : sr.G;
+    if constexpr (FIRST) {
+      const d4 D3 = mmT<4>(Wt, D1, zero4());
+      const d4 D4 = mmT<4>(D3, D1, H0);        // [H | 0 | hw]
+      if (j < NU || j == VC) {
+        double* gc = G + (j < NU ? j : NU + VC) * GC + g;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) gc[4 * q] = j < NU ? D4[q] : -D4[q];
+      }
+      pair_meet();   // the system is complete
+      double col[NU];
+      double* gc = G + (is_h ? hc : NU + rhs) * GC;
+#pragma unroll
+      for (int r = 0; r < NU; ++r) col[r] = gc[r];
+      if constexpr (newton) forward_eliminate(col, sr.Z + (is_h ? 16 : rhs) * GC, hc, ub);
+      else eliminate(col, ub);
+      wsync();
+      if (newton ? (!is_h || lane < NU) : !is_h) {
+#pragma unroll
+        for (int r = 0; r < NU; ++r) gc[r] = col[r];
+      }
+      pair_meet();   // it is eliminated
+      if (k > 0) pair_meet();   // the value function is known
+    } else {
+      const d4 D2 = mmT<4>(Wt, At, zero4());   // [W A | W d + q + s]
+      const d4 D5 = mmT<4>(D1, D2, zero4());   // Hwx
+      if (j != VC) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) G[(NU + j) * GC + 4 * q + g] = -D5[q];
+      }
+      pair_meet();   // the system is complete
+      const d4 SA = mmT<4>(At, D2, zero4());
+      if (k < ktop - 1) {
+        finish(k + 1);
+        if constexpr (!newton) st_map(prS + (size_t)(k + 1) * TS_S, TS_S, mS, Ss);
+      }
+      Ap = At;
+      Bp = Bt;
+      up = ub;
+      pair_meet();   // it is eliminated
+      d4 ZT = zero4(), YT = zero4();   // NEWTON: -z, D^-1 z; EQ: Hwx, [K | kap]
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        ZT[q] = newton ? -sr.Z[j * GC + 4 * q + g] : D5[q];
+        YT[q] = G[(NU + j) * GC + 4 * q + g];
+      }
+      KE = YT;
+      if (k > 0) {
+        const d4 S = mmT<3>(ZT, YT, SA);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sr.ST[(4 * q + g) * 17 + j] = S[q];
+        pair_meet();   // the value function is known
+      }
+    }
+  }
+  if constexpr (!FIRST) {
+    if (ktop > 0) finish(0);
+    gsync();       // the stores have arrived
+  }
+  pair_meet();
+}
+
+// The first wave's recursion and rollout.
+template <Mode mode, bool LONG>
+__device__ INLINE void riccati_pair(const Ctx& C, Sh& sh, int ktop) {
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
+  build<mode>(C, sh, ktop);
+  if (lane_id() == 0) pair_ctl = {mode == Mode::EQ ? PAIR_EQ : PAIR_NEWTON, ktop};
+  pair_meet();   // the command and the stage inputs
+  pair_backward<mode, true>(C, sh, ktop);
+  rollout<mode, LONG>(C, sh);
+}
+// The second wave: the first's commands until it releases it.
+template <bool NEWTON>
+__device__ INLINE void pair_helper(const Ctx& C, Sh& sh) {
+  for (;;) {
+    pair_meet();
+    const int op = __builtin_amdgcn_readfirstlane(pair_ctl.op);
+    const int ktop = __builtin_amdgcn_readfirstlane(pair_ctl.ktop);
+    if (op == PAIR_EXIT) return;
+    if (!NEWTON || op == PAIR_EQ) pair_backward<Mode::EQ, false>(C, sh, ktop);
+    else pair_backward<Mode::NEWTON, false>(C, sh, ktop);
+  }
+}
+__device__ inline void pair_release() {
+  if (lane_id() == 0) pair_ctl.op = PAIR_EXIT;
+  pair_meet();
 }
 
 // ---------------------------------------- associative scan over the horizon
@@ -1091,7 +1600,7 @@ __device__ inline double readlane_d(double v, int l) {
 // column c of the identity; each pivot's column reaches every lane by lane
 // reads.  buf: 256 doubles of LDS.
 __device__ INLINE d4 inv13(const d4& M, double* buf) {
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
 #pragma unroll
   for (int q = 0; q < 4; ++q) buf[(4 * q + g) * 16 + j] = M[q];
   wsync();
@@ -1177,14 +1686,14 @@ __device__ INLINE void riccati_scan(const Ctx& C, Sh& sh, int ktop) {
   ktop = (mode == Mode::EQ) ? __builtin_amdgcn_readfirstlane(ktop < N ? ktop : N) : N;
   build<mode>(C, sh, ktop);
   constexpr bool newton = (mode == Mode::NEWTON);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const int W = (int)(blockDim.x >> 6);
   const int nch = __builtin_amdgcn_readfirstlane(
       ktop / SCAN_MIN_CHUNK < W ? ktop / SCAN_MIN_CHUNK : W);
   const d4 Vk = (ktop < N) ? ld_map(uni(C.rS) + (size_t)ktop * TS_S, TS_S, map_S(false)) : zero4();
   if (nch < 2) {
-    backward<mode, false>(C, sh.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
-    forward<mode, LONG, false>(C, sh);
+    backward<mode, false>(C, sh.p.r, sh.unit, 0, ktop, Vk, nullptr, nullptr);
+    rollout<mode, LONG>(C, sh);
     return;
   }
   const ScanLds L = scan_lds(W);
@@ -1220,9 +1729,9 @@ __device__ INLINE void riccati_scan(const Ctx& C, Sh& sh, int ktop) {
     st_tile_lds(L.bnd + (size_t)(w - 1) * TILE_D, V);
   }
   __syncthreads();   // the boundary values reach the helpers
-  backward<mode, false>(C, sh.r, sh.unit, 0, (int)(ktop / nch), V, nullptr, nullptr);
+  backward<mode, false>(C, sh.p.r, sh.unit, 0, (int)(ktop / nch), V, nullptr, nullptr);
   __syncthreads();   // every chunk's gains and values are stored
-  forward<mode, LONG, false>(C, sh);
+  rollout<mode, LONG>(C, sh);
 }
 
 // A helper wave of a scanning workgroup: summary and recursion of its chunk
@@ -1268,9 +1777,12 @@ __device__ inline void scan_release() {
   if (lane_id() == 0) scan_ctl.op = SCAN_EXIT;
   __syncthreads();
 }
-template <Mode mode, bool LONG, bool SCAN>
+// How a problem's recursion runs: by one wave, by two, or as a scan over the horizon.
+enum class Waves { ONE, PAIR, SCAN };
+template <Mode mode, bool LONG, Waves WV>
 __device__ INLINE void riccati(const Ctx& C, Sh& sh, int ktop) {
-  if constexpr (SCAN) riccati_scan<mode, LONG>(C, sh, ktop);
+  if constexpr (WV == Waves::SCAN) riccati_scan<mode, LONG>(C, sh, ktop);
+  else if constexpr (WV == Waves::PAIR) riccati_pair<mode, LONG>(C, sh, ktop);
   else riccati_t<mode, LONG>(C, sh, ktop);
 }
 
@@ -1285,7 +1797,7 @@ __device__ INLINE void eq_point(const Ctx& C, Sh& sh) {
   const Buf rR = uref_buf(C), rU = rsrc(uni(C.ru), N * NU * 8);
   const auto ct = uni(C.contact);
   const auto fc = uni(C.faces);
-  for (int e = lane; e < N * 2; e += W64) {
+  for (int e = fresh_lane(); e < N * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
     float ur[6];
     const int code = fc[e];
@@ -1335,7 +1847,7 @@ __device__ INLINE void eq_point(const Ctx& C, Sh& sh) {
   }
   const Buf rX = rsrc(uni(C.x_ref), N * NX * 4);
   const gd px = uni(C.rx);
-  for (int e0 = lane; e0 < N * NX; e0 += 8 * W64) {
+  for (int e0 = fresh_lane(); e0 < N * NX; e0 += 8 * W64) {
     double x[8], xr[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -1361,11 +1873,11 @@ __device__ INLINE void eq_point(const Ctx& C, Sh& sh) {
 template <bool LONG>
 __device__ inline void load_point(const Ctx& C, Sh& sh) {
   gsync();
-  const int lane = lane_id(), N = C.N;
+  const int N = C.N;
   const StageBufs<LONG> sb(sh, C);
-  for (int e = lane; e < N * NX; e += W64)
+  for (int e = fresh_lane(); e < N * NX; e += W64)
     sb.PV[(e / NX) * 16 + e % NX] = C.Q[e % NX] * (C.rx[NX + e] - (double)C.x_ref[e]);
-  for (int e = lane; e < N * NU; e += W64) {
+  for (int e = fresh_lane(); e < N * NU; e += W64) {
     const double ur = C.u_ref ? (double)C.u_ref[e] : 0.0;
     sb.GV[(e / NU) * 16 + e % NU] = C.R[e % NU] * (C.ru[e] - ur);
   }
@@ -1380,7 +1892,7 @@ __device__ inline void load_point(const Ctx& C, Sh& sh) {
 template <bool LONG>
 __device__ INLINE double costates_grad(const Ctx& C, Sh& sh) {
   const StageBufs<LONG> sb(sh, C);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
   const int oA = j < NX ? (3 * g * NX + j) * 4 : OOB, oA0 = (g == 0 && j < NX) ? j * 4 : OOB;
@@ -1498,7 +2010,7 @@ template <bool LONG>
 __device__ INLINE void rollout_ru(const Ctx& C, Sh& sh) {
   gsync();
   const StageBufs<LONG> sb(sh, C);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const gcf pe = uni(C.e), pA = uni(C.A);
   const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
@@ -1577,7 +2089,7 @@ __device__ INLINE void rollout_ru(const Ctx& C, Sh& sh) {
   }
   bufsync<LONG>();
   if (lane < NX) C.rx[lane] = (double)C.x0[lane];
-  for (int e = lane; e < N * NX; e += W64) C.rx[NX + e] = sb.PV[(e / NX) * 16 + e % NX];
+  for (int e = fresh_lane(); e < N * NX; e += W64) C.rx[NX + e] = sb.PV[(e / NX) * 16 + e % NX];
   gsync();
 }
 
@@ -1606,7 +2118,6 @@ template <bool LONG>
 __device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC_NRES],
                                  double term_state, bool update, FaceUpdate* upd) {
   const StageBufs<LONG> sb(sh, C);
-  const int lane = lane_id();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const Scalars sc = scalars(C);
   const Buf rR = uref_buf(C), rU = rsrc(uni(C.ru), N * NU * 8);
@@ -1615,7 +2126,7 @@ __device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC
   double r_ineq = 0.0, stat = 0.0, term = term_state, comp = 0.0, mumax = 0.0, neg = 0.0;
   uint64_t hsh = 0;
   int kch = 0;
-  for (int e = lane; e < N * 2; e += W64) {
+  for (int e = fresh_lane(); e < N * 2; e += W64) {
     const int k = e >> 1, i = e & 1;
     // the contact-stage's inputs, gradient and multipliers in registers
     double u[6], g[6], mu[NROW];
@@ -1761,7 +2272,7 @@ __device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC
 // per 16-lane row, state j in lane j).
 __device__ INLINE double dyn_residual(const Ctx& C) {
   gsync();
-  const int g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const gcf pe = uni(C.e), pA = uni(C.A);
   const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * NU * 4);
@@ -1830,7 +2341,7 @@ __device__ INLINE void faces_from_u(const Ctx& C, double tol) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const Scalars sc = scalars(C);
   const Buf rU = rsrc(uni(C.ru), N * NU * 8);
-  for (int e = lane_id(); e < N * 2; e += W64) {
+  for (int e = fresh_lane(); e < N * 2; e += W64) {
     double u[6], gu[NROW];
     const bool on = uni(C.contact)[e];
     ld6(rU, e, u);
@@ -1851,11 +2362,11 @@ __device__ INLINE void faces_from_u(const Ctx& C, double tol) {
 // equality-constrained solve, whose tiles and factors are still in the scratch
 // block.  The pass's x is the FP64 rollout of its u, so its dynamics residual is
 // rounding only: it is checked once, on the final trajectory, by the caller.
-template <bool LONG, bool SCAN>
+template <bool LONG, Waves WV>
 __device__ INLINE double eq_pass(const Ctx& C, Sh& sh, double res[PINMPC_NRES], bool solve,
                                  int ktop, bool update, FaceUpdate* upd) {
   if (solve) {
-    riccati<Mode::EQ, LONG, SCAN>(C, sh, ktop);
+    riccati<Mode::EQ, LONG, WV>(C, sh, ktop);
     eq_point<LONG>(C, sh);
   } else {
     load_point<LONG>(C, sh);
@@ -1869,7 +2380,7 @@ __device__ INLINE void faces_from_zs(const Ctx& C) {
   gsync();
   const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
   const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
-  for (int e = lane_id(); e < N * 2; e += W64) {
+  for (int e = fresh_lane(); e < N * 2; e += W64) {
     double zv[NROW], sv[NROW];
     const bool on = uni(C.contact)[e];
     load_r(rZ, step, e, zv);
@@ -1908,7 +2419,7 @@ __device__ INLINE void newton_blocks(const Ctx& C, Sh& sh) {
   const Buf rU = rsrc(uni(C.ru), N * NU * 8), rR = uref_buf(C);
   const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
   const gd pT = uni(C.rT);
-  for (int e = lane_id(); e < N * 2; e += W64) {
+  for (int e = fresh_lane(); e < N * 2; e += W64) {
     double u[6], sv[NROW], zv[NROW];
     float ur[6];
     const bool on = uni(C.contact)[e];
@@ -1968,12 +2479,11 @@ struct IpmState {
 template <bool LONG>
 __device__ INLINE void ipm_start(const Ctx& C, Sh& sh, IpmState& st) {
   gsync();
-  const int lane = lane_id();
   const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
   const auto ct = uni(C.contact);
   // number of stance rows
   int mloc = 0;
-  for (int e = lane; e < N * 2; e += W64)
+  for (int e = fresh_lane(); e < N * 2; e += W64)
     if (ct[e]) mloc += NROW;
   st = {0, 0, wave_sum((double)mloc), 0.0, 0.0};
   // initial point: the current ru (the ADMM point) and its rollout in rx,
@@ -1984,7 +2494,7 @@ __device__ INLINE void ipm_start(const Ctx& C, Sh& sh, IpmState& st) {
   {
     const Scalars sc = scalars(C);
     const Buf rU = rsrc(uni(C.ru), N * NU * 8), rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
-    for (int e = lane; e < N * 2; e += W64) {
+    for (int e = fresh_lane(); e < N * 2; e += W64) {
       double u[6], gu[NROW], sv[NROW], zv[NROW];
       const bool on = ct[e];
       ld6(rU, e, u);
@@ -2006,7 +2516,7 @@ __device__ INLINE void ipm_start(const Ctx& C, Sh& sh, IpmState& st) {
   {
     const Buf rX = rsrc(uni(C.rx), (N + 1) * NX * 8), rXr = rsrc(uni(C.x_ref), N * NX * 4);
     const gd pq = uni(C.rq);
-    for (int e0 = lane; e0 < N * NX; e0 += 4 * W64) {
+    for (int e0 = fresh_lane(); e0 < N * NX; e0 += 4 * W64) {
       double x[4], xr[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -2022,10 +2532,9 @@ __device__ INLINE void ipm_start(const Ctx& C, Sh& sh, IpmState& st) {
     }
   }
 }
-template <bool LONG, bool SCAN>
+template <bool LONG, Waves WV>
 __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
   if (st.m == 0.0) return false;
-  const int lane = lane_id();
   const int N = __builtin_amdgcn_readfirstlane(C.N), step = __builtin_amdgcn_readfirstlane(C.n) * 16;
   const auto ct = uni(C.contact);
   const StageBufs<LONG> sb(sh, C);
@@ -2036,7 +2545,7 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
     const double sz = wave_sum(st.smz), muv = sz / st.m;
     if (scalar(muv <= 1e-10 && wave_max(st.rpn) <= 1e-9)) break;
     // predictor (affine target s z)
-    riccati<Mode::NEWTON, LONG, SCAN>(C, sh, N);
+    riccati<Mode::NEWTON, LONG, WV>(C, sh, N);
     const Scalars sc = scalars(C);
     const Buf rU = rsrc(uni(C.ru), N * NU * 8), rR = uref_buf(C);
     const Buf rS = row_buf(C, C.rs), rZ = row_buf(C, C.rz);
@@ -2047,7 +2556,7 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
     // input for the target s z + ds dz - sigma mu, whose part in sigma mu goes
     // to PV and the rest to GV
     double over = 1.0, sm1 = 0.0, sm2 = 0.0;
-    for (int e = lane; e < N * 2; e += W64) {
+    for (int e = fresh_lane(); e < N * 2; e += W64) {
       const int k = e >> 1, i = e & 1;
       double u[6], du[6], sv[NROW], zv[NROW];
       float ur[6];
@@ -2102,7 +2611,7 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
     // predictor's factors
     bufsync<LONG>();
     newton_vector<LONG>(C, sh, smu);
-    forward<Mode::NEWTON, LONG, true>(C, sh);
+    forward_map<LONG, true>(C, sh);
     // its row steps, and the largest step over distance
     over = 1.0;
     auto row_steps = [&](int e, bool on, RowState& w) __attribute__((always_inline)) {
@@ -2159,6 +2668,7 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
     double a;
     if (one_each) {
       RowState w;
+      const int lane = fresh_lane();
       const int e = lane < 2 * N ? lane : 2 * N - 1;   // surplus lanes repeat the last's loads
       const bool on = ct[e] && lane < 2 * N;
       row_steps(e, on, w);
@@ -2166,14 +2676,14 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
       if (on) advance(e, w, a);
     } else {
       const Buf rDs = row_buf(C, C.rds), rDz = row_buf(C, C.rdz);
-      for (int e = lane; e < N * 2; e += W64) {
+      for (int e = fresh_lane(); e < N * 2; e += W64) {
         RowState w;
         row_steps(e, ct[e], w);
         store_r(rDs, step, e, w.ds);
         store_r(rDz, step, e, w.dz);
       }
       a = 0.99 * recip(wave_max(over));
-      for (int e = lane; e < N * 2; e += W64) {
+      for (int e = fresh_lane(); e < N * 2; e += W64) {
         RowState w;
         const bool on = ct[e];
         ld6(rU, e, w.u);
@@ -2197,7 +2707,7 @@ __device__ INLINE bool ipm_run(const Ctx& C, Sh& sh, IpmState& st, int maxit) {
     {
       const Buf rX = rsrc(uni(C.rx), (N + 1) * NX * 8), rXr = rsrc(uni(C.x_ref), N * NX * 4);
       const gd px = uni(C.rx), pq = uni(C.rq);
-      for (int e0 = lane; e0 < N * NX; e0 += 8 * W64) {
+      for (int e0 = fresh_lane(); e0 < N * NX; e0 += 8 * W64) {
         double x[8], xr[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -2241,7 +2751,7 @@ __device__ INLINE void admm_point(const Ctx& C, gcf zsrc, gcf sf, float tsc) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const auto ct = uni(C.contact);
   const gd pu = uni(C.ru);
-  for (int e0 = lane_id(); e0 < N * NU; e0 += 4 * W64) {
+  for (int e0 = fresh_lane(); e0 < N * NU; e0 += 4 * W64) {
     float z[4], f[4];
     int on[4];
 #pragma unroll
@@ -2269,7 +2779,7 @@ __device__ INLINE void admm_point(const Ctx& C, gcf zsrc, gcf sf, float tsc) {
 // together instead of behind a second round of easy ones.
 // The doubles of a buffer as floats, zero past its end.
 __device__ inline void put_floats(float* out, Buf r, int count) {
-  for (int e0 = lane_id(); e0 < count; e0 += 8 * W64) {
+  for (int e0 = fresh_lane(); e0 < count; e0 += 8 * W64) {
     double v[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) v[t] = ldd(r, (e0 + t * W64) * 8, 0);
@@ -2280,16 +2790,20 @@ __device__ inline void put_floats(float* out, Buf r, int count) {
   }
 }
 
-// The first wave releases a scanning workgroup's helpers on every way out.
-template <bool SCAN>
-struct ScanRelease {
-  __device__ ~ScanRelease() {
-    if constexpr (SCAN) scan_release();
+// The first wave releases a workgroup's other waves on every way out.
+template <Waves WV>
+struct Release {
+  __device__ ~Release() {
+    if constexpr (WV == Waves::SCAN) scan_release();
+    if constexpr (WV == Waves::PAIR) pair_release();
   }
 };
 
-template <int PHASE, bool LONG, bool SCAN>
-__global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(Problem p, Workspace ws, float* out_u,
+constexpr int threads_of(Waves w) {
+  return w == Waves::SCAN ? W64 * SCAN_WMAX : (w == Waves::PAIR ? 2 * W64 : W64);
+}
+template <int PHASE, bool LONG, Waves WV>
+__global__ void __launch_bounds__(threads_of(WV), 2) refine_kernel(Problem p, Workspace ws, float* out_u,
                                                     float* out_x, float* out_res,
                                                     int32_t* out_iters, int32_t* out_status,
                                                     int32_t* out_detail,
@@ -2305,7 +2819,13 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     if ((int)blockIdx.x >= ws.rcount[0]) return;
     pb = ws.rlist[blockIdx.x];
   }
-  if constexpr (SCAN) {
+  if constexpr (WV == Waves::PAIR) {
+    if (threadIdx.x >= W64) {
+      pair_helper<PHASE == 2>(C, sh);
+      return;
+    }
+  }
+  if constexpr (WV == Waves::SCAN) {
     // with the horizon scan the workgroup holds one wave per chunk: all but
     // the first take the scan's commands until the first releases them
     if (threadIdx.x >= W64) {
@@ -2313,7 +2833,7 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
       return;
     }
   }
-  const ScanRelease<SCAN> release;
+  const Release<WV> release;
   const int lane = lane_id();
   if (lane == 0) {
   C.b = pb;
@@ -2341,9 +2861,9 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     const int n = C.n;
     gd blk = (gd)(ws.rblk + (size_t)C.b * refine_block_doubles(n));
     C.rT = blk;                       blk += (size_t)n * TS_T;
-    C.rT2 = blk;                      blk += (size_t)n * TS_T;
-    C.rK = blk;                       blk += (size_t)n * TS_K;
+    C.rT2 = C.rM = blk;               blk += (size_t)n * (TS_T + TS_PAD);
     C.rF = blk;                       blk += (size_t)n * TS_F;
+    C.rK = blk;                       blk += (size_t)n * TS_K;
     C.rS = blk;                       blk += (size_t)n * TS_S;
     C.ru = blk;                       blk += (size_t)n * NU;
     C.rq = blk;                       blk += (size_t)n * NX;
@@ -2353,7 +2873,6 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     C.rdz = blk;                      blk += (size_t)n * 2 * NROW;
     C.rrc = blk;                      blk += (size_t)n * 2 * NROW;
     C.rdu = blk;                      blk += (size_t)n * NU;
-    blk += (size_t)n * TS_PAD;
     C.rx = blk;                       blk += (size_t)(n + 1) * NX;
     C.rdx = blk;                      blk += (size_t)(n + 1) * NX;
     C.rPV = blk;                      blk += (size_t)n * 16;
@@ -2394,8 +2913,8 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
       nonfinite = wave_max_int(nf) > 0;
     }
     if (bad || nonfinite) {
-      for (int e = lane; e < C.n * NU; e += W64) out_u[ux + e] = 0.f;
-      for (int e = lane; e < (C.n + 1) * NX; e += W64) out_x[xx + e] = 0.f;
+      for (int e = fresh_lane(); e < C.n * NU; e += W64) out_u[ux + e] = 0.f;
+      for (int e = fresh_lane(); e < (C.n + 1) * NX; e += W64) out_x[xx + e] = 0.f;
       if (lane == 0) {
         if (out_status) out_status[C.b] = bad ? PINMPC_ST_BADINPUT : PINMPC_ST_NONFINITE;
         if (out_iters) out_iters[C.b] = 0;
@@ -2448,7 +2967,7 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
         part = INTERIOR;
       }
       if (part == INTERIOR) {
-        cross = ipm_run<LONG, SCAN>(C, sh, ist, ipm_max);
+        cross = ipm_run<LONG, WV>(C, sh, ist, ipm_max);
         if (!cross) {
           part = POLISH;
           left = pass_c;
@@ -2462,7 +2981,7 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
     FaceUpdate upd;
     const bool update = refine && !cross;
     const int kt = cross || ktop > N ? N : ktop;
-    const double kkt = eq_pass<LONG, SCAN>(C, sh, res, PHASE == 2 || refine, kt, update, &upd);
+    const double kkt = eq_pass<LONG, WV>(C, sh, res, PHASE == 2 || refine, kt, update, &upd);
     if (PHASE == 1 && !refine) break;
     ++cnt.eq;
     cnt.stf += kt;
@@ -2522,6 +3041,14 @@ __global__ void __launch_bounds__(SCAN ? 64 * SCAN_WMAX : 64, 2) refine_kernel(P
 
 }  // namespace
 
+// The first launch runs a problem by two waves up to this batch: 1024 pairs fill
+// the chip's 1024 SIMDs with two waves each (the registers allow no more).  With
+// more problems two single waves on a SIMD do the same work without the meetings.
+// The second launch always runs pairs: its few problems leave the chip nearly
+// empty, and each one's time is its chain (3001 problems of 8 to 60 stages: 7.8 ms
+// with one wave each, 6.8 ms with two; 24 of 160: 35 and 28 ms).
+constexpr int PAIR_BATCH = 1024;
+
 size_t scan_lds_bytes(int W) {
   return W > 1 ? (size_t)(W - 1) * sizeof(ShR) + (size_t)W * 4 * TILE_D * sizeof(double) : 0;
 }
@@ -2529,10 +3056,10 @@ size_t scan_lds_bytes(int W) {
 hipError_t refine_prepare() {
   // the scanning kernels may take more dynamic LDS than the default limit
   const int lds = (int)scan_lds_bytes(SCAN_WMAX);
-  const void* k[] = {reinterpret_cast<const void*>(&refine_kernel<1, false, true>),
-                     reinterpret_cast<const void*>(&refine_kernel<1, true, true>),
-                     reinterpret_cast<const void*>(&refine_kernel<2, false, true>),
-                     reinterpret_cast<const void*>(&refine_kernel<2, true, true>)};
+  const void* k[] = {reinterpret_cast<const void*>(&refine_kernel<1, false, Waves::SCAN>),
+                     reinterpret_cast<const void*>(&refine_kernel<1, true, Waves::SCAN>),
+                     reinterpret_cast<const void*>(&refine_kernel<2, false, Waves::SCAN>),
+                     reinterpret_cast<const void*>(&refine_kernel<2, true, Waves::SCAN>)};
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -2554,33 +3081,28 @@ hipError_t launch_refine(const Problem& p, const Workspace& w, const pinmpc_sett
   // buffers, the summaries and the boundary values
   const int W = s.scan > 1 ? s.scan : 1;
   const size_t lds = scan_lds_bytes(W);
-#define PINMPC_REFINE(PH, L, SC)                                                               \
-  hipLaunchKernelGGL((refine_kernel<PH, L, SC>), dim3(p.batch), dim3(64 * W), lds, st, p, w,     \
-                     out.u, out.x, out.res, out.iters, out.status, out.detail, s.iters, s.accel, \
-                     s.refine, s.refine_passes, s.ipm_iters, s.polish_passes, s.kkt_tol,        \
+#define PINMPC_REFINE(PH, L, WV, T)                                                               \
+  hipLaunchKernelGGL((refine_kernel<PH, L, Waves::WV>), dim3(p.batch), dim3(T), lds, st, p, w,     \
+                     out.u, out.x, out.res, out.iters, out.status, out.detail, s.iters, s.accel,   \
+                     s.refine, s.refine_passes, s.ipm_iters, s.polish_passes, s.kkt_tol,           \
                      s.first_passes)
+#define PINMPC_REFINE_L(PH, WV, T)              \
+  do {                                          \
+    if (lng) PINMPC_REFINE(PH, true, WV, T);    \
+    else PINMPC_REFINE(PH, false, WV, T);       \
+  } while (0)
   // horizons beyond PINMPC_NMAX keep the rollout's and the costates' stage
   // buffers in the scratch block (refine_block_doubles sizes it so)
   const bool lng = p.n_max > PINMPC_NMAX;
-  for (int ph = 1; ph <= (second ? 2 : 1); ++ph) {
-    if (ph == 1) {
-      if (W > 1) {
-        if (lng) PINMPC_REFINE(1, true, true);
-        else PINMPC_REFINE(1, false, true);
-      } else {
-        if (lng) PINMPC_REFINE(1, true, false);
-        else PINMPC_REFINE(1, false, false);
-      }
-    } else {
-      if (W > 1) {
-        if (lng) PINMPC_REFINE(2, true, true);
-        else PINMPC_REFINE(2, false, true);
-      } else {
-        if (lng) PINMPC_REFINE(2, true, false);
-        else PINMPC_REFINE(2, false, false);
-      }
-    }
+  if (W > 1) {
+    PINMPC_REFINE_L(1, SCAN, 64 * W);
+    if (second) PINMPC_REFINE_L(2, SCAN, 64 * W);
+  } else {
+    if (p.batch <= PAIR_BATCH) PINMPC_REFINE_L(1, PAIR, 128);
+    else PINMPC_REFINE_L(1, ONE, 64);
+    if (second) PINMPC_REFINE_L(2, PAIR, 128);
   }
+#undef PINMPC_REFINE_L
 #undef PINMPC_REFINE
   return hipGetLastError();
 }

@@ -43,6 +43,15 @@ __device__ inline void gsync() {
 __device__ inline bool scalar(bool c) { return __builtin_amdgcn_readfirstlane((int)c) != 0; }
 // lane within the wave (the workgroup may hold several waves)
 __device__ inline int lane_id() { return (int)(threadIdx.x & 63); }
+// The lane in a register of its own.  What a phase derives from it (offsets,
+// masks) stays with the phase: found equal to another phase's and kept in
+// registers across the whole kernel it is spilled, and its reload between the
+// loads of a stage waits for them.
+__device__ inline int fresh_lane() {
+  int l = lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
 
 // Reductions over the wave without LDS: the DPP permutations (quads, half rows,
 // rows) and the row and half-wave swaps, every lane ending with the result.
@@ -259,11 +268,11 @@ __device__ inline int t_offset(int r, int c) {
 struct SymWeights {
   d4 own, other;
 };
-__device__ inline SymWeights sym_weights() {
+__device__ inline SymWeights sym_weights(int lane = lane_id()) {
   SymWeights w;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int r = 4 * q + tg(), c = tj();
+    const int r = 4 * q + (lane >> 4), c = lane & 15;
     w.own[q] = (r < NX && c < NX) ? 0.5 : ((c == VC && r < NX) ? 1.0 : 0.0);
     w.other[q] = (r < NX && c < NX) ? 0.5 : ((r == VC && c < NX) ? 1.0 : 0.0);
   }
@@ -271,8 +280,8 @@ __device__ inline SymWeights sym_weights() {
 }
 // S so symmetrised (its rounding is not symmetric, and an asymmetric part is
 // carried back through the open-loop A and grows along the horizon).
-__device__ inline d4 symmetrize(d4 S, const SymWeights& w, double* buf) {
-  const int g = tg(), j = tj();
+__device__ inline d4 symmetrize(d4 S, const SymWeights& w, double* buf, int lane = lane_id()) {
+  const int g = lane >> 4, j = lane & 15;
 #pragma unroll
   for (int q = 0; q < 4; ++q) buf[(4 * q + g) * 17 + j] = S[q];
   wsync();
