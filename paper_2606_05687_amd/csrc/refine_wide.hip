@@ -139,14 +139,54 @@ __device__ inline void str(gd p, int rs, int e, const double v[NROW]) {
   for (int r = 0; r < NROW; ++r) p[r * rs + e] = v[r];
 }
 
+// The passes over the rows (one lane per contact-stage) load all they need before
+// any branch on it: each trip to memory costs about as much as a pass's
+// arithmetic, and a load under `if (u_ref)` or `if (stance)` is one more (six for
+// the components of u_ref).
+__device__ inline __amdgpu_buffer_rsrc_t uref_buf(const WCtx& C) {
+  const gcf p = uni(C.u_ref);   // none: an empty buffer, which reads as zeros
+  return rsrc(p ? p : uni(C.A), p ? C.N * U4 * 4 : 0);
+}
+struct RowLoads {
+  bool on;
+  double u[6], s[NROW], z[NROW];
+  float ur[6];
+};
+__device__ inline void load_rows(const WCtx& C, __amdgpu_buffer_rsrc_t rR, int rs, int e,
+                                 RowLoads& w) {
+  w.on = uni(C.contact)[e] != 0;
+  ldf3(rR, e * 24, 0, w.ur);
+  ldf3(rR, e * 24 + 12, 0, w.ur + 3);
+  ld6(uni(C.u) + e * 6, w.u);
+  ldr(uni(C.s), rs, e, w.s);
+  ldr(uni(C.z), rs, e, w.z);
+}
+__device__ inline void pin_rows(const RowLoads& w) {
+#pragma unroll
+  for (int r = 0; r < NROW; ++r) {
+    pin(w.s[r]);
+    pin(w.z[r]);
+  }
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    pin(w.u[t]);
+    asm volatile("" ::"v"(w.ur[t]));
+  }
+  pin_memory();
+}
+
 // Stage inputs of the Newton step, in parallel over (stage, contact): the R'
 // block and rho of every contact at the affine target s z (identity and zero on
 // a swing contact), and the state cost gradients q.
 __device__ inline void build_terms(const WCtx& C, WSh& sh) {
   const int rs = C4 * C.n;
+  const auto rR = uref_buf(C);
   __syncthreads();
-  for (int e = lane_id(); e < C.N * C4; e += W64) {
-    const int k = e / C4, i = e % C4;
+  for (int e = fresh_lane(); e < C.N * C4; e += W64) {
+    const int i = e % C4;
+    RowLoads w;
+    load_rows(C, rR, rs, e, w);
+    pin_rows(w);
     InputBlock t;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -156,16 +196,12 @@ __device__ inline void build_terms(const WCtx& C, WSh& sh) {
     }
 #pragma unroll
     for (int a = 0; a < 6; ++a) t.v[a] = 0.0;
-    const bool on = stance(C, k, i);
-    if (on) {
-      double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], d[NROW], c[NROW];
-      ld6(C.u + (size_t)k * U4 + 6 * i, u);
-      ldr(C.s, rs, e, sv);
-      ldr(C.z, rs, e, zv);
-      rows_of(C, u, gu, h, isc);
+    if (w.on) {
+      double gu[NROW], h[NROW], isc[NROW], d[NROW], c[NROW];
+      rows_of(C, w.u, gu, h, isc);
 #pragma unroll
       for (int r = 0; r < NROW; ++r) {
-        const double rp = fma(gu[r] - h[r], isc[r], sv[r]), zs = zv[r] * recip(sv[r]);
+        const double rp = fma(gu[r] - h[r], isc[r], w.s[r]), zs = w.z[r] * recip(w.s[r]);
         d[r] = zs * (isc[r] * isc[r]);
         c[r] = zs * rp * isc[r];
       }
@@ -175,8 +211,7 @@ __device__ inline void build_terms(const WCtx& C, WSh& sh) {
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
         const int j = 6 * i + a;
-        const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + j] : 0.0;
-        t.v[a] = fma(sh.R[j], u[a] - ur, rho[a]);
+        t.v[a] = fma(sh.R[j], w.u[a] - (double)w.ur[a], rho[a]);
       }
       t.m[0][0] = d[0] + d[1] + sh.R[6 * i];
       t.m[0][1] = t.m[1][0] = 0.0;
@@ -187,11 +222,28 @@ __device__ inline void build_terms(const WCtx& C, WSh& sh) {
 #pragma unroll
       for (int a = 0; a < 3; ++a) t.d[a] = d[5 + a] + d[8 + a] + sh.R[6 * i + 3 + a];
     }
-    reinterpret_cast<uint8_t*>(sh.unit)[e] = on ? 0 : 0x3F;
+    reinterpret_cast<uint8_t*>(sh.unit)[e] = w.on ? 0 : 0x3F;
     store_block(C.T + (size_t)e * 18, t);
   }
-  for (int e = lane_id(); e < C.N * NX; e += W64)
-    C.q[e] = sh.Q[e % NX] * (C.x[NX + e] - (double)C.x_ref[e]);
+  const int nx = C.N * NX;
+  const gd pq = uni(C.q), px = uni(C.x);
+  const gcf pr = uni(C.x_ref);
+  for (int e0 = fresh_lane(); e0 < nx; e0 += 8 * W64) {
+    double x[8];
+    float xr[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * W64 < nx ? e0 + t * W64 : e0;
+      x[t] = px[NX + e];
+      xr[t] = pr[e];
+    }
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * W64;
+      if (e < nx) pq[e] = sh.Q[e % NX] * (x[t] - (double)xr[t]);
+    }
+  }
   __syncthreads();
 }
 
@@ -230,8 +282,8 @@ struct WideRaw {
 // Backward recursion of the Newton step, stages N-1 .. 0: gains, feedforward and
 // factors of every stage into the scratch.  Tiles are homogeneous (row and
 // column VC carry the linear terms), as in the two-contact recursion.
-__device__ __attribute__((noinline)) void backward(const WCtx& C, WSh& sh) {
-  const int lane = lane_id(), g = tg(), j = tj();
+__device__ __attribute__((always_inline)) inline void backward(const WCtx& C, WSh& sh) {
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
   const auto rQ = rsrc(uni(C.q), N * NX * 8), rT = rsrc(uni(C.T), N * WT * 8);
@@ -424,10 +476,10 @@ __device__ __attribute__((noinline)) void backward(const WCtx& C, WSh& sh) {
 // dx_{k+1} = A_k dx_k + B_k du_k (into PV).  VECK: kap_k from GV (a corrector's)
 // instead of the stored gains.
 template <bool VECK>
-__device__ __attribute__((noinline)) void forward(const WCtx& C, WSh& sh) {
+__device__ __attribute__((always_inline)) inline void forward(const WCtx& C, WSh& sh) {
   __syncthreads();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   double* const PV = sh.c.PV;
   double* const GV = sh.c.GV;
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
@@ -506,9 +558,9 @@ __device__ __attribute__((noinline)) void forward(const WCtx& C, WSh& sh) {
 // recursion of the linear part, s <- A^T wv + K^T hw with wv = q + s and
 // hw = B^T wv + rho, is a chain; the feedforwards kap = -H^{-1} hw then follow
 // four stages at a time, by block triangular solves with Ua, Tab and Ub.
-__device__ __attribute__((noinline)) void newton_vector(const WCtx& C, WSh& sh) {
+__device__ __attribute__((always_inline)) inline void newton_vector(const WCtx& C, WSh& sh) {
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   double* const GV = sh.c.GV;
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
   const auto rK = rsrc(uni(C.K), N * WK * 8), rQ = rsrc(uni(C.q), N * NX * 8);
@@ -675,7 +727,7 @@ __device__ inline double dot_half(double u, const float (&b)[NU], double s) {
 __device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
   __syncthreads();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   double* const PV = sh.c.PV;
   const gcf pe = uni(C.e), pA = uni(C.A);
   const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
@@ -696,7 +748,7 @@ __device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
   }
   wsync();
   const int oA = j < NX ? (j * NX + 3 * g) * 4 : OOB;
-  constexpr int RD = 4;
+  constexpr int RD = 8;
   float ring[RD][4];
 #pragma unroll
   for (int d = 0; d < RD; ++d) {
@@ -718,7 +770,7 @@ __device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
     xv = row_total(dot4(turn_rows(xv), a, 0.0)) + t;
     if (lane < NX) PV[k * NX + j] = xv;
   };
-  static_assert(RD == 4, "one line below per ring slot");
+  static_assert(RD == 8, "one line below per ring slot");
   for (int k = 0;; k += RD) {
     if (!(k < N)) break;
     step(k, ring[0]);
@@ -728,31 +780,58 @@ __device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
     step(k + 2, ring[2]);
     if (!(k + 3 < N)) break;
     step(k + 3, ring[3]);
+    if (!(k + 4 < N)) break;
+    step(k + 4, ring[4]);
+    if (!(k + 5 < N)) break;
+    step(k + 5, ring[5]);
+    if (!(k + 6 < N)) break;
+    step(k + 6, ring[6]);
+    if (!(k + 7 < N)) break;
+    step(k + 7, ring[7]);
   }
   wsync();
-  for (int e = lane; e < N * NX; e += W64) C.x[NX + e] = PV[e];
+  for (int e = fresh_lane(); e < N * NX; e += W64) C.x[NX + e] = PV[e];
   __syncthreads();
 }
 
 // Dynamics residual of the FP64 trajectory (x, u), normalised by the largest
 // term of each entry.
 __device__ __attribute__((noinline)) double dyn_residual(const WCtx& C) {
+  // four stages at a time (one per 16-lane row, state j in lane j)
+  const int g = tg(), j = tj();
+  const int N = __builtin_amdgcn_readfirstlane(C.N);
+  const gcf pe = uni(C.e), pA = uni(C.A);
+  const auto rA = rsrc(pA, N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
+  const auto rE = rsrc(pe ? pe : pA, pe ? N * NX * 4 : 0);
+  const auto rU = rsrc(uni(C.u), N * U4 * 8), rX = rsrc(uni(C.x), (N + 1) * NX * 8);
+  const int oA = j < NX ? (g * NX + j) * NX * 4 : OOB, oB = j < NX ? (g * NX + j) * U4 * 4 : OOB;
+  const int oX = j < NX ? (g * NX + j) * 8 : OOB, oU = j < NU ? (g * U4 + j) * 8 : OOB;
+  const int oE = j < NX ? (g * NX + j) * 4 : OOB;
   double r = 0.0;
-  for (int e = lane_id(); e < C.N * NX; e += W64) {
-    const int k = e / NX, i = e % NX;
-    gcd x = C.x + k * NX;
-    gcd u = C.u + k * U4;
-    gcf A = C.A + (size_t)k * NX * NX + i * NX;
-    gcf B = C.B + (size_t)k * NX * U4 + i * U4;
-    double ax = 0.0, bu = 0.0;
+  for (int k0 = 0; k0 < N; k0 += 4) {
+    float a[NX], ba[NU], bb[NU];
 #pragma unroll
-    for (int l = 0; l < NX; ++l) ax += (double)A[l] * x[l];
+    for (int l = 0; l < NU; l += 4) {
+      ldf4(rA, oA + l * 4, k0 * (NX * NX * 4), a + l);
+      ldf4(rB, oB + l * 4, k0 * (NX * U4 * 4), ba + l);
+      ldf4(rB, oB + (NU + l) * 4, k0 * (NX * U4 * 4), bb + l);
+    }
+    a[NU] = ldf(rA, oA + NU * 4, k0 * (NX * NX * 4));
+    const double ee = (double)ldf(rE, oE, k0 * (NX * 4));
+    const double x = ldd(rX, oX, k0 * (NX * 8)), xn = ldd(rX, oX + NX * 8, k0 * (NX * 8));
+    const double ua = ldd(rU, oU, k0 * (U4 * 8)), ub = ldd(rU, oU + NU * 8, k0 * (U4 * 8));
+    double ad[NX], bd[NX], cd[NX];
 #pragma unroll
-    for (int l = 0; l < U4; ++l) bu += (double)B[l] * u[l];
-    const double ee = C.e ? (double)C.e[k * NX + i] : 0.0;
-    const double d = x[NX + i] - ax - bu - ee;
-    const double den = 1.0 + fmax(fabs(x[NX + i]), fmax(fabs(ax), fabs(bu)));
-    r = fmax(r, fabs(d) / den);
+    for (int l = 0; l < NX; ++l) {
+      ad[l] = (double)a[l];
+      bd[l] = l < NU ? (double)ba[l < NU ? l : 0] : 0.0;
+      cd[l] = l < NU ? (double)bb[l < NU ? l : 0] : 0.0;
+    }
+    const double ax = dot_row_bcast13(x, ad, 0.0);
+    const double bu = dot_row_bcast13(ub, cd, dot_row_bcast13(ua, bd, 0.0));
+    const double d = xn - ax - bu - ee;
+    const double den = 1.0 + fmax(fabs(xn), fmax(fabs(ax), fabs(bu)));
+    if (j < NX && k0 + g < N) r = fmax(r, fabs(d) / den);
   }
   return wave_max(r);
 }
@@ -850,11 +929,21 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
   rollout(C, sh);
   res[0] = dyn_residual(C);
   const int N = __builtin_amdgcn_readfirstlane(C.N);
-  const int lane = lane_id(), g = tg(), j = tj();
+  const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
   double* const PV = sh.c.PV;
   double* const GV = sh.c.GV;
-  for (int e = lane; e < N * NX; e += W64)
-    PV[e] = sh.Q[e % NX] * (PV[e] - (double)C.x_ref[e]);
+  const gcf pr = uni(C.x_ref);
+  for (int e0 = fresh_lane(); e0 < N * NX; e0 += 8 * W64) {
+    float xr[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) xr[t] = pr[e0 + t * W64 < N * NX ? e0 + t * W64 : e0];
+    pin_memory();
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * W64;
+      if (e < N * NX) PV[e] = sh.Q[e % NX] * (PV[e] - (double)xr[t]);
+    }
+  }
   wsync();
   // costates, backwards: p_{k+1} = Q (x_{k+1} - r_k) + A_{k+1}^T p_{k+2}
   const auto rA = rsrc(uni(C.A), N * NX * NX * 4), rB = rsrc(uni(C.B), N * NX * U4 * 4);
@@ -865,7 +954,7 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
 #pragma unroll
     for (int q = 1; q < 4; ++q) s[q] = ldf(rA, oA + q * NX * 4, at);
   };
-  constexpr int CD = 4;
+  constexpr int CD = 8;
   float ring[CD][4];
 #pragma unroll
   for (int d = 0; d < CD; ++d) {
@@ -888,7 +977,7 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
     terms = fmax(terms, fmax(fabs(qx), fmax(fabs(p), fabs(ap))));
     if (lane < NX) PV[k * NX + j] = p;
   };
-  static_assert(CD == 4, "one line below per ring slot");
+  static_assert(CD == 8, "one line below per ring slot");
   for (int k = N - 1;; k -= CD) {
     if (!(k >= 0)) break;
     step(k, ring[0]);
@@ -898,6 +987,14 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
     step(k - 2, ring[2]);
     if (!(k - 3 >= 0)) break;
     step(k - 3, ring[3]);
+    if (!(k - 4 >= 0)) break;
+    step(k - 4, ring[4]);
+    if (!(k - 5 >= 0)) break;
+    step(k - 5, ring[5]);
+    if (!(k - 6 >= 0)) break;
+    step(k - 6, ring[6]);
+    if (!(k - 7 >= 0)) break;
+    step(k - 7, ring[7]);
   }
   wsync();
   // B^T p, four stages at a time
@@ -920,11 +1017,22 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
   wsync();
   // per (stage, contact): gradient, multipliers, feasibility, complementarity
   double stat = 0.0, rin = 0.0, mmax = 0.0, comp = 0.0;
-  for (int e = lane; e < N * C4; e += W64) {
+  const auto rR = uref_buf(C);
+  for (int e = fresh_lane(); e < N * C4; e += W64) {
     const int k = e / C4, i = e % C4;
     double u[6];
-    ld6(C.u + (size_t)k * U4 + 6 * i, u);
-    if (!stance(C, k, i)) {
+    float ur[6];
+    const bool on = uni(C.contact)[e] != 0;
+    ldf3(rR, e * 24, 0, ur);
+    ldf3(rR, e * 24 + 12, 0, ur + 3);
+    ld6(uni(C.u) + e * 6, u);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      pin(u[t]);
+      asm volatile("" ::"v"(ur[t]));
+    }
+    pin_memory();
+    if (!on) {
 #pragma unroll
       for (int t = 0; t < 6; ++t) rin = fmax(rin, fabs(u[t]) / C.mg);
       continue;
@@ -935,8 +1043,7 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
       const int jj = 6 * i + t;
-      const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + jj] : 0.0;
-      const double ru = sh.R[jj] * (u[t] - ur), bl = GV[k * U4 + jj];
+      const double ru = sh.R[jj] * (u[t] - (double)ur[t]), bl = GV[k * U4 + jj];
       tr = fmax(tr, fabs(ru));
       tb = fmax(tb, fabs(bl));
       gr[t] = ru + bl;
@@ -987,16 +1094,16 @@ __device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
 
 // Interior point from the current u (its rollout in x).  Returns the
 // iterations; *ok tells whether the certificate was met (then res is it).
-__device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, double tol,
+__device__ __attribute__((always_inline)) inline int ipm(const WCtx& C, WSh& sh, int maxit, double tol,
                                             double res[PINMPC_NRES], bool* ok) {
-  const int lane = lane_id(), N = C.N, rs = C4 * C.n;
+  const int N = C.N, rs = C4 * C.n;
   double* const PV = sh.c.PV;
   double* const GV = sh.c.GV;
   *ok = false;
   // rows of stance contacts, starting slacks (at least 1) and multipliers 1
   double mloc = 0.0, smz = 0.0, rpn = 0.0;
   __syncthreads();
-  for (int e = lane; e < N * C4; e += W64) {
+  for (int e = fresh_lane(); e < N * C4; e += W64) {
     const int k = e / C4, i = e % C4;
     if (!stance(C, k, i)) continue;
     double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW];
@@ -1036,16 +1143,18 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
       // its row steps, the largest step to the boundary, and the sums that give
       // the complementarity after any step
       double amax = 1.0, sm1 = 0.0, sm2 = 0.0;
-      for (int e = lane; e < N * C4; e += W64) {
+      const auto rR = uref_buf(C);
+      for (int e = fresh_lane(); e < N * C4; e += W64) {
         const int k = e / C4, i = e % C4;
-        if (!stance(C, k, i)) continue;
-        double u[6], du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
-        ld6(C.u + (size_t)k * U4 + 6 * i, u);
+        RowLoads w;
+        load_rows(C, rR, rs, e, w);
+        pin_rows(w);
+        if (!w.on) continue;
+        double du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], cv[NROW];
+        const double(&sv)[NROW] = w.s, (&zv)[NROW] = w.z;
 #pragma unroll
         for (int t = 0; t < 6; ++t) du[t] = GV[k * U4 + 6 * i + t];
-        ldr(C.s, rs, e, sv);
-        ldr(C.z, rs, e, zv);
-        rows_of(C, u, gu, h, isc);
+        rows_of(C, w.u, gu, h, isc);
         rows_of(C, du, gdu, h, isc);
 #pragma unroll
         for (int r = 0; r < NROW; ++r) {
@@ -1067,16 +1176,19 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
       // its linear input term, the recursion's vector part and the rollout with
       // the predictor's factors (triangular solves, as accurate near the optimum
       // as factoring again; a product with the inverse is not)
-      for (int e = lane; e < N * C4; e += W64) {
+      for (int e = fresh_lane(); e < N * C4; e += W64) {
         const int k = e / C4, i = e % C4;
-        double rho[6] = {0, 0, 0, 0, 0, 0};
-        if (stance(C, k, i)) {
-          double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW], c[NROW];
-          ld6(C.u + (size_t)k * U4 + 6 * i, u);
-          ldr(C.s, rs, e, sv);
-          ldr(C.z, rs, e, zv);
-          ldr(C.rc, rs, e, cv);
-          rows_of(C, u, gu, h, isc);
+        double rho[6] = {0, 0, 0, 0, 0, 0}, cv[NROW];
+        RowLoads w;
+        load_rows(C, rR, rs, e, w);
+        ldr(uni(C.rc), rs, e, cv);
+#pragma unroll
+        for (int r = 0; r < NROW; ++r) pin(cv[r]);
+        pin_rows(w);
+        if (w.on) {
+          double gu[NROW], h[NROW], isc[NROW], c[NROW];
+          const double(&sv)[NROW] = w.s, (&zv)[NROW] = w.z;
+          rows_of(C, w.u, gu, h, isc);
 #pragma unroll
           for (int r = 0; r < NROW; ++r) {
             cv[r] -= smu;
@@ -1088,8 +1200,7 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
 #pragma unroll
           for (int t = 0; t < 6; ++t) {
             const int jj = 6 * i + t;
-            const double ur = C.u_ref ? (double)C.u_ref[(size_t)k * U4 + jj] : 0.0;
-            rho[t] = fma(sh.R[jj], u[t] - ur, rho[t]);
+            rho[t] = fma(sh.R[jj], w.u[t] - (double)w.ur[t], rho[t]);
           }
         }
 #pragma unroll
@@ -1100,17 +1211,20 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
       forward<true>(C, sh);
       // the step's rows, and its length
       amax = 1.0;
-      for (int e = lane; e < N * C4; e += W64) {
+      for (int e = fresh_lane(); e < N * C4; e += W64) {
         const int k = e / C4, i = e % C4;
-        if (!stance(C, k, i)) continue;
-        double u[6], du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], cv[NROW];
-        ld6(C.u + (size_t)k * U4 + 6 * i, u);
+        RowLoads w;
+        double du[6], gu[NROW], gdu[NROW], h[NROW], isc[NROW], cv[NROW];
+        load_rows(C, rR, rs, e, w);
+        ldr(uni(C.rc), rs, e, cv);
+#pragma unroll
+        for (int r = 0; r < NROW; ++r) pin(cv[r]);
+        pin_rows(w);
+        if (!w.on) continue;
+        const double(&sv)[NROW] = w.s, (&zv)[NROW] = w.z;
 #pragma unroll
         for (int t = 0; t < 6; ++t) du[t] = GV[k * U4 + 6 * i + t];
-        ldr(C.s, rs, e, sv);
-        ldr(C.z, rs, e, zv);
-        ldr(C.rc, rs, e, cv);
-        rows_of(C, u, gu, h, isc);
+        rows_of(C, w.u, gu, h, isc);
         rows_of(C, du, gdu, h, isc);
         double dsv[NROW], dzv[NROW];
 #pragma unroll
@@ -1130,21 +1244,30 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
     // contact-stage; swing inputs stay 0)
     smz = 0.0;
     rpn = 0.0;
-    for (int e = lane; e < N * C4; e += W64) {
+    for (int e = fresh_lane(); e < N * C4; e += W64) {
       const int k = e / C4, i = e % C4;
-      if (!stance(C, k, i)) continue;
       double u[6], gu[NROW], h[NROW], isc[NROW], sv[NROW], zv[NROW], dsv[NROW], dzv[NROW];
-      ld6(C.u + (size_t)k * U4 + 6 * i, u);
+      const bool on = uni(C.contact)[e] != 0;
+      ld6(uni(C.u) + e * 6, u);
+      ldr(uni(C.s), rs, e, sv);
+      ldr(uni(C.z), rs, e, zv);
+      ldr(uni(C.ds), rs, e, dsv);
+      ldr(uni(C.dz), rs, e, dzv);
+#pragma unroll
+      for (int r = 0; r < NROW; ++r) {
+        pin(sv[r]);
+        pin(zv[r]);
+        pin(dsv[r]);
+        pin(dzv[r]);
+      }
+      pin_memory();
+      if (!on) continue;
 #pragma unroll
       for (int t = 0; t < 6; ++t) {
         u[t] += a * GV[k * U4 + 6 * i + t];
         C.u[(size_t)k * U4 + 6 * i + t] = u[t];
       }
       rows_of(C, u, gu, h, isc);
-      ldr(C.s, rs, e, sv);
-      ldr(C.z, rs, e, zv);
-      ldr(C.ds, rs, e, dsv);
-      ldr(C.dz, rs, e, dzv);
 #pragma unroll
       for (int r = 0; r < NROW; ++r) {
         sv[r] += a * dsv[r];
@@ -1155,7 +1278,18 @@ __device__ __attribute__((noinline)) int ipm(const WCtx& C, WSh& sh, int maxit, 
       str(C.s, rs, e, sv);
       str(C.z, rs, e, zv);
     }
-    for (int e = lane; e < N * NX; e += W64) C.x[NX + e] += a * PV[e];
+    const gd px = uni(C.x);
+    for (int e0 = fresh_lane(); e0 < N * NX; e0 += 8 * W64) {
+      double x[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] = px[NX + (e0 + t * W64 < N * NX ? e0 + t * W64 : e0)];
+      pin_memory();
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int e = e0 + t * W64;
+        if (e < N * NX) px[NX + e] = x[t] + a * PV[e];
+      }
+    }
     wsync();
   }
   *ok = certificate(C, sh, res, tol) <= tol;
@@ -1229,8 +1363,8 @@ __global__ void __launch_bounds__(64, 2) refine_wide_kernel(Problem p, Workspace
   }
   const size_t ux = (size_t)C.b * C.n * U4, xx = (size_t)C.b * (C.n + 1) * NX;
   if (bad || nonfinite) {
-    for (int e = lane; e < C.n * U4; e += 64) out_u[ux + e] = 0.f;
-    for (int e = lane; e < (C.n + 1) * NX; e += 64) out_x[xx + e] = 0.f;
+    for (int e = fresh_lane(); e < C.n * U4; e += 64) out_u[ux + e] = 0.f;
+    for (int e = fresh_lane(); e < (C.n + 1) * NX; e += 64) out_x[xx + e] = 0.f;
     if (lane == 0) {
       if (out_status) out_status[C.b] = bad ? PINMPC_ST_BADINPUT : PINMPC_ST_NONFINITE;
       if (out_iters) out_iters[C.b] = 0;
@@ -1243,7 +1377,7 @@ __global__ void __launch_bounds__(64, 2) refine_wide_kernel(Problem p, Workspace
   // the ADMM point: unscaled inputs of the z iterate, zero on swing contacts
   const float* zsrc = (accel ? ws.cur : ws.hat) + s0 * NSTATE * L4;
   const float tsc = ws.tsc[C.b];
-  for (int e = lane; e < N * U4; e += 64) {
+  for (int e = fresh_lane(); e < N * U4; e += 64) {
     const int k = e / U4, j = e % U4;
     const double sc = (j % 6 < 3) ? (double)ws.sf[s0 + k] : (double)tsc;
     const double v = (double)zsrc[(size_t)k * NSTATE * L4 + NX + j] * sc;
@@ -1262,8 +1396,8 @@ __global__ void __launch_bounds__(64, 2) refine_wide_kernel(Problem p, Workspace
 
   // outputs
   __syncthreads();
-  for (int e = lane; e < C.n * U4; e += 64) out_u[ux + e] = (e < N * U4) ? (float)C.u[e] : 0.f;
-  for (int e = lane; e < (C.n + 1) * NX; e += 64)
+  for (int e = fresh_lane(); e < C.n * U4; e += 64) out_u[ux + e] = (e < N * U4) ? (float)C.u[e] : 0.f;
+  for (int e = fresh_lane(); e < (C.n + 1) * NX; e += 64)
     out_x[xx + e] = (e < (N + 1) * NX) ? (float)C.x[e] : 0.f;
   if (lane == 0) {
     atomicAdd(ws.work, (unsigned long long)its * (unsigned long long)N);
