@@ -56,26 +56,31 @@ REFINE_DENSE_FORWARD = 1250 + 650 + 500
 # interior-point iteration: two backward recursions, the predictor's a
 # factorisation of the stage system (W B 8112, W A 4394, B^T W B 14976, B^T W A
 # 8112, B^T w 624, Gauss-Jordan on the 24 x 38 system 41952, S and s 13468:
-# 91 638), the corrector's the vector part with the kept inverse (B^T w 624,
-# H^-1 hw 1152, A^T w 338, Hwx^T kappa 624: 2738) except near the optimum, where
-# it factors again; and two rollouts of the gains (1586 each).  The kernel
+# 91 638), the corrector's the vector part with the kept factors (B^T w 624,
+# triangular solves 1152, A^T w 338, K^T hw 624: 2738); and two rollouts of the
+# gains (1586 each).  The kernel
 # reports the stages its factoring recursions covered, so the flops of a solve
 # are counted from that mix.  Bytes: the iteration's data flow, each array crossing HBM once
 # per phase that uses it: the factorisation reads A, B (FP32), the stage terms
-# and x, and writes K, kappa, H^-1 and Hwx (13 216 B); the corrector's vector
-# pass reads B, A, rho, x, H^-1 and Hwx and writes kappa (9568 B); two rollouts
+# and q, and writes the gains and the factors of H (8748 B); the corrector's
+# vector pass reads A, B, rho, q, gains and factors and writes kappa (8556 B); two rollouts
 # of the gains (4908 B each); two builds of the stage terms (2592 B each); two
 # slack and multiplier steps (2144 B each); the step and the next residuals
 # (3736 B); the corrector's target (1760 B)
 WIDE_FACTOR_FLOPS = 8112 + 4394 + 14976 + 8112 + 624 + 41952 + 13468
 WIDE_VECTOR_FLOPS = 624 + 1152 + 338 + 624
 WIDE_ROLLOUT_FLOPS = 1586
-WIDE_BYTES_PER_IPM_STAGE = 13216 + 9568 + 2 * 4908 + 2 * 2592 + 2 * 2144 + 3736 + 1760
+WIDE_BYTES_PER_IPM_STAGE = 8748 + 8556 + 2 * 4908 + 2 * 2592 + 2 * 2144 + 3736 + 1760
 # its sweep per stage: operators A 676 + Bt 1248 + H packed 2812 + M packed
 # 1200 + qbar 148 + e 52 + contact 4 + force scale 4 = 6144 B read, iterates
 # (5 x 37 each) 1480 B read + 1480 B written; setup per stage: A_k, A_{k+1},
 # B_k, B_{k+1} read (3848 B), Bt, H, M, qbar written (5408 B)
 WIDE_SWEEP_BYTES_PER_STAGE = 6144 + 2960
+# and its flops: H 37 x 37, four 13 x 13, three 13 x 24, M 24 x 24 products, and
+# about 20 per entry beside them
+WIDE_SWEEP_FLOPS_PER_STAGE = 2 * (37 * 37 + 4 * 13 * 13 + 3 * 13 * 24 + 24 * 24) + 20 * 37
+# longest horizons of the fused sweep (two, four contacts); beyond them the sweep streams
+FUSED_STAGES = (40, 27)
 WIDE_SETUP_BYTES_PER_STAGE = 3848 + 5408
 # setup, once per stage: operators read, H, M, qbar and the scaled B written
 SETUP_BYTES_PER_STAGE = 3_200
@@ -239,9 +244,12 @@ KERNEL_SOURCES = {
 
 
 def _kernel_sha(path):
-    """Hash of a kernel's source together with the shared internal header."""
+    """Hash of a kernel's source together with the headers it shares."""
     h = hashlib.sha256()
-    for f in (path, os.path.join(os.path.dirname(path), "pinmpc_internal.h")):
+    shared = ["pinmpc_internal.h"]
+    if os.path.basename(path).startswith("refine"):
+        shared.append("refine_tiles.h")
+    for f in [path] + [os.path.join(os.path.dirname(path), n) for n in shared]:
         with open(f, "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -694,10 +702,12 @@ def main():
             "frac_finished_in_second_launch": float((det[:, 3] == 2).mean()),
             "stages_factored_per_equality_pass": float(stf.sum() / max(1, eq_p.sum())),
             "dense_flops_per_solve": dense_flops}
-    # four contacts take the streamed sweep whatever the form (all sweeps in one
-    # launch unless the form is 0)
-    form_name = ("streamed" if wide and settings["form"] != 0 else
-                 {0: "plain", 1: "fused", -1: "packed", 2: "split"}[settings["form"]])
+    # forms 0 and 1 are the same: fused where it fits, else streamed, all sweeps
+    # in one launch either way
+    streamed = settings["form"] in (0, 1) and int(batch["A"].shape[1]) > FUSED_STAGES[wide]
+    form_name = ("streamed" if streamed else
+                 {0: "fused", 1: "fused", -1: "packed", 2: "split"}[settings["form"]])
+    sweep_f = WIDE_SWEEP_FLOPS_PER_STAGE if wide else SWEEP_FLOPS_PER_STAGE
     kernels = {
         "setup_kernel": {"ms": setup_ms},
         "admm": {"ms": admm_ms, "form": form_name},
@@ -711,11 +721,11 @@ def main():
     kernels["refine_kernel"]["tflops"] = refine_flops / (refine_ms * 1e-3) / 1e12
     kernels["refine_kernel"]["gbs"] = refine_bytes / (refine_ms * 1e-3) / 1e9
     kernels["refine_kernel"]["dense_tflops"] = dense_flops / (refine_ms * 1e-3) / 1e12
-    if settings["form"] == 0 or wide:
+    if streamed:
         sweep_bytes = stages * sweep_b
         kernels["admm"]["gbs"] = sweep_bytes * K / (admm_ms * 1e-3) / 1e9
     else:
-        kernels["admm"]["tflops"] = stages * SWEEP_FLOPS_PER_STAGE * K / (admm_ms * 1e-3) / 1e12
+        kernels["admm"]["tflops"] = stages * sweep_f * K / (admm_ms * 1e-3) / 1e12
     dominant = max(kernels, key=lambda k: kernels[k]["ms"])
     if dominant == "refine_kernel":
         kname = "refine_wide_kernel" if wide else "refine_kernel"
@@ -733,20 +743,20 @@ def main():
                 "hbm_gbs": kernels["refine_kernel"]["gbs"],
                 "hbm_frac": kernels["refine_kernel"]["gbs"] / HBM_PEAK_GBS,
                 "bytes_per_pass_stage": bytes_ps, "dtype": "f64"}
-    elif dominant == "admm" and (settings["form"] == 0 or wide):
+    elif dominant == "admm" and streamed:
         src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", "admm_plain.hip")
         achieved = kernels["admm"]["gbs"]
         roof = {"kernel": "admm_sweep_kernel", "bound": "hbm", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": measured_traffic(src, "admm_sweep_kernel"),
-                "launch_ms": admm_ms / max(1, K), "bytes_per_launch": stages * sweep_b}
+                "launch_ms": admm_ms, "bytes_per_launch": stages * sweep_b * K}
     elif dominant == "admm":
         src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", "admm_fused.hip")
         achieved = kernels["admm"]["tflops"]
         roof = {"kernel": "admm_fused_kernel", "bound": "alu", "achieved": achieved,
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
                 "traffic": measured_traffic(src, "admm_fused_kernel"), "launch_ms": admm_ms,
-                "flops_per_launch": stages * SWEEP_FLOPS_PER_STAGE * K}
+                "flops_per_launch": stages * sweep_f * K}
     else:
         src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", "setup.hip")
         roof = {"kernel": "setup_kernel", "bound": "alu", "achieved": None,

@@ -1,5 +1,6 @@
-// FP64 refinement and certification of the ADMM result, one 64-lane wave per
-// problem (problems are independent, so each wave runs its own loop).
+// FP64 refinement and certification of the ADMM result, one workgroup per problem:
+// one 64-lane wave, two for the recursions (Waves::PAIR), or one per chunk of the
+// horizon (Waves::SCAN).
 //
 // The ADMM of Sec. III reaches the QP optimum only in the limit; its last
 // projection fixes a guess of the active faces of every contact's wrench set.
@@ -825,11 +826,12 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 // by 3g lanes, and the partial sums of the four rows meet through the row and
 // half-wave swaps.
 
-// Forward rollout of an equality pass after its recursion (all N stages): w = K x + kap,
-// x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w = w to
-// rounding: the gains lie in the range of the projector.)  Stage data is fetched a ring of
-// six stages ahead, about 3000 cycles, as a trip to memory takes (unconditionally, so every path back to the loop head has issued
-// the same loads).
+// Forward rollout of an equality pass after its recursion (all N stages): w = K
+// x + kap, x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w =
+// w to rounding: the gains lie in the range of the projector.)  Stage data is
+// fetched a ring of six stages ahead, about 3000 cycles, as a trip to memory
+// takes (unconditionally, so every path back to the loop head has issued the
+// same loads).
 template <bool LONG>
 __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   gsync();

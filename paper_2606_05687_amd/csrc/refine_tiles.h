@@ -21,7 +21,7 @@ typedef const GMEM float* gcf;
 typedef const GMEM double* gcd;
 typedef GMEM double* gd;
 
-// The refinement runs one 64-lane wave per workgroup.  LDS operations of a
+// A phase of the refinement runs in one 64-lane wave.  LDS operations of a
 // wave execute in issue order, so handing data between the lanes of the wave
 // through LDS needs only a point the compiler does not move memory accesses
 // across (wsync).  gsync is used where one phase's global outputs feed the next
