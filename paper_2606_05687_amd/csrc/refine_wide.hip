@@ -724,7 +724,7 @@ __device__ inline double dot_half(double u, const float (&b)[NU], double s) {
 
 // x = rollout of u from x0, in FP64: the stage terms B u + e for four stages at
 // a time, then the chain.  x_{k+1} is left in PV as well.
-__device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
+__device__ __attribute__((always_inline)) inline void rollout(const WCtx& C, WSh& sh) {
   __syncthreads();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
   const int lane = fresh_lane(), g = lane >> 4, j = lane & 15;
@@ -796,7 +796,7 @@ __device__ __attribute__((noinline)) void rollout(const WCtx& C, WSh& sh) {
 
 // Dynamics residual of the FP64 trajectory (x, u), normalised by the largest
 // term of each entry.
-__device__ __attribute__((noinline)) double dyn_residual(const WCtx& C) {
+__device__ __attribute__((always_inline)) inline double dyn_residual(const WCtx& C) {
   // four stages at a time (one per 16-lane row, state j in lane j)
   const int g = tg(), j = tj();
   const int N = __builtin_amdgcn_readfirstlane(C.N);
@@ -924,7 +924,7 @@ __device__ void force_refit(int am, double mu, const double gf[3], double m[5]) 
 // construction and stationarity measures how well u meets it.  (The interior
 // point's own multipliers lose their accuracy as the slacks of active rows
 // approach zero: their step divides by the slack.)  Returns max(res).
-__device__ __attribute__((noinline)) double certificate(const WCtx& C, WSh& sh,
+__device__ __attribute__((always_inline)) inline double certificate(const WCtx& C, WSh& sh,
                                                        double res[PINMPC_NRES], double tol) {
   rollout(C, sh);
   res[0] = dyn_residual(C);
@@ -1122,17 +1122,15 @@ __device__ __attribute__((always_inline)) inline int ipm(const WCtx& C, WSh& sh,
   }
   const double m = wave_sum(mloc);
   int it = 0;
-  for (; it < maxit; ++it) {
+  for (;; ++it) {
     const double sz = wave_sum(smz), muv = m > 0.0 ? sz / m : 0.0;
     rpn = wave_max(rpn);
-    if (muv <= 1e-8 && rpn <= 1e-8) {
-      if (certificate(C, sh, res, tol) <= tol) {
-        *ok = true;
-        return it;
-      }
-      // beyond this the steps of the multipliers of active rows (divided by
-      // slacks near zero) carry no accuracy
-      if (muv <= 1e-20) break;
+    // (beyond 1e-20 the steps of the multipliers of active rows, divided by
+    // slacks near zero, carry no accuracy)
+    const bool last = it >= maxit;
+    if (last || (muv <= 1e-8 && rpn <= 1e-8)) {
+      *ok = certificate(C, sh, res, tol) <= tol;
+      if (scalar(*ok || last || muv <= 1e-20)) return it;
     }
     // predictor: affine target s z
     build_terms(C, sh);
@@ -1292,8 +1290,6 @@ __device__ __attribute__((always_inline)) inline int ipm(const WCtx& C, WSh& sh,
     }
     wsync();
   }
-  *ok = certificate(C, sh, res, tol) <= tol;
-  return it;
 }
 
 __global__ void __launch_bounds__(64, 2) refine_wide_kernel(Problem p, Workspace ws, float* out_u,
