@@ -242,7 +242,7 @@ struct Sh {
     } p;
     struct {
       double PV[PINMPC_NMAX * 16];   // x_{k+1}, Q (x_{k+1} - r_k), p_{k+1}
-      double GV[PINMPC_NMAX * 16];   // w_k, R (u_k - u_ref_k), g_k
+      double GV[PINMPC_NMAX * 16];   // u_k, R (u_k - u_ref_k), g_k
     } c;
   };
   double Qd[NX], Rd[NU]; // diagonal weights of the problem
@@ -826,12 +826,31 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
 // by 3g lanes, and the partial sums of the four rows meet through the row and
 // half-wave swaps.
 
-// Forward rollout of an equality pass after its recursion (all N stages): w = K
-// x + kap, x' = A x + B (w + c) + e, with w_k in GV and x_{k+1} in PV.  (P w =
-// w to rounding: the gains lie in the range of the projector.)  Stage data is
-// fetched a ring of six stages ahead, about 3000 cycles, as a trip to memory
-// takes (unconditionally, so every path back to the loop head has issued the
-// same loads).
+// s + sum_a (w of lane a of this 16-lane row) * m[a] over the force components,
+// lanes 0..2 and 6..8.
+__device__ inline double dot_forces(double w, const double (&m)[6], double s) {
+  asm volatile("s_nop 1\n"
+               "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %5 row_newbcast:6 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %6 row_newbcast:7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               "v_fmac_f64_dpp %0, %1, %7 row_newbcast:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+               : "+v"(s)
+               : "v"(w), "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "v"(m[4]), "v"(m[5]));
+  return s;
+}
+
+// Forward rollout of an equality pass after its recursion (all N stages): u = P
+// (K x + kap) + c, x' = A x + B u + e, with u_k in GV and x_{k+1} in PV.  The
+// gains lie in the range of the projector only up to the elimination's rounding,
+// which is relative to H's largest entries, while outside that range H is the
+// identity: with inputs in units in which H is large the part outside is far above
+// the tolerance, and without P the states were not those of the inputs on their
+// faces (inputs in units of 10 kN: one problem in ten was not certified).  Stage
+// data is fetched a ring of six stages ahead, about 3000 cycles, as a trip to
+// memory takes (unconditionally, so every path back to the loop head has issued
+// the same loads).
 template <bool LONG>
 __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   gsync();
@@ -846,16 +865,20 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
   const int oK = j < NU ? (j * (NX + 1) + 3 * g) * 8 : OOB;
   const int oKap = (g == 0 && j < NU) ? (j * (NX + 1) + NX) * 8 : OOB;
   const int oE = (g == 0 && j < NX) ? j * 4 : OOB;
-  const int oC = j < NU ? t_offset(clampi(j, NU - 1), VC) : OOB;
+  // row j of [P | c]: three entries and c (forces), or the diagonal and c (moments)
+  const bool force = j % 6 < 3;
+  const int oP = j < NU ? ((j / 6) * 18 + (force ? 4 * (j % 6) : 12 + 2 * (j % 6 - 3))) * 8 : OOB;
+  const int oP2 = force ? oP + 16 : OOB;
   struct FwdRaw {
-    double k[4], kap, c;
+    double k[4], kap, p[4];
     float a[4], b[3], e;
   };
   auto ffetch = [&](int k, FwdRaw& s) {
     ldd2(rK, oK, k * (TS_K * 8), s.k);
     ldd2(rK, oK + 16, k * (TS_K * 8), s.k + 2);
     s.kap = ldd(rK, oKap, k * (TS_K * 8));
-    s.c = ldd(rT, oC, k * (TS_T * 8));
+    ldd2(rT, oP, k * (TS_T * 8), s.p);
+    ldd2(rT, oP2, k * (TS_T * 8), s.p + 2);
     ldf4(rA, oA, k * (NX * NX * 4), s.a);
     ldf3(rB, oB, k * (NX * NU * 4), s.b);
     s.e = ldf(rE, oE, k * (NX * 4));
@@ -882,15 +905,25 @@ __device__ INLINE void forward(const Ctx& C, Sh& sh) {
       b[q] = (double)r.b[q];
       pin(b[q]);
     }
-    const double kap = r.kap, cc = r.c, ee = (double)r.e;
-    pin(kap); pin(cc); pin(ee);
+    double pm[6];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      pm[q] = j < 3 ? r.p[q] : 0.0;
+      pm[3 + q] = (j >= 6 && j < 9) ? r.p[q] : 0.0;
+      pin(pm[q]);
+      pin(pm[3 + q]);
+    }
+    const double kap = r.kap, pd = force ? 0.0 : r.p[0], cc = force ? r.p[3] : r.p[1],
+                 ee = (double)r.e;
+    pin(kap); pin(pd); pin(cc); pin(ee);
     pin_memory();
     ffetch(k + FD < N ? k + FD : N - 1, r);
     const double xt = turn_rows(xv);
     const double w = row_total(dot4(xt, km, kap));
     const double ax = dot4(xt, a, ee);
-    xv = row_total(dot3(turn_rows(w + cc), b, ax));
-    if (lane < NU) sb.GV[k * 16 + j] = w;
+    const double u = dot_forces(w, pm, fma(pd, w, cc));
+    xv = row_total(dot3(turn_rows(u), b, ax));
+    if (lane < NU) sb.GV[k * 16 + j] = u;
     if (lane < NX) sb.PV[k * 16 + j] = xv;
   };
   static_assert(FD == 6, "one line below per ring slot");
@@ -1788,8 +1821,8 @@ __device__ INLINE void riccati(const Ctx& C, Sh& sh, int ktop) {
   else riccati_t<mode, LONG>(C, sh, ktop);
 }
 
-// The equality pass's point from its rollout (w_k in GV, x_{k+1} in PV): inputs
-// u = P w + c of the faces (closed form, exactly on each face), states, and what
+// The equality pass's point from its rollout (u_k in GV, x_{k+1} in PV): inputs
+// moved by rounding exactly onto their faces (closed form), states, and what
 // the costates start from, Q (x_{k+1} - r_k) in PV and R (u_k - u_ref_k) in GV.
 template <bool LONG>
 __device__ INLINE void eq_point(const Ctx& C, Sh& sh) {

@@ -1,0 +1,44 @@
+"""Results do not depend on the units of the data, and what is certified is finite.
+
+  * Inputs in another unit (forces and moments divided by s, so B times s and R
+    times s^2) pose the same problem: every problem stays certified, after the
+    same passes, and the inputs are the same to the parity bars.  The equality
+    passes eliminate P H P + (I - P), whose two parts then differ by s^2 in size.
+"""
+import numpy as np
+import pytest
+
+import mpcgen
+from gpu_common import TOL_ERR, _solve
+
+pytestmark = pytest.mark.gpu
+
+PLAIN = "plain_b4096_n20"
+
+
+def _in_units(batch, s):
+    out = {k: v.copy() if isinstance(v, np.ndarray) else v for k, v in batch.items()}
+    out["B"] *= np.float32(s)
+    out["R"] *= np.float32(s) * np.float32(s)
+    for k in ("fz_max", "tau_max", "weight", "u_ref", "u_prev"):
+        out[k] /= np.float32(s)
+    return out
+
+
+# one wave per problem, two, and the scan; the first passes and the interior point's
+# crossover passes
+@pytest.mark.parametrize("count,settings", [
+    (200, {}), (1100, dict(iters=3, rho=1.0, refine_passes=12, first_passes=0)),
+    (96, dict(iters=3, scan=4))])
+def test_units_of_the_inputs(solver, count, settings):
+    cfg = dict(mpcgen.CONFIGS[PLAIN], horizons=(8, 13, 20), batch=count, seed=47)
+    batch = mpcgen.make_batch(cfg, indices=range(count), offsets=True)
+    ref = _solve(solver, batch, **settings)
+    assert (ref["status"] == 0).all()
+    s = 8192.0   # a power of two: the same data, exactly
+    out = _solve(solver, _in_units(batch, s), **settings)
+    assert (out["status"] == 0).all(), np.flatnonzero(out["status"])
+    d = np.abs(out["u"].astype(np.float64) * s - ref["u"]).max((1, 2)) / batch["weight"]
+    assert d.max() <= TOL_ERR
+    assert np.abs(out["x"].astype(np.float64) - ref["x"]).max() <= TOL_ERR * np.abs(ref["x"]).max()
+    assert abs(int(out["iters"].sum()) - int(ref["iters"].sum())) <= 0.01 * int(ref["iters"].sum())
