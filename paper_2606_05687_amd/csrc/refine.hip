@@ -2269,7 +2269,7 @@ __device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
         term = fmax(term, fabs(gm[a]));
-        stat = fmax(stat, fabs(g[a] + gm[a]));
+        stat = fmax(stat, no_nan(fabs(g[a] + gm[a])));
       }
       fresh = settle_face(fresh);
     }
@@ -2295,11 +2295,11 @@ __device__ INLINE double multipliers_kkt(const Ctx& C, Sh& sh, double res[PINMPC
   neg = wave_max(neg);
   res[0] = 0.0;   // r_dyn: filled by the caller from the rollout
   res[1] = r_ineq;
-  res[2] = stat / (1.0 + term);
+  res[2] = term < __builtin_inf() ? stat / (1.0 + term) : term;
   res[3] = comp / (1.0 + mumax * sc.mg);
   res[4] = fmax(0.0, neg) / (1.0 + term);
   double kkt = 0.0;
-  for (int i = 1; i < PINMPC_NRES; ++i) kkt = fmax(kkt, res[i]);
+  for (int i = 1; i < PINMPC_NRES; ++i) kkt = fmax(kkt, no_nan(res[i]));
   return kkt;
 }
 
@@ -2356,7 +2356,7 @@ __device__ INLINE double dyn_residual(const Ctx& C) {
     const double ax = dot_row_bcast13(x, a, 0.0), bu = dot_row_bcast13(u, b, 0.0);
     const double d = xn - ax - bu - ee;
     const double den = 1.0 + fmax(fabs(xn), fmax(fabs(ax), fabs(bu)));
-    if (j < NX && k0 + g < N) res = fmax(res, fabs(d) / den);
+    if (j < NX && k0 + g < N) res = fmax(res, no_nan(fabs(d) / den));
   };
   static_assert(DD == 3, "one line below per ring slot");
   for (int k0 = 0;; k0 += 4 * DD) {

@@ -101,6 +101,9 @@ __device__ inline double wave_reduce(double v, F op) {
   swap_rows<true>(v, a, b);
   return op(a, b);
 }
+// v, or infinity if it is not a number: fmax drops a NaN, and a residual of NaNs
+// would pass for zero.
+__device__ inline double no_nan(double v) { return v == v ? v : __builtin_inf(); }
 __device__ inline double wave_max(double v) {
   return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }

@@ -831,7 +831,7 @@ __device__ __attribute__((always_inline)) inline double dyn_residual(const WCtx&
     const double bu = dot_row_bcast13(ub, cd, dot_row_bcast13(ua, bd, 0.0));
     const double d = xn - ax - bu - ee;
     const double den = 1.0 + fmax(fabs(xn), fmax(fabs(ax), fabs(bu)));
-    if (j < NX && k0 + g < N) r = fmax(r, fabs(d) / den);
+    if (j < NX && k0 + g < N) r = fmax(r, no_nan(fabs(d) / den));
   }
   return wave_max(r);
 }
@@ -1068,7 +1068,7 @@ __device__ __attribute__((always_inline)) inline double certificate(const WCtx& 
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
       tgm = fmax(tgm, fabs(gm[t]));
-      stat = fmax(stat, fabs(gr[t] + gm[t]));
+      stat = fmax(stat, no_nan(fabs(gr[t] + gm[t])));
     }
 #pragma unroll
     for (int r = 0; r < NROW; ++r) {
@@ -1083,12 +1083,12 @@ __device__ __attribute__((always_inline)) inline double certificate(const WCtx& 
   mmax = wave_max(mmax);
   comp = wave_max(comp) / (1.0 + mmax * C.mg);
   res[1] = wave_max(rin);
-  res[2] = wave_max(stat) / (1.0 + terms);
+  res[2] = terms < __builtin_inf() ? wave_max(stat) / (1.0 + terms) : terms;
   res[3] = comp;
   res[4] = 0.0;   // the refitted multipliers are nonnegative
   double m = 0.0;
 #pragma unroll
-  for (int i = 0; i < PINMPC_NRES; ++i) m = fmax(m, res[i]);
+  for (int i = 0; i < PINMPC_NRES; ++i) m = fmax(m, no_nan(res[i]));
   return m;
 }
 

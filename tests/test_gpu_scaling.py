@@ -13,7 +13,7 @@ from gpu_common import TOL_ERR, _solve
 
 pytestmark = pytest.mark.gpu
 
-PLAIN = "plain_b4096_n20"
+PLAIN, HANDS = "plain_b4096_n20", "hands_b4096_n20"
 
 
 def _in_units(batch, s):
@@ -42,3 +42,19 @@ def test_units_of_the_inputs(solver, count, settings):
     assert d.max() <= TOL_ERR
     assert np.abs(out["x"].astype(np.float64) - ref["x"]).max() <= TOL_ERR * np.abs(ref["x"]).max()
     assert abs(int(out["iters"].sum()) - int(ref["iters"].sum())) <= 0.01 * int(ref["iters"].sum())
+
+
+@pytest.mark.parametrize("base,n,settings", [
+    (PLAIN, 20, dict(ipm_iters=0)), (PLAIN, 20, dict(refine_passes=0)),
+    (PLAIN, 33, dict(iters=3, scan=4)), (PLAIN, 70, dict(form=2, iters=3)),
+    (HANDS, 40, dict(iters=5))])
+def test_certified_results_are_finite(solver, base, n, settings):
+    cfg = dict(mpcgen.CONFIGS[base], horizons=(n, n // 2), batch=48, seed=48)
+    batch = mpcgen.make_batch(cfg, indices=range(48), offsets=True)
+    batch["A"] *= np.float32(3.0)
+    out = _solve(solver, batch, **settings)
+    ok = out["status"] == 0
+    finite = np.isfinite(out["u"]).all((1, 2)) & np.isfinite(out["x"]).all((1, 2))
+    print("certified", int(ok.sum()), "finite", int(finite.sum()))
+    assert finite[ok].all(), np.flatnonzero(ok & ~finite)
+    assert (out["res"][ok] <= 1e-9).all()
