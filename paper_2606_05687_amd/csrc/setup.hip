@@ -1,7 +1,7 @@
 // Per-stage ADMM setup (Sec. III cached quantities), one workgroup per stage.
 //
 // For stage k of problem b, with block-constant input scaling S_k
-// (force triples m g / stance count, moment triples tau_max):
+// (force triples m g / stance count, moment triples tau_max, or 1 if that is 0):
 //   Bt_k = B_k S_k                                  (scaled inputs u = S ut)
 //   M_k  = (Bt_k^T Bt_k + I)^{-1}                   (so J_k w = M_k (Bt^T w_x + w_u))
 //   H_k  = (Qbar_k + rho I + [k < N-1] rho Abar_{k+1}^T Abar_{k+1})^{-1}
@@ -24,13 +24,18 @@ __device__ inline int stance_count(const uint8_t* c) {
   return n;
 }
 
+// The moments' scale: their bound, or 1 where it is zero (contacts without moments).
+__device__ inline float moment_scale(const Problem& p, int b) {
+  const float tm = p.tau_max[b];
+  return tm > 0.f ? tm : 1.f;
+}
 template <int NC>
 __device__ inline float scale_of(const Problem& p, int b, int k, int j, bool scaling) {
   if (!scaling) return 1.f;
   const size_t s = (size_t)b * p.n_max + k;
   const int ns = stance_count<NC>(p.contact + NC * s);
   const float sf = weight_of(p, b) / (float)(ns > 0 ? ns : 1);
-  return (j % 6) < 3 ? sf : p.tau_max[b];
+  return (j % 6) < 3 ? sf : moment_scale(p, b);
 }
 
 // 1/a from the hardware estimate and one Newton step (SPD pivots: finite and
@@ -116,7 +121,7 @@ __global__ void __launch_bounds__(64 * (NC / 2)) setup_kernel(Problem p, Workspa
   }
   if (tid == 0) {
     ws.sf[s] = sfk;
-    if (k == 0) ws.tsc[b] = sc ? p.tau_max[b] : 1.f;
+    if (k == 0) ws.tsc[b] = sc ? moment_scale(p, b) : 1.f;
   }
   if (bf16) {
     const float* A = p.A + (size_t)s * NX * NX;

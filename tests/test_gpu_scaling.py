@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import mpcgen
-from gpu_common import TOL_ERR, _solve
+from gpu_common import TOL_ERR, _check_invariants, _compare, _solve
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +58,14 @@ def test_certified_results_are_finite(solver, base, n, settings):
     print("certified", int(ok.sum()), "finite", int(finite.sum()))
     assert finite[ok].all(), np.flatnonzero(ok & ~finite)
     assert (out["res"][ok] <= 1e-9).all()
+
+
+def test_four_contacts_without_moments(solver):
+    cfg = dict(mpcgen.CONFIGS[HANDS], horizons=(5, 13, 20), batch=24, seed=49)
+    batch = mpcgen.make_batch(cfg, indices=range(24), offsets=True)
+    batch["tau_max"][::2] = 0.0
+    out = _solve(solver, batch, iters=10)
+    _check_invariants(batch, out, range(24))
+    _compare(batch, out, range(24))
+    u = out["u"].reshape(24, -1, 4, 6)
+    assert np.abs(u[::2, :, :, 3:]).max() <= 1e-6
