@@ -289,17 +289,28 @@ int pinmpc_stats_back(pinmpc_ctx c, int32_t back, double* total_ms, double* setu
                       double* admm_ms, double* refine_ms);
 
 /* Algorithmic HBM bytes of the last solve and their rate over its measured
- * time (host pointers; either may be NULL).  The byte model counts, per
- * stage, PINMPC_SETUP_BYTES once (operators read, H_k, M_k, qbar_k and the
- * scaled B written), PINMPC_SWEEP_BYTES per ADMM sweep (FP32 operators and
- * both iterate sets streamed), and PINMPC_REFINE_BYTES per stage of every
- * equality-constrained pass and interior-point iteration of the FP64
- * refinement (counted on the device).  Blocks until the last solve finished;
- * only valid while no later solve on this context has been enqueued.
+ * time (host pointers; either may be NULL).  The byte model counts, per stage
+ * (padding included), at FP32 sizes whatever settings.precision:
+ *   PINMPC_SETUP_BYTES once: operators read, H_k, M_k, qbar_k and the scaled B
+ *     written (3200), both iterate sets read and written by the sweeps (2000);
+ *   PINMPC_SWEEP_BYTES per reading of the operators: once where the sweeps
+ *     keep them in registers (see settings.form), in every sweep where they
+ *     are streamed (longer horizons; of form -1 the problems of more than 40
+ *     stages) or the horizon is split;
+ *   PINMPC_ITERATE_BYTES for every sweep but the first of a split horizon,
+ *     whose launches hand the iterates on through memory;
+ *   PINMPC_REFINE_BYTES per stage of every equality-constrained pass and
+ *     interior-point iteration of the FP64 refinement (counted on the device).
+ * The _4 constants hold for four contacts.  Blocks until the last solve
+ * finished; only valid while no later solve on this context has been enqueued.
  * PINMPC_EINVAL if the context has made no solve. */
-#define PINMPC_SETUP_BYTES 3200
-#define PINMPC_SWEEP_BYTES 5070
+#define PINMPC_SETUP_BYTES 5200
+#define PINMPC_SWEEP_BYTES 3070
+#define PINMPC_ITERATE_BYTES 2000
 #define PINMPC_REFINE_BYTES 4500
+#define PINMPC_SETUP_BYTES_4 12216
+#define PINMPC_SWEEP_BYTES_4 6144
+#define PINMPC_REFINE_BYTES_4 42088
 int pinmpc_stats_traffic(pinmpc_ctx c, double* bytes, double* gbytes_per_s);
 
 /* Release the context and its workspace (waits for the device first). */

@@ -36,6 +36,16 @@ static bool same_key(const GraphKey& a, const GraphKey& b) {
          a.stream == b.stream && a.mem == b.mem;
 }
 
+// What pinmpc_stats_traffic needs to know of a solve: its shape, sweeps and the
+// device counters of its refinement work and horizon classes.
+struct SolveTraffic {
+  int32_t batch = 0, n_max = 0;
+  int nc = NCONTACT, iters = 0;
+  SweepRoute route = SweepRoute::FUSED;
+  const unsigned long long* work = nullptr;
+  const int32_t* counts = nullptr;
+};
+
 struct pinmpc_ctx_s {
   int device = 0;
   size_t budget = 0;
@@ -51,10 +61,8 @@ struct pinmpc_ctx_s {
   bool have_timing = false;
   hipGraphExec_t gexec = nullptr;
   GraphKey gkey{};
-  // the last solve's shape, sweep count and refinement work counter
-  size_t last_stages = 0;
-  int last_iters = 0;
-  const unsigned long long* last_work = nullptr;
+  SolveTraffic last;    // of the last solve
+  SolveTraffic glast;   // of the captured graph
 };
 
 namespace {
@@ -179,32 +187,43 @@ Problem to_problem(const pinmpc_batch* in) {
   return p;
 }
 
-// The ADMM sweeps in the form the settings ask for.  Forms 0 and 1 run all
-// sweeps in one launch: with the operators in registers where one workgroup
-// holds a problem's rows (fused_fits: 25 rows a stage up to 40 stages, 37 rows
-// with four contacts up to 27), else with the operators streamed.  (One launch
-// per sweep, what form 0 once was, took 100 sweeps in 13.6 ms at 4096 x 10
-// stages and in 1.3 ms at one problem; the same sweeps in one launch, bitwise
-// equal, take 1.4 ms and 0.3 ms.)
+// The kernels that a batch's sweeps run on.  Forms 0 and 1 run all sweeps in one
+// launch: with the operators in registers where one workgroup holds a problem's
+// rows (fused_fits: 25 rows a stage up to 40 stages, 37 rows with four contacts up
+// to 27), else with the operators streamed.  (One launch per sweep, what form 0 once
+// was, took 100 sweeps in 13.6 ms at 4096 x 10 stages and in 1.3 ms at one problem;
+// the same sweeps in one launch, bitwise equal, take 1.4 ms and 0.3 ms.)
+SweepRoute sweep_route(const pinmpc_settings& s, int nc, int n_max) {
+  if (nc == NCONTACT) {   // four contacts are neither split nor packed
+    // the horizon split across workgroups: every horizon up to PINMPC_NMAX_LONG
+    if (s.form == 2 || n_max > PINMPC_NMAX) return SweepRoute::SPLIT;
+    if (s.form == -1 && n_max > CLASS_N[0]) return SweepRoute::PACKED;
+  }
+  return fused_fits(nc, n_max) ? SweepRoute::FUSED : SweepRoute::STREAMED;
+}
+
 int launch_admm_phase(const pinmpc_settings& s, const Problem& p, const Workspace& w, int iters,
                       hipStream_t st) {
   if (iters <= 0) return PINMPC_OK;
-  const bool wide = p.nc != NCONTACT;   // four contacts: neither split nor packed
-  if (!wide && (s.form == 2 || p.n_max > PINMPC_NMAX)) {
-    // the horizon split across workgroups: every horizon up to PINMPC_NMAX_LONG
-    if (launch_admm_split(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
-  } else if (!wide && s.form == -1 && p.n_max > CLASS_N[0]) {
-    // pack problems by horizon class: fused kernels sized for each class,
-    // the persistent streaming kernel for the longest horizons
-    if (launch_classify(p, w, st) != hipSuccess) return PINMPC_EDEVICE;
-    for (int cls = 0; cls < 2; ++cls)
-      if (launch_admm_fused_class(p, w, s, iters, cls, st) != hipSuccess) return PINMPC_EDEVICE;
-    if (p.n_max > CLASS_N[1] && launch_admm_sweep_class(p, w, s, 2, iters, st) != hipSuccess)
-      return PINMPC_EDEVICE;
-  } else if (fused_fits(p.nc, p.n_max)) {
-    if (launch_admm_fused(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
-  } else if (launch_admm_sweep(p, w, s, iters, st) != hipSuccess) {
-    return PINMPC_EDEVICE;
+  switch (sweep_route(s, p.nc, p.n_max)) {
+    case SweepRoute::SPLIT:
+      if (launch_admm_split(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
+      break;
+    case SweepRoute::PACKED:
+      // problems packed by horizon class: fused kernels sized for each class, the
+      // streaming kernel for the longest horizons
+      if (launch_classify(p, w, st) != hipSuccess) return PINMPC_EDEVICE;
+      for (int cls = 0; cls < 2; ++cls)
+        if (launch_admm_fused_class(p, w, s, iters, cls, st) != hipSuccess) return PINMPC_EDEVICE;
+      if (p.n_max > CLASS_N[1] && launch_admm_sweep_class(p, w, s, 2, iters, st) != hipSuccess)
+        return PINMPC_EDEVICE;
+      break;
+    case SweepRoute::FUSED:
+      if (launch_admm_fused(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
+      break;
+    case SweepRoute::STREAMED:
+      if (launch_admm_sweep(p, w, s, iters, st) != hipSuccess) return PINMPC_EDEVICE;
+      break;
   }
   return PINMPC_OK;
 }
@@ -233,6 +252,7 @@ int ensure_workspace(pinmpc_ctx c, int32_t batch, int32_t n, int nc, hipStream_t
       (void)hipFree(c->mem);
       c->mem = nullptr;
       c->mem_bytes = 0;
+      c->last = {};   // its counters went with the workspace
     }
     if (hipMalloc(&c->mem, need) != hipSuccess) {
       c->mem = nullptr;
@@ -247,9 +267,7 @@ int ensure_workspace(pinmpc_ctx c, int32_t batch, int32_t n, int nc, hipStream_t
 int run_admm(pinmpc_ctx c, const Problem& p, const Workspace& w, int iters, hipStream_t st) {
   // the refinement adds its work to this counter (a fill kernel: graph-safe)
   if (launch_fill_i32((int32_t*)w.work, 2, 0, 0, st) != hipSuccess) return PINMPC_EDEVICE;
-  c->last_stages = (size_t)p.batch * p.n_max;
-  c->last_iters = iters;
-  c->last_work = w.work;
+  c->last = {p.batch, p.n_max, p.nc, iters, sweep_route(c->s, p.nc, p.n_max), w.work, w.counts};
   if (launch_setup(p, w, c->s, st) != hipSuccess) return PINMPC_EDEVICE;
   if (launch_admm_init(p, w, st) != hipSuccess) return PINMPC_EDEVICE;
   if (c->have_timing) (void)hipEventRecord(c->ev[1], st);
@@ -393,7 +411,9 @@ int solve_internal(pinmpc_ctx c, const pinmpc_batch* in, const pinmpc_out* out_i
       if (g) (void)hipGraphDestroy(g);
       if (crc) return crc;
       std::memcpy(&c->gkey, &key, sizeof(key));
+      c->glast = c->last;
     }
+    c->last = c->glast;
     const int slot = (int)(c->nsolves % PINMPC_STATS_RING);
     c->ev = c->ring[slot];
     c->ring_graph[slot] = true;
@@ -518,17 +538,29 @@ int pinmpc_stats(pinmpc_ctx c, double* total_ms, double* setup_ms, double* admm_
 }
 
 int pinmpc_stats_traffic(pinmpc_ctx c, double* bytes, double* gbytes_per_s) {
-  if (!c || !c->have_timing || c->nsolves == 0 || !c->last_work) return PINMPC_EINVAL;
+  if (!c || !c->have_timing || c->nsolves == 0 || !c->last.work) return PINMPC_EINVAL;
   hipEvent_t* ev = c->ring[(c->nsolves - 1) % PINMPC_STATS_RING];
   if (hipEventSynchronize(ev[3]) != hipSuccess) return PINMPC_EDEVICE;
+  const SolveTraffic& t = c->last;
   unsigned long long pass_stages = 0;
+  int32_t streamed = 0;   // problems of a packed batch whose operators are streamed
   if (hipSetDevice(c->device) != hipSuccess ||
-      hipMemcpy(&pass_stages, c->last_work, sizeof(pass_stages), hipMemcpyDeviceToHost) !=
-          hipSuccess)
+      hipMemcpy(&pass_stages, t.work, sizeof(pass_stages), hipMemcpyDeviceToHost) != hipSuccess)
     return PINMPC_EDEVICE;
-  const double b = (double)c->last_stages *
-                       (PINMPC_SETUP_BYTES + (double)c->last_iters * PINMPC_SWEEP_BYTES) +
-                   (double)pass_stages * PINMPC_REFINE_BYTES;
+  if (t.route == SweepRoute::PACKED && t.n_max > CLASS_N[1] && t.iters > 0 &&
+      hipMemcpy(&streamed, t.counts + 2, sizeof(streamed), hipMemcpyDeviceToHost) != hipSuccess)
+    return PINMPC_EDEVICE;
+  const double stages = (double)t.batch * t.n_max, iters = t.iters, once = t.iters > 0 ? 1.0 : 0.0;
+  const bool wide = t.nc != NCONTACT;
+  double readings = stages * iters, handed_on = 0.0;   // of the operators, of the iterates
+  if (t.route == SweepRoute::FUSED) readings = stages * once;
+  if (t.route == SweepRoute::PACKED)
+    readings = (stages - (double)streamed * t.n_max) * once + (double)streamed * t.n_max * iters;
+  if (t.route == SweepRoute::SPLIT) handed_on = stages * (iters - once);
+  const double b = stages * (wide ? PINMPC_SETUP_BYTES_4 : PINMPC_SETUP_BYTES) +
+                   readings * (wide ? PINMPC_SWEEP_BYTES_4 : PINMPC_SWEEP_BYTES) +
+                   handed_on * PINMPC_ITERATE_BYTES +
+                   (double)pass_stages * (wide ? PINMPC_REFINE_BYTES_4 : PINMPC_REFINE_BYTES);
   float ms = 0.f;
   if (hipEventElapsedTime(&ms, ev[0], ev[3]) != hipSuccess) return PINMPC_EDEVICE;
   if (bytes) *bytes = b;

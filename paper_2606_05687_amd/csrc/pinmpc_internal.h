@@ -347,13 +347,15 @@ int reserve_internal(pinmpc_ctx c, int32_t batch, int32_t n);
 // Host-side pieces of a solve shared by the entry points (api.cpp): carve the
 // workspace for batch x n out of `base` (or only size it when base is null;
 // returns the bytes), validate settings and a batch, view a batch as the
-// kernels' Problem, and enqueue the ADMM sweeps in the form the settings ask
-// for.
+// kernels' Problem, and choose and enqueue the ADMM sweeps in the form the settings
+// ask for.
 size_t carve_workspace(char* base, int32_t batch, int32_t n, Workspace* w, int nc = NCONTACT);
 int check_settings(const pinmpc_settings* s);
 int check_batch(const pinmpc_batch* in);
 int contacts_of(const pinmpc_batch* in);   // 2 or 4
 Problem to_problem(const pinmpc_batch* in);
+enum class SweepRoute { FUSED, STREAMED, SPLIT, PACKED };
+SweepRoute sweep_route(const pinmpc_settings& s, int nc, int n_max);
 int launch_admm_phase(const pinmpc_settings& s, const Problem& p, const Workspace& w, int iters,
                       hipStream_t st);
 
