@@ -76,16 +76,12 @@ __device__ inline float sum(const float* p, float acc) {
   return acc;
 }
 
-// Four waves per SIMD with two contacts, so that a second workgroup's operator
-// loads and barriers fill the first one's waits: 207 us instead of 373 for three
-// sweeps at 4096 x 20, 1372 instead of 1698 for a hundred at 4096 x 10, against
-// 8 spilled registers (one problem alone: 292 instead of 272).  With four
-// contacts a row's operators leave no room for it.
-template <int MAXT, bool BF16, int PPW, int NC>
-__global__ void __launch_bounds__(MAXT, (NC == 2 && MAXT <= 512) ? 4 : 1) admm_fused_kernel(Problem p, Workspace ws, float rho,
-                                                          int accel, float eta, int iters,
-                                                          const int32_t* order,
-                                                          const int32_t* count, int lds_n) {
+// WAVES: waves per SIMD that the registers must leave room for (see wants_room).
+template <int MAXT, bool BF16, int PPW, int NC, int WAVES>
+__global__ void __launch_bounds__(MAXT, WAVES) admm_fused_kernel(Problem p, Workspace ws, float rho,
+                                                                 int accel, float eta, int iters,
+                                                                 const int32_t* order,
+                                                                 const int32_t* count, int lds_n) {
   constexpr int NU = Dims<NC>::U, NL = Dims<NC>::L, NH = Dims<NC>::H, NM = Dims<NC>::M;
   constexpr int V = VS<NC>;
   OpLoad<BF16> op;
@@ -313,6 +309,22 @@ int fit_ppw(int ppw, int nl, int n) {
   return ppw < 1 ? 1 : ppw;
 }
 
+// Whether the two-contact kernel of up to 512 threads should run in its build for
+// four waves per SIMD: a second workgroup's operator loads and barriers then fill the
+// first one's waits (207 us instead of 373 for three sweeps at 4096 x 20, 1.33 ms
+// instead of 1.68 for a hundred at 4096 x 10), against 8 spilled registers, or 30 with
+// several problems per workgroup (none with room for two waves).  Where a CU's share
+// of the launch is two waves per SIMD or less there is no second one to make room
+// for: 274 us instead of 299 for a hundred sweeps of one problem of 10 stages, 310
+// instead of 383 for 64 of them in pairs, 300 instead of 417 for 512 of 5 stages in
+// fours.  With one problem per workgroup the build without spills takes 3 us longer to
+// start, which about 15 sweeps make up.
+bool wants_room(unsigned grid, int threads, int ppw, int iters) {
+  const unsigned cus = (unsigned)device_cus();
+  const unsigned waves = (grid + cus - 1) / cus * (unsigned)(threads / 64);   // of a CU
+  return waves > 8 || (ppw == 1 && iters < 16);
+}
+
 template <bool BF16, int NC>
 hipError_t fused(const Problem& p, const Workspace& w, const pinmpc_settings& s, int iters,
                  int cap, const int32_t* ord, const int32_t* cnt, hipStream_t st) {
@@ -320,25 +332,29 @@ hipError_t fused(const Problem& p, const Workspace& w, const pinmpc_settings& s,
   const int threads = ppw * (((Dims<NC>::L * cap + 63) / 64) * 64);
   const dim3 grid((unsigned)((p.batch + ppw - 1) / ppw));
   const size_t lds = (size_t)ppw * fused_lds_floats<NC>(cap) * sizeof(float);
-  // a kernel bound to fewer threads may use more registers: the operators of
-  // one row (63 floats, 87 with four contacts) fit without spilling up to 768
-#define PINMPC_FUSED(T, G)                                                                    \
-  hipLaunchKernelGGL((admm_fused_kernel<T, BF16, G, NC>), grid, dim3(threads), lds, st, p, w, \
+  // a kernel bound to fewer threads may use more registers (one row's operators are
+  // 63 floats, 87 with four contacts); those of 1024 threads spill
+#define PINMPC_FUSED(T, G, W)                                                                    \
+  hipLaunchKernelGGL((admm_fused_kernel<T, BF16, G, NC, W>), grid, dim3(threads), lds, st, p, w, \
                      s.rho, s.accel, s.restart_eta, iters, ord, cnt, cap)
   if constexpr (NC == 2) {
-    if (threads <= 512) {
-      if (ppw == 1) PINMPC_FUSED(512, 1);
-      else if (ppw == 2) PINMPC_FUSED(512, 2);
-      else PINMPC_FUSED(512, 4);
+    if (threads > 512) {
+      if (ppw == 1) PINMPC_FUSED(1024, 1, 1);
+      else if (ppw == 2) PINMPC_FUSED(1024, 2, 1);
+      else PINMPC_FUSED(1024, 4, 1);
+    } else if (wants_room(grid.x, threads, ppw, iters)) {
+      if (ppw == 1) PINMPC_FUSED(512, 1, 4);
+      else if (ppw == 2) PINMPC_FUSED(512, 2, 4);
+      else PINMPC_FUSED(512, 4, 4);
     } else {
-      if (ppw == 1) PINMPC_FUSED(1024, 1);
-      else if (ppw == 2) PINMPC_FUSED(1024, 2);
-      else PINMPC_FUSED(1024, 4);
+      if (ppw == 1) PINMPC_FUSED(512, 1, 1);
+      else if (ppw == 2) PINMPC_FUSED(512, 2, 1);
+      else PINMPC_FUSED(512, 4, 1);
     }
   } else {
-    if (threads <= 512) PINMPC_FUSED(512, 1);
-    else if (threads <= 768) PINMPC_FUSED(768, 1);
-    else PINMPC_FUSED(1024, 1);
+    if (threads <= 512) PINMPC_FUSED(512, 1, 1);
+    else if (threads <= 768) PINMPC_FUSED(768, 1, 1);
+    else PINMPC_FUSED(1024, 1, 1);
   }
 #undef PINMPC_FUSED
   return hipGetLastError();
@@ -346,6 +362,10 @@ hipError_t fused(const Problem& p, const Workspace& w, const pinmpc_settings& s,
 
 }  // namespace
 
+// (Four contacts beyond 20 stages run the 1024-thread build, which spills 48
+// registers, and are still faster than with their operators streamed: 59 us instead of
+// 146 for five sweeps of one problem of 27 stages, 823 instead of 1957 for 2048,
+// 9.3 ms instead of 33 for a hundred.)
 bool fused_fits(int nc, int n_max) { return (NX + 6 * nc) * n_max <= 1024; }
 
 hipError_t launch_admm_fused(const Problem& p, const Workspace& w, const pinmpc_settings& s,

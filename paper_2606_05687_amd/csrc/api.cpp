@@ -467,6 +467,15 @@ int solve_in_buffer(pinmpc_ctx c, const pinmpc_batch* in, const pinmpc_out* out_
   return PINMPC_OK;
 }
 
+int device_cus() {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1)
+    return 256;
+  return cus;
+}
+
 int context_device(pinmpc_ctx c) { return c ? c->device : -1; }
 
 int reserve_internal(pinmpc_ctx c, int32_t batch, int32_t n) {

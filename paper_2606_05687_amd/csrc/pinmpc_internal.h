@@ -338,6 +338,9 @@ int solve_internal(pinmpc_ctx c, const pinmpc_batch* in, const pinmpc_out* out,
 int solve_in_buffer(pinmpc_ctx c, const pinmpc_batch* in, const pinmpc_out* out,
                     hipStream_t st, void* base, size_t capacity);
 
+// Compute units of the current device (a whole MI355X: 256, of four SIMDs each).
+int device_cus();
+
 // The HIP device a context solves on (-1 for a null context).
 int context_device(pinmpc_ctx c);
 

@@ -64,3 +64,27 @@ def test_without_acceleration(solver, base, n, streamed):
     a = _iterates(solver, base, n, n, 20, accel=0)
     b = _iterates(solver, base, n, streamed, 20, accel=0)
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+# the builds of the register kernel, with and without spilled registers: chosen by
+# how many workgroups a CU gets (up to 512 threads per workgroup)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,group,many", [(5, 1, 1100), (5, 2, 1100), (5, 4, 1100),
+                                          (10, 1, 600), (10, 2, 600), (20, 1, 300)])
+def test_few_and_many_problems_agree_bitwise(solver, n, group, many, precision):
+    import torch
+    from paper_2606_05687_amd import binding
+    cfg = dict(mpcgen.CONFIGS[PLAIN], horizons=(n, max(1, n // 2)), batch=COUNT, seed=51)
+    few = mpcgen.make_batch(cfg, indices=range(COUNT), n_max=n, offsets=True)
+    rep = np.arange(many) % COUNT
+    z = []
+    for batch in (few, mpcgen.problem_slice(few, rep)):
+        reset_settings(solver)
+        solver.set(group=group, precision=precision)
+        z.append([solver.admm(binding.to_device(batch), k) for k in (3, 20, 50)])
+        torch.cuda.synchronize()
+        z[-1] = [v.cpu().numpy() for v in z[-1]]
+    for a, b in zip(*z):
+        for i in range(COUNT):
+            k = few["N"][i]
+            assert (b[rep == i][:, :k] == a[i, :k]).all()
