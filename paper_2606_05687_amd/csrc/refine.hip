@@ -2844,14 +2844,17 @@ __global__ void __launch_bounds__(threads_of(WV), 2) refine_kernel(Problem p, Wo
                                                     int32_t* out_detail,
                                                     int admm_iters, int accel, int refine,
                                                     int pass_a, int ipm_max, int pass_c,
-                                                    double tol, int pass_1) {
+                                                    double tol, int pass_1, int pair_max) {
   __shared__ Sh sh;
   // the problem context lives in LDS: its pointers are loaded where they are
   // used instead of being held in registers across the whole kernel
   __shared__ Ctx C;
   int pb = blockIdx.x;
   if (PHASE == 2) {
-    if ((int)blockIdx.x >= ws.rcount[0]) return;
+    const int listed = ws.rcount[0];
+    if ((int)blockIdx.x >= listed) return;
+    // of the two builds launched, the one that this many problems are faster with
+    if (WV != Waves::SCAN && (listed <= pair_max) != (WV == Waves::PAIR)) return;
     pb = ws.rlist[blockIdx.x];
   }
   if constexpr (WV == Waves::PAIR) {
@@ -3076,13 +3079,24 @@ __global__ void __launch_bounds__(threads_of(WV), 2) refine_kernel(Problem p, Wo
 
 }  // namespace
 
-// The first launch runs a problem by two waves up to this batch: 1024 pairs fill
-// the chip's 1024 SIMDs with two waves each (the registers allow no more).  With
-// more problems two single waves on a SIMD do the same work without the meetings.
-// The second launch always runs pairs: its few problems leave the chip nearly
-// empty, and each one's time is its chain (3001 problems of 8 to 60 stages: 7.8 ms
-// with one wave each, 6.8 ms with two; 24 of 160: 35 and 28 ms).
-constexpr int PAIR_BATCH = 1024;
+// The first launch runs a problem by two waves while two waves per SIMD hold the
+// whole batch (the registers allow no more).  With more problems two single waves on
+// a SIMD do the same work without the meetings.
+// The second launch's problems are fewer, and each one's time is its chain, so pairs
+// pay longer: 3001 problems of 8 to 60 stages, half of them listed, 7.8 ms with one
+// wave each, 6.8 ms with two; 24 of 160 stages 35 and 28 ms; 2 to 10 % up to 2.5 listed
+// problems per SIMD.  Beyond (first_passes or refine_passes of a few leave it most of a
+// large batch) one wave is faster throughout: both phases of 4096 x 20 with first_passes
+// = 2 take 3.16 ms with one, 3.56 with two, of 3001 x 40 6.24 and 6.70, of 4096 x 10
+// without active-set passes 1.78 and 2.21.  The device alone knows the number, so above that batch
+// both builds are launched and one exits at once (a few microseconds).
+struct PairRule {
+  int first, second;   // most problems run by pairs in either launch
+};
+PairRule pair_rule() {
+  const int simds = 4 * device_cus();
+  return {simds, simds * 5 / 2};
+}
 
 size_t scan_lds_bytes(int W) {
   return W > 1 ? (size_t)(W - 1) * sizeof(ShR) + (size_t)W * 4 * TILE_D * sizeof(double) : 0;
@@ -3120,7 +3134,7 @@ hipError_t launch_refine(const Problem& p, const Workspace& w, const pinmpc_sett
   hipLaunchKernelGGL((refine_kernel<PH, L, Waves::WV>), dim3(p.batch), dim3(T), lds, st, p, w,     \
                      out.u, out.x, out.res, out.iters, out.status, out.detail, s.iters, s.accel,   \
                      s.refine, s.refine_passes, s.ipm_iters, s.polish_passes, s.kkt_tol,           \
-                     s.first_passes)
+                     s.first_passes, rule.second)
 #define PINMPC_REFINE_L(PH, WV, T)              \
   do {                                          \
     if (lng) PINMPC_REFINE(PH, true, WV, T);    \
@@ -3129,13 +3143,15 @@ hipError_t launch_refine(const Problem& p, const Workspace& w, const pinmpc_sett
   // horizons beyond PINMPC_NMAX keep the rollout's and the costates' stage
   // buffers in the scratch block (refine_block_doubles sizes it so)
   const bool lng = p.n_max > PINMPC_NMAX;
+  const PairRule rule = pair_rule();
   if (W > 1) {
     PINMPC_REFINE_L(1, SCAN, 64 * W);
     if (second) PINMPC_REFINE_L(2, SCAN, 64 * W);
   } else {
-    if (p.batch <= PAIR_BATCH) PINMPC_REFINE_L(1, PAIR, 128);
+    if (p.batch <= rule.first) PINMPC_REFINE_L(1, PAIR, 128);
     else PINMPC_REFINE_L(1, ONE, 64);
     if (second) PINMPC_REFINE_L(2, PAIR, 128);
+    if (second && p.batch > rule.second) PINMPC_REFINE_L(2, ONE, 64);
   }
 #undef PINMPC_REFINE_L
 #undef PINMPC_REFINE
