@@ -1528,7 +1528,7 @@ __device__ INLINE void pair_backward(const Ctx& C, Sh& sh, int ktop) {
   }
   if constexpr (!FIRST) {
     if (ktop > 0) finish(0);
-    gsync();       // the stores have arrived
+    gsync();       // the stores come before the first wave's loads
   }
   pair_meet();
 }
@@ -2828,7 +2828,7 @@ __device__ inline void put_floats(float* out, Buf r, int count) {
 // The first wave releases a workgroup's other waves on every way out.
 template <Waves WV>
 struct Release {
-  __device__ ~Release() {
+  __device__ INLINE ~Release() {
     if constexpr (WV == Waves::SCAN) scan_release();
     if constexpr (WV == Waves::PAIR) pair_release();
   }
@@ -3084,12 +3084,15 @@ __global__ void __launch_bounds__(threads_of(WV), 2) refine_kernel(Problem p, Wo
 // a SIMD do the same work without the meetings.
 // The second launch's problems are fewer, and each one's time is its chain, so pairs
 // pay longer: 3001 problems of 8 to 60 stages, half of them listed, 7.8 ms with one
-// wave each, 6.8 ms with two; 24 of 160 stages 35 and 28 ms; 2 to 10 % up to 2.5 listed
-// problems per SIMD.  Beyond (first_passes or refine_passes of a few leave it most of a
-// large batch) one wave is faster throughout: both phases of 4096 x 20 with first_passes
-// = 2 take 3.16 ms with one, 3.56 with two, of 3001 x 40 6.24 and 6.70, of 4096 x 10
-// without active-set passes 1.78 and 2.21.  The device alone knows the number, so above that batch
-// both builds are launched and one exits at once (a few microseconds).
+// wave each, 6.8 ms with two; 24 of 160 stages 35 and 28 ms.  From about 1.2 to 2.5
+// listed problems per SIMD either may win by up to 15 %: pairs where the listed have
+// different lengths or mostly need a few passes more, single waves where every one
+// needs the interior point in 10 or 20 stages.  Beyond (first_passes or refine_passes of
+// a few leave it most of a large batch) one wave is as fast or faster: both launches of
+// 4096 x 20 with first_passes = 2 take 3.16 ms with one, 3.56 with two, of 3001 x 40
+// 6.24 and 6.70, of 4096 x 10 without active-set passes 1.78 and 2.21.  The device alone
+// knows the number, so above that batch both builds are launched and one exits at once
+// (a few microseconds).
 struct PairRule {
   int first, second;   // most problems run by pairs in either launch
 };

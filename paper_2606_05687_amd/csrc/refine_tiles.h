@@ -31,10 +31,11 @@ __device__ inline void wsync() {
   __builtin_amdgcn_wave_barrier();
 }
 // Global memory written by one lane and read by another: the fence at workgroup
-// scope (it waits for the stores; the waves of a workgroup share the CU's caches).
-// No barrier: with the associative scan of the backward recursion a problem's
-// workgroup holds several waves, the others join the first only at the scan's own
-// barriers.
+// scope.  It orders the accesses; it does not wait for the stores, nor need it to: the
+// waves of a workgroup share a CU, whose vector memory path and L1 take their accesses
+// in the order of issue.  No barrier: where a problem's workgroup holds several waves
+// (a pair's second wave, one per chunk of the associative scan), the others join the
+// first only at the recursion's own meetings, after which they read what it stored.
 __device__ inline void gsync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
