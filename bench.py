@@ -28,11 +28,14 @@ KKT_BAR = 1e-5
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 
-# Algorithmic bytes of one plain ADMM sweep per stage (FP32):
-#   operators A 676 + Bt 624 + H packed 1300 + M packed 312 + qbar 100
-#   + e 52 + contact 2 + force scale 4 = 3070 B read,
-#   iterates (current and extrapolated, 5 x 25 each) 1000 B read + 1000 B written
-SWEEP_BYTES_PER_STAGE = 3070 + 2000
+# Algorithmic bytes of the ADMM sweeps per stage (FP32): a reading of the operators
+#   A 676 + Bt 624 + H packed 1300 + M packed 312 + qbar 100
+#   + e 52 + contact 2 + force scale 4 = 3070 B,
+# once per solve where they stay in registers, every sweep where they are streamed or
+# the horizon is split; and the iterates (current and extrapolated, 5 x 25 each) 1000 B
+# read + 1000 B written, once per solve, every sweep where the horizon is split
+SWEEP_BYTES_PER_STAGE = 3070
+ITERATE_BYTES_PER_STAGE = 2000
 # Algorithmic flops of one sweep per stage: block 1 (Abar^T y 338, Bt^T w 312,
 # M t 288, H htilde 1250, vector ops 100), block 2 (Abar xi 650, Bbar du 312,
 # vector ops + projection 150), block 3 and the restart test 200
@@ -71,16 +74,19 @@ WIDE_FACTOR_FLOPS = 8112 + 4394 + 14976 + 8112 + 624 + 41952 + 13468
 WIDE_VECTOR_FLOPS = 624 + 1152 + 338 + 624
 WIDE_ROLLOUT_FLOPS = 1586
 WIDE_BYTES_PER_IPM_STAGE = 8748 + 8556 + 2 * 4908 + 2 * 2592 + 2 * 2144 + 3736 + 1760
-# its sweep per stage: operators A 676 + Bt 1248 + H packed 2812 + M packed
-# 1200 + qbar 148 + e 52 + contact 4 + force scale 4 = 6144 B read, iterates
+# its sweeps per stage: operators A 676 + Bt 1248 + H packed 2812 + M packed
+# 1200 + qbar 148 + e 52 + contact 4 + force scale 4 = 6144 B a reading, iterates
 # (5 x 37 each) 1480 B read + 1480 B written; setup per stage: A_k, A_{k+1},
 # B_k, B_{k+1} read (3848 B), Bt, H, M, qbar written (5408 B)
-WIDE_SWEEP_BYTES_PER_STAGE = 6144 + 2960
+WIDE_SWEEP_BYTES_PER_STAGE = 6144
+WIDE_ITERATE_BYTES_PER_STAGE = 2960
 # and its flops: H 37 x 37, four 13 x 13, three 13 x 24, M 24 x 24 products, and
 # about 20 per entry beside them
 WIDE_SWEEP_FLOPS_PER_STAGE = 2 * (37 * 37 + 4 * 13 * 13 + 3 * 13 * 24 + 24 * 24) + 20 * 37
-# longest horizons of the fused sweep (two, four contacts); beyond them the sweep streams
+# longest horizons of the fused sweep (two, four contacts), of the shortest class of
+# a packed batch, and beyond which a horizon is always split
 FUSED_STAGES = (40, 27)
+PACKED_FROM, SPLIT_FROM = 20, 64
 WIDE_SETUP_BYTES_PER_STAGE = 3848 + 5408
 # setup, once per stage: operators read, H, M, qbar and the scaled B written
 SETUP_BYTES_PER_STAGE = 3_200
@@ -98,7 +104,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=10)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--iters", type=int, default=100, help="ADMM sweeps per solve")
-    ap.add_argument("--form", type=int, default=0, help="0 plain, 1 fused, -1 packed")
+    ap.add_argument("--form", type=int, default=0, help="0, 1 all sweeps in one launch, -1 packed, 2 split")
     ap.add_argument("--rho", type=float, default=10.0)
     ap.add_argument("--refine-passes", type=int, default=8,
                     help="active-set passes before the interior-point fallback")
@@ -145,6 +151,30 @@ def parse():
                     help="1: time captured-graph replays (phase times then come from a "
                          "second, uncaptured loop)")
     return ap.parse_args()
+
+
+def sweep_route(form, n, wide):
+    """The kernels that the sweeps of a batch padded to n stages run on, as the library
+    chooses them (wide: four contacts)."""
+    if not wide and (form == 2 or n > SPLIT_FROM):
+        return "split"
+    if not wide and form == -1 and n > PACKED_FROM:
+        return "packed"
+    return "fused" if n <= FUSED_STAGES[wide] else "streamed"
+
+
+def sweep_bytes(route, K, N, wide):
+    """Algorithmic bytes of K sweeps per padded stage (N: the problems' horizons)."""
+    import numpy as np
+    ops = WIDE_SWEEP_BYTES_PER_STAGE if wide else SWEEP_BYTES_PER_STAGE
+    its = WIDE_ITERATE_BYTES_PER_STAGE if wide else ITERATE_BYTES_PER_STAGE
+    if K == 0:
+        return 0.0
+    if route == "split":
+        return float(K * (ops + its))
+    readings = {"fused": 1.0, "streamed": float(K),
+                "packed": float(np.where(np.asarray(N) > FUSED_STAGES[0], K, 1).mean())}[route]
+    return readings * ops + its
 
 
 def _oracle_chunk(idx):
@@ -693,7 +723,6 @@ def main():
         dense_flops = float(factored * WIDE_FACTOR_FLOPS +
                             (2 * pass_stages - factored) * WIDE_VECTOR_FLOPS +
                             2 * pass_stages * WIDE_ROLLOUT_FLOPS)
-    sweep_b = WIDE_SWEEP_BYTES_PER_STAGE if wide else SWEEP_BYTES_PER_STAGE
     setup_b = WIDE_SETUP_BYTES_PER_STAGE if wide else SETUP_BYTES_PER_STAGE
     work = {"pass_stages": pass_stages,
             "equality_passes_mean": float(eq_p.mean()),
@@ -702,11 +731,9 @@ def main():
             "frac_finished_in_second_launch": float((det[:, 3] == 2).mean()),
             "stages_factored_per_equality_pass": float(stf.sum() / max(1, eq_p.sum())),
             "dense_flops_per_solve": dense_flops}
-    # forms 0 and 1 are the same: fused where it fits, else streamed, all sweeps
-    # in one launch either way
-    streamed = settings["form"] in (0, 1) and int(batch["A"].shape[1]) > FUSED_STAGES[wide]
-    form_name = ("streamed" if streamed else
-                 {0: "fused", 1: "fused", -1: "packed", 2: "split"}[settings["form"]])
+    form_name = sweep_route(settings["form"], int(batch["A"].shape[1]), wide)
+    sweep_b = sweep_bytes(form_name, K, N_b, wide)   # of all K sweeps
+    by_bytes = form_name in ("streamed", "split")
     sweep_f = WIDE_SWEEP_FLOPS_PER_STAGE if wide else SWEEP_FLOPS_PER_STAGE
     kernels = {
         "setup_kernel": {"ms": setup_ms},
@@ -721,9 +748,8 @@ def main():
     kernels["refine_kernel"]["tflops"] = refine_flops / (refine_ms * 1e-3) / 1e12
     kernels["refine_kernel"]["gbs"] = refine_bytes / (refine_ms * 1e-3) / 1e9
     kernels["refine_kernel"]["dense_tflops"] = dense_flops / (refine_ms * 1e-3) / 1e12
-    if streamed:
-        sweep_bytes = stages * sweep_b
-        kernels["admm"]["gbs"] = sweep_bytes * K / (admm_ms * 1e-3) / 1e9
+    if by_bytes:
+        kernels["admm"]["gbs"] = stages * sweep_b / (admm_ms * 1e-3) / 1e9
     else:
         kernels["admm"]["tflops"] = stages * sweep_f * K / (admm_ms * 1e-3) / 1e12
     dominant = max(kernels, key=lambda k: kernels[k]["ms"])
@@ -743,13 +769,15 @@ def main():
                 "hbm_gbs": kernels["refine_kernel"]["gbs"],
                 "hbm_frac": kernels["refine_kernel"]["gbs"] / HBM_PEAK_GBS,
                 "bytes_per_pass_stage": bytes_ps, "dtype": "f64"}
-    elif dominant == "admm" and streamed:
-        src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", "admm_plain.hip")
+    elif dominant == "admm" and by_bytes:
+        kname, src = {"streamed": ("admm_sweep_kernel", "admm_plain.hip"),
+                      "split": ("admm_split kernels", "admm_split.hip")}[form_name]
+        src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", src)
         achieved = kernels["admm"]["gbs"]
-        roof = {"kernel": "admm_sweep_kernel", "bound": "hbm", "achieved": achieved,
+        roof = {"kernel": kname, "bound": "hbm", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                "traffic": measured_traffic(src, "admm_sweep_kernel"),
-                "launch_ms": admm_ms, "bytes_per_launch": stages * sweep_b * K}
+                "traffic": measured_traffic(src, kname),
+                "launch_ms": admm_ms, "bytes_per_launch": stages * sweep_b}
     elif dominant == "admm":
         src = os.path.join(ROOT, "paper_2606_05687_amd", "csrc", "admm_fused.hip")
         achieved = kernels["admm"]["tflops"]
@@ -763,10 +791,10 @@ def main():
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": None,
                 "traffic": measured_traffic(src, "setup_kernel<4>" if wide else "setup_kernel<2>"),
                 "launch_ms": setup_ms}
-    # the whole solve against HBM: setup once per stage, K sweeps of operators
-    # and iterates, the refinement's pass-stages, over the throughput interval
-    # (solves in flight) and over one uncontended solve
-    solve_bytes = float(stages * (setup_b + K * sweep_b) + refine_bytes)
+    # the whole solve against HBM: setup once per stage, the sweeps' readings of
+    # operators and iterates, the refinement's pass-stages, over the throughput
+    # interval (solves in flight) and over one uncontended solve
+    solve_bytes = float(stages * (setup_b + sweep_b) + refine_bytes)
     whole = {"bytes_per_solve": solve_bytes,
              "interval_ms": ms_per_step,
              "gbs": solve_bytes / (ms_per_step * 1e-3) / 1e9,
