@@ -702,7 +702,8 @@ __device__ INLINE d4 backward(const Ctx& C, ShR& sr,
     if (k > k_lo) fetch(k - 1, raw);
 
     const d4 D3 = mmT<4>(Wt, D1, zero4());   // [W Bp | 0 | W d + q + s], row VC Bp^T (q + s)
-    const d4 D4 = mmT<4>(D3, D1, H0);        // [H | 0 | hw]
+    // H0 added once: where R dominates, each product added to it would round u
+    const d4 D4 = mmT<4>(D3, D1, zero4()) + H0;   // [H | 0 | hw]
     const d4 D2 = mmT<4>(Wt, At, zero4());   // [W A | W d + q + s]
     const d4 D5 = mmT<4>(D1, D2, zero4());   // Hwx
 #pragma unroll
@@ -1474,7 +1475,7 @@ __device__ INLINE void pair_backward(const Ctx& C, Sh& sh, int ktop) {
     double* G = (k & 1) ? sh.p.G1 : sr.G;
     if constexpr (FIRST) {
       const d4 D3 = mmT<4>(Wt, D1, zero4());
-      const d4 D4 = mmT<4>(D3, D1, H0);        // [H | 0 | hw]
+      const d4 D4 = mmT<4>(D3, D1, zero4()) + H0;   // [H | 0 | hw]
       if (j < NU || j == VC) {
         double* gc = G + (j < NU ? j : NU + VC) * GC + g;
 #pragma unroll

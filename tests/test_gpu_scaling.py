@@ -44,6 +44,15 @@ def test_units_of_the_inputs(solver, count, settings):
     assert abs(int(out["iters"].sum()) - int(ref["iters"].sum())) <= 0.01 * int(ref["iters"].sum())
 
 
+def test_stationarity_with_dominant_input_weights(solver):
+    cfg = dict(mpcgen.CONFIGS[PLAIN], horizons=(12,), batch=1000, seed=53)
+    batch = mpcgen.make_batch(cfg, indices=range(1000), offsets=True)
+    batch["R"] = (batch["R"] * np.float32(1e12)).astype(np.float32)
+    out = _solve(solver, batch, ipm_iters=0)
+    print("mean r_stat", out["res"][:, 2].mean(), "certified", int((out["status"] == 0).sum()))
+    assert out["res"][:, 2].mean() <= 1.1 * 7.1e-10
+
+
 @pytest.mark.parametrize("base,n,settings", [
     (PLAIN, 20, dict(ipm_iters=0)), (PLAIN, 20, dict(refine_passes=0)),
     (PLAIN, 33, dict(iters=3, scan=4)), (PLAIN, 70, dict(form=2, iters=3)),
