@@ -126,7 +126,8 @@ typedef struct {
                               solve of every active-set pass and the factored
                               Newton step of every interior-point iteration):
                               0: sequential over the horizon, one wave per
-                              problem; 2, 4 or 8: an associative scan over
+                              problem or, where the device has room, two; 2, 4
+                              or 8: an associative scan over
                               that many chunks of the horizon (one wave per
                               chunk; depth about 3 N / W + W stage steps
                               instead of N; results equal the sequential
